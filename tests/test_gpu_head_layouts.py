@@ -1,0 +1,60 @@
+"""Head and batch counts that do not fill whole rounds of the eight XCDs: the work-group mapping deals the
+left-over (batch, kv head) keys tile by tile over all XCDs, and long launches walk an XCD's keys one after the
+other where short ones run them side by side.  Every work-group owns its outputs, so a tile that the mapping
+dropped or dealt twice to different heads shows as a wrong element against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import burst_oracle as oc
+from paper_2509_19836_amd import workloads as wl
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+
+def step_case(lib, B, Hq, Hkv, d, sq, sk, causal, seed, q_pos=0, k_pos=0):
+    """One forward step (step result) and one backward step (overwriting) against the oracle, every element."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(wl.BASE_SEED + 61000 + seed))
+    desc = f"B={B} heads={Hq}/{Hkv} d={d} sq={sq}@{q_pos} sk={sk}@{k_pos} causal={causal}"
+    print(desc, flush=True)
+    draw = lambda *shape: wl.f32_to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+    qb, kb, vb, gb = draw(B, sq, Hq, d), draw(B, sk, Hkv, d), draw(B, sk, Hkv, d), draw(B, sq, Hq, d)
+    Q, K, V, G = (hp.widen(x) for x in (qb, kb, vb, gb))
+    q, k, v, g = (hp.dev_bf16(x) for x in (qb, kb, vb, gb))
+    mask = lib.burst_mask_t()
+    mask.mode = lib.BURST_MASK_CAUSAL if causal else lib.BURST_MASK_FULL
+    mask.q_nseg = mask.k_nseg = mask.pos_stride = 1
+    mask.q_seg_len, mask.k_seg_len = sq, sk
+    mask.q_seg_pos[0], mask.k_seg_pos[0] = q_pos, k_pos
+    vis = oc.visibility(q_pos + np.arange(sq), k_pos + np.arange(sk), causal)
+    scale = 1.0 / float(np.sqrt(d))
+    shp = lib.shape(B, Hq, Hkv, d, sq, sk, scale)
+    O_ref, lse_ref = oc.mha_step_fwd(Q, K, V, scale, vis)
+    nan = lambda *shape: torch.full(shape, float("nan"), device="cuda", dtype=torch.float32)
+    o, lse = nan(B, sq, Hq, d), nan(B, Hq, sq)
+    lib.burst_attn_step_fwd(shp, mask, q, k, v, o_part=o, lse_part=lse)
+    torch.cuda.synchronize()
+    assert hp.rel_err(o.cpu().numpy(), O_ref) <= hp.REL_TOL, desc
+    assert hp.lse_err(lse.cpu().numpy(), lse_ref) <= hp.LSE_TOL, desc
+    lse_in = np.where(np.isfinite(lse_ref), lse_ref, 0.0).astype(np.float32) + np.float32(0.25)
+    D_in = rng.standard_normal((B, Hq, sq)).astype(np.float32)
+    ref = oc.mha_step_bwd(Q, K, V, G, lse_in.astype(np.float64), D_in.astype(np.float64), scale, vis)
+    out = nan(B, sq, Hq, d), nan(B, sk, Hkv, d), nan(B, sk, Hkv, d)
+    lib.burst_attn_step_bwd(shp, mask, q, k, v, g, torch.from_numpy(lse_in).cuda(), torch.from_numpy(D_in).cuda(),
+                            dq=out[0], dk=out[1], dv=out[2])
+    torch.cuda.synchronize()
+    for name, got, want in zip(("dQ", "dK", "dV"), out, ref):
+        assert hp.rel_err(got.cpu().numpy(), want) <= hp.REL_TOL, (name, desc)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,n,causal", [
+    (1, 1, 1, 64, 300, True),        # one key: tiles dealt over all XCDs
+    (1, 6, 3, 128, 520, True),       # three keys, groups of two
+    (1, 9, 9, 64, 260, False),       # one whole round and one key left over
+    (5, 3, 3, 64, 513, True),        # fifteen keys over the batch
+    (2, 28, 7, 128, 257, True),      # groups of four
+    (8, 40, 5, 64, 1800, True),      # five whole rounds, groups of eight: more than a short launch
+])
+def test_head_layouts(lib, B, Hq, Hkv, d, n, causal):
+    step_case(lib, B, Hq, Hkv, d, n, n, causal, B * 1000 + Hq)
