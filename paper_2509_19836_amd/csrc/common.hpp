@@ -639,6 +639,11 @@ __host__ __device__ __forceinline__ BlockMap map_block(int n, int n_keys, int gr
     m.valid = local_key < full;
   }
   m.tile = HIGH_FIRST ? tiles - 1 - t : t;
+#ifdef __HIP_DEVICE_COMPILE__   // results of divisions, which the compiler leaves in vector registers
+  m.key = __builtin_amdgcn_readfirstlane(m.key);
+  m.head_in_group = __builtin_amdgcn_readfirstlane(m.head_in_group);
+  m.tile = __builtin_amdgcn_readfirstlane(m.tile);
+#endif
   return m;
 }
 inline int mapped_grid(int n_keys, int group, int tiles) {

@@ -1,16 +1,23 @@
 // Forward step kernel: O_ij, Lse_cur of a query chunk against one key/value chunk (Eq. 5-6),
 // optionally folded into the running (O_i, Lse_i) in the epilogue (forward algorithm).
 //
-// One work-group = 8 waves = 256 query rows of one (batch, head); wave w owns rows [32w, 32w+32),
-// two waves per SIMD.  The key/value chunk streams through LDS in tiles of 64 rows, double buffered,
-// one barrier per tile.  Everything is computed transposed so that a lane always owns one query row:
+// One work-group = 8 waves = 256 query rows of one (batch, head); wave w owns rows [32w, 32w+32), two waves per
+// SIMD.  The key/value chunk streams through LDS in tiles of 64 rows.  Everything is computed transposed so that a
+// lane always owns query rows (two of them):
 //   S^T = K Q^T   (A = K rows from LDS, B = Q held in registers),
-//   P^T = exp2(..) in the accumulator registers, packed to bf16 and fed straight back as the
-//   B operand of  O^T = V^T P^T  (A = V columns via transposing LDS reads).
-// Row max / row sum / rescale are then per-lane scalars; the two half-waves exchange one value
-// per tile.
+//   P^T = exp2(..) in the accumulator registers, packed to bf16 and fed straight back as the B operand of
+//   O^T = V^T P^T (A = V columns via transposing LDS reads).
+//
+// What bounds it at d = 128: the matrix pipe and the vector unit need about the same time for a tile (64 MFMAs of
+// 16 clocks; 131 vector instructions, of them 32 exponentials, about 1000 clocks for a wave alone), and the chip
+// holds a power limit on top.  So the two waves of a SIMD take the phases in turn, and the products use
+// 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed 2102 against 1772-1874 TFLOP/s).
+// Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
+// 131072 x 131072 rows x 32 heads: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s); matrix pipe busy 52 -> 61 % at 1.55 GHz.
+// At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma16.hpp"
 
 namespace burst {
 
@@ -19,19 +26,18 @@ namespace burst {
 #endif
 constexpr int kFwdBQ = BURST_FWD_BQ;   // query rows per work-group: 32 per wave
 
-template <int D, int NW>
+template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdParams p) {
-  constexpr int BK = 64, KB = BK / 32, DK = D / 16, DB = D / 32, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int PITCH = 2 * D + 16;
-  constexpr int TILE = BK * PITCH;
-  extern __shared__ __attribute__((aligned(16))) char smem[];  // [2 buffers][K tile, V tile]
+  constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
+  constexpr int TILE = BK * 2 * D, SLOTS = 4, AHEAD = kAhead16;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
 
   const int group = p.q_heads / p.kv_heads;
   const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total());
   if (!bm.valid) return;
-  const int b = bm.key / p.kv_heads, hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
+  const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
 
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: everything derived from it stays wave-uniform
   const int sq = p.sq, sk = p.sk;
   const MaskDev mk = p.mask;
@@ -40,198 +46,228 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   const int q_w0 = q_blk0 + wave * 32;                   // first row of the wave
   const int q_w1 = min(q_w0 + 32, sq);                   // may be <= q_w0: the wave only helps staging
 
-  // Q as the B operand of S^T = K Q^T: lane holds Q[row][16*ks + 8h .. +7]
-  bf16x8 qreg[DK];
-  const int row = min(q_w0 + r, sq - 1);
-  const int qpos = axis_position(axis_of<true>(mk), row);
-  {
-    const __bf16* src = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * h;
+  // Q as the B operand of S^T = K Q^T: lane holds rows q_w0 + 16 nb + r, columns 32 ks + 8g .. +7
+  bf16x8 qreg[DK][NB];
+  int klo[NB], khi[NB];   // key rows that the lane's query rows see
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(src + ks * 16);
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = min(q_w0 + 16 * nb + r, sq - 1);
+    visible_rows<true>(mk, axis_position(axis_of<true>(mk), row), sk, klo[nb], khi[nb]);
+    const __bf16* src = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) qreg[ks][nb] = *reinterpret_cast<const bf16x8*>(src + ks * 32);
   }
 
-  f32x16 o[DB];
+  f32x4 o[DB][NB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float c = p.scale * kLog2e;
+    for (int nb = 0; nb < NB; ++nb) o[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float c = p.scale * kLog2e, slack = kLazyLog2 / c;
+  // running maximum, what a score must exceed for a rescale, c * maximum (0 while there is none), running sum
+  float m_run[NB] = {-INFINITY, -INFINITY}, limit[NB] = {-INFINITY, -INFINITY}, msub[NB] = {0.f, 0.f};
+  f32x4 l_run[NB] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // four independent chains
 
   // Key tiles the work-group can see, and the class of each against this wave's 32 query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
   range_minmax<true>(mk, q_blk0, q_blk1, qlo_blk, qhi_blk);
   if (q_w0 < q_w1) range_minmax<true>(mk, q_w0, q_w1, qlo_w, qhi_w);
-  BlockClassifier<false> k_class;
-  k_class.init(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1);
-  auto tile_class = [&](int k0_) { return k_class(mk, k0_, min(k0_ + BK, sk), k0_ + BK > sk); };   // wave-uniform
+  TileRanges tiles;
+  tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
 
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
-  if (mk.blk) {
-    open_flags = reinterpret_cast<uint8_t*>(smem + 4 * TILE);
+  if (BLK) {
+    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE);
     fill_open_flags<true, BK>(mk, open_flags, q_blk0, sk, tid, NT);
     __syncthreads();
   }
-  KvWalk<D, BK, NT> walk;
-  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, tid, open_flags);
+  OperandAddr<D> ad;
+  ad.init(lane);
+  KvStream<D, BK, NW, BLK> walk;
+  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
   wait_global_loads();
-  int k0 = 0, cls = TILE_SKIP;   // first key row and class of the tile in LDS
-  bool have = walk.valid();
-  if (have) {
-    walk.issue(tid);
-    walk.commit(smem, smem + TILE);
-    k0 = walk.k0;
-    cls = tile_class(k0);
-    walk.advance();
-  }
-  __syncthreads();
-  int buf = 0;
-  while (have) {
-    const bool more = walk.valid();
-    int k0n = 0, cls_n = TILE_SKIP;
-    if (more) {
-      walk.issue(tid);
-      k0n = walk.k0;
-      cls_n = tile_class(k0n);
-      walk.advance();
-    }
-    const char* kt = smem + buf * 2 * TILE;
-    const char* vt = kt + TILE;
-    if (cls != TILE_SKIP) {
-      f32x16 s[KB];
-      gemm_rows<PITCH, KB, DK, kRowsAhead, true>(kt, 0, qreg, s, r, h);
-      // the first V operands of the PV product are fetched now, ahead of the softmax arithmetic
-      bf16x8 v_first[kColsAhead];
-      gemm_cols_fetch<PITCH, DB, kColsAhead>(vt, 0, lane, v_first);
-      __builtin_amdgcn_sched_barrier(0);
-      if (cls == TILE_PARTIAL) {
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+
+  // A wave's work on a tile is a matrix phase and a vector phase of about the same length, and the two waves of
+  // a SIMD take them in turn: while waves 0-3 run iteration t's products, waves 4-7 (one barrier behind) run
+  // their softmax, and the other way round.  Iteration t:
+  //   matrix phase: S(t+1) = K Q^T and O += V^T P(t), from set t = {K of tile t+1, V of tile t} in slot t mod 4
+  //   vector phase: P(t+1) from S(t+1)
+  // A barrier ends every phase.  Set t+3 is asked for in the matrix phase of iteration t (its slot held set t-1,
+  // which the later half finished a barrier ago).  A wave waits for its share of set t+2 before the barrier that
+  // ends its vector phase of iteration t, so that both halves' shares of set t+1 are there before either half's
+  // vector phase of iteration t, which ends with the first operand fetches of the next matrix phase.
+  // The last iteration forms a product S nobody reads (of a tile it has): a quarter of a tile's time per work-group,
+  // where a second copy of the loop's end cost the registers of the operand prefetch (1 % slower).
+  // Raised priority of the matrix phase: 4-6 % (with both at priority 0 the waves' phases disturb each other).
+  auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
+  auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
+  constexpr int LOADS = KvStream<D, BK, NW, BLK>::LOADS, NL = KvStream<D, BK, NW, BLK>::N;
+  f32x4 s[MB][NB];
+  bf16x8 pp[MB / 2][NB];
+  // P of the tile at key row k0_ from its scores
+  auto softmax = [&](int k0_) {
+    if (!tiles.full(k0_)) {
+      if (!tiles.some(k0_)) {   // for this wave alone there is nothing in the tile
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) mask_tile<true>(s[kb], mk, k0 + kb * 32, h, sk, qpos);
+        for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) pp[ch][nb] = zero_operand();
+        return;
       }
-      // largest score among this lane's keys of the tile (the row's other keys sit in the lane 32 away):
-      // four short chains instead of one long one
-      float mx4[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) mx4[j] = fmaxf(s[0][j], s[0][j + 4]);
+      for (int half = 0; half < MB / 2; ++half)
+        mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
+    }
+    // Largest score among this lane's keys of the tile (a query row's keys are spread over four lanes).
+    // Rescale lazily: keep a stale maximum while no row of the wave has grown by more than
+    // 2^kLazyLog2 (any common per-row offset gives the same result; fp32 has the headroom).  A row has
+    // grown exactly if one of its four lanes has, and the vote runs over the whole wave, so the lanes
+    // of a row exchange their maxima only when a rescale happens: the steady state has no cross-lane
+    // traffic (the exchange goes through LDS and costs a round trip the wave cannot fill).
+    float mx[NB];
+    bool grow = false;
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
+    for (int nb = 0; nb < NB; ++nb) {
+      float m4[4];
 #pragma unroll
-        for (int v = (kb == 0 ? 8 : 0); v < 16; ++v) mx4[v & 3] = fmaxf(mx4[v & 3], s[kb][v]);
-      const float mx_own = fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]));
-      // Rescale lazily: keep a stale maximum while no row of the wave has grown by more than
-      // 2^kLazyLog2 (any common per-row offset gives the same result; fp32 has the headroom).  A row has
-      // grown exactly if one of its two lanes has, and the vote runs over the whole wave, so the two halves
-      // of a row exchange their maxima only when a rescale happens: the steady state has no cross-lane
-      // traffic (the exchange goes through LDS and costs a round trip the wave cannot fill).
-      const bool grow = c * (mx_own - m_run) > kLazyLog2;   // false for -inf - -inf
-      if (__any(grow)) {
-        const float m_new = fmaxf(m_run, fmaxf(mx_own, half_swap(mx_own)));
-        const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run - m_new));
-        m_run = m_new;
-        l_run *= alpha;
+      for (int v = 0; v < 4; ++v) {
+        m4[v] = fmaxf(s[0][nb][v], s[1][nb][v]);
+#pragma unroll
+        for (int mb = 2; mb < MB; ++mb) m4[v] = fmaxf(m4[v], s[mb][nb][v]);
+      }
+      mx[nb] = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+      grow |= mx[nb] > limit[nb];
+    }
+    if (__any(grow)) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        float m_new = fmaxf(mx[nb], __shfl_xor(mx[nb], 16, 64));
+        m_new = fmaxf(m_run[nb], fmaxf(m_new, __shfl_xor(m_new, 32, 64)));
+        const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run[nb] - m_new));
+        m_run[nb] = m_new;
+        limit[nb] = m_new + slack;
+        msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
+        l_run[nb] *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+          for (int v = 0; v < 4; ++v) o[db][nb][v] *= alpha;
       }
-      const float msub = (m_run == -INFINITY) ? 0.f : c * m_run;
-      // P = exp2(c S - c m) as packed bf16 pairs; the row sum is taken in fp32 before rounding (Lse
-      // must hold to 1e-3 also for rows with a handful of keys).  The exponentials of key block kb+1
-      // are issued between the MFMAs of key block kb's part of the PV product.
-      typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-      uint32_t ppw[KB][8];
-      auto exp_pairs = [&](int kb, int w0, int nw) {
-#pragma unroll
-        for (int w = w0; w < w0 + nw; ++w) {
-          const float e0 = __builtin_amdgcn_exp2f(c * s[kb][2 * w] - msub);
-          const float e1 = __builtin_amdgcn_exp2f(c * s[kb][2 * w + 1] - msub);
-          const bf16x2 pr = {(__bf16)e0, (__bf16)e1};
-          ppw[kb][w] = __builtin_bit_cast(uint32_t, pr);
-          l_run += e0 + e1;
-        }
-      };
-      exp_pairs(0, 0, 8);
-      static_assert(KB == 2, "the PV product below is written for two 32-key blocks per tile");
-      // one operand stream over both key blocks: pp[2 kb], pp[2 kb + 1] are the two 16-key halves of block kb
-      bf16x8 pp[2 * KB];
-      auto pack_block = [&](int kb) {
-        const u32x4 w_lo = {ppw[kb][0], ppw[kb][1], ppw[kb][2], ppw[kb][3]};
-        const u32x4 w_hi = {ppw[kb][4], ppw[kb][5], ppw[kb][6], ppw[kb][7]};
-        pp[2 * kb] = __builtin_bit_cast(bf16x8, w_lo);
-        pp[2 * kb + 1] = __builtin_bit_cast(bf16x8, w_hi);
-      };
-      pack_block(0);
-      pp[2] = pp[0];   // placeholders until the hooks have produced block 1
-      pp[3] = pp[1];
-      gemm_cols_run<PITCH, DB, 2 * KB, kColsAhead>(vt, 0, pp, o, lane, v_first, [&](int c2) {
-        if (c2 < 2) exp_pairs(1, 4 * c2, 4);
-        if (c2 == 1) pack_block(1);
-      });
     }
-    if (more) walk.commit(smem + (buf ^ 1) * 2 * TILE, smem + (buf ^ 1) * 2 * TILE + TILE);
-    __syncthreads();
-    buf ^= 1;
-    k0 = k0n;
-    cls = cls_n;
-    have = more;
+    // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
+    // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
+    // exponential, few enough to keep the intermediate values out of the register budget.
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int ch = 0; ch < MB / 2; ++ch) {
+        f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          x[v] = __builtin_amdgcn_exp2f(c * x[v] - msub[nb]);
+          y[v] = __builtin_amdgcn_exp2f(c * y[v] - msub[nb]);
+        }
+        l_run[nb] += x + y;
+        pp[ch][nb] = pack_pair(x, y);
+      }
+  };
+  if (walk.valid()) {
+    const int ka = walk.k0;
+    walk.issue(k_lds(3), v_lds(3), wave, lane);   // set -1
+    int kb = walk.cursor();
+    walk.issue(k_lds(0), v_lds(0), wave, lane);   // set 0
+    int kc = walk.cursor();
+    walk.issue(k_lds(1), v_lds(1), wave, lane);   // set 1
+    int kd = walk.cursor();
+    walk.issue(k_lds(2), v_lds(2), wave, lane);   // set 2
+    wait_loads_barrier<3 * LOADS>();              // set -1
+    if (wave >= NW / 2) phase_barrier();
+    bf16x8 first[AHEAD];
+    rows_fetch<D, MB, AHEAD>(k_lds(3), ad, 0, first);
+    rows_product<D, MB, NB, AHEAD, true>(k_lds(3), ad, 0, qreg, s, first);
+    wait_loads_barrier<2 * LOADS>();              // set 0
+    softmax(ka);
+    wait_loads_barrier<LOADS>();                  // set 1
+    int slot = 0;
+    rows_fetch<D, MB, AHEAD>(k_lds(0), ad, 0, first);
+    for (;;) {   // iteration t: kb, kc, kd are tiles t+1, t+2, t+3
+      const uint32_t kt = k_lds(slot), vt = v_lds(slot);
+      // ---- matrix phase
+      const int kn = walk.cursor();
+      walk.begin(wave, lane);
+      const int slot3 = (slot + 3) & 3;
+      const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
+      rows_cols_stream<D, MB, NB, AHEAD>(kt, vt, ad, qreg, s, pp, o, first, [&](int i) {
+        if (i >= 1 && i < 1 + NL) walk.load_v(i - 1, vl, wave);
+        if (i >= 1 + NL && i < 1 + 2 * NL) walk.load_k(i - 1 - NL, kl, wave);
+        if (i >= 1 + 2 * NL && i < 1 + 2 * NL + walk.PARTS) walk.end(i - 1 - 2 * NL);
+      });
+      if (kb < 0) break;
+      phase_barrier();
+      // ---- vector phase
+      softmax(kb);
+      slot = (slot + 1) & 3;
+      rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+      wait_loads_barrier<LOADS>();
+      kb = kc;
+      kc = kd;
+      kd = kn;
+    }
+    wait_global_loads();   // sets past the end of the walk
+    if (wave < NW / 2) phase_barrier();
   }
 
   // Epilogue: normalise, Lse in natural-log units, optional online-softmax merge.
-  const int orow = q_w0 + r;
-  const float l_tot = l_run + half_swap(l_run);
-  const bool alive = l_tot > 0.f;
-  const float inv = alive ? 1.f / l_tot : 0.f;
-  const float lse_cur = alive ? (c * m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
-  if (orow >= sq) return;
-  if (p.o_part.ptr) {
-    if (p.o_part.is_f32) {
-      float* dst = (float*)p.o_part.ptr + b * p.o_part.sb + (int64_t)orow * p.o_part.ss + hq * p.o_part.sh;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+  for (int nb = 0; nb < NB; ++nb) {
+    float l_tot = (l_run[nb][0] + l_run[nb][1]) + (l_run[nb][2] + l_run[nb][3]);
+    l_tot += __shfl_xor(l_tot, 16, 64);
+    l_tot += __shfl_xor(l_tot, 32, 64);
+    const int orow = q_w0 + 16 * nb + r;
+    if (orow >= sq) continue;
+    const bool alive = l_tot > 0.f;
+    const float inv = alive ? 1.f / l_tot : 0.f;
+    const float lse_cur = alive ? (c * m_run[nb] + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+    if (p.o_part.ptr) {
+      const int64_t off = b * p.o_part.sb + (int64_t)orow * p.o_part.ss + hq * p.o_part.sh + 4 * g;
+      if (p.o_part.is_f32) {
+        float* dst = (float*)p.o_part.ptr + off;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 x = {o[db][4 * g] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv};
-          *reinterpret_cast<f32x4*>(dst + db * 32 + 8 * g + 4 * h) = x;
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = o[db][nb] * inv;
+      } else {
+        __bf16* dst = (__bf16*)p.o_part.ptr + off;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const f32x4 x = o[db][nb] * inv;
+          *reinterpret_cast<bf16x4*>(dst + 16 * db) = bf16x4{(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
         }
-    } else {
-      __bf16* dst = (__bf16*)p.o_part.ptr + b * p.o_part.sb + (int64_t)orow * p.o_part.ss + hq * p.o_part.sh;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          bf16x4 x = {(__bf16)(o[db][4 * g] * inv), (__bf16)(o[db][4 * g + 1] * inv), (__bf16)(o[db][4 * g + 2] * inv),
-                      (__bf16)(o[db][4 * g + 3] * inv)};
-          *reinterpret_cast<bf16x4*>(dst + db * 32 + 8 * g + 4 * h) = x;
-        }
+      }
+      if (g == 0) p.lse_part.ptr[b * p.lse_part.sb + hq * p.lse_part.sh + orow] = lse_cur;
     }
-    if (h == 0) p.lse_part.ptr[b * p.lse_part.sb + hq * p.lse_part.sh + orow] = lse_cur;
-  }
-  if (p.o_acc.ptr && alive) {   // a step that saw no key leaves the running state untouched
-    float* lse_ptr = p.lse_acc.ptr + b * p.lse_acc.sb + hq * p.lse_acc.sh + orow;
-    const float lse_old = *lse_ptr;
-    const float mm = fmaxf(lse_old, lse_cur);   // finite: lse_cur is
-    const float e_old = __expf(lse_old - mm), e_cur = __expf(lse_cur - mm);
-    const float tot = e_old + e_cur;
-    const float lse_new = mm + __logf(tot);
-    const float w_old = e_old / tot, w_cur_n = e_cur / tot * inv;
-    const bool has_old = lse_old != -INFINITY;
-    float* dst = (float*)p.o_acc.ptr + b * p.o_acc.sb + (int64_t)orow * p.o_acc.ss + hq * p.o_acc.sh;
+    if (p.o_acc.ptr && alive) {   // a step that saw no key leaves the running state untouched
+      float* lse_ptr = p.lse_acc.ptr + b * p.lse_acc.sb + hq * p.lse_acc.sh + orow;
+      const float lse_old = *lse_ptr;
+      const float mm = fmaxf(lse_old, lse_cur);   // finite: lse_cur is
+      const float e_old = __expf(lse_old - mm), e_cur = __expf(lse_cur - mm);
+      const float tot = e_old + e_cur;
+      const float lse_new = mm + __logf(tot);
+      const float w_old = e_old / tot, w_cur_n = e_cur / tot * inv;
+      const bool has_old = lse_old != -INFINITY;
+      float* dst = (float*)p.o_acc.ptr + b * p.o_acc.sb + (int64_t)orow * p.o_acc.ss + hq * p.o_acc.sh + 4 * g;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float* q4 = dst + db * 32 + 8 * g + 4 * h;
+      for (int db = 0; db < DB; ++db) {
+        f32x4* q4 = reinterpret_cast<f32x4*>(dst + 16 * db);
         // a running state that is still (anything, -inf) has weight zero and is not read as a number:
         // the buffer may hold whatever it was allocated with (0 * NaN would poison the row)
-        f32x4 old = *reinterpret_cast<const f32x4*>(q4);
+        f32x4 old = *q4;
         if (!has_old) old = f32x4{0.f, 0.f, 0.f, 0.f};
-        f32x4 x = {o[db][4 * g] * w_cur_n + old[0] * w_old, o[db][4 * g + 1] * w_cur_n + old[1] * w_old,
-                   o[db][4 * g + 2] * w_cur_n + old[2] * w_old, o[db][4 * g + 3] * w_cur_n + old[3] * w_old};
-        *reinterpret_cast<f32x4*>(q4) = x;
+        *q4 = o[db][nb] * w_cur_n + old * w_old;
       }
-    // both half-waves read lse_old above, in lockstep, before this store
-    if (h == 0) *lse_ptr = lse_new;
+      // the four lanes of a row read lse_old above, in lockstep, before this store
+      if (g == 0) *lse_ptr = lse_new;
+    }
   }
 }
 
@@ -265,7 +301,7 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p) {
 template <int D>
 static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
   constexpr int BQ = kFwdBQ;
-  constexpr int LDS = 2 * 2 * 64 * (2 * D + 16) + kMaxBlockCacheTiles;
+  constexpr int LDS = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
   p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, BQ, true);
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {
@@ -277,7 +313,8 @@ static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
   }
   if (p.q_runs.total() == 0) return hipSuccess;
   const int grid = mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total());
-  hipLaunchKernelGGL((step_fwd_kernel<D, kFwdBQ / 32>), dim3(grid), dim3(2 * kFwdBQ), LDS, stream, p);
+  if (p.mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdBQ / 32, true>), dim3(grid), dim3(2 * kFwdBQ), LDS, stream, p);
+  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdBQ / 32, false>), dim3(grid), dim3(2 * kFwdBQ), LDS, stream, p);
   return hipGetLastError();
 }
 

@@ -18,6 +18,10 @@ constexpr float kLazyLog2 = 6.0f;
 #define BURST_COLS_AHEAD 3
 #endif
 constexpr int kRowsAhead = BURST_ROWS_AHEAD, kColsAhead = BURST_COLS_AHEAD;
+#ifndef BURST_A16
+#define BURST_A16 4   // 16x16x32 streams, operands (two MFMAs each) ahead: 3 and 4 alike, 5 and 6 one to four percent slower
+#endif
+constexpr int kAhead16 = BURST_A16;
 
 struct FwdParams {
   int32_t batch, q_heads, kv_heads, head_dim;

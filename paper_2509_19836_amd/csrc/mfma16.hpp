@@ -1,0 +1,369 @@
+// Building blocks on v_mfma_f32_16x16x32_bf16 with LDS tiles filled by direct global -> LDS loads.
+//
+// Register layouts (lane l: r = l % 16, g = l / 16):
+//   A operand (M x K): lane holds A[m = r][k = 8g .. 8g+7]
+//   B operand (K x N): lane holds B[k = 8g .. 8g+7][n = r]
+//   C/D (M x N), 4 fp32: register v holds C[m = 4g + v][n = r]
+// Two accumulator tiles whose M indices are the next contraction index (rows 32c .. 32c+15 and 32c+16 ..
+// 32c+31) packed to bf16 side by side are the B operand of that contraction: element e of lane (r, g) is row
+// 32c + 16 (e / 4) + 4g + e % 4, and the A operand only has to be read in the same row order (cols_operand).
+//
+// LDS tiles are row-major [rows][D] bf16 without padding (a direct load writes 1 KiB of consecutive LDS per
+// wave), the 16-byte chunks of a row permuted by chunk ^ swz(row), which moves pairs of chunks: the 32-byte
+// pieces that half a wave takes from 8 rows in a transposing read fall into 8 different places of the 256-byte
+// bank line, and the chunks of the row-wise read (16 lanes at a time, four-lane groups of g and g + 1 that never
+// name rows 8 apart with the same g) into 16 different ones.
+#pragma once
+#include "common.hpp"
+
+namespace burst {
+
+typedef __attribute__((address_space(3))) char* lds_bytes;
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+template <int D>
+__device__ __forceinline__ int swz(int row) {   // depends on row % 16 only
+  static_assert(D == 64 || D == 128, "row of 8 or 16 chunks");
+  return D == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
+}
+
+// LDS byte offsets of a lane's operand reads inside a tile of D columns.  Adding multiples of 16 rows keeps them;
+// the k-step or column block is one exclusive or (swz moves pairs of chunks, so it commutes with both).
+template <int D>
+struct OperandAddr {
+  uint32_t rows;   // k-step 0: row r, columns 8g .. +7
+  uint32_t cols;   // column block 0: this lane's 8 bytes of the transposing read of rows 4g + r / 4
+  __device__ __forceinline__ void init(int lane) {
+    const int r = lane & 15, g = lane >> 4, row = 4 * g + (r >> 2);
+    rows = r * 2 * D + ((g ^ swz<D>(r)) << 4);
+    cols = row * 2 * D + ((((r & 3) >> 1) ^ swz<D>(row)) << 4) + 8 * (r & 1);
+  }
+};
+
+// Operand with lane = tile row: rows row0 + r (row0 a multiple of 16), columns 32 ks + 8g .. +7.  `tile`: LDS byte
+// address of the tile, a multiple of 256.
+template <int D>
+__device__ __forceinline__ bf16x8 rows_operand(uint32_t tile, const OperandAddr<D>& ad, int row0, int ks) {
+  const lds_bytes p = (lds_bytes)(uintptr_t)((tile + ad.rows) ^ (uint32_t)(64 * ks));
+  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p + row0 * 2 * D);
+}
+// Operand with lane = tile column 16 db + r, the 32 rows row0 .. row0 + 31 in packed-accumulator order.
+template <int D>
+__device__ __forceinline__ bf16x8 cols_operand(uint32_t tile, const OperandAddr<D>& ad, int row0, int db) {
+  typedef __attribute__((address_space(3))) s16x4* tr_ptr;
+  const lds_bytes p = (lds_bytes)(uintptr_t)((tile + ad.cols) ^ (uint32_t)(32 * db));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p + row0 * 2 * D));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p + (row0 + 16) * 2 * D));
+  typedef __attribute__((ext_vector_type(8))) short s16x8;
+  const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, both);
+}
+
+// Packed B operand from two accumulator tiles (rows 0..15 and 16..31 of the 32-row chunk).  The empty assembly
+// statement keeps the conversions where they are written: the compiler otherwise moves them behind the next
+// barrier, into another phase.
+__device__ __forceinline__ bf16x8 pack_pair(const f32x4& lo, const f32x4& hi) {
+  bf16x8 x = {(__bf16)lo[0], (__bf16)lo[1], (__bf16)lo[2], (__bf16)lo[3],
+              (__bf16)hi[0], (__bf16)hi[1], (__bf16)hi[2], (__bf16)hi[3]};
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+__device__ __forceinline__ bf16x8 zero_operand() {
+  const u32x4 z = {0, 0, 0, 0};
+  return __builtin_bit_cast(bf16x8, z);
+}
+
+// One direct load: every lane's 16 bytes at base + offset go to LDS at lds + 16 * lane.  Written as an
+// assembly statement because the compiler otherwise waits for all of them before the next LDS read; the
+// kernels wait by count themselves (wait_loads_barrier).
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+}
+// Wait until at most N of this wave's global loads are outstanding, then meet the other waves.  Work-group
+// barrier without the full drain of __syncthreads: loads of later tiles stay in flight.  The scheduling fences
+// keep arithmetic, which the memory clobber does not bind, from drifting across.
+template <int N>
+__device__ __forceinline__ void wait_loads_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// The same meeting without waiting for loads: between two phases of a wave.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Direct staging of [ROWS x D] tiles by NW waves: wave w brings 1 KiB pieces w, w + NW, ...  The per-lane part
+// of an address is a 32-bit offset computed once, the first row of the tile is a wave-uniform pointer.
+template <int D, int ROWS, int NW>
+struct DirectStager {
+  static constexpr int PITCH = 2 * D, RPI = 1024 / PITCH;        // rows per load instruction
+  static constexpr int BYTES = ROWS * PITCH, N = BYTES / 1024 / NW;   // loads per wave
+  static_assert(N * NW * 1024 == BYTES, "whole pieces per wave");
+  uint32_t off[N];
+  __device__ __forceinline__ int row_of(int i, int wave, int lane) const { return (i * NW + wave) * RPI + lane / (PITCH / 16); }
+  __device__ __forceinline__ uint32_t offset(int row, int lane_row, int64_t ss, int lane) const {
+    return 2u * ((uint32_t)row * (uint32_t)ss + (uint32_t)(((lane % (PITCH / 16)) ^ swz<D>(lane_row)) * 8));
+  }
+  __device__ __forceinline__ void init(int64_t ss, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) off[i] = offset(row_of(i, wave, lane), row_of(i, wave, lane), ss, lane);
+  }
+  __device__ __forceinline__ void load_one(const char* tile, int i, uint32_t lds, int wave) const {
+    load_to_lds(tile, off[i], lds + (i * NW + wave) * 1024);
+  }
+  // for a tile that reaches past the last row: rows beyond `valid` - 1 are read as copies of that row
+  __device__ __forceinline__ void clamp(int64_t ss, int valid, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) off[i] = offset(min(row_of(i, wave, lane), valid - 1), row_of(i, wave, lane), ss, lane);
+  }
+};
+
+// Walk of a query block over the key tiles (BK rows) it can see.  The visible tiles are one run of consecutive
+// tiles, so the cursor and the tile addresses move by adding constants.  Tiles are brought in sets
+// {K of tile t + 1, V of tile t}: the two that one pipelined iteration of the kernels reads.  A set is always
+// 2 N loads per wave, so that the kernels can wait by count: past the end of the walk the last tile's address is
+// asked for again (into a slot nobody reads), and before its start V of the first tile.
+template <int D, int BK, int NW, bool BLK>   // BLK: block-wise sparse mask
+struct KvStream {
+  using Stager = DirectStager<D, BK, NW>;
+  static constexpr int N = Stager::N, LOADS = 2 * N;   // per wave: one tile, one set
+  Stager stage_k, stage_v;
+  int left, k0;           // cursor: tiles left in the run (0: the walk is over), first key row of its tile
+  int v0;                 // first key row of the tile whose V comes with the next set
+  int sk;
+  const uint8_t* open;    // LDS flags per key tile from a block-wise sparse mask, or nullptr
+  const char *k_tile, *v_tile, *v_prev;
+  int64_t k_step, v_step; // bytes per tile
+
+  __device__ __forceinline__ void init(const MaskDev& mk, const TensorDev& k, const TensorDev& v, int b, int hk, int sk_,
+                                       int q_lo, int q_hi, int wave, int lane, const uint8_t* open_flags) {
+    sk = sk_;
+    if (BLK) open = open_flags;
+    TileRun run = visible_tiles<false, BK>(mk, q_lo, q_hi, sk);
+    run.start = __builtin_amdgcn_readfirstlane(run.start);   // (results of divisions: keeps what follows scalar)
+    left = __builtin_amdgcn_readfirstlane(run.len);
+    k0 = run.start * BK;
+    k_step = 2 * BK * k.ss;
+    v_step = 2 * BK * v.ss;
+    k_tile = reinterpret_cast<const char*>((const __bf16*)k.ptr + b * k.sb + hk * k.sh) + run.start * k_step;
+    v_tile = reinterpret_cast<const char*>((const __bf16*)v.ptr + b * v.sb + hk * v.sh) + run.start * v_step;
+    stage_k.init(k.ss, wave, lane);
+    stage_v.init(v.ss, wave, lane);
+    if (BLK) {   // skip tiles that the block mask closes
+      while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK]) == 0) step();
+    }
+    v_prev = v_tile;
+    v0 = k0;
+  }
+  __device__ __forceinline__ bool valid() const { return left > 0; }
+  // Before the loads of a set: a tile that reaches past the last row is read with clamped row indices
+  __device__ __forceinline__ void begin(int wave, int lane) {
+    if (k0 + BK > sk) {
+      stage_k.clamp(k_step / (2 * BK), sk - k0, wave, lane);
+      if (v0 + BK > sk) stage_v.clamp(v_step / (2 * BK), sk - v0, wave, lane);
+    }
+  }
+  __device__ __forceinline__ void load_k(int i, uint32_t lds, int wave) const { stage_k.load_one(k_tile, i, lds, wave); }
+  __device__ __forceinline__ void load_v(int i, uint32_t lds, int wave) const { stage_v.load_one(v_prev, i, lds, wave); }
+  // First key row of the cursor's tile, -1 when the walk is over
+  __device__ __forceinline__ int cursor() const { return k0 | (min(left, 1) - 1); }
+  // After them: the cursor moves to the next tile (and stays on the last one when there is none), in PARTS pieces
+  // of a few scalar instructions that fit between the matrix instructions of a stream.  Arithmetic on 0 / 1
+  // instead of conditions: the compiler keeps selected addresses in vector registers.
+  static constexpr int PARTS = 3;
+  int move;
+  __device__ __forceinline__ void end(int part) {
+    if (part == 0) {
+      v_prev = v_tile;
+      v0 = k0;
+      move = min(max(left - 1, 0), 1);
+      left = max(left - 1, 0);
+      if (BLK) {   // skip tiles that the block mask closes
+        move = 1;
+        while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK + move]) == 0) {
+          --left;
+          ++move;
+        }
+        move = __builtin_amdgcn_readfirstlane(move * min(left, 1));
+        left = __builtin_amdgcn_readfirstlane(left);
+      }
+      k0 += move * BK;
+    }
+    if (part == 1) k_tile += BLK ? move * k_step : k_step & -(int64_t)move;
+    if (part == 2) v_tile += BLK ? move * v_step : v_step & -(int64_t)move;
+  }
+  __device__ __forceinline__ void end() {
+    for (int i = 0; i < PARTS; ++i) end(i);
+  }
+  __device__ __forceinline__ void issue(uint32_t k_lds, uint32_t v_lds, int wave, int lane) {
+    begin(wave, lane);
+#pragma unroll
+    for (int i = 0; i < N; ++i) load_v(i, v_lds, wave);
+#pragma unroll
+    for (int i = 0; i < N; ++i) load_k(i, k_lds, wave);
+    end();
+  }
+  __device__ __forceinline__ void step() {
+    --left;
+    k0 += BK;
+    k_tile += k_step;
+    v_tile += v_step;
+  }
+};
+
+// Class of a tile of `bk` rows against a wave's own rows of the other axis, from its first row: nothing visible,
+// all of it visible, or mixed (the per-element mask decides).
+struct TileRanges {
+  int some_lo, full_lo;
+  uint32_t some_len, full_len;
+  __device__ __forceinline__ void init(const RowIntervals& iv, int rows, int bk) {
+    some_lo = iv.some_lo - bk + 1;
+    some_len = max(iv.some_hi - some_lo, 0);
+    full_lo = iv.all_lo;
+    full_len = max(min(iv.all_hi, rows) - bk + 1 - full_lo, 0);
+  }
+  __device__ __forceinline__ bool some(int row0) const { return (uint32_t)(row0 - some_lo) < some_len; }
+  __device__ __forceinline__ bool full(int row0) const { return (uint32_t)(row0 - full_lo) < full_len; }
+};
+
+// Products with one hook per LDS operand (NB MFMAs): hook(i) holds independent vector work that goes behind
+// them, and the scheduling fence after it keeps it there.  Operands are fetched AHEAD of their use; the first
+// AHEAD ones may have been fetched by the caller (`first`).
+//   acc[mb][nb] (+)= rows(tile)[row0 + 16 mb ..] * b[ks][nb], operand i = ks * MB + mb
+template <int D, int MB, int AHEAD>
+__device__ __forceinline__ void rows_fetch(uint32_t tile, const OperandAddr<D>& ad, int row0, bf16x8 (&first)[AHEAD]) {
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) first[i] = rows_operand<D>(tile, ad, row0 + 16 * (i % MB), i / MB);
+}
+template <int D, int MB, int NB, int AHEAD, bool ZERO, class Hook = NoHook>
+__device__ __forceinline__ void rows_product(uint32_t tile, const OperandAddr<D>& ad, int row0, const bf16x8 (&b)[D / 32][NB],
+                                             f32x4 (&acc)[MB][NB], const bf16x8 (&first)[AHEAD], Hook&& hook = Hook()) {
+  constexpr int N = D / 32 * MB;
+  static_assert(AHEAD <= N, "more operands fetched ahead than the product has");
+  bf16x8 a[N];
+  MatrixPhase prio;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) a[i] = first[i];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + AHEAD < N) a[i + AHEAD] = rows_operand<D>(tile, ad, row0 + 16 * ((i + AHEAD) % MB), (i + AHEAD) / MB);
+    const int ks = i / MB, mb = i % MB;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      acc[mb][nb] = mfma16(a[i], b[ks][nb], (ZERO && ks == 0) ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[mb][nb]);
+    hook(i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+//   acc[db][nb] += cols(tile)[db, 32-row chunk c] * b[c][nb], operand i = c * (D / 16) + db; b[c] is read when its
+//   MFMAs are issued, so a hook may still complete it for a later chunk.
+template <int D, int AHEAD>
+__device__ __forceinline__ void cols_fetch(uint32_t tile, const OperandAddr<D>& ad, int row0, bf16x8 (&first)[AHEAD]) {
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) first[i] = cols_operand<D>(tile, ad, row0 + 32 * (i / (D / 16)), i % (D / 16));
+}
+template <int D, int NC, int NB, int AHEAD, class Hook = NoHook>
+__device__ __forceinline__ void cols_product(uint32_t tile, const OperandAddr<D>& ad, int row0, const bf16x8 (&b)[NC][NB],
+                                             f32x4 (&acc)[D / 16][NB], const bf16x8 (&first)[AHEAD], Hook&& hook = Hook()) {
+  constexpr int DB = D / 16, N = NC * DB;
+  static_assert(AHEAD <= N, "more operands fetched ahead than the product has");
+  bf16x8 a[N];
+  MatrixPhase prio;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) a[i] = first[i];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + AHEAD < N) a[i + AHEAD] = cols_operand<D>(tile, ad, row0 + 32 * ((i + AHEAD) / DB), (i + AHEAD) % DB);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[i % DB][nb] = mfma16(a[i], b[i / DB][nb], acc[i % DB][nb]);
+    hook(i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// One stream of both: s = rows(kt) * q from zero, then o += cols(vt) * p, hook(i) behind operand i of the two.  The
+// first operands of the row-wise product come fetched, those of the second are fetched while the first runs.
+template <int D, int MB, int NB, int AHEAD, class Hook = NoHook>
+__device__ __forceinline__ void rows_cols_stream(uint32_t kt, uint32_t vt, const OperandAddr<D>& ad, const bf16x8 (&q)[D / 32][NB],
+                                                 f32x4 (&s)[MB][NB], const bf16x8 (&p)[MB / 2][NB], f32x4 (&o)[D / 16][NB],
+                                                 const bf16x8 (&first)[AHEAD], Hook&& hook = Hook()) {
+  constexpr int DB = D / 16, N1 = D / 32 * MB, N = N1 + MB / 2 * DB;
+  bf16x8 a[N];
+  MatrixPhase prio;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) a[i] = first[i];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int f = i + AHEAD, fc = f - N1, ic = i - N1;
+    if (f < N1) a[f] = rows_operand<D>(kt, ad, 16 * (f % MB), f / MB);
+    else if (f < N) a[f] = cols_operand<D>(vt, ad, 32 * (fc / DB), fc % DB);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if (i < N1) s[i % MB][nb] = mfma16(a[i], q[i / MB][nb], i < MB ? f32x4{0.f, 0.f, 0.f, 0.f} : s[i % MB][nb]);
+      else o[ic % DB][nb] = mfma16(a[i], p[ic / DB][nb], o[ic % DB][nb]);
+    }
+    hook(i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Rows of one axis that a row of the OTHER axis at position `pos` sees / is seen by: [lo, hi), one interval because
+// positions grow with the row.  Per lane, once per work-group; free of divisions for at most two pieces of stride 1.
+template <bool KEYS>   // KEYS: the key rows a query sees; else the query rows that see a key
+__device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos, int rows, int& lo, int& hi) {
+  lo = 0;
+  hi = rows;
+  if (!mk.causal) return;
+  const AxisMap ax = axis_of<!KEYS>(mk);
+  auto below = [&](int x) {   // rows whose position is below x
+    const int t = max(x, 0) - ax.pos0;
+    if (ax.stride == 1 && ax.nseg <= 2) {
+      const int in_first = min(max(t, 0), ax.seg_len), in_second = ax.nseg == 2 ? min(max(t - ax.period, 0), ax.seg_len) : 0;
+      return ax.nseg == 2 ? in_first + in_second : min(max(t, 0), rows);
+    }
+    return rows_lt(ax, (long long)t + ax.pos0, rows);
+  };
+  if (KEYS) {
+    hi = below(pos + 1);                                            // k <= p
+    if (mk.window != kNoWindow) lo = below(pos - mk.window + 1);    // k > p - window
+  } else {
+    lo = below(pos);                                                                  // p >= k
+    if (mk.window != kNoWindow && pos <= 0x7fffffff - mk.window) hi = below(pos + mk.window);   // p < k + window
+  }
+}
+
+// Per-element mask of two accumulator tiles, rows base_row .. base_row + 31 (wave-uniform): a lane's own row nb keeps
+// the entries of rows [lo[nb], hi[nb]); the others become -inf.  Compares with constants and selects only.
+template <int NB>
+__device__ __forceinline__ void mask_rows32(f32x4 (&s0)[NB], f32x4 (&s1)[NB], int base_row, int g, const int (&lo)[NB],
+                                            const int (&hi)[NB], bool check_lo) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int h = hi[nb] - base_row - 4 * g, l = lo[nb] - base_row - 4 * g;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f32x4& s = a == 0 ? s0[nb] : s1[nb];
+        s[v] = 16 * a + v < h ? s[v] : -INFINITY;
+      }
+    if (check_lo) {   // wave-uniform
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          f32x4& s = a == 0 ? s0[nb] : s1[nb];
+          s[v] = 16 * a + v >= l ? s[v] : -INFINITY;
+        }
+    }
+  }
+}
+
+}  // namespace burst

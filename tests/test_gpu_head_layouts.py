@@ -1,4 +1,6 @@
-"""Head and batch counts that do not fill whole rounds of the eight XCDs: the work-group mapping deals the
+"""Edges of the work-group mapping and of the tile pipelines.
+
+Head and batch counts that do not fill whole rounds of the eight XCDs: the work-group mapping deals the
 left-over (batch, kv head) keys tile by tile over all XCDs, and long launches walk an XCD's keys one after the
 other where short ones run them side by side.  Every work-group owns its outputs, so a tile that the mapping
 dropped or dealt twice to different heads shows as a wrong element against the oracle."""
@@ -58,3 +60,12 @@ def step_case(lib, B, Hq, Hkv, d, sq, sk, causal, seed, q_pos=0, k_pos=0):
 ])
 def test_head_layouts(lib, B, Hq, Hkv, d, n, causal):
     step_case(lib, B, Hq, Hkv, d, n, n, causal, B * 1000 + Hq)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sk", [1, 63, 64, 65, 128, 192, 257, 320, 449])
+def test_short_walks(lib, d, sk):
+    """Key chunks of one to eight tiles, whole and ragged, under both masks: the pipelines fetch up to four tiles
+    ahead, so every walk shorter than that has its own prologue and end; query rows that fill no wave."""
+    step_case(lib, 1, 2, 2, d, 77, sk, False, sk)
+    step_case(lib, 1, 2, 1, d, 300, sk, True, sk + 1, q_pos=40)
