@@ -4,11 +4,13 @@
 //
 // Two kernels, each owning its outputs outright (no atomics, results are run-to-run identical):
 //
-//  * dQ kernel, query-stationary (same orientation as the forward kernel): a lane owns one query
-//    row; S^T = K Q^T and dP^T = V dO^T come out with the key index in the accumulator registers,
-//    dS^T is packed to bf16 in place and fed back as the B operand of dQ^T = K^T dS^T, whose A
-//    operand is the K tile read column-wise (transposing LDS reads) from the same LDS copy that
-//    served S^T row-wise.
+//  * dQ kernel, query-stationary, the forward kernel's structure (16x16x32 MFMAs, direct LDS loads, the two waves of
+//    a SIMD taking matrix and vector phases in turn): S^T = K Q^T and dP^T = V dO^T come out with the key index
+//    in the accumulator registers, dS^T is packed to bf16 in place and fed back as the B operand of
+//    dQ^T = K^T dS^T, whose A operand is the K tile read column-wise (transposing LDS reads) from the same LDS
+//    copy that served S^T row-wise.  Bound by the matrix pipe under the chip's power limit: 96 MFMAs of 16 clocks
+//    per tile and wave against about 900 clocks of vector work, which the other wave's matrix phase hides.
+//    128K-token ring backward (dQ and dK/dV): 56.3 -> 52.6 ms against the 32x32x16 kernel with register staging.
 //
 //  * dK/dV kernel, key-stationary: a lane owns one key row; K and V rows live in registers as B
 //    operands, S = Q K^T and dP = dO V^T come out with the query index in the accumulator registers,
@@ -18,6 +20,7 @@
 //    group, so dK and dV are summed over the group in registers.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma16.hpp"
 
 namespace burst {
 
@@ -25,9 +28,6 @@ namespace burst {
 #define BURST_FOLD_SCALE 1   // dK/dV kernel: softmax scale folded into the K operand (see dkdv_role)
 #endif
 constexpr bool kFoldScale = BURST_FOLD_SCALE != 0;
-#ifndef BURST_DQ_KB
-#define BURST_DQ_KB 2   // 32-row key blocks per LDS tile of the dQ kernel
-#endif
 #ifndef BURST_DQ_BQ
 #define BURST_DQ_BQ 256
 #endif
@@ -42,122 +42,173 @@ __device__ __forceinline__ void zero16(f32x16& x) {
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int KB, int NW>
+template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(BwdParams p) {
-  constexpr int BK = 32 * KB, DK = D / 16, DB = D / 32, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int PITCH = 2 * D + 16;
-  constexpr int TILE = BK * PITCH;
-  extern __shared__ __attribute__((aligned(16))) char smem[];  // [2 buffers][K tile, V tile]
+  constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
+  constexpr int TILE = BK * 2 * D, SLOTS = 4, AHEAD = BLK ? 3 : kAhead16;   // (the block flags take the registers of one operand)
+  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
 
   const int group = p.q_heads / p.kv_heads;
   const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total());
   if (!bm.valid) return;
-  const int b = bm.key / p.kv_heads, hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
+  const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
 
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: everything derived from it stays wave-uniform
   const int sq = p.sq, sk = p.sk;
   const MaskDev mk = p.mask;
   const int q_blk0 = p.q_runs.tile_of(bm.tile) * BQ, q_blk1 = min(q_blk0 + BQ, sq);
   const int q_w0 = q_blk0 + wave * 32, q_w1 = min(q_w0 + 32, sq);
 
-  const int row = min(q_w0 + r, sq - 1);
-  const int qpos = axis_position(axis_of<true>(mk), row);
-  bf16x8 qreg[DK], doreg[DK];
-  {
-    const __bf16* qs = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * h;
-    const __bf16* gs = (const __bf16*)p.d_o.ptr + b * p.d_o.sb + hq * p.d_o.sh + (int64_t)row * p.d_o.ss + 8 * h;
+  // Q and dO as B operands: lane holds rows q_w0 + 16 nb + r, columns 32 ks + 8g .. +7
+  bf16x8 qreg[DK][NB], doreg[DK][NB];
+  int klo[NB], khi[NB];   // key rows that the lane's query rows see
+  float lse2[NB], dval[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = min(q_w0 + 16 * nb + r, sq - 1);
+    visible_rows<true>(mk, axis_position(axis_of<true>(mk), row), sk, klo[nb], khi[nb]);
+    const __bf16* qs = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * g;
+    const __bf16* gs = (const __bf16*)p.d_o.ptr + b * p.d_o.sb + hq * p.d_o.sh + (int64_t)row * p.d_o.ss + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) {
-      qreg[ks] = *reinterpret_cast<const bf16x8*>(qs + ks * 16);
-      doreg[ks] = *reinterpret_cast<const bf16x8*>(gs + ks * 16);
+      qreg[ks][nb] = *reinterpret_cast<const bf16x8*>(qs + ks * 32);
+      doreg[ks][nb] = *reinterpret_cast<const bf16x8*>(gs + ks * 32);
     }
+    lse2[nb] = lse_to_log2(p.lse.ptr[b * p.lse.sb + hq * p.lse.sh + row]);
+    dval[nb] = p.d.ptr[b * p.d.sb + hq * p.d.sh + row];
   }
-  const float lse2 = lse_to_log2(p.lse.ptr[b * p.lse.sb + hq * p.lse.sh + row]);
-  const float dval = p.d.ptr[b * p.d.sb + hq * p.d.sh + row];
   const float c = p.scale * kLog2e;
 
-  f32x16 dq[DB];
+  f32x4 dq[DB][NB];
 #pragma unroll
-  for (int db = 0; db < DB; ++db) zero16(dq[db]);
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) dq[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Key tiles the work-group can see, and the class of each against this wave's 32 query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
   range_minmax<true>(mk, q_blk0, q_blk1, qlo_blk, qhi_blk);
   if (q_w0 < q_w1) range_minmax<true>(mk, q_w0, q_w1, qlo_w, qhi_w);
-  BlockClassifier<false> k_class;
-  k_class.init(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1);
-  auto tile_class = [&](int k0_) { return k_class(mk, k0_, min(k0_ + BK, sk), k0_ + BK > sk); };   // wave-uniform
+  TileRanges tiles;
+  tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
 
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
-  if (mk.blk) {
-    open_flags = reinterpret_cast<uint8_t*>(smem + 4 * TILE);
+  if (BLK) {
+    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE);
     fill_open_flags<true, BK>(mk, open_flags, q_blk0, sk, tid, NT);
     __syncthreads();
   }
-  KvWalk<D, BK, NT> walk;
-  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, tid, open_flags);
+  OperandAddr<D> ad;
+  ad.init(lane);
+  KvStream<D, BK, NW, BLK, false> walk;
+  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
   wait_global_loads();
-  int k0 = 0, cls = TILE_SKIP;   // first key row and class of the tile in LDS
-  bool have = walk.valid();
-  if (have) {
-    walk.issue(tid);
-    walk.commit(smem, smem + TILE);
-    k0 = walk.k0;
-    cls = tile_class(k0);
-    walk.advance();
-  }
-  __syncthreads();
-  int buf = 0;
-  while (have) {
-    const bool more = walk.valid();
-    int k0n = 0, cls_n = TILE_SKIP;
-    if (more) {
-      walk.issue(tid);
-      k0n = walk.k0;
-      cls_n = tile_class(k0n);
-      walk.advance();
-    }
-    const char* kt = smem + buf * 2 * TILE;
-    const char* vt = kt + TILE;
-    if (cls != TILE_SKIP) {
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+
+  // The two waves of a SIMD take a tile's matrix phase and its vector phase in turn, as in the forward kernel:
+  // waves 4-7 run one barrier behind waves 0-3.  Iteration t, tile t in slot t mod 4:
+  //   matrix phase: dQ += K(t)^T dS(t), then S(t+1) = K Q^T and dP(t+1) = V dO^T
+  //   vector phase: dS(t+1)
+  // A barrier ends every phase.  Tile t+3 is asked for in the matrix phase of iteration t (its slot held tile
+  // t-1, which the later half finished a barrier ago).  At the end of that phase a wave waits for its share of tile
+  // t+2, so that both halves' shares are there a barrier before either half's products of iteration t+1 read it.
+  auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
+  auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
+  constexpr int LOADS = KvStream<D, BK, NW, BLK, false>::LOADS, NL = KvStream<D, BK, NW, BLK, false>::N;
+  f32x4 s[MB][NB], dp[MB][NB];
+  bf16x8 ds[MB / 2][NB];
+  // dS of the tile at key row k0_ from its scores and dP
+  auto d_scores = [&](int k0_) {
+    if (!tiles.full(k0_)) {
+      if (!tiles.some(k0_)) {   // for this wave alone there is nothing in the tile
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        f32x16 sd[2];   // S^T and dP^T of this key block: two independent accumulator chains
+        for (int ch = 0; ch < MB / 2; ++ch)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sd[1][v] = -dval;   // dP - D comes out of the GEMM: the lane owns the row, D is its constant
-        gemm_rows_pair<PITCH, DK, kRowsAhead, true>(kt, vt, kb * 32, qreg, doreg, sd[0], sd[1], r, h);   // sd[0] starts from a literal zero
-        if (cls == TILE_PARTIAL) mask_tile<true>(sd[0], mk, k0 + kb * 32, h, sk, qpos);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float pr = __builtin_amdgcn_exp2f(c * sd[0][v] - lse2);
-          sd[0][v] = pr * sd[1][v];
-        }
-        bf16x8 ds[2] = {pack8(sd[0], 0), pack8(sd[0], 1)};
-        gemm_cols<PITCH, DB, 2, kColsAhead>(kt, kb * 32, ds, dq, lane);
+          for (int nb = 0; nb < NB; ++nb) ds[ch][nb] = zero_operand();
+        return;
       }
+#pragma unroll
+      for (int half = 0; half < MB / 2; ++half)
+        mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
     }
-    if (more) walk.commit(smem + (buf ^ 1) * 2 * TILE, smem + (buf ^ 1) * 2 * TILE + TILE);
-    __syncthreads();
-    buf ^= 1;
-    k0 = k0n;
-    cls = cls_n;
-    have = more;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int ch = 0; ch < MB / 2; ++ch) {
+        f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (dp[2 * ch][nb][v] - dval[nb]);
+          y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (dp[2 * ch + 1][nb][v] - dval[nb]);
+        }
+        ds[ch][nb] = pack_pair(x, y);
+      }
+  };
+  if (walk.valid()) {
+    const int ka = walk.k0;
+    walk.issue(k_lds(0), v_lds(0), wave, lane);
+    int kb = walk.cursor();
+    walk.issue(k_lds(1), v_lds(1), wave, lane);
+    int kc = walk.cursor();
+    walk.issue(k_lds(2), v_lds(2), wave, lane);
+    wait_loads_barrier<2 * LOADS>();              // tile 0
+    if (wave >= NW / 2) phase_barrier();
+    bf16x8 first[AHEAD];
+    rows_fetch<D, MB, AHEAD>(k_lds(0), ad, 0, first);
+    rows_product_pair<D, MB, NB, AHEAD>(k_lds(0), v_lds(0), ad, qreg, doreg, s, dp, first);
+    wait_loads_barrier<LOADS>();                  // tile 1
+    d_scores(ka);
+    int slot = 0;
+    cols_fetch<D, AHEAD>(k_lds(0), ad, 0, first);
+    phase_barrier();
+    for (;;) {   // iteration t: kb, kc are the first rows of tiles t+1, t+2
+      // ---- matrix phase
+      const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
+      const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
+      const int kn = walk.cursor();
+      walk.begin(wave, lane);
+      bf16x8 first_rows[AHEAD];
+      constexpr int NCOLS = MB / 2 * DB;
+      cols_product<D, MB / 2, NB, AHEAD>(k_lds(slot), ad, 0, ds, dq, first, [&](int i) {
+        if (i < NL) walk.load_v(i, vl, wave);
+        if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
+        if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
+        if (i >= NCOLS - AHEAD) {
+          const int f = i - (NCOLS - AHEAD);
+          first_rows[f] = rows_operand<D>(k_lds(slot1), ad, 16 * (f % MB), f / MB);
+        }
+      });
+      if (kb < 0) break;
+      rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first_rows);
+      wait_loads_barrier<LOADS>();                // tile t+2
+      // ---- vector phase
+      d_scores(kb);
+      slot = slot1;
+      cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+      phase_barrier();
+      kb = kc;
+      kc = kn;
+    }
+    wait_global_loads();   // tiles past the end of the walk
+    if (wave < NW / 2) phase_barrier();
   }
 
-  if (q_w0 + r < sq) {
-    float* dst = (float*)p.dq.ptr + b * p.dq.sb + (int64_t)(q_w0 + r) * p.dq.ss + hq * p.dq.sh;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = q_w0 + 16 * nb + r;
+    if (row >= sq) continue;
+    float* dst = (float*)p.dq.ptr + b * p.dq.sb + (int64_t)row * p.dq.ss + hq * p.dq.sh + 4 * g;
+    f32x4 old[DB];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float* q4 = dst + db * 32 + 8 * g + 4 * h;
-        f32x4 x = {dq[db][4 * g] * p.scale, dq[db][4 * g + 1] * p.scale, dq[db][4 * g + 2] * p.scale,
-                   dq[db][4 * g + 3] * p.scale};
-        if (p.acc_dq) x += *reinterpret_cast<const f32x4*>(q4);
-        *reinterpret_cast<f32x4*>(q4) = x;
-      }
+    for (int db = 0; db < DB; ++db) old[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (p.acc_dq) {   // all loads before the first store
+#pragma unroll
+      for (int db = 0; db < DB; ++db) old[db] = *reinterpret_cast<const f32x4*>(dst + 16 * db);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = dq[db][nb] * p.scale + old[db];
   }
 }
 
@@ -534,8 +585,7 @@ __global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
 template <int D>
 static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  constexpr int KB = BURST_DQ_KB;
-  constexpr int LDS = 2 * 2 * 32 * KB * (2 * D + 16) + kMaxBlockCacheTiles;
+  constexpr int LDS = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
   p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, kDqBQ, true);
   // query tiles that see no key get no work-group: "=" must still leave zeros there
   if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ) {
@@ -544,7 +594,8 @@ static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
   }
   if (p.q_runs.total() == 0) return hipSuccess;
   const int grid = mapped_grid(n_keys, group, p.q_runs.total());
-  hipLaunchKernelGGL((step_bwd_dq_kernel<D, KB, kDqBQ / 32>), dim3(grid), dim3(2 * kDqBQ), LDS, stream, p);
+  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, true>), dim3(grid), dim3(2 * kDqBQ), LDS, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, false>), dim3(grid), dim3(2 * kDqBQ), LDS, stream, p);
   return hipGetLastError();
 }
 

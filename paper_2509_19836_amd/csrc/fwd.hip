@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   }
   OperandAddr<D> ad;
   ad.init(lane);
-  KvStream<D, BK, NW, BLK> walk;
+  KvStream<D, BK, NW, BLK, true> walk;
   walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
   wait_global_loads();
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // Raised priority of the matrix phase: 4-6 % (with both at priority 0 the waves' phases disturb each other).
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
-  constexpr int LOADS = KvStream<D, BK, NW, BLK>::LOADS, NL = KvStream<D, BK, NW, BLK>::N;
+  constexpr int LOADS = KvStream<D, BK, NW, BLK, true>::LOADS, NL = KvStream<D, BK, NW, BLK, true>::N;
   f32x4 s[MB][NB];
   bf16x8 pp[MB / 2][NB];
   // P of the tile at key row k0_ from its scores

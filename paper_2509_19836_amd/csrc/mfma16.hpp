@@ -81,7 +81,7 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 // assembly statement because the compiler otherwise waits for all of them before the next LDS read; the
 // kernels wait by count themselves (wait_loads_barrier).
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
 // Wait until at most N of this wave's global loads are outstanding, then meet the other waves.  Work-group
 // barrier without the full drain of __syncthreads: loads of later tiles stay in flight.  The scheduling fences
@@ -126,17 +126,18 @@ struct DirectStager {
 };
 
 // Walk of a query block over the key tiles (BK rows) it can see.  The visible tiles are one run of consecutive
-// tiles, so the cursor and the tile addresses move by adding constants.  Tiles are brought in sets
-// {K of tile t + 1, V of tile t}: the two that one pipelined iteration of the kernels reads.  A set is always
-// 2 N loads per wave, so that the kernels can wait by count: past the end of the walk the last tile's address is
-// asked for again (into a slot nobody reads), and before its start V of the first tile.
-template <int D, int BK, int NW, bool BLK>   // BLK: block-wise sparse mask
+// tiles, so the cursor and the tile addresses move by adding constants.  Tiles are brought in sets:
+// {K of tile t + 1, V of tile t} with LAG, the two that one pipelined iteration of the forward kernel reads,
+// {K, V of tile t} without.  A set is always 2 N loads per wave, so that the kernels can wait by count: past the
+// end of the walk the last tile's address is asked for again (into a slot nobody reads), and with LAG V of the
+// first tile before its start.
+template <int D, int BK, int NW, bool BLK, bool LAG>   // BLK: block-wise sparse mask
 struct KvStream {
   using Stager = DirectStager<D, BK, NW>;
   static constexpr int N = Stager::N, LOADS = 2 * N;   // per wave: one tile, one set
   Stager stage_k, stage_v;
   int left, k0;           // cursor: tiles left in the run (0: the walk is over), first key row of its tile
-  int v0;                 // first key row of the tile whose V comes with the next set
+  int v0;                 // LAG: first key row of the tile whose V comes with the next set
   int sk;
   const uint8_t* open;    // LDS flags per key tile from a block-wise sparse mask, or nullptr
   const char *k_tile, *v_tile, *v_prev;
@@ -167,11 +168,12 @@ struct KvStream {
   __device__ __forceinline__ void begin(int wave, int lane) {
     if (k0 + BK > sk) {
       stage_k.clamp(k_step / (2 * BK), sk - k0, wave, lane);
-      if (v0 + BK > sk) stage_v.clamp(v_step / (2 * BK), sk - v0, wave, lane);
+      const int v_row = LAG ? v0 : k0;
+      if (v_row + BK > sk) stage_v.clamp(v_step / (2 * BK), sk - v_row, wave, lane);
     }
   }
   __device__ __forceinline__ void load_k(int i, uint32_t lds, int wave) const { stage_k.load_one(k_tile, i, lds, wave); }
-  __device__ __forceinline__ void load_v(int i, uint32_t lds, int wave) const { stage_v.load_one(v_prev, i, lds, wave); }
+  __device__ __forceinline__ void load_v(int i, uint32_t lds, int wave) const { stage_v.load_one(LAG ? v_prev : v_tile, i, lds, wave); }
   // First key row of the cursor's tile, -1 when the walk is over
   __device__ __forceinline__ int cursor() const { return k0 | (min(left, 1) - 1); }
   // After them: the cursor moves to the next tile (and stays on the last one when there is none), in PARTS pieces
@@ -181,8 +183,10 @@ struct KvStream {
   int move;
   __device__ __forceinline__ void end(int part) {
     if (part == 0) {
-      v_prev = v_tile;
-      v0 = k0;
+      if (LAG) {
+        v_prev = v_tile;
+        v0 = k0;
+      }
       move = min(max(left - 1, 0), 1);
       left = max(left - 1, 0);
       if (BLK) {   // skip tiles that the block mask closes
@@ -284,6 +288,33 @@ __device__ __forceinline__ void cols_product(uint32_t tile, const OperandAddr<D>
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[i % DB][nb] = mfma16(a[i], b[i / DB][nb], acc[i % DB][nb]);
     hook(i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Two row-wise products of the same rows of two tiles, one after the other: acc0 = rows(tile0) * b0, then
+// acc1 = rows(tile1) * b1, both from zero.  The first AHEAD operands come fetched.
+template <int D, int MB, int NB, int AHEAD>
+__device__ __forceinline__ void rows_product_pair(uint32_t tile0, uint32_t tile1, const OperandAddr<D>& ad,
+                                                  const bf16x8 (&b0)[D / 32][NB], const bf16x8 (&b1)[D / 32][NB],
+                                                  f32x4 (&acc0)[MB][NB], f32x4 (&acc1)[MB][NB],
+                                                  const bf16x8 (&first)[AHEAD]) {
+  constexpr int N1 = D / 32 * MB, N = 2 * N1;
+  bf16x8 a[N];
+  MatrixPhase prio;
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) a[i] = first[i];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int f = i + AHEAD, f1 = f - N1, i1 = i - N1;
+    if (f < N1) a[f] = rows_operand<D>(tile0, ad, 16 * (f % MB), f / MB);
+    else if (f < N) a[f] = rows_operand<D>(tile1, ad, 16 * (f1 % MB), f1 / MB);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      if (i < N1) acc0[i % MB][nb] = mfma16(a[i], b0[i / MB][nb], i < MB ? zero : acc0[i % MB][nb]);
+      else acc1[i1 % MB][nb] = mfma16(a[i], b1[i1 / MB][nb], i1 < MB ? zero : acc1[i1 % MB][nb]);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
