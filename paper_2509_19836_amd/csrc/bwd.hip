@@ -24,10 +24,6 @@
 
 namespace burst {
 
-#ifndef BURST_FOLD_SCALE
-#define BURST_FOLD_SCALE 1   // dK/dV kernel: softmax scale folded into the K operand (see dkdv_role)
-#endif
-constexpr bool kFoldScale = BURST_FOLD_SCALE != 0;
 #ifndef BURST_DQ_BQ
 #define BURST_DQ_BQ 256
 #endif
@@ -35,11 +31,6 @@ constexpr int kDqBQ = BURST_DQ_BQ;   // query rows per work-group of the dQ kern
 
 // lse in log2 units, with -inf mapped to +inf so that exp2(x - lse2) = 0 for a dead row
 __device__ __forceinline__ float lse_to_log2(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
-
-__device__ __forceinline__ void zero16(f32x16& x) {
-#pragma unroll
-  for (int v = 0; v < 16; ++v) x[v] = 0.f;
-}
 
 // ---------------------------------------------------------------------------------------------
 template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
@@ -215,370 +206,248 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(B
 // ---------------------------------------------------------------------------------------------
 // dK/dV kernel.  Eight waves per work-group, two per SIMD, in two roles that share each block of 32 key rows:
 //   P-wave  (waves 0-3): K rows in registers; S = Q K^T, P = exp2(..) -> bf16, handed over through LDS,
-//                        dV^T += dO^T P.  Also stages the query tiles.
+//                        dV^T += dO^T P.
 //   dS-wave (waves 4-7): V rows in registers; dP = dO V^T - D, dS = P o dP, dK^T += Q^T dS.
 // Each role carries one 32 x D accumulator and one stationary operand, which is what lets two waves fit on a
-// SIMD; the two roles are separate instruction streams, register-allocated on their own.  Each stream is
-// software-pipelined: the vector work of one unit of 32 query rows is sliced behind the MFMAs of the next
-// unit, so both waves of a SIMD offer MFMAs to the matrix pipe nearly all the time:
-//   P-wave,  unit u:  S(u+1) = Q K^T  with the slices of P(u) = exp2(c S(u) - lse) behind its MFMAs,
-//                     then dV^T += dO^T P(u)  (its first MFMAs carry the last slices), P(u) -> LDS;
-//   dS-wave, unit u:  dP(u+1) = dO V^T - D  with the slices of dS(u) = P(u) o dP(u) behind its MFMAs,
-//                     then dK^T += Q^T dS(u).
-// Query tiles are 64 rows (two units, a and b).  One barrier per tile, which the P-waves pass between the two
-// units of tile t and the dS-waves before they start tile t: a dS-wave then works on dP of tile t and on dS / dK
-// of unit b of tile t-1 and unit a of tile t, whose P the P-waves wrote before that barrier.  Q tiles live in
-// four LDS slots (t-2 and t-1 for dK, t and t+1 for S, one of them being written), dO tiles, lse and -D rows in
-// three, the P hand-over area in two per unit.  The P-waves stage the tiles.
+// SIMD; the two roles are separate instruction streams.  A wave's work on a query tile (64 rows) is a matrix phase
+// and a vector phase, a barrier ends every phase, and the dS-waves run one phase behind, so that the two waves of a
+// SIMD hand the matrix pipe to each other.  Iteration t:
+//   P-wave:  matrix: dV^T += dO(t)^T P(t), then S(t+1) from Q(t+1) and -lse      vector: P(t+1), stored to LDS
+//   dS-wave: matrix: dK^T += Q(t)^T dS(t), then dP(t+1) from dO(t+1) and -D      vector: dS(t+1) from P(t+1)
+// P(t+1) is stored in the phase before the one that reads it and read a phase before P(t+2) is stored: one copy.
+// Tile t+3 is asked for in the matrix phase of iteration t, into the slot (of four) of tile t-1, which the dS-waves
+// left a barrier ago; a wave waits for its share of tile t+2 at the end of that phase, two barriers before either
+// role's products read it.  lse or D rows come with a tile into the wave's own LDS, raw, and are brought into the form
+// the accumulators start from in the vector phase before.
+// What bounds it: the matrix pipe under the chip's power limit (64 MFMAs of 16 clocks per wave and tile; the vector
+// phases, 32 exponentials or 32 products and the packing, are shorter and run behind the other wave's MFMAs).
+// 128K-token ring backward 52.6 -> 48.7 ms against 32x32x16 MFMAs with tiles staged through registers by the P-waves
+// and the vector work sliced behind each wave's own MFMAs; d = 64, 1500 rows, 4 x 12 heads: 120 -> 95 us per step.
 template <int D>
 struct DkdvLds {
-  static constexpr int BQ = 64, PITCH = 2 * D + 16, TILE = BQ * PITCH;
-  static constexpr int Q_OFF = 0, DO_OFF = 4 * TILE, LSE_OFF = 7 * TILE, D_OFF = LSE_OFF + 3 * BQ * 4;
-  static constexpr int P_OFF = D_OFF + 3 * BQ * 4;
-  static constexpr int P_UNIT = 4 * 2 * 64;                // bf16x8 per unit: [pair][half][lane]
-  static constexpr int BYTES = P_OFF + 2 * 2 * P_UNIT * 16;   // [tile parity][unit]
+  static constexpr int BQ = 64, SLOTS = 4, TILE = BQ * 2 * D;
+  static constexpr int Q_OFF = 0, DO_OFF = SLOTS * TILE;
+  static constexpr int ROW_OFF = DO_OFF + SLOTS * TILE, ROW = BQ * 4;   // [wave][slot]
+  static constexpr int P_OFF = ROW_OFF + 8 * SLOTS * ROW, P_PAIR = BQ * 32 * 2;   // [pair][chunk, key block][lane]
+  static constexpr int BYTES = P_OFF + 4 * P_PAIR;
 };
 
-template <int D, int ROLE>
-__device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b, int hk, int kv_tile, int pair) {
-  constexpr int DK = D / 16, DB = D / 32, BQ = 64, BKV = 128, NT = 256;
-  constexpr int PRE_R = kRowsAhead, PRE_C = kColsAhead;
+template <int D, int ROLE, bool BLK>
+__device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b, int hk, int kv_tile, int wave) {
+  constexpr int BQ = 64, MB = BQ / 16, NB = 2, DK = D / 32, DB = D / 16, BKV = 128, NW = 8, AHEAD = kAhead16;
   using L = DkdvLds<D>;
-  constexpr int PITCH = L::PITCH, TILE = L::TILE;
-  float* lse_slots = reinterpret_cast<float*>(smem + L::LSE_OFF);
-  float* d_slots = reinterpret_cast<float*>(smem + L::D_OFF);
-  bf16x8* pbuf = reinterpret_cast<bf16x8*>(smem + L::P_OFF);
 
   const int group = p.q_heads / p.kv_heads;
-  const int tid = threadIdx.x & 255, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4, pair = wave & 3;
   const int sq = p.sq, sk = p.sk;
   const MaskDev mk = p.mask;
   const int k_blk0 = p.k_runs.tile_of(kv_tile) * BKV, k_blk1 = min(k_blk0 + BKV, sk);
   const int k_w0 = k_blk0 + pair * 32, k_w1 = min(k_w0 + 32, sk);
-
-  const int krow = min(k_w0 + r, sk - 1);
-  const int kpos = axis_position(axis_of<false>(mk), krow);
-  bf16x8 xreg[DK];   // K rows (P-wave) or V rows (dS-wave) as the B operand
-  {
-    const TensorDev& src = ROLE == 0 ? p.k : p.v;
-    const __bf16* s_ = (const __bf16*)src.ptr + b * src.sb + hk * src.sh + (int64_t)krow * src.ss + 8 * h;
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) xreg[ks] = *reinterpret_cast<const bf16x8*>(s_ + ks * 16);
-  }
   const float c = p.scale * kLog2e;
-  if (ROLE == 0 && kFoldScale) {
-    // K rows carry the factor scale * log2(e) (rounded to bf16 once per work-group) and the S accumulators start
-    // from -lse: P = exp2 of the accumulator, no per-score multiply-add.  The extra rounding of K moves P by a
-    // few 1e-3 relative, the size of the bf16 rounding P undergoes anyway before the dV product (the paper
-    // fixes no precision); only this kernel does it: the forward kernel's Lse is held to 1e-3 absolute and
-    // keeps the exact multiply-add.
+
+  // K rows (P-wave) or V rows (dS-wave) as the B operand: lane holds rows k_w0 + 16 nb + r, columns 32 ks + 8g .. +7
+  bf16x8 xreg[DK][NB];
+  int qlo[NB], qhi[NB];   // query rows that see the lane's key rows (P-wave)
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks)
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = min(k_w0 + 16 * nb + r, sk - 1);
+    if (ROLE == 0) visible_rows<false>(mk, axis_position(axis_of<false>(mk), row), sq, qlo[nb], qhi[nb]);
+    const TensorDev& src = ROLE == 0 ? p.k : p.v;
+    const __bf16* x = (const __bf16*)src.ptr + b * src.sb + hk * src.sh + (int64_t)row * src.ss + 8 * g;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) xreg[ks][e] = (__bf16)((float)xreg[ks][e] * c);
+    for (int ks = 0; ks < DK; ++ks) {
+      xreg[ks][nb] = *reinterpret_cast<const bf16x8*>(x + ks * 32);
+      // K rows carry the factor scale * log2(e) (rounded to bf16 once per work-group) and the S accumulators start
+      // from -lse: P = exp2 of the accumulator, no per-score multiply-add.  The extra rounding of K moves P by a
+      // few 1e-3 relative, the size of the bf16 rounding P undergoes anyway before the dV product (the paper
+      // fixes no precision); only this kernel does it: the forward kernel's Lse is held to 1e-3 absolute and
+      // keeps the exact multiply-add.
+      if (ROLE == 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xreg[ks][nb][e] = (__bf16)((float)xreg[ks][nb][e] * c);
+      }
+    }
   }
 
-  f32x16 acc[DB];   // dV^T (P-wave) or dK^T (dS-wave)
+  f32x4 acc[DB][NB];   // dV^T (P-wave) or dK^T (dS-wave)
 #pragma unroll
-  for (int db = 0; db < DB; ++db) zero16(acc[db]);
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   int klo_blk, khi_blk, klo_w = 0, khi_w = 0;
   range_minmax<false>(mk, k_blk0, k_blk1, klo_blk, khi_blk);
-  const bool has_keys = k_w0 < k_w1;
-  if (has_keys) range_minmax<false>(mk, k_w0, k_w1, klo_w, khi_w);
-  // A tile runs under the per-element predicate unless all of it is visible to this pair's keys; tiles that
-  // are empty for this pair alone do too (their P is 0), so that the pipeline has no per-wave holes.
-  BlockClassifier<true> q_class;
-  q_class.init(mk, klo_w, khi_w, sq, !has_keys);
-  auto tile_masked = [&](int q0_) { return q_class(mk, q0_, min(q0_ + BQ, sq), q0_ + BQ > sq) != TILE_FULL; };
+  if (k_w0 < k_w1) range_minmax<false>(mk, k_w0, k_w1, klo_w, khi_w);
+  TileRanges tiles;
+  tiles.init(row_intervals<true>(mk, klo_w, khi_w, sq, k_w0 >= k_w1), sq, BQ);
 
-  // Walk over (query head of the group, query tile that can see the key block) as one sequence; both roles
-  // move the same cursor, only the P-waves load.
-  const TileRun qr = visible_tiles<true, BQ>(mk, klo_blk, khi_blk, sq);
-  bool c_valid = qr.len > 0;
-  int c_left = qr.len, c_head = 0;
-  int q0n = qr.start * BQ;
-
-  TileStager<D, BQ, NT> stage_q, stage_do;   // P-wave only
-  float stage_row = 0.f;
-  const char *q_tile = nullptr, *do_tile = nullptr;
-  const float* row_head = nullptr;
-  const int64_t q_step = (int64_t)BQ * p.q.ss * 2, do_step = (int64_t)BQ * p.d_o.ss * 2;
-  if (ROLE == 0) {
-    stage_q.init(p.q.ss, tid);
-    stage_do.init(p.d_o.ss, tid);
-  }
-  const bool stages_lse = tid < BQ;
-  const float* const rowvec_ptr = stages_lse ? p.lse.ptr : p.d.ptr;
-  const int64_t rowvec_sb = stages_lse ? p.lse.sb : p.d.sb, rowvec_sh = stages_lse ? p.lse.sh : p.d.sh;
-  auto point = [&]() {
-    if (ROLE != 0) return;
-    const int hq = hk * group + c_head;
-    q_tile = reinterpret_cast<const char*>((const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)q0n * p.q.ss);
-    do_tile = reinterpret_cast<const char*>((const __bf16*)p.d_o.ptr + b * p.d_o.sb + hq * p.d_o.sh +
-                                            (int64_t)q0n * p.d_o.ss);
-    row_head = rowvec_ptr + b * rowvec_sb + hq * rowvec_sh;
-  };
-  const uint8_t* open_flags = nullptr;
-  if (mk.blk) {
-    uint8_t* flags = reinterpret_cast<uint8_t*>(smem + L::BYTES);
-    if (ROLE == 0) fill_open_flags<false, BQ>(mk, flags, k_blk0, sq, tid, NT);
-    open_flags = flags;
+  uint8_t* open_flags = nullptr;
+  if (BLK) {
+    open_flags = reinterpret_cast<uint8_t*>(smem + L::BYTES);
+    if (ROLE == 0) fill_open_flags<false, BQ>(mk, open_flags, k_blk0, sq, tid, 256);
     __syncthreads();
   }
-  auto is_open = [&](int q0_) { return !open_flags || __builtin_amdgcn_readfirstlane(open_flags[q0_ / BQ]) != 0; };
-  auto step = [&]() {
-    if (--c_left > 0) {
-      q0n += BQ;
-      q_tile += q_step;
-      do_tile += do_step;
-    } else {
-      ++c_head;
-      c_left = qr.len;
-      q0n = qr.start * BQ;
-      if (c_head < group) point();
-      else c_valid = false;
-    }
-  };
-  auto advance = [&]() {
-    do step();
-    while (c_valid && !is_open(q0n));
-  };
-  auto issue = [&]() {
-    if (ROLE != 0) return;
-    if (q0n + BQ <= sq) {
-      stage_q.load_at(q_tile);
-      stage_do.load_at(do_tile);
-    } else {
-      stage_q.load(reinterpret_cast<const __bf16*>(q_tile) - (int64_t)q0n * p.q.ss, p.q.ss, q0n, sq, tid);
-      stage_do.load(reinterpret_cast<const __bf16*>(do_tile) - (int64_t)q0n * p.d_o.ss, p.d_o.ss, q0n, sq, tid);
-    }
-    if (tid < 2 * BQ) stage_row = row_head[min(q0n + (tid & (BQ - 1)), sq - 1)];
-  };
-  auto commit = [&](int q_slot, int o_slot) {
-    if (ROLE != 0) return;
-    stage_q.store(smem + L::Q_OFF + q_slot * TILE);
-    stage_do.store(smem + L::DO_OFF + o_slot * TILE);
-    if (tid < BQ) lse_slots[o_slot * BQ + tid] = kFoldScale ? -lse_to_log2(stage_row) : lse_to_log2(stage_row);
-    else if (tid < 2 * BQ) d_slots[o_slot * BQ + tid - BQ] = -stage_row;   // -D: the dP accumulators start from it
-  };
-
+  OperandAddr<D> ad;
+  ad.init(lane);
+  QStream<D, BQ, NW, BLK> walk;
+  walk.init(p.q, p.d_o, ROLE == 0 ? p.lse : p.d, b, hk * group, group, visible_tiles<true, BQ>(mk, klo_blk, khi_blk, sq), sq, wave,
+            lane, open_flags);
   wait_global_loads();
-  if (c_valid) {
-    point();
-    if (!is_open(q0n)) advance();
-  }
-  if (c_valid) {   // uniform over the work-group: both roles take the same number of barriers
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    // 16 per-row values of a unit (rows 8g + 4h + j of its 32) from an LDS row vector
-    auto rows16 = [&](const float* vec, f32x16& out) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(vec + 8 * g + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[4 * g + j] = x[j];
-      }
-    };
-    auto words_to_operand = [&](const uint32_t (&w)[8], int half) {
-      const u32x4 x = {w[4 * half], w[4 * half + 1], w[4 * half + 2], w[4 * half + 3]};
-      return __builtin_bit_cast(bf16x8, x);
-    };
-    // Values of a lane's 16 that go behind slot j of the first stream of a unit (DK MFMAs: values 0..11) and of
-    // the first DB MFMAs of the second (values 12..15): the second stream's chunk 0 needs values 0..7 only.
-    auto first_lo = [](int j) { return 12 * j / DK; };
-    auto second_lo = [](int j) { return 12 + 4 * j / DB; };
-    const int p_lane = pair * 2 * 64 + lane;   // this pair's place inside a unit of the hand-over area
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+  auto q_lds = [&](int s_) { return lds0 + L::Q_OFF + s_ * L::TILE; };
+  auto o_lds = [&](int s_) { return lds0 + L::DO_OFF + s_ * L::TILE; };
+  auto row_off = [&](int s_) { return L::ROW_OFF + (wave * L::SLOTS + s_) * L::ROW; };
+  auto rows_lds = [&](int s_) { return ROLE == 0 ? q_lds(s_) : o_lds(s_); };   // of the product that starts from a row vector
+  auto cols_lds = [&](int s_) { return ROLE == 0 ? o_lds(s_) : q_lds(s_); };   // of the product that fills acc
+  bf16x8* const hand = reinterpret_cast<bf16x8*>(smem + L::P_OFF + pair * L::P_PAIR) + lane;
+  constexpr int LOADS = QStream<D, BQ, NW, BLK>::LOADS;
 
-    // cursor bookkeeping shared by the roles
-    issue();
-    commit(0, 0);
-    int q0_cur = q0n;
-    bool msk_cur = tile_masked(q0n);
-    advance();
-    bool more = c_valid;
-    int q0_nxt = 0;
-    bool msk_nxt = false;
-    if (more) {
-      issue();
-      q0_nxt = q0n;
-      msk_nxt = tile_masked(q0n);
-      advance();
-    }
-    __syncthreads();   // tile 0 is in LDS
-    int qs = 0, os = 0, par = 0;   // Q slot, dO / row slot and hand-over parity of the current tile
-
+  f32x4 s[MB][NB], init[MB];   // S or dP - D of a tile; -lse2 or -D of the lane's rows of it
+  bf16x8 ps[MB / 2][NB];       // P or dS
+  auto issue = [&](int s_) {
+    walk.begin(wave, lane);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) walk.load(i, q_lds(s_), o_lds(s_), lds0 + row_off(s_), wave);
+    walk.advance();
+  };
+  // raw row vector -> accumulator start (a dead row's lse of -inf gives P = 0)
+  auto prepare_rows = [&](int s_) {
+    float* x = reinterpret_cast<float*>(smem + row_off(s_)) + lane;
+    *x = ROLE == 0 ? -lse_to_log2(*x) : -*x;
+  };
+  auto init_rows = [&](int s_, int mb) { init[mb] = *reinterpret_cast<const f32x4*>(smem + row_off(s_) + 4 * (16 * mb + 4 * g)); };
+  // The vector phase, of the tile at query row q0_
+  auto vector_phase = [&](int q0_) {
     if (ROLE == 0) {
-      f32x16 s0, s1, l2;
-      uint32_t pw[8];
-      bf16x8 pk[2];
-      // P(u) slices: values [v0, v1) of tile s
-      auto p_vals = [&](f32x16& s, int v0, int v1) {
+      const bool some = tiles.some(q0_);
+      if (some && !tiles.full(q0_)) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (v < v0 || v >= v1) continue;
-          s[v] = kFoldScale ? __builtin_amdgcn_exp2f(s[v]) : __builtin_amdgcn_exp2f(c * s[v] - l2[v]);
-          if (v & 1) {
-            const bf16x2 pr = {(__bf16)s[v - 1], (__bf16)s[v]};
-            pw[v >> 1] = __builtin_bit_cast(uint32_t, pr);
-          }
-        }
-      };
-      // second half of a unit: dV^T += dO^T P with the last slices and the hand-over store behind its MFMAs
-      auto dv_stream = [&](f32x16& s, int o_slot, int row0, int unit) {
-        pk[0] = words_to_operand(pw, 0);
-        pk[1] = pk[0];   // placeholder until the hooks below have produced values 8..15
-        bf16x8* dst = pbuf + (par * 2 + unit) * L::P_UNIT + p_lane;
-        cols_stream<PITCH, DB, 2, PRE_C>(smem + L::DO_OFF + o_slot * TILE, row0, pk, acc, lane, [&](int i) {
-          if (i < DB) p_vals(s, second_lo(i), second_lo(i + 1));
-          if (i == DB - 1) pk[1] = words_to_operand(pw, 1);
-          if (i == DB) dst[0] = pk[0];
-          if (i == DB + 1) dst[64] = pk[1];
-        });
-      };
-      // S of the unit at rows row0 of the tile in (q_slot, o_slot) with hook(j) behind MFMA j
-      auto s_stream = [&](f32x16& s, int q_slot, int o_slot, int row0, auto&& hook) {
-        if (kFoldScale) {
-          rows16(lse_slots + o_slot * BQ + row0, s);
-          rows_stream<PITCH, DK, PRE_R, false>(smem + L::Q_OFF + q_slot * TILE, row0, xreg, s, r, h, hook);
-        } else {
-          rows_stream<PITCH, DK, PRE_R, true>(smem + L::Q_OFF + q_slot * TILE, row0, xreg, s, r, h, hook);
-        }
-      };
-      s_stream(s0, 0, 0, 0, NoHook());
-      for (;;) {
-        const int qs1 = (qs + 1) & 3, os1 = os == 2 ? 0 : os + 1;
-        // unit a of the tile (s0); S of unit b is produced meanwhile (s1)
-        if (!kFoldScale) rows16(lse_slots + os * BQ, l2);
-        if (msk_cur) mask_tile<false>(s0, mk, q0_cur, h, sq, kpos);
-        s_stream(s1, qs, os, 32, [&](int j) { p_vals(s0, first_lo(j), first_lo(j + 1)); });
-        dv_stream(s0, os, 0, 0);
-        if (more) commit(qs1, os1);
-        __syncthreads();
-        const bool more2 = more && c_valid;
-        int q0_n2 = 0;
-        bool msk_n2 = false;
-        if (more2) {
-          issue();
-          q0_n2 = q0n;
-          msk_n2 = tile_masked(q0n);
-          advance();
-        }
-        // unit b (s1); S of the next tile's unit a is produced meanwhile (s0)
-        if (!kFoldScale) rows16(lse_slots + os * BQ + 32, l2);
-        if (msk_cur) mask_tile<false>(s1, mk, q0_cur + 32, h, sq, kpos);
-        if (more) {
-          s_stream(s0, qs1, os1, 0, [&](int j) { p_vals(s1, first_lo(j), first_lo(j + 1)); });
-        } else {
-          p_vals(s1, 0, 12);
-        }
-        dv_stream(s1, os, 32, 1);
-        if (!more) break;
-        qs = qs1;
-        os = os1;
-        par ^= 1;
-        q0_cur = q0_nxt;
-        msk_cur = msk_nxt;
-        q0_nxt = q0_n2;
-        msk_nxt = msk_n2;
-        more = more2;
+        for (int half = 0; half < MB / 2; ++half)
+          mask_rows32<NB>(s[2 * half], s[2 * half + 1], q0_ + 32 * half, g, qlo, qhi, true);
       }
-      __syncthreads();   // the last unit's P is in LDS
+      if (some) {
+#pragma unroll
+        for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              x[v] = __builtin_amdgcn_exp2f(x[v]);
+              y[v] = __builtin_amdgcn_exp2f(y[v]);
+            }
+            ps[ch][nb] = pack_pair(x, y);
+          }
+      } else {   // for this pair alone there is nothing in the tile
+#pragma unroll
+        for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) ps[ch][nb] = zero_operand();
+      }
+#pragma unroll
+      for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) hand[(ch * NB + nb) * 64] = ps[ch][nb];
     } else {
-      f32x16 dpa, dpb;   // dP - D of unit a / unit b
-      uint32_t dw[8];
-      bf16x8 dsk[2], p0, p1;
-      // dS(u) slices: values [v0, v1) from the P words p0 / p1 and the dP - D tile
-      auto ds_vals = [&](f32x16& dpv, int v0, int v1) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (v < v0 || v >= v1) continue;
-          const float pr = (float)(v < 8 ? p0[v & 7] : p1[v & 7]);
-          dpv[v] = pr * dpv[v];
-          if (v & 1) {
-            const bf16x2 x = {(__bf16)dpv[v - 1], (__bf16)dpv[v]};
-            dw[v >> 1] = __builtin_bit_cast(uint32_t, x);
+      for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const bf16x8 pr = hand[(ch * NB + nb) * 64];
+          f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            x[v] *= (float)pr[v];
+            y[v] *= (float)pr[v + 4];
           }
+          ps[ch][nb] = pack_pair(x, y);
         }
-      };
-      auto load_p = [&](int parity, int unit) {
-        const bf16x8* src = pbuf + (parity * 2 + unit) * L::P_UNIT + p_lane;
-        p0 = src[0];
-        p1 = src[64];
-      };
-      // dP - D of the unit at rows row0 of the tile in o_slot, with dS slices of tile `dsv` behind its MFMAs
-      auto dp_stream = [&](f32x16& dpv, int o_slot, int row0, f32x16* dsv) {
-        rows16(d_slots + o_slot * BQ + row0, dpv);
-        if (dsv) {
-          rows_stream<PITCH, DK, PRE_R, false>(smem + L::DO_OFF + o_slot * TILE, row0, xreg, dpv, r, h,
-                                                    [&](int j) { ds_vals(*dsv, first_lo(j), first_lo(j + 1)); });
-        } else {
-          rows_stream<PITCH, DK, PRE_R, false>(smem + L::DO_OFF + o_slot * TILE, row0, xreg, dpv, r, h);
-        }
-      };
-      auto dk_stream = [&](f32x16& dsv, int q_slot, int row0) {
-        dsk[0] = words_to_operand(dw, 0);
-        dsk[1] = dsk[0];
-        cols_stream<PITCH, DB, 2, PRE_C>(smem + L::Q_OFF + q_slot * TILE, row0, dsk, acc, lane, [&](int i) {
-          if (i < DB) ds_vals(dsv, second_lo(i), second_lo(i + 1));
-          if (i == DB - 1) dsk[1] = words_to_operand(dw, 1);
-        });
-      };
-      bool first = true;
-      for (;;) {
-        __syncthreads();   // P of unit a of this tile and of unit b of the previous one is in LDS
-        const int qs1 = (qs + 1) & 3, os1 = os == 2 ? 0 : os + 1;
-        const bool more2 = more && c_valid;
-        if (more2) advance();
-        if (!first) {
-          load_p(par ^ 1, 1);
-          dp_stream(dpa, os, 0, &dpb);
-          dk_stream(dpb, (qs + 3) & 3, 32);
-        } else {
-          dp_stream(dpa, os, 0, nullptr);
-        }
-        load_p(par, 0);
-        dp_stream(dpb, os, 32, &dpa);
-        dk_stream(dpa, qs, 0);
-        first = false;
-        if (!more) break;
-        qs = qs1;
-        os = os1;
-        par ^= 1;
-        more = more2;
-      }
-      __syncthreads();
-      load_p(par, 1);
-      ds_vals(dpb, 0, 12);
-      dk_stream(dpb, qs, 32);
     }
+  };
+
+  if (walk.valid()) {   // uniform over the work-group: all waves take the same number of barriers
+    const int ta = walk.cursor();
+    issue(0);
+    int tb = walk.cursor();
+    issue(1);
+    int tc = walk.cursor();
+    issue(2);
+    wait_loads_barrier<2 * LOADS>();              // tile 0
+    if (ROLE == 1) phase_barrier();
+    bf16x8 first[AHEAD];
+    prepare_rows(0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) init_rows(0, mb);
+    rows_fetch<D, MB, AHEAD>(rows_lds(0), ad, 0, first);
+    rows_product<D, MB, NB, AHEAD>(rows_lds(0), ad, 0, xreg, s, init, first);
+    wait_loads_barrier<LOADS>();                  // tile 1
+    prepare_rows(1);
+    vector_phase(ta);
+    cols_fetch<D, AHEAD>(cols_lds(0), ad, 0, first);
+    stores_barrier();
+    int slot = 0;
+    for (;;) {   // iteration t: tb, tc are the first rows of tiles t+1, t+2
+      // ---- matrix phase
+      const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
+      const uint32_t ql = q_lds(slot3), ol = o_lds(slot3), rl = lds0 + row_off(slot3);
+      const int tn = walk.cursor();
+      walk.begin(wave, lane);
+      bf16x8 first_rows[AHEAD];
+      constexpr int NCOLS = MB / 2 * DB;
+      static_assert(LOADS <= NCOLS && MB <= NCOLS && AHEAD <= NCOLS, "a hook per operand");
+      cols_product<D, MB / 2, NB, AHEAD>(cols_lds(slot), ad, 0, ps, acc, first, [&](int i) {
+        if (i < LOADS) walk.load(i, ql, ol, rl, wave);
+        if (i >= NCOLS - MB) init_rows(slot1, i - (NCOLS - MB));
+        if (i >= NCOLS - AHEAD) {
+          const int f = i - (NCOLS - AHEAD);
+          first_rows[f] = rows_operand<D>(rows_lds(slot1), ad, 16 * (f % MB), f / MB);
+        }
+      });
+      if (tb < 0) break;
+      rows_product<D, MB, NB, AHEAD>(rows_lds(slot1), ad, 0, xreg, s, init, first_rows);
+      wait_loads_barrier<LOADS>();                // tile t+2
+      // ---- vector phase
+      slot = slot1;
+      walk.advance();
+      prepare_rows((slot + 1) & 3);
+      vector_phase(tb);
+      cols_fetch<D, AHEAD>(cols_lds(slot), ad, 0, first);
+      stores_barrier();
+      tb = tc;
+      tc = tn;
+    }
+    wait_global_loads();   // tiles past the end of the walk
+    if (ROLE == 0) phase_barrier();
   }
 
-  if (k_w0 + r < sk) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = k_w0 + 16 * nb + r;
+    if (row >= sk) continue;
     const TensorDev& dst = ROLE == 0 ? p.dv : p.dk;
-    const bool accumulate = ROLE == 0 ? p.acc_dv : p.acc_dk;
     const float mul = ROLE == 0 ? 1.f : p.scale;
-    float* dp_ = (float*)dst.ptr + b * dst.sb + (int64_t)(k_w0 + r) * dst.ss + hk * dst.sh;
+    float* out = (float*)dst.ptr + b * dst.sb + (int64_t)row * dst.ss + hk * dst.sh + 4 * g;
+    f32x4 old[DB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db) old[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (ROLE == 0 ? p.acc_dv : p.acc_dk) {   // all loads before the first store
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int off = db * 32 + 8 * g + 4 * h;
-        f32x4 x = {acc[db][4 * g] * mul, acc[db][4 * g + 1] * mul, acc[db][4 * g + 2] * mul, acc[db][4 * g + 3] * mul};
-        if (accumulate) x += *reinterpret_cast<const f32x4*>(dp_ + off);
-        *reinterpret_cast<f32x4*>(dp_ + off) = x;
-      }
+      for (int db = 0; db < DB; ++db) old[db] = *reinterpret_cast<const f32x4*>(out + 16 * db);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(out + 16 * db) = acc[db][nb] * mul + old[db];
   }
 }
 
-template <int D>
+template <int D, bool BLK>
 __global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // laid out by DkdvLds
+  extern __shared__ __attribute__((aligned(1024))) char smem[];   // laid out by DkdvLds, then the open flags
   const BlockMap bm = map_block<false>(blockIdx.x, p.batch * p.kv_heads, 1, p.k_runs.total());
   if (!bm.valid) return;
-  const int b = bm.key / p.kv_heads, hk = bm.key - b * p.kv_heads;
+  const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 4) dkdv_role<D, 0>(p, smem, b, hk, bm.tile, wave);
-  else dkdv_role<D, 1>(p, smem, b, hk, bm.tile, wave - 4);
+  if (wave < 4) dkdv_role<D, 0, BLK>(p, smem, b, hk, bm.tile, wave);
+  else dkdv_role<D, 1, BLK>(p, smem, b, hk, bm.tile, wave);
 }
 
 
@@ -613,7 +482,8 @@ static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
   }
   if (p.k_runs.total() == 0) return hipSuccess;
   const int grid = mapped_grid(n_keys, 1, p.k_runs.total());
-  hipLaunchKernelGGL((step_bwd_dkdv_kernel<D>), dim3(grid), dim3(512), LDS, stream, p);
+  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true>), dim3(grid), dim3(512), LDS, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false>), dim3(grid), dim3(512), LDS, stream, p);
   return hipGetLastError();
 }
 

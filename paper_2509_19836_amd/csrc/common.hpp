@@ -205,35 +205,6 @@ struct BlockClassifier {
   }
 };
 
-// Per-element mask of one 32x32 accumulator tile whose 16 registers of a lane run over rows
-// base_row + 4*h + 8*(v/4) + (v%4) of the OTHER side than the lane's own row (base_row: first of the 32
-// rows, wave-uniform): KEYS_IN_REGS = true, registers are key rows and the lane owns a query (position
-// lane_pos); false, registers are query rows and the lane owns a key.  Invisible entries and rows
-// >= n_rows become -inf.  The 32 rows lie in at most two consecutive pieces (a piece has at least 32
-// rows whenever there are more than two, checked on the host).  Written with selects only, no
-// divergent control flow.
-template <bool KEYS_IN_REGS>
-__device__ __forceinline__ void mask_tile(f32x16& s, const MaskDev& mk, int base_row, int h, int n_rows, int lane_pos) {
-  const AxisMap ax = axis_of<!KEYS_IN_REGS>(mk);
-  int split = 0x7fffffff, pos_a = ax.pos0, pos_b = ax.pos0;   // position = pos_a (rows < split) or pos_b, + row * stride
-  if (ax.nseg > 1) {
-    int s0 = base_row / ax.seg_len;
-    s0 = s0 < ax.nseg - 1 ? s0 : ax.nseg - 1;
-    pos_a = ax.pos0 + s0 * (ax.period - ax.seg_len * ax.stride);
-    pos_b = pos_a + ax.period - ax.seg_len * ax.stride;
-    split = s0 < ax.nseg - 1 ? (s0 + 1) * ax.seg_len : 0x7fffffff;
-  }
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int row = base_row + 4 * h + 8 * (v >> 2) + (v & 3);
-    const int pos = (row >= split ? pos_b : pos_a) + row * ax.stride;
-    const int diff = KEYS_IN_REGS ? lane_pos - pos : pos - lane_pos;   // pos(q) - pos(k)
-    const bool ordered = (diff >= 0) & (diff < mk.window);
-    const bool vis = (row < n_rows) & ((mk.causal == 0) | ordered);
-    s[v] = vis ? s[v] : -INFINITY;
-  }
-}
-
 __device__ __forceinline__ int lds_row(int tile_row) {
   // tile row 16c + 4a + b  ->  LDS row 16c + 4b + a
   return (tile_row & ~15) | ((tile_row & 3) << 2) | ((tile_row >> 2) & 3);
@@ -367,69 +338,6 @@ struct TileStager {
   }
 };
 
-// Walk of a query block over the key tiles (BK rows of K and of V) it can see, with the staging
-// of the tiles.  The visible tiles are one run of consecutive tiles, so the cursor and the two tile
-// addresses move by adding constants and a load needs no address arithmetic.
-template <int D, int BK, int NT>
-struct KvWalk {
-  TileStager<D, BK, NT> stage_k, stage_v;
-  int left, k0;           // cursor: tiles left in the run (0: the walk is over), first key row of its tile
-  int sk;
-  const uint8_t* open;    // LDS flags per key tile from a block-wise sparse mask, or nullptr
-  const char *k_base, *v_base, *k_tile, *v_tile;   // row 0 of the head; first row of the cursor's tile
-  int64_t k_row, v_row;   // bytes per key row
-
-  // [q_lo, q_hi]: positions spanned by the query rows of the work-group.  The cursor starts on the
-  // first tile to visit.
-  __device__ __forceinline__ void init(const MaskDev& mk, const TensorDev& k, const TensorDev& v, int b, int hk, int sk_,
-                                       int q_lo, int q_hi, int tid, const uint8_t* open_flags) {
-    sk = sk_;
-    open = open_flags;
-    const TileRun run = visible_tiles<false, BK>(mk, q_lo, q_hi, sk);
-    left = run.len;
-    k0 = run.start * BK;
-    k_row = k.ss * 2;
-    v_row = v.ss * 2;
-    k_base = reinterpret_cast<const char*>((const __bf16*)k.ptr + b * k.sb + hk * k.sh);
-    v_base = reinterpret_cast<const char*>((const __bf16*)v.ptr + b * v.sb + hk * v.sh);
-    k_tile = k_base + k0 * k_row;
-    v_tile = v_base + k0 * v_row;
-    stage_k.init(k.ss, tid);
-    stage_v.init(v.ss, tid);
-    seek();
-  }
-  __device__ __forceinline__ bool valid() const { return left > 0; }
-  __device__ __forceinline__ void issue(int tid) {   // loads of the cursor's tile
-    if (k0 + BK <= sk) {
-      stage_k.load_at(k_tile);
-      stage_v.load_at(v_tile);
-    } else {   // last tile of a ragged chunk: row indices clamped per thread
-      stage_k.load(reinterpret_cast<const __bf16*>(k_base), k_row >> 1, k0, sk, tid);
-      stage_v.load(reinterpret_cast<const __bf16*>(v_base), v_row >> 1, k0, sk, tid);
-    }
-  }
-  __device__ __forceinline__ void step() {
-    --left;
-    k0 += BK;
-    k_tile += BK * k_row;
-    v_tile += BK * v_row;
-  }
-  // skip tiles that the block mask closes
-  __device__ __forceinline__ void seek() {
-    if (open) {
-      while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK]) == 0) step();
-    }
-  }
-  __device__ __forceinline__ void advance() {
-    step();
-    seek();
-  }
-  __device__ __forceinline__ void commit(char* k_lds, char* v_lds) const {
-    stage_k.store(k_lds);
-    stage_v.store(v_lds);
-  }
-};
-
 // Scope of a stream of MFMAs: the wave runs at raised issue priority.  A SIMD issues one vector-class
 // instruction at a time and picks the oldest ready wave; without this, a co-resident wave in a
 // dense vector phase (softmax, dS) keeps winning the issue slot and the matrix pipe idles, although
@@ -442,153 +350,6 @@ struct MatrixPhase {
 struct NoHook {
   __device__ __forceinline__ void operator()(int) const {}
 };
-
-// acc[nb] (+)= A_nb * B for NB row blocks of an LDS tile: A_nb = tile rows row0 + 32*nb .. +31 (all D
-// columns, read row-wise), B = DK register operands.  The k-step is the outer loop so consecutive
-// MFMAs hit different accumulators, and LDS operands are fetched PRE k-steps ahead of their use;
-// the scheduling fences keep the compiler from hoisting more (registers) or less (latency).
-// ZERO: the accumulators start from 0 (first MFMA takes the constant, no register clearing).
-// hook(ks) runs after the MFMAs of k-step ks, inside the same scheduling region: independent
-// vector work placed there issues while the matrix pipe is busy.
-template <int PITCH, int NB, int DK, int PRE, bool ZERO = false, class Hook = NoHook>
-__device__ __forceinline__ void gemm_rows(const char* tile, int row0, const bf16x8 (&breg)[DK], f32x16 (&acc)[NB],
-                                          int r, int h, Hook&& hook = Hook()) {
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 a[DK][NB];
-  MatrixPhase prio;
-#pragma unroll
-  for (int ks = 0; ks < PRE && ks < DK; ++ks)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) a[ks][nb] = lds_rows_operand<PITCH>(tile, row0 + 32 * nb, ks * 16, r, h);
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) {
-    if (ks + PRE < DK) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        a[ks + PRE][nb] = lds_rows_operand<PITCH>(tile, row0 + 32 * nb, (ks + PRE) * 16, r, h);
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma32(a[ks][nb], breg[ks], (ZERO && ks == 0) ? zero : acc[nb]);
-    hook(ks);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// Two row-wise GEMMs sharing the row block, interleaved so consecutive MFMAs alternate between the
-// two accumulators:  acc0 += rows(tile0) * b0,  acc1 += rows(tile1) * b1.
-template <int PITCH, int DK, int PRE, bool ZERO0 = false>   // ZERO0: acc0 starts from zero (not read)
-__device__ __forceinline__ void gemm_rows_pair(const char* tile0, const char* tile1, int row0, const bf16x8 (&b0)[DK],
-                                               const bf16x8 (&b1)[DK], f32x16& acc0, f32x16& acc1, int r, int h) {
-  bf16x8 a0[DK], a1[DK];
-  MatrixPhase prio;
-#pragma unroll
-  for (int ks = 0; ks < PRE && ks < DK; ++ks) {
-    a0[ks] = lds_rows_operand<PITCH>(tile0, row0, ks * 16, r, h);
-    a1[ks] = lds_rows_operand<PITCH>(tile1, row0, ks * 16, r, h);
-  }
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) {
-    if (ks + PRE < DK) {
-      a0[ks + PRE] = lds_rows_operand<PITCH>(tile0, row0, (ks + PRE) * 16, r, h);
-      a1[ks + PRE] = lds_rows_operand<PITCH>(tile1, row0, (ks + PRE) * 16, r, h);
-    }
-    acc0 = mfma32(a0[ks], b0[ks], (ZERO0 && ks == 0) ? f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f} : acc0);
-    acc1 = mfma32(a1[ks], b1[ks], acc1);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// acc[db] += A_db,c * b[c]: A = LDS tile read column-wise (columns 32*db .. +31, rows
-// row0 + 16*c .. +15 in packed-accumulator order), b[c] = packed register operands, c < NC.
-// One step = one 16-row chunk across all DB accumulators; operands fetched PRE steps ahead.
-template <int PITCH, int DB, int NC, int PRE, class Hook = NoHook>
-__device__ __forceinline__ void gemm_cols(const char* tile, int row0, const bf16x8 (&b)[NC], f32x16 (&acc)[DB],
-                                          int lane, Hook&& hook = Hook()) {
-  // operands in use order: i = c * DB + db; fetched AHEAD operands before use
-  constexpr int N = NC * DB, AHEAD = PRE;   // PRE counts operands here
-  bf16x8 a[N];
-  MatrixPhase prio;
-#pragma unroll
-  for (int i = 0; i < AHEAD && i < N; ++i) a[i] = lds_cols_operand<PITCH>(tile, row0 + 16 * (i / DB), (i % DB) * 32, lane);
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (i + AHEAD < N)
-      a[i + AHEAD] = lds_cols_operand<PITCH>(tile, row0 + 16 * ((i + AHEAD) / DB), ((i + AHEAD) % DB) * 32, lane);
-    acc[i % DB] = mfma32(a[i], b[i / DB], acc[i % DB]);
-    if (i % DB == DB - 1) hook(i / DB);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// The same product with its first PRE operands fetched by the caller ahead of time (gemm_cols_fetch),
-// e.g. before a stretch of vector work, so that the first MFMA does not wait for LDS.
-template <int PITCH, int DB, int PRE>
-__device__ __forceinline__ void gemm_cols_fetch(const char* tile, int row0, int lane, bf16x8 (&first)[PRE]) {
-#pragma unroll
-  for (int i = 0; i < PRE; ++i) first[i] = lds_cols_operand<PITCH>(tile, row0 + 16 * (i / DB), (i % DB) * 32, lane);
-}
-template <int PITCH, int DB, int NC, int PRE, class Hook = NoHook>
-__device__ __forceinline__ void gemm_cols_run(const char* tile, int row0, const bf16x8 (&b)[NC], f32x16 (&acc)[DB],
-                                              int lane, const bf16x8 (&first)[PRE], Hook&& hook = Hook()) {
-  constexpr int N = NC * DB;
-  static_assert(PRE <= N, "more operands fetched ahead than the product has");
-  bf16x8 a[N];
-  MatrixPhase prio;
-#pragma unroll
-  for (int i = 0; i < PRE; ++i) a[i] = first[i];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (i + PRE < N)
-      a[i + PRE] = lds_cols_operand<PITCH>(tile, row0 + 16 * ((i + PRE) / DB), ((i + PRE) % DB) * 32, lane);
-    acc[i % DB] = mfma32(a[i], b[i / DB], acc[i % DB]);
-    if (i % DB == DB - 1) hook(i / DB);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// Streams with one hook per MFMA, for software-pipelined kernels: hook(i) holds the few vector or LDS
-// instructions of ANOTHER unit of work that go behind MFMA i, and the scheduling fence after it keeps them
-// there, so that a wave's vector work runs in the shadow of matrix work that does not depend on it.
-//   acc (+)= rows(tile)[row0 .. row0+31] * b   (ZERO: starts from a literal zero)
-template <int PITCH, int DK, int PRE, bool ZERO, class Hook = NoHook>
-__device__ __forceinline__ void rows_stream(const char* tile, int row0, const bf16x8 (&b)[DK], f32x16& acc, int r, int h,
-                                            Hook&& hook = Hook()) {
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 a[DK];
-#pragma unroll
-  for (int ks = 0; ks < PRE && ks < DK; ++ks) a[ks] = lds_rows_operand<PITCH>(tile, row0, ks * 16, r, h);
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) {
-    if (ks + PRE < DK) a[ks + PRE] = lds_rows_operand<PITCH>(tile, row0, (ks + PRE) * 16, r, h);
-    acc = mfma32(a[ks], b[ks], (ZERO && ks == 0) ? zero : acc);
-    hook(ks);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-//   acc[db] += cols(tile)[db, c] * b[c]  (as gemm_cols), hook(i) behind MFMA i = c * DB + db; b is read when
-//   its MFMA is issued, so a hook may still complete b[c] for a later chunk c.
-template <int PITCH, int DB, int NC, int PRE, class Hook = NoHook>
-__device__ __forceinline__ void cols_stream(const char* tile, int row0, const bf16x8 (&b)[NC], f32x16 (&acc)[DB], int lane,
-                                            Hook&& hook = Hook()) {
-  constexpr int N = NC * DB;
-  bf16x8 a[N];
-#pragma unroll
-  for (int i = 0; i < PRE && i < N; ++i) a[i] = lds_cols_operand<PITCH>(tile, row0 + 16 * (i / DB), (i % DB) * 32, lane);
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (i + PRE < N) a[i + PRE] = lds_cols_operand<PITCH>(tile, row0 + 16 * ((i + PRE) / DB), ((i + PRE) % DB) * 32, lane);
-    acc[i % DB] = mfma32(a[i], b[i / DB], acc[i % DB]);
-    hook(i);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-__device__ __forceinline__ bf16x8 pack8(const f32x16& x, int c) {
-  bf16x8 o;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (__bf16)x[8 * c + e];
-  return o;
-}
 
 // Work-group index -> (kv key = batch*Hkv + kv head, head within group, tile).  Work-group n runs on XCD
 // n mod 8 (they are dealt round-robin), each XCD with its own L2.

@@ -186,7 +186,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     if (wave >= NW / 2) phase_barrier();
     bf16x8 first[AHEAD];
     rows_fetch<D, MB, AHEAD>(k_lds(3), ad, 0, first);
-    rows_product<D, MB, NB, AHEAD, true>(k_lds(3), ad, 0, qreg, s, first);
+    const f32x4 zero[MB] = {};
+    rows_product<D, MB, NB, AHEAD>(k_lds(3), ad, 0, qreg, s, zero, first);
     wait_loads_barrier<2 * LOADS>();              // set 0
     softmax(ka);
     wait_loads_barrier<LOADS>();                  // set 1

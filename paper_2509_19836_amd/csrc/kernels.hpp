@@ -10,14 +10,6 @@ namespace burst {
 // 2^kLazyLog2; exp2 arguments then stay <= kLazyLog2, far inside fp32 / bf16 range.
 constexpr float kLazyLog2 = 6.0f;
 
-// LDS operand prefetch distances: k-steps ahead for row-wise GEMMs, operands ahead for column-wise.
-#ifndef BURST_ROWS_AHEAD
-#define BURST_ROWS_AHEAD 2
-#endif
-#ifndef BURST_COLS_AHEAD
-#define BURST_COLS_AHEAD 3
-#endif
-constexpr int kRowsAhead = BURST_ROWS_AHEAD, kColsAhead = BURST_COLS_AHEAD;
 #ifndef BURST_A16
 #define BURST_A16 4   // 16x16x32 streams, operands (two MFMAs each) ahead: 3 and 4 alike, 5 and 6 one to four percent slower
 #endif

@@ -83,6 +83,10 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
+// The same with 4 bytes per lane.
+__device__ __forceinline__ void load_dword_to_lds(const char* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+}
 // Wait until at most N of this wave's global loads are outstanding, then meet the other waves.  Work-group
 // barrier without the full drain of __syncthreads: loads of later tiles stay in flight.  The scheduling fences
 // keep arithmetic, which the memory clobber does not bind, from drifting across.
@@ -96,6 +100,13 @@ __device__ __forceinline__ void wait_loads_barrier() {
 __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The same with this wave's LDS stores done, for a phase whose results the other half reads.
+__device__ __forceinline__ void stores_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -222,6 +233,100 @@ struct KvStream {
   }
 };
 
+// Walk of a key block over (query head of its group, query tile of BQ rows that can see it): per tile the Q and dO
+// rows, which all NW waves bring together, and BQ values of the row vector that the wave itself reads (64 lanes: its
+// own copy).  A tile is always 2 N + 1 loads per wave; past the end of the walk the last tile is asked for again.
+template <int D, int BQ, int NW, bool BLK>   // BLK: block-wise sparse mask
+struct QStream {
+  using Stager = DirectStager<D, BQ, NW>;
+  static constexpr int N = Stager::N, LOADS = 2 * N + 1;
+  static_assert(BQ == 64, "a row vector value per lane");
+  Stager stage_q, stage_o;
+  uint32_t row_off;
+  int left, heads, q0;    // cursor: tiles left of this head, heads left (0: the walk is over), first row of its tile
+  int run_start, run_len, sq;
+  bool clamped;
+  const uint8_t* open;    // LDS flags per query tile from a block-wise sparse mask
+  const char *q_head, *o_head, *row_head;   // first tile of the run, at the cursor's head
+  const char *q_tile, *o_tile, *row_tile;
+  int64_t q_step, o_step; // bytes per tile
+  int64_t q_next, o_next, row_next;         // bytes per head
+
+  __device__ __forceinline__ void init(const TensorDev& q, const TensorDev& d_o, const RowvecDev& vec, int b, int hq, int group,
+                                       TileRun run, int sq_, int wave, int lane, const uint8_t* open_flags) {
+    sq = sq_;
+    if (BLK) open = open_flags;
+    run_start = __builtin_amdgcn_readfirstlane(run.start);   // (results of divisions: keeps what follows scalar)
+    run_len = __builtin_amdgcn_readfirstlane(run.len);
+    heads = run_len > 0 ? group : 0;
+    left = run_len;
+    q0 = run_start * BQ;
+    q_step = 2 * BQ * q.ss;
+    o_step = 2 * BQ * d_o.ss;
+    q_next = 2 * q.sh;
+    o_next = 2 * d_o.sh;
+    row_next = 4 * vec.sh;
+    q_head = reinterpret_cast<const char*>((const __bf16*)q.ptr + b * q.sb + hq * q.sh) + run_start * q_step;
+    o_head = reinterpret_cast<const char*>((const __bf16*)d_o.ptr + b * d_o.sb + hq * d_o.sh) + run_start * o_step;
+    row_head = reinterpret_cast<const char*>(vec.ptr + b * vec.sb + hq * vec.sh + q0);
+    first_of_head();
+    offsets(BQ, wave, lane);
+    clamped = false;
+    if (BLK) {
+      if (heads > 0 && !is_open()) advance();
+    }
+  }
+  __device__ __forceinline__ void first_of_head() {
+    left = run_len;
+    q0 = run_start * BQ;
+    q_tile = q_head;
+    o_tile = o_head;
+    row_tile = row_head;
+  }
+  __device__ __forceinline__ void offsets(int valid, int wave, int lane) {
+    stage_q.clamp(q_step / (2 * BQ), valid, wave, lane);
+    stage_o.clamp(o_step / (2 * BQ), valid, wave, lane);
+    row_off = 4 * min(lane, valid - 1);
+  }
+  __device__ __forceinline__ bool is_open() const { return __builtin_amdgcn_readfirstlane(open[q0 / BQ]) != 0; }
+  __device__ __forceinline__ bool valid() const { return heads > 0; }
+  // First row of the cursor's tile, -1 when the walk is over
+  __device__ __forceinline__ int cursor() const { return heads > 0 ? q0 : -1; }
+  // To the next tile; at the end of the walk the cursor stays where it is
+  __device__ __forceinline__ void advance() {
+    if (heads == 0) return;
+    do {
+      if (left > 1) {
+        --left;
+        q0 += BQ;
+        q_tile += q_step;
+        o_tile += o_step;
+        row_tile += 4 * BQ;
+      } else {
+        if (--heads == 0) return;
+        q_head += q_next;
+        o_head += o_next;
+        row_head += row_next;
+        first_of_head();
+      }
+    } while (BLK && !is_open());
+  }
+  // Before the loads of a tile: rows past the last one are read as copies of it
+  __device__ __forceinline__ void begin(int wave, int lane) {
+    const bool ragged = q0 + BQ > sq;
+    if (ragged != clamped) {
+      offsets(ragged ? sq - q0 : BQ, wave, lane);
+      clamped = ragged;
+    }
+  }
+  // Load i of a tile
+  __device__ __forceinline__ void load(int i, uint32_t q_lds, uint32_t o_lds, uint32_t row_lds, int wave) const {
+    if (i < N) stage_q.load_one(q_tile, i, q_lds, wave);
+    else if (i < 2 * N) stage_o.load_one(o_tile, i - N, o_lds, wave);
+    else load_dword_to_lds(row_tile, row_off, row_lds);
+  }
+};
+
 // Class of a tile of `bk` rows against a wave's own rows of the other axis, from its first row: nothing visible,
 // all of it visible, or mixed (the per-element mask decides).
 struct TileRanges {
@@ -240,15 +345,15 @@ struct TileRanges {
 // Products with one hook per LDS operand (NB MFMAs): hook(i) holds independent vector work that goes behind
 // them, and the scheduling fence after it keeps it there.  Operands are fetched AHEAD of their use; the first
 // AHEAD ones may have been fetched by the caller (`first`).
-//   acc[mb][nb] (+)= rows(tile)[row0 + 16 mb ..] * b[ks][nb], operand i = ks * MB + mb
+//   acc[mb][nb] = init[mb] + rows(tile)[row0 + 16 mb ..] * b[ks][nb], operand i = ks * MB + mb
 template <int D, int MB, int AHEAD>
 __device__ __forceinline__ void rows_fetch(uint32_t tile, const OperandAddr<D>& ad, int row0, bf16x8 (&first)[AHEAD]) {
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i) first[i] = rows_operand<D>(tile, ad, row0 + 16 * (i % MB), i / MB);
 }
-template <int D, int MB, int NB, int AHEAD, bool ZERO, class Hook = NoHook>
+template <int D, int MB, int NB, int AHEAD>
 __device__ __forceinline__ void rows_product(uint32_t tile, const OperandAddr<D>& ad, int row0, const bf16x8 (&b)[D / 32][NB],
-                                             f32x4 (&acc)[MB][NB], const bf16x8 (&first)[AHEAD], Hook&& hook = Hook()) {
+                                             f32x4 (&acc)[MB][NB], const f32x4 (&init)[MB], const bf16x8 (&first)[AHEAD]) {
   constexpr int N = D / 32 * MB;
   static_assert(AHEAD <= N, "more operands fetched ahead than the product has");
   bf16x8 a[N];
@@ -260,9 +365,7 @@ __device__ __forceinline__ void rows_product(uint32_t tile, const OperandAddr<D>
     if (i + AHEAD < N) a[i + AHEAD] = rows_operand<D>(tile, ad, row0 + 16 * ((i + AHEAD) % MB), (i + AHEAD) / MB);
     const int ks = i / MB, mb = i % MB;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      acc[mb][nb] = mfma16(a[i], b[ks][nb], (ZERO && ks == 0) ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[mb][nb]);
-    hook(i);
+    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma16(a[i], b[ks][nb], ks == 0 ? init[mb] : acc[mb][nb]);
     __builtin_amdgcn_sched_barrier(0);
   }
 }

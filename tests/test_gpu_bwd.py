@@ -158,6 +158,51 @@ def test_ragged_single_step_backward(lib, d, sq, sk, qoff):
         assert np.abs(dq2.cpu().numpy() - dQ).max() <= tol(dQ)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sq,sk", [(1, 1), (63, 65), (65, 63), (192, 256), (257, 129), (320, 449)])
+def test_backward_ragged_tails_beside_poisoned_rows(lib, d, sq, sk):
+    """Walks of one to seven tiles whose last one is cut anywhere, over the heads of a group (each head starts again on a
+    whole tile), with NaN in the rows right behind every tensor and row vector; a row with lse = -inf adds nothing."""
+    torch = _torch()
+    B, Hq, Hkv, pad = 1, 6, 2, 64
+    rng = np.random.Generator(np.random.PCG64(wl.BASE_SEED + 9700 + sq * 1000 + sk + d))
+    bits = [wl.f32_to_bf16_bits(rng.standard_normal(s, dtype=np.float32))
+            for s in ((B, sq, Hq, d), (B, sk, Hkv, d), (B, sk, Hkv, d), (B, sq, Hq, d))]
+    Qh, Kh, Vh, Gh = (hp.widen(x) for x in bits)
+    scale = 1.0 / np.sqrt(d)
+    lse_h = (oc.mha_step_fwd(Qh, Kh, Vh, scale, None)[1] + rng.uniform(0.1, 1.0, (B, Hq, sq))).astype(np.float32)
+    D_h = rng.standard_normal((B, Hq, sq)).astype(np.float32)
+    dead = sq // 2 if sq > 1 else None
+
+    def guarded(x, axis, dtype):
+        shape = list(x.shape)
+        shape[axis] += pad
+        full = torch.full(shape, float("nan"), device="cuda", dtype=dtype)
+        view = full.narrow(axis, 0, x.shape[axis])
+        view.copy_(x)
+        return view
+
+    q, k, v, g = (guarded(hp.dev_bf16(x), 1, torch.bfloat16) for x in bits)
+    lse_t = torch.from_numpy(lse_h.copy())
+    if dead is not None:
+        lse_t[:, :, dead] = -float("inf")
+    lse, D = (guarded(x.cuda(), 2, torch.float32) for x in (lse_t, torch.from_numpy(D_h)))
+    for causal in (False, True):
+        qoff = sk // 2
+        vis = oc.visibility(qoff + np.arange(sq), np.arange(sk), causal).copy()
+        if dead is not None:
+            vis[dead] = False
+        ref = oc.mha_step_bwd(Qh, Kh, Vh, Gh, lse_h.astype(np.float64), D_h.astype(np.float64), scale, vis)
+        out = [torch.full(s, float("nan"), device="cuda") for s in ((B, sq, Hq, d), (B, sk, Hkv, d), (B, sk, Hkv, d))]
+        print(f"d={d} sq={sq} sk={sk} causal={causal}", flush=True)
+        lib.burst_attn_step_bwd(lib.shape(B, Hq, Hkv, d, sq, sk, scale),
+                                lib.burst_mask_t(int(causal), 1, 1, 0, (qoff, 0), (0, 0), sq, sk, 1), q, k, v, g, lse, D,
+                                dq=out[0], dk=out[1], dv=out[2])
+        torch.cuda.synchronize()
+        for name, got, want in zip(("dq", "dk", "dv"), out, ref):
+            assert np.abs(got.cpu().numpy() - want).max() <= hp.REL_TOL * max(np.abs(want).max(), 1e-30), (name, causal)
+
+
 def test_backward_strided_views_and_guard_rows(lib):
     torch = _torch()
     B, S, H, d, pad = 1, 192, 2, 128, 64
