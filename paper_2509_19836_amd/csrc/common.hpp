@@ -1,20 +1,4 @@
-// Shared device-side building blocks of libburstattn's gfx950 kernels.
-//
-// MFMA 32x32x16 bf16 register layouts (lane l: r = l % 32, h = l / 32):
-//   A operand (M x K): lane holds A[m = r][k = 8h .. 8h+7]
-//   B operand (K x N): lane holds B[k = 8h .. 8h+7][n = r]
-//   C/D (M x N), 16 fp32: register v holds C[m = 8*(v/4) + 4h + v%4][n = r]
-// The contraction index k may be permuted freely as long as A and B use the same permutation.
-// An accumulator tile whose M index is the next contraction index can therefore be fed back as
-// an operand after a bf16 pack: registers 8c .. 8c+7 of lane (r, h) hold the eight M rows
-//   16c + 8t + 4h + j   (t = 0,1; j = 0..3)
-// of column r, and the other operand only has to be read in that same row order.
-//
-// LDS tiles are row-major [rows][D] bf16 with a row pitch of 2*D + 16 bytes (a multiple of 16 B
-// that is an odd number of 16 B units, so 16 lanes reading 16 B from 16 different rows hit 64
-// different banks).  Rows are stored permuted inside each group of 16: tile row 16c + 4a + b sits
-// at LDS row 16c + 4b + a.  With that, the four rows a transposing read needs per 16-lane group
-// (tile rows 8t+4h+0..3) are four LDS rows 4 apart, i.e. 16 banks apart: conflict free.
+// Shared device-side building blocks of libburstattn's gfx950 kernels: types, the mask, tiles, work-group mapping.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -205,45 +189,8 @@ struct BlockClassifier {
   }
 };
 
-__device__ __forceinline__ int lds_row(int tile_row) {
-  // tile row 16c + 4a + b  ->  LDS row 16c + 4b + a
-  return (tile_row & ~15) | ((tile_row & 3) << 2) | ((tile_row >> 2) & 3);
-}
-// Variant for tiles whose rows are the contraction index of a GEMM whose other operand is read
-// row-wise: tile row 16c + 8h + 4t + j -> LDS row 16c + 4j + 2t + h, so that the column-wise operand
-// read hands half-wave h the rows 16c + 8h .. 8h+7 in order, the same eight k that lds_rows_operand
-// hands it (with lds_row it would be rows 4h..4h+3 and 8+4h..8+4h+3, the accumulator order).
-__device__ __forceinline__ int lds_row_k8(int tile_row) {
-  return (tile_row & ~15) | ((tile_row & 3) << 2) | (((tile_row >> 2) & 1) << 1) | ((tile_row >> 3) & 1);
-}
-
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// Operand with lane = tile row, eight consecutive columns: rows row_base + r (r = lane % 32),
-// columns col0 + 8h .. +7 (bf16 elements).
-template <int PITCH>
-__device__ __forceinline__ bf16x8 lds_rows_operand(const char* tile, int row_base, int col0, int r, int h) {
-  const char* p = tile + lds_row(row_base + r) * PITCH + (col0 + 8 * h) * 2;
-  return *reinterpret_cast<const bf16x8*>(p);
-}
-
-// Operand with lane = tile column, eight rows: column col_base + r, rows
-// row16 + 8t + 4h + j (t = 0,1; j = 0..3) of a 16-row group starting at tile row row16
-// (a multiple of 16).  Element order 4t + j, matching packed accumulator registers.
-template <int PITCH>
-__device__ __forceinline__ bf16x8 lds_cols_operand(const char* tile, int row16, int col_base, int lane) {
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const int i16 = lane & 15, g2 = (lane >> 4) & 1, h = lane >> 5;
-  // LDS row of tile row 8t+4h+j is 4j + 2t + h; lanes 4j .. 4j+3 of a 16-lane group supply row j
-  const int j = i16 >> 2;
-  const char* p = tile + (row16 + 4 * j + h) * PITCH + (col_base + 16 * g2 + 4 * (i16 & 3)) * 2;
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 2 * PITCH));
-  typedef __attribute__((ext_vector_type(8))) short s16x8;
-  s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, both);
 }
 
 // Wait for every outstanding global load of this wave.  Used once, before a tile loop, after the
@@ -251,11 +198,6 @@ __device__ __forceinline__ bf16x8 lds_cols_operand(const char* tile, int row16, 
 // path that they have landed and re-inserts vmcnt waits inside the loop, which then also wait for
 // the tile prefetch issued just before them.
 __device__ __forceinline__ void wait_global_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-
-__device__ __forceinline__ float half_swap(float x) {
-  // value held by the lane 32 away
-  return __shfl_xor(x, 32, 64);
-}
 
 // The tiles of an axis that have any visible pair against the WHOLE other chunk, as up to two runs of
 // consecutive tile indices (found by the host; with more runs every tile is launched).  Only these are
@@ -280,63 +222,6 @@ __host__ __device__ __forceinline__ TileRun visible_tiles(const MaskDev& mk, int
   const int first = iv.some_lo / TILE;
   return TileRun{first, (iv.some_hi + TILE - 1) / TILE - first};
 }
-
-// Stage a [ROWS x D] bf16 tile: global (row-major, row stride `ss` elements) -> registers -> LDS,
-// by THREADS threads.  Split in two so the loads can be issued before the compute they overlap
-// with.  The per-lane part of the address is one 32-bit element offset computed once; the
-// per-tile and per-pass parts are wave-uniform, so a load costs no vector arithmetic.  Tiles that
-// reach past the last row take a slower path that clamps row indices instead.
-template <int D, int ROWS, int THREADS = 256, bool K8 = false>   // K8: rows permuted by lds_row_k8
-struct TileStager {
-  static constexpr int CPR = D / 8;              // 16-byte chunks per row
-  static constexpr int RPP = THREADS / CPR;      // rows per pass
-  static constexpr int PASSES = ROWS / RPP;
-  static constexpr int PITCH = 2 * D + 16;
-  static_assert(ROWS % RPP == 0, "tile rows must be a multiple of rows per pass");
-  u32x4 regs[PASSES];
-  uint32_t lane_off;    // (tid / CPR) * ss + (tid % CPR) * 8, elements
-  uint32_t lds_off[PASSES];
-  uint32_t src_off[PASSES];   // byte offset of this thread's chunk of pass i from the tile's first row
-
-  // valid_rows < ROWS: load_at() reads the tile's rows beyond valid_rows - 1 as copies of that row,
-  // for tiles that reach past the end of a matrix whose extra rows must only be finite.
-  __device__ __forceinline__ void init(int64_t ss, int tid, int valid_rows = ROWS) {
-    lane_off = (uint32_t)(tid / CPR) * (uint32_t)ss + (uint32_t)(tid % CPR) * 8u;
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-      lds_off[i] = (K8 ? lds_row_k8(tid / CPR + i * RPP) : lds_row(tid / CPR + i * RPP)) * PITCH + (tid % CPR) * 16;
-      src_off[i] = 2u * ((uint32_t)min(tid / CPR + i * RPP, valid_rows - 1) * (uint32_t)ss + (uint32_t)(tid % CPR) * 8u);
-    }
-  }
-  __device__ __forceinline__ void load_pass(const char* tile, int i) { regs[i] = *reinterpret_cast<const u32x4*>(tile + src_off[i]); }
-  __device__ __forceinline__ void store_pass(char* tile, int i) const { *reinterpret_cast<u32x4*>(tile + lds_off[i]) = regs[i]; }
-  // A tile that lies wholly inside the tensor, given the (wave-uniform) address of its first row:
-  // uniform base plus a precomputed 32-bit lane offset, no address arithmetic per load.
-  __device__ __forceinline__ void load_at(const char* tile) {
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) regs[i] = *reinterpret_cast<const u32x4*>(tile + src_off[i]);
-  }
-  // base: first row of the tensor slice; row0: first tile row; nrows: rows in the slice (> row0)
-  __device__ __forceinline__ void load(const __bf16* base, int64_t ss, int row0, int nrows, int tid) {
-    if (row0 + ROWS <= nrows) {
-      const __bf16* tile = base + (int64_t)row0 * ss;    // uniform
-#pragma unroll
-      for (int i = 0; i < PASSES; ++i)
-        regs[i] = *reinterpret_cast<const u32x4*>(tile + (int64_t)i * RPP * ss + lane_off);
-    } else {
-      const int c = tid % CPR, rr = tid / CPR;
-#pragma unroll
-      for (int i = 0; i < PASSES; ++i) {
-        int row = min(row0 + rr + i * RPP, nrows - 1);
-        regs[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)row * ss + c * 8);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char* tile) const {
-#pragma unroll
-    for (int i = 0; i < PASSES; ++i) *reinterpret_cast<u32x4*>(tile + lds_off[i]) = regs[i];
-  }
-};
 
 // Scope of a stream of MFMAs: the wave runs at raised issue priority.  A SIMD issues one vector-class
 // instruction at a time and picks the oldest ready wave; without this, a co-resident wave in a

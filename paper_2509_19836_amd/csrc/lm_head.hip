@@ -13,189 +13,177 @@
 //   3. lm_dh_kernel           dH_i  = dLogits W_head          (contraction over the vocabulary)
 //   4. lm_transpose_h_kernel + lm_dw_kernel
 //                             dW^T += H_i^T dLogits           (contraction over the tile's tokens)
-// The three GEMMs share one main loop: 256 x 256 output tile per work-group of 8 waves (wave tile
-// 128 x 64, 128 accumulator registers), k-tiles of 64 double-buffered in LDS, operands read from LDS
-// either row-wise (the matrix is stored with the contraction index contiguous) or column-wise with
-// the transposing LDS read (the contraction index is the storage row).  Only H_i, a few MB per
-// sequence tile, is ever transposed in memory.  The wave tile is as large as 128 accumulator
-// registers allow (0.75 KB of LDS operand reads per MFMA); the loop over the k-tiles has no branches
-// and carries the staging of the next k-tile between its MFMAs.
-#include <type_traits>
-
+// The three GEMMs share one main loop (LmGemm below).  An operand whose contraction index is the storage row is
+// read with the transposing LDS read; only H_i, a few MB per sequence tile, is ever transposed in memory.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma16.hpp"
 
 namespace burst {
 
 namespace {
 
-// Output tile of a work-group: 256 x kLmBN, k-tiles of kLmBK, one wave per 128 x kLmWN sub-tile.
-// The defaults (256, 64, 64: eight waves, one work-group per CU) measured fastest; 128 x 128 wave
-// tiles at one wave per SIMD and two 256 x 128 work-groups per CU with k-tiles of 32 build from the
-// same source and were slower.
-#ifndef LM_BN
-#define LM_BN 256
-#endif
-#ifndef LM_BK
-#define LM_BK 64
-#endif
-#ifndef LM_WN
-#define LM_WN 64
-#endif
-constexpr int kLmBM = 256, kLmBN = LM_BN, kLmBK = LM_BK, kLmKS = kLmBK / 16, kLmWN = LM_WN, kLmNB = kLmWN / 32;
-constexpr int kLmWaves = (kLmBM / 128) * (kLmBN / kLmWN), kLmThreads = 64 * kLmWaves;
-constexpr int kLmPerCU = kLmWN == 128 ? 1 : 512 / kLmThreads;
+// Output tile of a work-group of eight waves, and the k-tile; 128 accumulator registers per wave.
+constexpr int kLmBM = 256, kLmBN = 256, kLmBK = 64, kLmThreads = 512;
 
-// One GEMM operand: where its k-tiles come from and how they are staged.  X: extent of the tile
-// along the operand's own (non-contracted) index.
-//   COLS = false: storage [x][k], k contiguous; the tile is rows x0 .. x0+X-1, columns k0 .. k0+BK-1.
-//                 lim = number of valid storage rows; rows beyond are read as the last valid row
-//                 (the clamp is folded into the per-thread offsets once).
-//   COLS = true : storage [k][x], x contiguous; the tile is rows k0 .. k0+BK-1, columns x0 .. x0+X-1
-//                 (always inside the row), its rows permuted in LDS so that the column-wise read
-//                 hands out k in the row-wise operand's order.  lim = number of valid k rows: the
-//                 k-tiles that reach past it take the slower load with per-row clamping.
-template <bool COLS, int X>
+// One GEMM operand: where its k-tiles come from and how they lie in LDS (32 KiB).  A k-tile is four direct loads
+// per wave.
+//   COLS = false: storage [x][k], k contiguous.  LDS: [256 x][64 k].  lim = valid storage rows; rows beyond are
+//                 read as the last one (folded into the per-lane offsets once).
+//   COLS = true : storage [k][x], x contiguous.  LDS: two tiles [64 k][128 x], the k rows permuted so that the
+//                 transposing read, which hands out rows 16 (e / 4) + 4 g + e % 4 of 32, gives k = 8 g + e as the
+//                 row-wise operand has it.  lim = valid k rows; a k-tile that reaches past them reads copies of
+//                 the last one.
+template <bool COLS>
 struct LmOperand {
-  using Stager = std::conditional_t<COLS, TileStager<X, kLmBK, kLmThreads, true>, TileStager<kLmBK, X, kLmThreads>>;
-  static constexpr int BYTES = (COLS ? kLmBK : X) * Stager::PITCH;
-  static constexpr int PASSES = Stager::PASSES;
-  Stager st;
-  const __bf16* base;
-  const char* tile;     // next k-tile to stage
+  static constexpr int N = 4, BYTES = 256 * kLmBK * 2;
+  using Rows = DirectStager<64, 256, 8>;
+  using Cols = DirectStager<128, kLmBK, 8>;   // one of the two tiles
+  Rows rows;
+  uint32_t col_off[Cols::N];
+  const char* tile;     // k-tile to ask for
   int64_t ld, step;
-  int lim, k0;
+  int left, valid;      // k-tiles behind it; valid k rows from its first one on (COLS)
 
-  __device__ __forceinline__ void init(const __bf16* ptr, int64_t ld_, int lim_, int x0, int tid) {
+  __device__ __forceinline__ void init(const __bf16* ptr, int64_t ld_, int lim, int x0, int nk, int wave, int lane) {
     ld = ld_;
-    lim = lim_;
-    k0 = 0;
-    base = COLS ? ptr + x0 : ptr;
+    left = nk - 1;
     tile = reinterpret_cast<const char*>(COLS ? ptr + x0 : ptr + (int64_t)x0 * ld);
     step = COLS ? kLmBK * ld * 2 : kLmBK * 2;
-    st.init(ld, tid, COLS ? kLmBK : min(X, lim - x0));
+    if (COLS) {
+      valid = lim;
+      offsets(wave, lane);
+    } else {
+      rows.clamp(ld, min(256, lim - x0), wave, lane);
+    }
   }
-  // leading k-tiles that the plain loads can stage
-  __device__ __forceinline__ int plain_tiles(int nk) const { return COLS ? min(nk, lim / kLmBK) : nk; }
-  __device__ __forceinline__ void load_pass(int i) { st.load_pass(tile, i); }   // plain k-tiles only
-  __device__ __forceinline__ void next() {
-    tile += step;
-    k0 += kLmBK;
+  __device__ __forceinline__ void offsets(int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < Cols::N; ++i) {
+      const int at = (i * 8 + wave) * Cols::RPI + lane / 16;   // row in LDS
+      const int k = (at & 32) + 8 * ((at >> 2) & 3) + 4 * ((at >> 4) & 1) + (at & 3);
+      col_off[i] = 2u * ((uint32_t)min(k, valid - 1) * (uint32_t)ld + (uint32_t)(((lane % 16) ^ swz<128>(at)) * 8));
+    }
   }
-  __device__ __forceinline__ void issue(int tid) {   // any k-tile
-    if (!COLS || k0 + kLmBK <= lim) st.load_at(tile);
-    else st.load(base, ld, k0, lim, tid);
-    next();
+  // To the next k-tile; on the last one the cursor stays (that tile is then asked for again and not read)
+  __device__ __forceinline__ void next(int wave, int lane) {
+    const int move = min(left, 1);   // (arithmetic on 0 / 1: the compiler keeps selected addresses in vector registers)
+    left -= move;
+    tile += step & -(int64_t)move;
+    if (COLS) {
+      valid -= kLmBK * move;
+      if (valid < kLmBK) offsets(wave, lane);
+    }
   }
-  __device__ __forceinline__ void commit(char* lds) const { st.store(lds); }
-  // fragment for the 16-wide k-step ks of the tile in LDS: lane -> row / column x_off + (lane & 31)
-  static __device__ __forceinline__ bf16x8 frag(const char* lds, int x_off, int ks, int lane) {
-    if (COLS) return lds_cols_operand<Stager::PITCH>(lds, ks * 16, x_off, lane);
-    return lds_rows_operand<Stager::PITCH>(lds, x_off, ks * 16, lane & 31, lane >> 5);
+  __device__ __forceinline__ void load(int i, uint32_t lds, int wave) const {
+    if (COLS) load_to_lds(tile + (i / 2) * 256, col_off[i % 2], lds + (i / 2) * Cols::BYTES + ((i % 2) * 8 + wave) * 1024);
+    else rows.load_one(tile, i, lds, wave);
   }
 };
 
-template <bool A_COLS, bool B_COLS>
+// The main loop.  The matrix pipe bounds it (2048 clocks per k-tile and SIMD, against 1536 clocks of LDS reads and
+// 512 of LDS writes per CU); what is to be avoided is waiting at the barriers.
+//  - 16x16x32 MFMAs, k-tiles by direct global -> LDS loads: no staging registers, no LDS store instructions.
+//  - A k-tile is two phases, each over one half of the 256 A rows and all of B (a wave: 64 of the 128 A rows against
+//    its 64 B columns, 32 MFMAs).  B stays in registers for the second phase, so B and the lower half of A are free
+//    after the first one: their successors of k-tile t + 2 are asked for in phase 2 of t, those of the upper half of
+//    A in phase 1 of t + 1, and every load has two phases until its tile is announced by a barrier, a full phase
+//    before it is read.  The first operands of a phase are therefore fetched in the one before, across the barrier.
+// 8192 tokens, d = 4096, 32000 words, per launch: logits 1.72 ms (1250 TFLOP/s), dH 1.51 (1420), dW 1.69 (1270); with
+// 32x32x16 MFMAs, tiles staged through registers and one barrier per k-tile: 2.10, 1.86, 2.09.  A k-tile takes 1.51 us;
+// the rest of logits and dW (13 and 23 us per output tile) is their fp32 output, which all CUs write at the same time.
+template <bool B_COLS>
 struct LmGemm {
-  using OpA = LmOperand<A_COLS, kLmBM>;
-  using OpB = LmOperand<B_COLS, kLmBN>;
-  static constexpr int STAGE = OpA::BYTES + OpB::BYTES;
-  static constexpr int LDS = 2 * STAGE;
-  static constexpr int NMFMA = 4 * kLmNB;     // MFMAs per 16-wide k-step
+  using OpA = LmOperand<false>;
+  using OpB = LmOperand<B_COLS>;
+  static constexpr int SLOT = OpA::BYTES + OpB::BYTES, LDS = 2 * SLOT, AHEAD = 3;
+  f32x4 acc[2][4][4];   // [half][mb][nb]: rows 128 half + 64 wm + 16 mb + 4 g + v, column 64 wn + 16 nb + r
+  bf16x8 bf[2][4];      // [k-step][nb]
+  bf16x8 first[AHEAD];
+  OperandAddr<64> ad;
+  OperandAddr<128> adc;
 
-  // The MFMAs of the k-tile in LDS buffer `cur`.  STAGE_NEXT: 0 = nothing else; 1 = the next k-tile
-  // is staged into buffer `nxt` with plain loads, one load or LDS write slipped in after every few
-  // MFMAs (loads during the first half of the k-steps, LDS writes during the second), so that the
-  // waves of a work-group, which the barrier keeps in phase, do not all queue at the memory pipe
-  // and then at the LDS write port while the matrix pipe idles; 2 = the next k-tile needs the
-  // clamping loads: issued whole before the MFMAs, written whole after them.
-  template <int STAGE_NEXT>
-  static __device__ __forceinline__ void k_tile(f32x16 (&acc)[4][kLmNB], const char* cur, char* nxt, OpA& a, OpB& b, int wm,
-                                                int wn, int tid, int lane) {
-    const char* at = cur;
-    const char* bt = cur + OpA::BYTES;
-    bf16x8 af[2][4], bf[2][kLmNB];
+  __device__ __forceinline__ bf16x8 a_operand(uint32_t slot, int half, int wm, int i) const {   // i: 4 k-steps + mb
+    return rows_operand<64>(slot + half * (OpA::BYTES / 2) + wm * (64 * 128), ad, 16 * (i % 4), i / 4);
+  }
+  __device__ __forceinline__ bf16x8 b_operand(uint32_t slot, int wn, int ks, int nb) const {
+    if (B_COLS) return cols_operand<128>(slot + OpA::BYTES + (wn >> 1) * LmOperand<true>::Cols::BYTES, adc, 32 * ks, nb);
+    return rows_operand<64>(slot + OpA::BYTES + wn * (64 * 128), ad, 16 * nb, ks);
+  }
+  // The 32 MFMAs of a phase, hook(i) behind the four of operand i.  The next phase reads half HALF ^ 1 from slot `next`.
+  template <int HALF, class Hook>
+  __device__ __forceinline__ void phase(uint32_t slot, uint32_t next, int wm, int wn, Hook&& hook) {
+    bf16x8 a[8 + AHEAD];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) af[0][mb] = OpA::frag(at, wm * 128 + 32 * mb, 0, lane);
+    for (int i = 0; i < AHEAD; ++i) a[i] = first[i];
 #pragma unroll
-    for (int nb = 0; nb < kLmNB; ++nb) bf[0][nb] = OpB::frag(bt, wn * kLmWN + 32 * nb, 0, lane);
-    if (STAGE_NEXT == 2) {
-      a.issue(tid);
-      b.issue(tid);
-    }
-    constexpr int HALF = kLmKS / 2 > 0 ? kLmKS / 2 : 1;                 // k-steps that carry loads
-    constexpr int SLOTS = HALF * NMFMA;                                 // MFMAs that may be followed by a load
-    constexpr int NOPS = OpA::PASSES + OpB::PASSES;
-    constexpr int EVERY = SLOTS / NOPS > 0 ? SLOTS / NOPS : 1;
+    for (int i = 0; i < 8; ++i) {
+      a[i + AHEAD] = i + AHEAD < 8 ? a_operand(slot, HALF, wm, i + AHEAD) : a_operand(next, HALF ^ 1, wm, i + AHEAD - 8);
+      if (HALF == 0 && (i == 1 || i == 2)) {   // second k-step of this tile
 #pragma unroll
-    for (int ks = 0; ks < kLmKS; ++ks) {
-      if (ks + 1 < kLmKS) {
+        for (int j = 0; j < 2; ++j) bf[1][2 * (i - 1) + j] = b_operand(slot, wn, 1, 2 * (i - 1) + j);
+      }
+      if (HALF == 1 && (i == 4 || i == 5)) {   // first k-step of the next tile
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) af[(ks + 1) & 1][mb] = OpA::frag(at, wm * 128 + 32 * mb, ks + 1, lane);
-#pragma unroll
-        for (int nb = 0; nb < kLmNB; ++nb) bf[(ks + 1) & 1][nb] = OpB::frag(bt, wn * kLmWN + 32 * nb, ks + 1, lane);
+        for (int j = 0; j < 2; ++j) bf[0][2 * (i - 4) + j] = b_operand(next, wn, 0, 2 * (i - 4) + j);
       }
 #pragma unroll
-      for (int m = 0; m < NMFMA; ++m) {
-        const int mb = m / kLmNB, nb = m % kLmNB;
-        acc[mb][nb] = mfma32(af[ks & 1][mb], bf[ks & 1][nb], acc[mb][nb]);
-        if (STAGE_NEXT == 1) {
-          const int slot = (ks % HALF) * NMFMA + m;       // position within its half
-          if (slot % EVERY == EVERY - 1 && slot / EVERY < NOPS) {
-            const int op = slot / EVERY;
-            if (ks < HALF || kLmKS == 1) {
-              if (op < OpA::PASSES) a.load_pass(op);
-              else b.load_pass(op - OpA::PASSES);
-            }
-            if (ks >= HALF || kLmKS == 1) {
-              if (op < OpA::PASSES) a.st.store_pass(nxt, op);
-              else b.st.store_pass(nxt + OpA::BYTES, op - OpA::PASSES);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      }
+      for (int nb = 0; nb < 4; ++nb) acc[HALF][i % 4][nb] = mfma16(a[i], bf[i / 4][nb], acc[HALF][i % 4][nb]);
+      hook(i);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (STAGE_NEXT == 1) {
-      a.next();
-      b.next();
-    }
-    if (STAGE_NEXT == 2) {
-      a.commit(nxt);
-      b.commit(nxt + OpA::BYTES);
-    }
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) first[i] = a[8 + i];
   }
 
-  // acc[mb][nb]: rows 32 mb + ... of the wave's 128, columns 32 nb + ... of its kLmWN.  nk >= 1 k-tiles,
-  // double-buffered in LDS, one barrier per k-tile.  The loop over the k-tiles that plain loads can
-  // stage is free of branches.
-  static __device__ __forceinline__ void run(f32x16 (&acc)[4][kLmNB], char* smem, OpA& a, OpB& b, int nk, int wm, int wn,
-                                             int tid, int lane) {
+  // nk >= 1 k-tiles, of which a and b point at the first
+  __device__ __forceinline__ void run(char* smem, OpA& a, OpB& b, int nk, int wm, int wn, int wave, int lane) {
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+    ad.init(lane);
+    adc.init(lane);
+    adc.cols ^= (uint32_t)(wn & 1) << 7;   // column blocks 4 .. 7 of the tile
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int half = 0; half < 2; ++half)
 #pragma unroll
-      for (int nb = 0; nb < kLmNB; ++nb)
+      for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
-    const int n_plain = min(a.plain_tiles(nk), b.plain_tiles(nk));   // k-tiles 0 .. n_plain-1 are plain
-    a.issue(tid);
-    b.issue(tid);
-    a.commit(smem);
-    b.commit(smem + OpA::BYTES);
-    __syncthreads();
-    int kt = 0, buf = 0;
-    for (; kt + 1 < n_plain; ++kt) {        // stages tile kt + 1 < n_plain
-      k_tile<1>(acc, smem + buf * STAGE, smem + (buf ^ 1) * STAGE, a, b, wm, wn, tid, lane);
-      __syncthreads();
-      buf ^= 1;
+        for (int nb = 0; nb < 4; ++nb) acc[half][mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load_b_lower_a = [&](int i, uint32_t slot) {
+      if (i < 4) b.load(i, slot + OpA::BYTES, wave);
+      else a.load(i - 4, slot, wave);
+    };
+    wait_global_loads();
+#pragma unroll
+    for (int i = 0; i < 6; ++i) load_b_lower_a(i, lds0);
+#pragma unroll
+    for (int i = 2; i < 4; ++i) a.load(i, lds0, wave);
+    a.next(wave, lane);
+    b.next(wave, lane);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) load_b_lower_a(i, lds0 + SLOT);
+    wait_loads_barrier<6>();               // tile 0
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) bf[0][nb] = b_operand(lds0, wn, 0, nb);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) first[i] = a_operand(lds0, 0, wm, i);
+    __builtin_amdgcn_s_waitcnt(0xc07f);    // lgkmcnt(0): lets the compiler count the LDS reads at the head of the loop
+    uint32_t slot = lds0, other = lds0 + SLOT;
+    for (int t = 0; t < nk; ++t) {
+      phase<0>(slot, slot, wm, wn, [&](int i) {
+        if (i >= 2 && i < 4) a.load(i, other, wave);         // upper half of A, tile t + 1
+      });
+      a.next(wave, lane);
+      b.next(wave, lane);
+      wait_loads_barrier<2>();             // B and lower half of A, tile t + 1
+      phase<1>(slot, other, wm, wn, [&](int i) {
+        if (i < 6) load_b_lower_a(i, slot);                  // tile t + 2
+      });
+      wait_loads_barrier<6>();             // upper half of A, tile t + 1
+      const uint32_t x = slot;
+      slot = other;
+      other = x;
     }
-    for (; kt + 1 < nk; ++kt) {
-      k_tile<2>(acc, smem + buf * STAGE, smem + (buf ^ 1) * STAGE, a, b, wm, wn, tid, lane);
-      __syncthreads();
-      buf ^= 1;
-    }
-    k_tile<0>(acc, smem + buf * STAGE, nullptr, a, b, wm, wn, tid, lane);
+    wait_global_loads();                   // tiles past the end
   }
 };
 
@@ -226,50 +214,53 @@ __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l
 // ---------------------------------------------------------------------------------------------
 // 1. Logits^T tile (rows: words, columns: tokens of the sequence tile), Alg. 3 forward sweep.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, kLmPerCU) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
-  using G = LmGemm<false, false>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
+  using G = LmGemm<false>;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn;
   if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN;
+  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = p.d_model / kLmBK;
   G::OpA a;
   G::OpB b;
-  a.init(p.w, p.ld_w, p.vocab, m0, tid);
-  b.init(p.h + (int64_t)s0 * p.ld_h, p.ld_h, n_rows, n0, tid);
-  f32x16 acc[4][kLmNB];
-  G::run(acc, smem, a, b, p.d_model / kLmBK, wm, wn, tid, lane);
+  a.init(p.w, p.ld_w, p.vocab, m0, nk, wave, lane);
+  b.init(p.h + (int64_t)s0 * p.ld_h, p.ld_h, n_rows, n0, nk, wave, lane);
+  G gemm;
+  gemm.run(smem, a, b, nk, wm, wn, wave, lane);
 
-  const int word0 = m0 + wm * 128;                 // first word of the wave
+  const int word0 = m0 + wm * 64 + 4 * g;              // first word of the lane
 #pragma unroll
-  for (int nb = 0; nb < kLmNB; ++nb) {
-    const int token = n0 + wn * kLmWN + 32 * nb + r;  // < tile_tokens: the tile count covers n_rows only
-    float* dst = p.logits + (int64_t)token * p.v_pad + word0 + 4 * h;
+  for (int nb = 0; nb < 4; ++nb) {
+    const int token = n0 + wn * 64 + 16 * nb + r;      // < tile_tokens: the tile count covers n_rows only
+    float* dst = p.logits + (int64_t)token * p.v_pad + word0;
     float mx = -INFINITY;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int half = 0; half < 2; ++half)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 x = {acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
-        *reinterpret_cast<f32x4*>(dst + 32 * mb + 8 * g) = x;
+      for (int mb = 0; mb < 4; ++mb) {
+        f32x4& x = gemm.acc[half][mb][nb];
+        *reinterpret_cast<f32x4*>(dst + 128 * half + 16 * mb) = x;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const bool real = word0 + 32 * mb + 8 * g + 4 * h + j < p.vocab;   // padding words stay out of Lse
-          acc[mb][nb][4 * g + j] = real ? x[j] : -INFINITY;
-          mx = fmaxf(mx, acc[mb][nb][4 * g + j]);
+        for (int v = 0; v < 4; ++v) {
+          x[v] = word0 + 128 * half + 16 * mb + v < p.vocab ? x[v] : -INFINITY;   // padding words stay out of Lse
+          mx = fmaxf(mx, x[v]);
         }
       }
-    mx = fmaxf(mx, half_swap(mx));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
     float sum = 0.f;
     if (mx != -INFINITY) {
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int half = 0; half < 2; ++half)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sum += __expf(acc[mb][nb][v] - mx);
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sum += __expf(gemm.acc[half][mb][nb][v] - mx);
     }
-    sum += half_swap(sum);
-    if (h == 0) p.part[(int64_t)(tm * 2 + wm) * p.tile_tokens + token] = float2{mx, sum};
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    if (g == 0) p.part[(int64_t)(tm * 2 + wm) * p.tile_tokens + token] = float2{mx, sum};
   }
 }
 
@@ -335,33 +326,36 @@ __global__ __launch_bounds__(256) void lm_loss_dlogits_kernel(LmHeadParams p, in
 // ---------------------------------------------------------------------------------------------
 // 3. dH_i = dLogits W_head (rows: tokens, columns: hidden, contraction: words).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, kLmPerCU) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
-  using G = LmGemm<false, true>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__global__ __launch_bounds__(kLmThreads, 2) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
+  using G = LmGemm<true>;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn;
   if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN;
+  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = (p.vocab + kLmBK - 1) / kLmBK;
   G::OpA a;
   G::OpB b;
-  a.init(p.dlogits, p.v_pad, p.tile_tokens, m0, tid);
-  b.init(p.w, p.ld_w, p.vocab, n0, tid);
-  f32x16 acc[4][kLmNB];
-  G::run(acc, smem, a, b, (p.vocab + kLmBK - 1) / kLmBK, wm, wn, tid, lane);   // dLogits is zero beyond the vocabulary
+  a.init(p.dlogits, p.v_pad, p.tile_tokens, m0, nk, wave, lane);
+  b.init(p.w, p.ld_w, p.vocab, n0, nk, wave, lane);
+  G gemm;
+  gemm.run(smem, a, b, nk, wm, wn, wave, lane);   // dLogits is zero beyond the vocabulary
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int half = 0; half < 2; ++half)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = m0 + wm * 128 + 32 * mb + 8 * (v >> 2) + 4 * h + (v & 3);
-      if (row >= n_rows) continue;
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < kLmNB; ++nb) {
-        const int64_t off = (int64_t)(s0 + row) * p.ld_dh + n0 + wn * kLmWN + 32 * nb + r;
-        if (p.dh_is_f32) ((float*)p.dh)[off] = acc[mb][nb][v];
-        else ((__bf16*)p.dh)[off] = (__bf16)acc[mb][nb][v];
+      for (int v = 0; v < 4; ++v) {
+        const int row = m0 + 128 * half + wm * 64 + 16 * mb + 4 * g + v;
+        if (row >= n_rows) continue;
+        const int64_t off = (int64_t)(s0 + row) * p.ld_dh + n0 + wn * 64 + r;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+          const float x = gemm.acc[half][mb][nb][v];
+          if (p.dh_is_f32) ((float*)p.dh)[off + 16 * nb] = x;
+          else ((__bf16*)p.dh)[off + 16 * nb] = (__bf16)x;
+        }
       }
-    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -393,34 +387,34 @@ __global__ __launch_bounds__(256) void lm_transpose_h_kernel(LmHeadParams p, int
   }
 }
 
-__global__ __launch_bounds__(kLmThreads, kLmPerCU) void lm_dw_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int accumulate) {
-  using G = LmGemm<false, true>;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__global__ __launch_bounds__(kLmThreads, 2) void lm_dw_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int accumulate) {
+  using G = LmGemm<true>;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn;
   if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN;      // first hidden column, first word
+  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = (n_rows + kLmBK - 1) / kLmBK;      // m0: hidden column, n0: word
   G::OpA a;
   G::OpB b;
-  a.init(p.ht, p.tile_tokens, p.d_model, m0, tid);
-  b.init(p.dlogits, p.v_pad, p.tile_tokens, n0, tid);
-  f32x16 acc[4][kLmNB];
-  G::run(acc, smem, a, b, (n_rows + kLmBK - 1) / kLmBK, wm, wn, tid, lane);    // both factors are zero beyond n_rows
+  a.init(p.ht, p.tile_tokens, p.d_model, m0, nk, wave, lane);
+  b.init(p.dlogits, p.v_pad, p.tile_tokens, n0, nk, wave, lane);
+  G gemm;
+  gemm.run(smem, a, b, nk, wm, wn, wave, lane);    // both factors are zero beyond n_rows
 #pragma unroll
-  for (int nb = 0; nb < kLmNB; ++nb) {
-    const int word = n0 + wn * kLmWN + 32 * nb + r;
+  for (int nb = 0; nb < 4; ++nb) {
+    const int word = n0 + wn * 64 + 16 * nb + r;
     if (word >= p.vocab) continue;
-    float* dst = p.dw + (int64_t)word * p.ld_dw + m0 + wm * 128 + 4 * h;
+    float* dst = p.dw + (int64_t)word * p.ld_dw + m0 + wm * 64 + 4 * g;
+    f32x4 old[2][4];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int i = 0; i < 8; ++i) old[i / 4][i % 4] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (accumulate) {   // all loads before the first store
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 x = {acc[mb][nb][4 * g], acc[mb][nb][4 * g + 1], acc[mb][nb][4 * g + 2], acc[mb][nb][4 * g + 3]};
-        f32x4* q4 = reinterpret_cast<f32x4*>(dst + 32 * mb + 8 * g);
-        if (accumulate) x += *q4;
-        *q4 = x;
-      }
+      for (int i = 0; i < 8; ++i) old[i / 4][i % 4] = *reinterpret_cast<const f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4));
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb] + old[i / 4][i % 4];
   }
 }
 
@@ -441,7 +435,7 @@ int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_mo
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {
   const int want_grad = (p.dh || p.dw) ? 1 : 0;
   const int TD = p.d_model / kLmBN, TV = p.v_pad / kLmBM;   // column tiles of dH / dW, row tiles over the vocabulary
-  constexpr int kLdsLogits = LmGemm<false, false>::LDS, kLdsDh = LmGemm<false, true>::LDS, kLdsDw = LmGemm<false, true>::LDS;
+  constexpr int kLdsLogits = LmGemm<false>::LDS, kLdsGrad = LmGemm<true>::LDS;
   if (p.n_tokens == 0 && p.dw && !p.acc_dw) {
     hipLaunchKernelGGL(lm_zero_dw_kernel, dim3(2048), dim3(256), 0, stream, p);
     return hipGetLastError();
@@ -453,11 +447,11 @@ hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {
                        n_rows, TV, TTn);
     hipLaunchKernelGGL(lm_loss_dlogits_kernel, dim3(want_grad ? k_rows : n_rows), dim3(256), 0, stream, p, s0, n_rows, want_grad);
     if (p.dh)
-      hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD)), dim3(kLmThreads), kLdsDh, stream, p, s0, n_rows,
+      hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD)), dim3(kLmThreads), kLdsGrad, stream, p, s0, n_rows,
                          TT, TD);
     if (p.dw) {
       hipLaunchKernelGGL(lm_transpose_h_kernel, dim3(k_rows / 64, p.d_model / 64), dim3(256), 0, stream, p, s0, n_rows);
-      hipLaunchKernelGGL(lm_dw_kernel, dim3(lm_grid(p.d_model / kLmBM, p.v_pad / kLmBN)), dim3(kLmThreads), kLdsDw, stream, p,
+      hipLaunchKernelGGL(lm_dw_kernel, dim3(lm_grid(p.d_model / kLmBM, p.v_pad / kLmBN)), dim3(kLmThreads), kLdsGrad, stream, p,
                          s0, n_rows, p.d_model / kLmBM, p.v_pad / kLmBN, (p.acc_dw || s0 > 0) ? 1 : 0);
     }
     hipError_t e = hipGetLastError();
