@@ -15,6 +15,8 @@
 //                             dW^T += H_i^T dLogits           (contraction over the tile's tokens)
 // The three GEMMs share one main loop (LmGemm below).  An operand whose contraction index is the storage row is
 // read with the transposing LDS read; only H_i, a few MB per sequence tile, is ever transposed in memory.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
@@ -187,11 +189,26 @@ struct LmGemm {
   }
 };
 
-// Work-group -> output tile.  Work-group n runs on XCD n mod 8; each XCD takes groups of 4 x 8
-// tiles (one per CU), so the 32 work-groups that share an L2 at a time read 4 + 8 operand panels.
-__device__ __forceinline__ bool lm_tile(int bid, int TM, int TN, int& tm, int& tn) {
+// Work-group -> output tile and, where the contraction is split, its part of the k-tiles.  Work-group n runs on XCD
+// n mod 8.
+//  - More than one work-group per CU (kLmOneRound): each XCD takes groups of 4 x 8 tiles (one per CU), so the 32
+//    work-groups that share an L2 at a time read 4 + 8 operand panels.
+//  - Else every XCD takes an eighth of the tiles, neighbours in m first: what counts is that no CU gets two while
+//    another has none (16 tiles of dH for 256 tokens are one group of eight on two XCDs).
+constexpr int kLmOneRound = 256;
+__device__ __forceinline__ bool lm_tile(int bid, int TM, int TN, int splits, int& tm, int& tn, int& split) {
+  const int xcd = bid & 7, slot = bid >> 3, total = TM * TN * splits;
+  split = 0;
+  if (total <= kLmOneRound) {
+    const int per = (total + 7) / 8, i = xcd * per + slot;
+    if (slot >= per || i >= total) return false;
+    split = i / (TM * TN);
+    const int t = i - split * (TM * TN);
+    tn = t / TM;
+    tm = t - tn * TM;
+    return true;
+  }
   const int groups_m = (TM + 3) / 4, groups_n = (TN + 7) / 8;
-  const int xcd = bid & 7, slot = bid >> 3;
   const int group = (slot >> 5) * 8 + xcd, within = slot & 31;
   if (group >= groups_m * groups_n) return false;
   const int gm = group % groups_m, gn = group / groups_m;
@@ -199,9 +216,23 @@ __device__ __forceinline__ bool lm_tile(int bid, int TM, int TN, int& tm, int& t
   tn = gn * 8 + (within >> 2);
   return tm < TM && tn < TN;
 }
-int lm_grid(int TM, int TN) {
+int lm_grid(int TM, int TN, int splits = 1) {
+  const int total = TM * TN * splits;
+  if (total <= kLmOneRound) return (total + 7) / 8 * 8;
   const int groups = ((TM + 3) / 4) * ((TN + 7) / 8);
   return (groups + 7) / 8 * 8 * 32;
+}
+
+// dH contracts over the vocabulary, hundreds of k-tiles, and has few output tiles when the sequence tile is short: its
+// k-tiles are then dealt to `splits` work-groups per output tile, as many as fill the CUs, which leave fp32 partial
+// sums for lm_dh_sum_kernel in the logits buffer (read for the last time before).  Bounds: that buffer, and 16 k-tiles
+// a part, below which starting a work-group and the extra pass over the partial sums cost more than they give.
+// 256 tokens, d = 4096, 32000 words (16 output tiles, 7 parts): dH 650 -> 117 us with the sum; the call over 1000
+// tokens in such tiles 3866 -> 1887 us.
+int lm_dh_splits(const LmHeadParams& p, int TM, int TN) {
+  const int64_t fits = (int64_t)p.tile_tokens * p.v_pad / ((int64_t)TM * kLmBM * p.d_model);
+  const int64_t s = std::min<int64_t>({kLmOneRound / (TM * TN), fits, p.vocab / (16 * kLmBK)});
+  return (int)std::max<int64_t>(s, 1);
 }
 
 // (max, sum of exp(x - max)) pairs combine like the log-sum-exp merge of the attention forward.
@@ -217,8 +248,8 @@ __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l
 __global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
   using G = LmGemm<false>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  int tm, tn;
-  if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
+  int tm, tn, split;
+  if (!lm_tile(blockIdx.x, TM, TN, 1, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
   const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = p.d_model / kLmBK;
@@ -326,20 +357,25 @@ __global__ __launch_bounds__(256) void lm_loss_dlogits_kernel(LmHeadParams p, in
 // ---------------------------------------------------------------------------------------------
 // 3. dH_i = dLogits W_head (rows: tokens, columns: hidden, contraction: words).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, 2) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
+__global__ __launch_bounds__(kLmThreads, 2) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
   using G = LmGemm<true>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  int tm, tn;
-  if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
+  int tm, tn, split;
+  if (!lm_tile(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = (p.vocab + kLmBK - 1) / kLmBK;
+  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk_all = (p.vocab + kLmBK - 1) / kLmBK;
+  const int kt0 = (int)((int64_t)nk_all * split / splits), nk = (int)((int64_t)nk_all * (split + 1) / splits) - kt0;
+  const int word0 = kt0 * kLmBK;
   G::OpA a;
   G::OpB b;
-  a.init(p.dlogits, p.v_pad, p.tile_tokens, m0, nk, wave, lane);
-  b.init(p.w, p.ld_w, p.vocab, n0, nk, wave, lane);
+  a.init(p.dlogits + word0, p.v_pad, p.tile_tokens, m0, nk, wave, lane);
+  b.init(p.w + (int64_t)word0 * p.ld_w, p.ld_w, p.vocab - word0, n0, nk, wave, lane);
   G gemm;
   gemm.run(smem, a, b, nk, wm, wn, wave, lane);   // dLogits is zero beyond the vocabulary
+  const bool partial = splits > 1;
+  float* out_f32 = partial ? p.logits + (int64_t)split * TM * kLmBM * p.d_model : (float*)p.dh + (int64_t)s0 * p.ld_dh;
+  const int64_t ld = partial ? p.d_model : p.ld_dh;
 #pragma unroll
   for (int half = 0; half < 2; ++half)
 #pragma unroll
@@ -348,14 +384,37 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_dh_kernel(LmHeadParams p, in
       for (int v = 0; v < 4; ++v) {
         const int row = m0 + 128 * half + wm * 64 + 16 * mb + 4 * g + v;
         if (row >= n_rows) continue;
-        const int64_t off = (int64_t)(s0 + row) * p.ld_dh + n0 + wn * 64 + r;
+        const int64_t off = row * ld + n0 + wn * 64 + r;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
           const float x = gemm.acc[half][mb][nb][v];
-          if (p.dh_is_f32) ((float*)p.dh)[off + 16 * nb] = x;
-          else ((__bf16*)p.dh)[off + 16 * nb] = (__bf16)x;
+          if (partial || p.dh_is_f32) out_f32[off + 16 * nb] = x;
+          else ((__bf16*)p.dh)[(int64_t)s0 * p.ld_dh + off + 16 * nb] = (__bf16)x;
         }
       }
+}
+
+// dH rows from the partial sums of a split contraction: one work-item per eight columns.  stride: elements per part.
+__global__ __launch_bounds__(256) void lm_dh_sum_kernel(LmHeadParams p, int s0, int n_rows, int splits, int64_t stride) {
+  const int d8 = p.d_model / 8;
+  const int64_t i = blockIdx.x * 256ll + threadIdx.x;
+  if (i >= (int64_t)n_rows * d8) return;
+  const int64_t row = i / d8, col = (i - row * d8) * 8;
+  const float* src = p.logits + row * p.d_model + col;
+  f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
+  for (int s = 1; s < splits; ++s) {
+    x0 += *reinterpret_cast<const f32x4*>(src + s * stride);
+    x1 += *reinterpret_cast<const f32x4*>(src + s * stride + 4);
+  }
+  const int64_t off = (s0 + row) * p.ld_dh + col;
+  if (p.dh_is_f32) {
+    *reinterpret_cast<f32x4*>((float*)p.dh + off) = x0;
+    *reinterpret_cast<f32x4*>((float*)p.dh + off + 4) = x1;
+  } else {
+    const bf16x8 y = {(__bf16)x0[0], (__bf16)x0[1], (__bf16)x0[2], (__bf16)x0[3],
+                      (__bf16)x1[0], (__bf16)x1[1], (__bf16)x1[2], (__bf16)x1[3]};
+    *reinterpret_cast<bf16x8*>((__bf16*)p.dh + off) = y;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -390,8 +449,8 @@ __global__ __launch_bounds__(256) void lm_transpose_h_kernel(LmHeadParams p, int
 __global__ __launch_bounds__(kLmThreads, 2) void lm_dw_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int accumulate) {
   using G = LmGemm<true>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  int tm, tn;
-  if (!lm_tile(blockIdx.x, TM, TN, tm, tn)) return;
+  int tm, tn, split;
+  if (!lm_tile(blockIdx.x, TM, TN, 1, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
   const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = (n_rows + kLmBK - 1) / kLmBK;      // m0: hidden column, n0: word
@@ -446,9 +505,14 @@ hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {
     hipLaunchKernelGGL(lm_logits_kernel, dim3(lm_grid(TV, TTn)), dim3(kLmThreads), kLdsLogits, stream, p, s0,
                        n_rows, TV, TTn);
     hipLaunchKernelGGL(lm_loss_dlogits_kernel, dim3(want_grad ? k_rows : n_rows), dim3(256), 0, stream, p, s0, n_rows, want_grad);
-    if (p.dh)
-      hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD)), dim3(kLmThreads), kLdsGrad, stream, p, s0, n_rows,
-                         TT, TD);
+    if (p.dh) {
+      const int splits = lm_dh_splits(p, TT, TD);
+      hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD, splits)), dim3(kLmThreads), kLdsGrad, stream, p, s0, n_rows, TT, TD,
+                         splits);
+      if (splits > 1)
+        hipLaunchKernelGGL(lm_dh_sum_kernel, dim3((uint32_t)(((int64_t)n_rows * (p.d_model / 8) + 255) / 256)), dim3(256), 0, stream,
+                           p, s0, n_rows, splits, (int64_t)TT * kLmBM * p.d_model);
+    }
     if (p.dw) {
       hipLaunchKernelGGL(lm_transpose_h_kernel, dim3(k_rows / 64, p.d_model / 64), dim3(256), 0, stream, p, s0, n_rows);
       hipLaunchKernelGGL(lm_dw_kernel, dim3(lm_grid(p.d_model / kLmBM, p.v_pad / kLmBN)), dim3(kLmThreads), kLdsGrad, stream, p,
