@@ -18,6 +18,8 @@
 //    whose A operands are the dO and Q tiles read column-wise from the LDS copies that served
 //    S and dP row-wise.  With grouped-query attention the work-group walks the query heads of its
 //    group, so dK and dV are summed over the group in registers.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
@@ -232,9 +234,13 @@ struct DkdvLds {
   static constexpr int BYTES = P_OFF + 4 * P_PAIR;
 };
 
-template <int D, int ROLE, bool BLK>
+//
+// BKV = 128: the four pairs own 32 key rows each and run through all 64 rows of a query tile.  BKV = 64, for launches
+// with too few key tiles to fill the CUs: two pairs share 32 key rows, each runs through 32 of the 64 query rows (the
+// same operand reads per MFMA, half the MFMAs per phase), and the second one's sums are added through LDS at the end.
+template <int D, int ROLE, bool BLK, int BKV>
 __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b, int hk, int kv_tile, int wave) {
-  constexpr int BQ = 64, MB = BQ / 16, NB = 2, DK = D / 32, DB = D / 16, BKV = 128, NW = 8, AHEAD = kAhead16;
+  constexpr int BQ = 64, QS = 128 / BKV, ROWS = BQ / QS, MB = ROWS / 16, NB = 2, DK = D / 32, DB = D / 16, NW = 8, AHEAD = kAhead16;
   using L = DkdvLds<D>;
 
   const int group = p.q_heads / p.kv_heads;
@@ -242,7 +248,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   const int sq = p.sq, sk = p.sk;
   const MaskDev mk = p.mask;
   const int k_blk0 = p.k_runs.tile_of(kv_tile) * BKV, k_blk1 = min(k_blk0 + BKV, sk);
-  const int k_w0 = k_blk0 + pair * 32, k_w1 = min(k_w0 + 32, sk);
+  const int k_w0 = k_blk0 + (QS == 1 ? pair : pair & 1) * 32, k_w1 = min(k_w0 + 32, sk);
+  const int row0 = QS == 1 ? 0 : (pair >> 1) * ROWS;   // first row of the wave's part of a query tile
   const float c = p.scale * kLog2e;
 
   // K rows (P-wave) or V rows (dS-wave) as the B operand: lane holds rows k_w0 + 16 nb + r, columns 32 ks + 8g .. +7
@@ -279,7 +286,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   range_minmax<false>(mk, k_blk0, k_blk1, klo_blk, khi_blk);
   if (k_w0 < k_w1) range_minmax<false>(mk, k_w0, k_w1, klo_w, khi_w);
   TileRanges tiles;
-  tiles.init(row_intervals<true>(mk, klo_w, khi_w, sq, k_w0 >= k_w1), sq, BQ);
+  tiles.init(row_intervals<true>(mk, klo_w, khi_w, sq, k_w0 >= k_w1), sq, ROWS);
 
   uint8_t* open_flags = nullptr;
   if (BLK) {
@@ -297,8 +304,9 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   auto q_lds = [&](int s_) { return lds0 + L::Q_OFF + s_ * L::TILE; };
   auto o_lds = [&](int s_) { return lds0 + L::DO_OFF + s_ * L::TILE; };
   auto row_off = [&](int s_) { return L::ROW_OFF + (wave * L::SLOTS + s_) * L::ROW; };
-  auto rows_lds = [&](int s_) { return ROLE == 0 ? q_lds(s_) : o_lds(s_); };   // of the product that starts from a row vector
-  auto cols_lds = [&](int s_) { return ROLE == 0 ? o_lds(s_) : q_lds(s_); };   // of the product that fills acc
+  // the wave's rows of the tile of the product that starts from a row vector, and of the product that fills acc
+  auto rows_lds = [&](int s_) { return (ROLE == 0 ? q_lds(s_) : o_lds(s_)) + row0 * 2 * D; };
+  auto cols_lds = [&](int s_) { return (ROLE == 0 ? o_lds(s_) : q_lds(s_)) + row0 * 2 * D; };
   bf16x8* const hand = reinterpret_cast<bf16x8*>(smem + L::P_OFF + pair * L::P_PAIR) + lane;
   constexpr int LOADS = QStream<D, BQ, NW, BLK>::LOADS;
 
@@ -315,10 +323,11 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
     float* x = reinterpret_cast<float*>(smem + row_off(s_)) + lane;
     *x = ROLE == 0 ? -lse_to_log2(*x) : -*x;
   };
-  auto init_rows = [&](int s_, int mb) { init[mb] = *reinterpret_cast<const f32x4*>(smem + row_off(s_) + 4 * (16 * mb + 4 * g)); };
-  // The vector phase, of the tile at query row q0_
-  auto vector_phase = [&](int q0_) {
+  auto init_rows = [&](int s_, int mb) { init[mb] = *reinterpret_cast<const f32x4*>(smem + row_off(s_) + 4 * (row0 + 16 * mb + 4 * g)); };
+  // The vector phase, of the tile at query row tile_q0
+  auto vector_phase = [&](int tile_q0) {
     if (ROLE == 0) {
+      const int q0_ = tile_q0 + row0;
       const bool some = tiles.some(q0_);
       if (some && !tiles.full(q0_)) {
 #pragma unroll
@@ -420,6 +429,19 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
     if (ROLE == 0) phase_barrier();
   }
 
+  if (QS == 2) {   // the sums of pairs 2 and 3 through the tiles' LDS, which all waves have left
+    static_assert(4 * DB * NB * 64 * 16 <= L::ROW_OFF, "the sums of four waves fit where the tiles were");
+    f32x4* const sums = reinterpret_cast<f32x4*>(smem) + (2 * ROLE + (pair & 1)) * (DB * NB * 64) + lane;
+    __syncthreads();
+    if (pair >= 2) {
+#pragma unroll
+      for (int i = 0; i < DB * NB; ++i) sums[i * 64] = acc[i / NB][i % NB];
+    }
+    __syncthreads();
+    if (pair >= 2) return;
+#pragma unroll
+    for (int i = 0; i < DB * NB; ++i) acc[i / NB][i % NB] += sums[i * 64];
+  }
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int row = k_w0 + 16 * nb + r;
@@ -439,15 +461,15 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   }
 }
 
-template <int D, bool BLK>
+template <int D, bool BLK, int BKV>
 __global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];   // laid out by DkdvLds, then the open flags
   const BlockMap bm = map_block<false>(blockIdx.x, p.batch * p.kv_heads, 1, p.k_runs.total());
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 4) dkdv_role<D, 0, BLK>(p, smem, b, hk, bm.tile, wave);
-  else dkdv_role<D, 1, BLK>(p, smem, b, hk, bm.tile, wave);
+  if (wave < 4) dkdv_role<D, 0, BLK, BKV>(p, smem, b, hk, bm.tile, wave);
+  else dkdv_role<D, 1, BLK, BKV>(p, smem, b, hk, bm.tile, wave);
 }
 
 
@@ -468,13 +490,33 @@ static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether the dK/dV kernel takes key tiles of 64 rows.  A tile of 64 costs 0.6-0.7 of one of 128 (more barriers and LDS
+// traffic per MFMA), so it pays where the tiles of 128 leave half the CUs idle, and, up to one per CU, where the walks
+// are uneven, as the mask makes them, and the longest one decides.  One step, full mask, tiles of 128: 64 of them 61 us
+// against 45 with tiles of 64, 128 (16/2 heads, 8192 rows) 1556 against 1125, but 160 258 against 332, 256 68 against
+// 82.  Own shard, causal: 160 252 against 169, 256 63 against 53, 288 87 against 81, 384 48 against 54.
+static bool narrow_key_tiles(const MaskDev& mk, int sq, int sk, int n_keys, const TileRuns& runs128) {
+  const int n = n_keys * runs128.total();
+  if (mk.blk || n == 0 || n > 256) return false;
+  if (n <= 128) return true;
+  auto walk = [&](int tile) {   // query tiles that see some of the key tile
+    int lo, hi;
+    range_minmax<false>(mk, tile * 128, std::min(tile * 128 + 128, sk), lo, hi);
+    return visible_tiles<true, 64>(mk, lo, hi, sq).len;
+  };
+  return 2 * walk(runs128.tile_of(runs128.total() - 1)) <= walk(runs128.tile_of(0));
+}
+
 template <int D>
 static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads;
   constexpr int LDS = DkdvLds<D>::BYTES + kMaxBlockCacheTiles;
   static_assert(LDS <= 160 * 1024, "LDS of a CU");
   p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 128, false);
-  if (p.k_runs.total() < (p.sk + 127) / 128) {
+  const bool narrow = narrow_key_tiles(p.mask, p.sq, p.sk, n_keys, p.k_runs);
+  if (narrow) p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 64, false);
+  const int tile = narrow ? 64 : 128;
+  if (p.k_runs.total() < (p.sk + tile - 1) / tile) {
     hipError_t e = hipSuccess;
     if (!p.acc_dk) e = launch_zero_tensor(p.dk, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
     if (e == hipSuccess && !p.acc_dv) e = launch_zero_tensor(p.dv, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
@@ -482,8 +524,9 @@ static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
   }
   if (p.k_runs.total() == 0) return hipSuccess;
   const int grid = mapped_grid(n_keys, 1, p.k_runs.total());
-  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true>), dim3(grid), dim3(512), LDS, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false>), dim3(grid), dim3(512), LDS, stream, p);
+  if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 64>), dim3(grid), dim3(512), LDS, stream, p);
+  else if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, 128>), dim3(grid), dim3(512), LDS, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 128>), dim3(grid), dim3(512), LDS, stream, p);
   return hipGetLastError();
 }
 

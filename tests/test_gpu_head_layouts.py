@@ -69,3 +69,18 @@ def test_short_walks(lib, d, sk):
     ahead, so every walk shorter than that has its own prologue and end; query rows that fill no wave."""
     step_case(lib, 1, 2, 2, d, 77, sk, False, sk)
     step_case(lib, 1, 2, 1, d, 300, sk, True, sk + 1, q_pos=40)
+
+
+@pytest.mark.parametrize("B,H,d,sq,sk,causal", [
+    (1, 1, 128, 33, 1, False),       # one key row
+    (1, 3, 64, 97, 65, True),        # second key tile of one row; the second pair of a key block has one query row
+    (2, 2, 128, 161, 191, True),     # pairs that see nothing of a tile
+    (4, 32, 64, 130, 128, False),    # 128 tiles of 128: the last count that takes tiles of 64
+    (4, 33, 64, 130, 128, False),    # 132: tiles of 128 where the walks are even,
+    (3, 40, 128, 257, 257, True),    # 360: more than one per CU, tiles of 128
+    (2, 40, 128, 200, 250, True),    # 160, uneven: tiles of 64
+    (1, 256, 64, 190, 90, True),     # 256, one tile a head: even walks
+])
+def test_key_tile_heights(lib, B, H, d, sq, sk, causal):
+    """The dK/dV kernel's two key tile heights, at the counts where the launcher changes from one to the other."""
+    step_case(lib, B, H, H, d, sq, sk, causal, B * 1000 + H + sk)
