@@ -35,14 +35,13 @@ constexpr int kDqBQ = BURST_DQ_BQ;   // query rows per work-group of the dQ kern
 __device__ __forceinline__ float lse_to_log2(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(BwdParams p) {
+template <int D, int NW, bool BLK, int AHEAD>   // BLK: with a block-wise sparse mask
+__device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int block) {   // smem: [SLOTS][K tile, V tile], open flags
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int TILE = BK * 2 * D, SLOTS = 4, AHEAD = BLK ? 3 : kAhead16;   // (the block flags take the registers of one operand)
-  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
+  constexpr int TILE = BK * 2 * D, SLOTS = 4;
 
   const int group = p.q_heads / p.kv_heads;
-  const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total());
+  const BlockMap bm = map_block<true>(block, p.batch * p.kv_heads, group, p.q_runs.total());
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
 
@@ -462,9 +461,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
 }
 
 template <int D, bool BLK, int BKV>
-__global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];   // laid out by DkdvLds, then the open flags
-  const BlockMap bm = map_block<false>(blockIdx.x, p.batch * p.kv_heads, 1, p.k_runs.total());
+__device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int block) {   // smem: laid out by DkdvLds, then the open flags
+  const BlockMap bm = map_block<false>(block, p.batch * p.kv_heads, 1, p.k_runs.total());
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -472,22 +470,32 @@ __global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
   else dkdv_role<D, 1, BLK, BKV>(p, smem, b, hk, bm.tile, wave);
 }
 
-
-template <int D>
-static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
-  const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  constexpr int LDS = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
-  p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, kDqBQ, true);
-  // query tiles that see no key get no work-group: "=" must still leave zeros there
-  if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ) {
-    hipError_t e = launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
-    if (e != hipSuccess) return e;
+// ---------------------------------------------------------------------------------------------
+template <int D, int NW, bool BLK>
+__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(BwdParams p) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dq_block<D, NW, BLK, BLK ? 3 : kAhead16>(p, smem, blockIdx.x);   // (the block flags take the registers of one operand)
+}
+template <int D, bool BLK, int BKV>
+__global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dkdv_block<D, BLK, BKV>(p, smem, blockIdx.x);
+}
+// Both in one launch (they share nothing but inputs): work-groups 0 .. n_dkdv - 1 (a multiple of 8, as the mapping to
+// XCDs needs) are the dK/dV kernel's, whose walks are the longer ones, the others the dQ kernel's.
+template <int D, int BKV>
+__global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams p, int n_dkdv) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // each side reads its own arguments: loaded for both at the start they would not fit the scalar registers
+  typedef const __attribute__((address_space(4))) BwdParams* args_ptr;
+  args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  if ((int)blockIdx.x < n_dkdv) {
+    asm volatile("" : "+s"(args));
+    dkdv_block<D, false, BKV>(*(const BwdParams*)args, smem, blockIdx.x);
+  } else {
+    asm volatile("" : "+s"(args));
+    dq_block<D, 8, false, 3>(*(const BwdParams*)args, smem, blockIdx.x - n_dkdv);
   }
-  if (p.q_runs.total() == 0) return hipSuccess;
-  const int grid = mapped_grid(n_keys, group, p.q_runs.total());
-  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, true>), dim3(grid), dim3(2 * kDqBQ), LDS, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, false>), dim3(grid), dim3(2 * kDqBQ), LDS, stream, p);
-  return hipGetLastError();
 }
 
 // Whether the dK/dV kernel takes key tiles of 64 rows.  A tile of 64 costs 0.6-0.7 of one of 128 (more barriers and LDS
@@ -507,32 +515,89 @@ static bool narrow_key_tiles(const MaskDev& mk, int sq, int sk, int n_keys, cons
   return 2 * walk(runs128.tile_of(runs128.total() - 1)) <= walk(runs128.tile_of(0));
 }
 
-template <int D>
-static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
-  const int n_keys = p.batch * p.kv_heads;
-  constexpr int LDS = DkdvLds<D>::BYTES + kMaxBlockCacheTiles;
-  static_assert(LDS <= 160 * 1024, "LDS of a CU");
+// The work-groups of a kernel: the tiles that see something, and zeros into what gets no work-group under "=".
+static hipError_t plan_dq(BwdParams& p, hipStream_t stream) {
+  p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, kDqBQ, true);
+  if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ)
+    return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
+  return hipSuccess;
+}
+static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
   p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 128, false);
-  const bool narrow = narrow_key_tiles(p.mask, p.sq, p.sk, n_keys, p.k_runs);
+  narrow = narrow_key_tiles(p.mask, p.sq, p.sk, p.batch * p.kv_heads, p.k_runs);
   if (narrow) p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 64, false);
   const int tile = narrow ? 64 : 128;
+  hipError_t e = hipSuccess;
   if (p.k_runs.total() < (p.sk + tile - 1) / tile) {
-    hipError_t e = hipSuccess;
     if (!p.acc_dk) e = launch_zero_tensor(p.dk, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
     if (e == hipSuccess && !p.acc_dv) e = launch_zero_tensor(p.dv, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
-    if (e != hipSuccess) return e;
   }
-  if (p.k_runs.total() == 0) return hipSuccess;
-  const int grid = mapped_grid(n_keys, 1, p.k_runs.total());
-  if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 64>), dim3(grid), dim3(512), LDS, stream, p);
-  else if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, 128>), dim3(grid), dim3(512), LDS, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 128>), dim3(grid), dim3(512), LDS, stream, p);
+  return e;
+}
+static int dq_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total()); }
+static int dkdv_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, 1, p.k_runs.total()); }
+
+template <int D>
+constexpr int kDqLds = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
+template <int D>
+constexpr int kDkdvLds = DkdvLds<D>::BYTES + kMaxBlockCacheTiles;
+
+template <int D>
+static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
+  const hipError_t e = plan_dq(p, stream);
+  const int grid = dq_grid(p);
+  if (e != hipSuccess || grid == 0) return e;
+  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, true>), dim3(grid), dim3(2 * kDqBQ), kDqLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, false>), dim3(grid), dim3(2 * kDqBQ), kDqLds<D>, stream, p);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
+  static_assert(kDkdvLds<D> <= 160 * 1024, "LDS of a CU");
+  bool narrow = false;
+  const hipError_t e = plan_dkdv(p, narrow, stream);
+  const int grid = dkdv_grid(p);
+  if (e != hipSuccess || grid == 0) return e;
+  if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  return hipGetLastError();
+}
+
+// Work-groups (dQ tiles of 256 rows and key tiles of 128) up to which a step's two kernels go out as one launch: the
+// second one's work-groups then fill the CUs that the last round of the first leaves idle, and there is one start
+// less.  One step, d = 128, two launches against one: 6 work-groups 33 -> 21 us, 4 heads x 2048 rows (96) 115 -> 78,
+// 12 heads x 3000 (432) 262 -> 189, 48 x 1500 (864) 260 -> 217, causal 16 x 6000 (1136) 479 -> 446; alike from 32 x 4096
+// (1536) on, 772 and 770, causal 422 and 428.
+constexpr int kBothLaunch = 1280;
+
+// One launch for a short step; `done` says whether it was taken.
+template <int D>
+static hipError_t launch_both_t(BwdParams p, bool& done, hipStream_t stream) {
+  const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
+  const int64_t most = (int64_t)n_keys * group * ((p.sq + kDqBQ - 1) / kDqBQ) + (int64_t)n_keys * ((p.sk + 127) / 128);
+  done = !p.mask.blk && p.sq <= chunk_rows() && p.sk <= chunk_rows() && most <= kBothLaunch;
+  if (!done) return hipSuccess;
+  bool narrow = false;
+  hipError_t e = plan_dq(p, stream);
+  if (e == hipSuccess) e = plan_dkdv(p, narrow, stream);
+  const int n_dkdv = dkdv_grid(p), grid = n_dkdv + dq_grid(p);
+  if (e != hipSuccess || grid == 0) return e;
+  constexpr int LDS = kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>;
+  if (narrow) hipLaunchKernelGGL((step_bwd_both_kernel<D, 64>), dim3(grid), dim3(512), LDS, stream, p, n_dkdv);
+  else hipLaunchKernelGGL((step_bwd_both_kernel<D, 128>), dim3(grid), dim3(512), LDS, stream, p, n_dkdv);
   return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_bwd_t(const BwdParams& p0, hipStream_t stream) {
   hipError_t e = hipSuccess;
+  if (p0.dq.ptr && p0.dk.ptr) {
+    bool done = false;
+    e = launch_both_t<D>(p0, done, stream);
+    if (done) return e;
+  }
   if (p0.dq.ptr) {   // the dQ kernel streams the key axis
     const std::vector<RowRange> ranges = chunk_ranges(p0.mask.k_nseg, p0.mask.k_seg_len, p0.sk, p0.mask.blk ? p0.mask.blk_k : 0);
     bool first = true;

@@ -84,3 +84,35 @@ def test_short_walks(lib, d, sk):
 def test_key_tile_heights(lib, B, H, d, sq, sk, causal):
     """The dK/dV kernel's two key tile heights, at the counts where the launcher changes from one to the other."""
     step_case(lib, B, H, H, d, sq, sk, causal, B * 1000 + H + sk)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,sq,sk,causal", [
+    (1, 1, 1, 64, 1, 1, True),
+    (1, 4, 2, 128, 300, 191, True),    # key tiles of 64
+    (2, 33, 33, 64, 259, 333, False),  # key tiles of 128, work-groups of all eight XCDs in both parts
+    (1, 2, 2, 128, 700, 1100, True),   # key tiles that see nothing: zeros are written before the launch
+])
+def test_gradients_together_and_apart(lib, B, Hq, Hkv, d, sq, sk, causal):
+    """A short step computes dQ and dK/dV in one launch; asked for one by one they take a launch each.  The order of
+    every sum is the same; 1e-6 of the largest entry is left for the compiler's contraction of products and sums."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(wl.BASE_SEED + sq + sk)
+    f32 = dict(device="cuda", dtype=torch.float32)
+    draw = lambda *shape: torch.randn(*shape, generator=gen, **f32)
+    q, g = (draw(B, sq, Hq, d).to(torch.bfloat16) for _ in range(2))
+    k, v = (draw(B, sk, Hkv, d).to(torch.bfloat16) for _ in range(2))
+    lse, D = 5 + draw(B, Hq, sq), draw(B, Hq, sq)
+    mask = lib.burst_mask_t()
+    mask.mode = lib.BURST_MASK_CAUSAL if causal else lib.BURST_MASK_FULL
+    mask.q_nseg = mask.k_nseg = mask.pos_stride = 1
+    mask.q_seg_len, mask.k_seg_len = sq, sk
+    shp = lib.shape(B, Hq, Hkv, d, sq, sk, d ** -0.5)
+    for flags in (0, lib.BURST_ACC_DQ | lib.BURST_ACC_DK | lib.BURST_ACC_DV):
+        both, apart = ([torch.full(x.shape, 0.5 if flags else float("nan"), **f32) for x in (q, k, v)] for _ in range(2))
+        print(f"together / apart B={B} {Hq}/{Hkv} d={d} {sq}x{sk} causal={causal} flags={flags}", flush=True)
+        lib.burst_attn_step_bwd(shp, mask, q, k, v, g, lse, D, dq=both[0], dk=both[1], dv=both[2], accumulate_flags=flags)
+        lib.burst_attn_step_bwd(shp, mask, q, k, v, g, lse, D, dq=apart[0], accumulate_flags=flags)
+        lib.burst_attn_step_bwd(shp, mask, q, k, v, g, lse, D, dk=apart[1], dv=apart[2], accumulate_flags=flags)
+        torch.cuda.synchronize()
+        for name, x, y in zip(("dQ", "dK", "dV"), both, apart):
+            assert (x - y).abs().max() <= 1e-6 * y.abs().max(), (name, flags)
