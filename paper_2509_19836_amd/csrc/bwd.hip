@@ -2,7 +2,8 @@
 //   S = scale Q K^T; P = exp(S - Lse); dV += P^T dO; dP = dO V^T; dS = P o (dP - D);
 //   dK += scale dS^T Q; dQ += scale dS K.
 //
-// Two kernels, each owning its outputs outright (no atomics, results are run-to-run identical):
+// Two kernels, each owning its outputs outright (no atomics, results are run-to-run identical); a short step launches
+// the work-groups of both together (step_bwd_both_kernel):
 //
 //  * dQ kernel, query-stationary, the forward kernel's structure (16x16x32 MFMAs, direct LDS loads, the two waves of
 //    a SIMD taking matrix and vector phases in turn): S^T = K Q^T and dP^T = V dO^T come out with the key index
@@ -233,7 +234,6 @@ struct DkdvLds {
   static constexpr int BYTES = P_OFF + 4 * P_PAIR;
 };
 
-//
 // BKV = 128: the four pairs own 32 key rows each and run through all 64 rows of a query tile.  BKV = 64, for launches
 // with too few key tiles to fill the CUs: two pairs share 32 key rows, each runs through 32 of the 64 query rows (the
 // same operand reads per MFMA, half the MFMAs per phase), and the second one's sums are added through LDS at the end.

@@ -79,7 +79,8 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 
 // One direct load: every lane's 16 bytes at base + offset go to LDS at lds + 16 * lane.  Written as an
 // assembly statement because the compiler otherwise waits for all of them before the next LDS read; the
-// kernels wait by count themselves (wait_loads_barrier).
+// kernels wait by count themselves (wait_loads_barrier).  m0 is a reserved register, which the compiler keeps no
+// value in; nothing else in these kernels uses it.
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
