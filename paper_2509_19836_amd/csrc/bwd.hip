@@ -107,21 +107,16 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
   // A barrier ends every phase.  Tile t+3 is asked for in the matrix phase of iteration t (its slot held tile
   // t-1, which the later half finished a barrier ago).  At the end of that phase a wave waits for its share of tile
   // t+2, so that both halves' shares are there a barrier before either half's products of iteration t+1 read it.
+  // Before and behind the run of tiles of which its rows see something a wave only asks for loads and meets the others,
+  // as in the forward kernel.
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
   constexpr int LOADS = KvStream<D, BK, NW, BLK, false>::LOADS, NL = KvStream<D, BK, NW, BLK, false>::N;
   f32x4 s[MB][NB], dp[MB][NB];
   bf16x8 ds[MB / 2][NB];
-  // dS of the tile at key row k0_ from its scores and dP
+  // dS of the tile at key row k0_, of which the wave sees something, from its scores and dP
   auto d_scores = [&](int k0_) {
     if (!tiles.full(k0_)) {
-      if (!tiles.some(k0_)) {   // for this wave alone there is nothing in the tile
-#pragma unroll
-        for (int ch = 0; ch < MB / 2; ++ch)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) ds[ch][nb] = zero_operand();
-        return;
-      }
 #pragma unroll
       for (int half = 0; half < MB / 2; ++half)
         mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
@@ -140,49 +135,75 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
       }
   };
   if (walk.valid()) {
-    const int ka = walk.k0;
+    int kb = walk.k0;   // iteration t: kb, kc are the first rows of tiles t+1, t+2
     walk.issue(k_lds(0), v_lds(0), wave, lane);
-    int kb = walk.cursor();
-    walk.issue(k_lds(1), v_lds(1), wave, lane);
     int kc = walk.cursor();
+    walk.issue(k_lds(1), v_lds(1), wave, lane);
+    int kn = walk.cursor();
     walk.issue(k_lds(2), v_lds(2), wave, lane);
     wait_loads_barrier<2 * LOADS>();              // tile 0
     if (wave >= NW / 2) phase_barrier();
+    int slot = 3;
+    bool live;
     bf16x8 first[AHEAD];
-    rows_fetch<D, MB, AHEAD>(k_lds(0), ad, 0, first);
-    rows_product_pair<D, MB, NB, AHEAD>(k_lds(0), v_lds(0), ad, qreg, doreg, s, dp, first);
-    wait_loads_barrier<LOADS>();                  // tile 1
-    d_scores(ka);
-    int slot = 0;
-    cols_fetch<D, AHEAD>(k_lds(0), ad, 0, first);
-    phase_barrier();
-    for (;;) {   // iteration t: kb, kc are the first rows of tiles t+1, t+2
-      // ---- matrix phase
-      const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
-      const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
-      const int kn = walk.cursor();
-      walk.begin(wave, lane);
-      bf16x8 first_rows[AHEAD];
-      constexpr int NCOLS = MB / 2 * DB;
-      cols_product<D, MB / 2, NB, AHEAD>(k_lds(slot), ad, 0, ds, dq, first, [&](int i) {
-        if (i < NL) walk.load_v(i, vl, wave);
-        if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
-        if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
-        if (i >= NCOLS - AHEAD) {
-          const int f = i - (NCOLS - AHEAD);
-          first_rows[f] = rows_operand<D>(k_lds(slot1), ad, 16 * (f % MB), f / MB);
-        }
-      });
-      if (kb < 0) break;
-      rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first_rows);
+    for (;;) {   // iterations -1 .., up to the wave's first tile
+      const int slot1 = (slot + 1) & 3;
+      live = tiles.some(kb);
+      if (live) {
+        rows_fetch<D, MB, AHEAD>(k_lds(slot1), ad, 0, first);
+        rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first);
+      }
       wait_loads_barrier<LOADS>();                // tile t+2
-      // ---- vector phase
-      d_scores(kb);
       slot = slot1;
-      cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+      if (live) {
+        d_scores(kb);
+        cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+      }
       phase_barrier();
       kb = kc;
       kc = kn;
+      if (live || kb < 0) break;
+      kn = walk.cursor();
+      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
+    }
+    if (live) {
+      for (;;) {
+        // ---- matrix phase
+        const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
+        const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
+        kn = walk.cursor();
+        walk.begin(wave, lane);
+        bf16x8 first_rows[AHEAD];
+        constexpr int NCOLS = MB / 2 * DB;
+        cols_product<D, MB / 2, NB, AHEAD>(k_lds(slot), ad, 0, ds, dq, first, [&](int i) {
+          if (i < NL) walk.load_v(i, vl, wave);
+          if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
+          if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
+          if (i >= NCOLS - AHEAD) {
+            const int f = i - (NCOLS - AHEAD);
+            first_rows[f] = rows_operand<D>(k_lds(slot1), ad, 16 * (f % MB), f / MB);
+          }
+        });
+        if (tiles.behind(kb)) break;
+        rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first_rows);
+        wait_loads_barrier<LOADS>();              // tile t+2
+        // ---- vector phase
+        d_scores(kb);
+        slot = slot1;
+        cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+        phase_barrier();
+        kb = kc;
+        kc = kn;
+      }
+    }
+    while (kb >= 0) {   // the rest of the walk is the other waves'
+      wait_loads_barrier<LOADS>();
+      slot = (slot + 1) & 3;
+      phase_barrier();
+      kb = kc;
+      kc = kn;
+      kn = walk.cursor();
+      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
     }
     wait_global_loads();   // tiles past the end of the walk
     if (wave < NW / 2) phase_barrier();

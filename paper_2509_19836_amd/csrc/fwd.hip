@@ -98,6 +98,11 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // which the later half finished a barrier ago).  A wave waits for its share of set t+2 before the barrier that
   // ends its vector phase of iteration t, so that both halves' shares of set t+1 are there before either half's
   // vector phase of iteration t, which ends with the first operand fetches of the next matrix phase.
+  // The tiles of which a wave's rows see something are one run of the walk.  Before and behind it the wave only asks for
+  // its share of the loads and meets the others: what its rows may not see does not reach them, be it infinite or NaN
+  // (zeros in place of P would let 0 * inf through), and in a step of few query rows the waves without rows leave the
+  // matrix pipe and the LDS to the others: one query row, 32/8 heads, 4096 keys, d = 128: 94 us with all waves in the
+  // products, 70 so (dQ 121 and 82); a 1024-token window 379 and 367.
   // The last iteration forms a product S nobody reads (of a tile it has): a quarter of a tile's time per work-group,
   // where a second copy of the loop's end cost the registers of the operand prefetch (1 % slower).
   // Raised priority of the matrix phase: 4-6 % (with both at priority 0 the waves' phases disturb each other).
@@ -106,16 +111,9 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   constexpr int LOADS = KvStream<D, BK, NW, BLK, true>::LOADS, NL = KvStream<D, BK, NW, BLK, true>::N;
   f32x4 s[MB][NB];
   bf16x8 pp[MB / 2][NB];
-  // P of the tile at key row k0_ from its scores
+  // P of the tile at key row k0_, of which the wave sees something, from its scores
   auto softmax = [&](int k0_) {
     if (!tiles.full(k0_)) {
-      if (!tiles.some(k0_)) {   // for this wave alone there is nothing in the tile
-#pragma unroll
-        for (int ch = 0; ch < MB / 2; ++ch)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) pp[ch][nb] = zero_operand();
-        return;
-      }
 #pragma unroll
       for (int half = 0; half < MB / 2; ++half)
         mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
@@ -158,7 +156,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     }
     // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
     // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
-    // exponential, few enough to keep the intermediate values out of the register budget.
+    // exponential, few enough to keep the intermediate values out of the register budget.  The fence keeps the
+    // groups apart: with the 32 exponentials in a row the d = 64 kernel is 2-3 % slower (12 heads x 12000 rows 665, 636 us).
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -171,50 +170,78 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
         }
         l_run[nb] += x + y;
         pp[ch][nb] = pack_pair(x, y);
+        __builtin_amdgcn_sched_barrier(0);
       }
   };
   if (walk.valid()) {
-    const int ka = walk.k0;
+    int kb = walk.k0;   // iteration t: kb, kc, kd are the first rows of tiles t+1, t+2, t+3
     walk.issue(k_lds(3), v_lds(3), wave, lane);   // set -1
-    int kb = walk.cursor();
-    walk.issue(k_lds(0), v_lds(0), wave, lane);   // set 0
     int kc = walk.cursor();
-    walk.issue(k_lds(1), v_lds(1), wave, lane);   // set 1
+    walk.issue(k_lds(0), v_lds(0), wave, lane);   // set 0
     int kd = walk.cursor();
+    walk.issue(k_lds(1), v_lds(1), wave, lane);   // set 1
+    int kn = walk.cursor();
     walk.issue(k_lds(2), v_lds(2), wave, lane);   // set 2
     wait_loads_barrier<3 * LOADS>();              // set -1
     if (wave >= NW / 2) phase_barrier();
+    int slot = 3;
+    bool live;
     bf16x8 first[AHEAD];
-    rows_fetch<D, MB, AHEAD>(k_lds(3), ad, 0, first);
-    const f32x4 zero[MB] = {};
-    rows_product<D, MB, NB, AHEAD>(k_lds(3), ad, 0, qreg, s, zero, first);
-    wait_loads_barrier<2 * LOADS>();              // set 0
-    softmax(ka);
-    wait_loads_barrier<LOADS>();                  // set 1
-    int slot = 0;
-    rows_fetch<D, MB, AHEAD>(k_lds(0), ad, 0, first);
-    for (;;) {   // iteration t: kb, kc, kd are tiles t+1, t+2, t+3
-      const uint32_t kt = k_lds(slot), vt = v_lds(slot);
-      // ---- matrix phase
-      const int kn = walk.cursor();
-      walk.begin(wave, lane);
-      const int slot3 = (slot + 3) & 3;
-      const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
-      rows_cols_stream<D, MB, NB, AHEAD>(kt, vt, ad, qreg, s, pp, o, first, [&](int i) {
-        if (i >= 1 && i < 1 + NL) walk.load_v(i - 1, vl, wave);
-        if (i >= 1 + NL && i < 1 + 2 * NL) walk.load_k(i - 1 - NL, kl, wave);
-        if (i >= 1 + 2 * NL && i < 1 + 2 * NL + walk.PARTS) walk.end(i - 1 - 2 * NL);
-      });
-      if (kb < 0) break;
-      phase_barrier();
-      // ---- vector phase
-      softmax(kb);
+    for (;;) {   // iterations -1 .., up to the wave's first tile
+      live = tiles.some(kb);
+      if (live) {
+        const f32x4 zero[MB] = {};
+        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+        rows_product<D, MB, NB, AHEAD>(k_lds(slot), ad, 0, qreg, s, zero, first);
+      }
+      wait_loads_barrier<2 * LOADS>();            // set 0 (later ones have been waited for)
       slot = (slot + 1) & 3;
-      rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+      if (live) {
+        softmax(kb);
+        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+      }
       wait_loads_barrier<LOADS>();
       kb = kc;
       kc = kd;
       kd = kn;
+      if (live || kb < 0) break;
+      kn = walk.cursor();
+      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
+    }
+    if (live) {
+      for (;;) {
+        const uint32_t kt = k_lds(slot), vt = v_lds(slot);
+        // ---- matrix phase
+        kn = walk.cursor();
+        walk.begin(wave, lane);
+        const int slot3 = (slot + 3) & 3;
+        const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
+        rows_cols_stream<D, MB, NB, AHEAD>(kt, vt, ad, qreg, s, pp, o, first, [&](int i) {
+          if (i >= 1 && i < 1 + NL) walk.load_v(i - 1, vl, wave);
+          if (i >= 1 + NL && i < 1 + 2 * NL) walk.load_k(i - 1 - NL, kl, wave);
+          if (i >= 1 + 2 * NL && i < 1 + 2 * NL + walk.PARTS) walk.end(i - 1 - 2 * NL);
+        });
+        if (tiles.behind(kb)) break;
+        phase_barrier();
+        // ---- vector phase
+        softmax(kb);
+        slot = (slot + 1) & 3;
+        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+        wait_loads_barrier<LOADS>();
+        kb = kc;
+        kc = kd;
+        kd = kn;
+      }
+    }
+    while (kb >= 0) {   // the rest of the walk is the other waves'
+      phase_barrier();
+      slot = (slot + 1) & 3;
+      wait_loads_barrier<LOADS>();
+      kb = kc;
+      kc = kd;
+      kd = kn;
+      kn = walk.cursor();
+      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
     }
     wait_global_loads();   // sets past the end of the walk
     if (wave < NW / 2) phase_barrier();

@@ -342,15 +342,18 @@ struct QStream {
 // all of it visible, or mixed (the per-element mask decides).
 struct TileRanges {
   int some_lo, full_lo;
-  uint32_t some_len, full_len;
+  uint32_t some_len, full_len, end;
   __device__ __forceinline__ void init(const RowIntervals& iv, int rows, int bk) {
     some_lo = iv.some_lo - bk + 1;
-    some_len = max(iv.some_hi - some_lo, 0);
+    some_len = iv.some_hi > iv.some_lo ? iv.some_hi - some_lo : 0;
+    end = iv.some_hi;
     full_lo = iv.all_lo;
     full_len = max(min(iv.all_hi, rows) - bk + 1 - full_lo, 0);
   }
   __device__ __forceinline__ bool some(int row0) const { return (uint32_t)(row0 - some_lo) < some_len; }
   __device__ __forceinline__ bool full(int row0) const { return (uint32_t)(row0 - full_lo) < full_len; }
+  // Behind the last tile of which something is visible; so is -1, the end of a walk
+  __device__ __forceinline__ bool behind(int row0) const { return (uint32_t)row0 >= end; }
 };
 
 // Products with one hook per LDS operand (NB MFMAs): hook(i) holds independent vector work that goes behind
