@@ -97,7 +97,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // A barrier ends every phase.  Set t+3 is asked for in the matrix phase of iteration t (its slot held set t-1,
   // which the later half finished a barrier ago).  A wave waits for its share of set t+2 before the barrier that
   // ends its vector phase of iteration t, so that both halves' shares of set t+1 are there before either half's
-  // vector phase of iteration t, which ends with the first operand fetches of the next matrix phase.
+  // vector phase of iteration t, which ends with the first operand fetches of the next matrix phase.  Iteration -1 has
+  // no such barrier before it: the later half waits for its share of set 0 where it drops behind by a barrier.
   // The tiles of which a wave's rows see something are one run of the walk.  Before and behind it the wave only asks for
   // its share of the loads and meets the others: what its rows may not see does not reach them, be it infinite or NaN
   // (zeros in place of P would let 0 * inf through), and in a step of few query rows the waves without rows leave the
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     int kn = walk.cursor();
     walk.issue(k_lds(2), v_lds(2), wave, lane);   // set 2
     wait_loads_barrier<3 * LOADS>();              // set -1
-    if (wave >= NW / 2) phase_barrier();
+    if (wave >= NW / 2) wait_loads_barrier<2 * LOADS>();   // set 0: the first half's first vector phase reads its K
     int slot = 3;
     bool live;
     bf16x8 first[AHEAD];
