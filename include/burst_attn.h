@@ -29,7 +29,7 @@
  *     empty chunks are handled).
  *   - An infinity or NaN in k or v reaches O, Lse and dQ of the query rows that see it, and may reach
  *     rows that do not where 32 of them share a tile of 64 keys with it and one sees some of that
- *     tile; one in q, dO, lse or D likewise dK and dV, by tiles of up to 128 keys and 64 query rows.
+ *     tile (or has a window that falls between the positions of two of its keys); one in q, dO, lse or D likewise dK and dV, by tiles of up to 128 keys and 64 query rows.
  *     It reaches nothing else (a tile of which the rows see nothing is not multiplied).
  */
 #ifndef BURST_ATTN_H

@@ -16,14 +16,21 @@ extern "C" {
  *
  * burst_attn_tile_class: class of the block of query rows [q0, q1) against key rows [k0, k1):
  * 0 = no pair visible (the kernels skip the tile), 1 = every pair visible (no per-element predicate),
- * 2 = mixed.  method 0: the direct position-range test; 1: the per-segment row thresholds the
- * key-stationary kernel derives once for a fixed key range; 2: the same for a fixed query range
- * (query-stationary kernels).  All three must agree.  Negative burst_status_t on a bad argument.
+ * 2 = mixed.  method 0: the direct position-range test (launch plan); 1: the query tile [q0, q1) as a dK/dV
+ * wave that owns the keys [k0, k1) classifies it while it walks (TileRanges); 2: the key tile [k0, k1) as a
+ * forward or dQ wave that owns the query rows [q0, q1) does.  These three must agree.  3 and 4: as 1 and 2 with a
+ * tile of 64 rows from q0 or k0 on, as the kernels have it at the end of a chunk: never 1 where rows are missing.
+ * Negative burst_status_t on a bad argument.
+ *
+ * burst_attn_visible_rows: the rows [out[0], out[1]) of the query axis that see key row `row` (query_axis !=
+ * 0), or of the key axis that query row `row` sees; the interval is empty where out[0] >= out[1].  It is what a lane compares
+ * with, row by row, in a mixed tile.  The block mask is not part of it.
  *
  * burst_attn_visible_tile_runs: the tiles of `tile_rows` rows along the query axis (query_axis != 0;
  * tile_rows 64 or 256) or the key axis (tile_rows 64 or 128) that can hold a pair visible to rows
- * [r0, r1) of the other axis, as at most two runs: out = {start0, len0, start1, len1} in tiles. */
+ * [r0, r1) of the other axis: one run, out = {start, length, 0, 0} in tiles. */
 int burst_attn_tile_class(const burst_mask_t* mask, int64_t q0, int64_t q1, int64_t k0, int64_t k1, int32_t method);
+int burst_attn_visible_rows(const burst_mask_t* mask, int32_t query_axis, int64_t row, int32_t out_lo_hi[2]);
 int burst_attn_visible_tile_runs(const burst_mask_t* mask, int32_t query_axis, int32_t tile_rows, int64_t r0, int64_t r1,
                                  int32_t out_start_len[4]);
 

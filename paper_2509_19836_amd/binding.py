@@ -72,6 +72,8 @@ _lib.burst_attn_tile_class.restype = C.c_int
 _lib.burst_attn_tile_class.argtypes = [_P(burst_mask_t)] + [C.c_int64] * 4 + [C.c_int32]
 _lib.burst_attn_visible_tile_runs.restype = C.c_int
 _lib.burst_attn_visible_tile_runs.argtypes = [_P(burst_mask_t), C.c_int32, C.c_int32, C.c_int64, C.c_int64, _P(C.c_int32 * 4)]
+_lib.burst_attn_visible_rows.restype = C.c_int
+_lib.burst_attn_visible_rows.argtypes = [_P(burst_mask_t), C.c_int32, C.c_int64, _P(C.c_int32 * 2)]
 _lib.burst_attn_set_chunk_rows.restype = C.c_int
 _lib.burst_attn_set_chunk_rows.argtypes = [C.c_int32]
 _lib.burst_attn_chunk_plan.restype = C.c_int
@@ -105,7 +107,7 @@ _lib.burst_attn_version.restype = C.c_char_p
 EXPORTS = ["burst_attn_step_fwd", "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
            "burst_attn_fill_zigzag_mask", "burst_attn_fill_contiguous_mask", "burst_attn_fill_striped_mask",
            "burst_attn_fill_block_striped_mask",
-           "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
+           "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
            "burst_attn_version", "burst_lm_head_workspace_bytes", "burst_lm_head_loss",
            "burst_lm_head_static_scratch_bytes", "burst_lm_head_loss_noalloc"]
 
@@ -288,6 +290,13 @@ def burst_lm_head_loss_noalloc(shp, h_last, w_head, y, loss, lse=None, d_h=None,
                                            ptr(y), ptr(loss), ptr(lse), ptr(d_h), dh_dtype,
                                            0 if d_h is None else d_h.stride(0), ptr(d_w),
                                            0 if d_w is None else d_w.stride(0), int(accumulate_dw), _stream(stream)))
+
+
+def burst_attn_visible_rows(mask, query_axis, row):
+    """(lo, hi): rows of the query axis that see key row `row`, or of the key axis that query row `row` sees."""
+    out = (C.c_int32 * 2)()
+    _check(_lib.burst_attn_visible_rows(C.byref(mask), int(query_axis), int(row), C.byref(out)))
+    return out[0], out[1]
 
 
 def burst_attn_set_chunk_rows(rows):

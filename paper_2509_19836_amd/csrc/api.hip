@@ -444,20 +444,35 @@ int burst_attn_tile_class(const burst_mask_t* mask, int64_t q0, int64_t q1, int6
   BURST_TRY(check_mask(mask, sq, sk, &mk));
   if (q0 < 0 || q1 > sq || q0 >= q1 || k0 < 0 || k1 > sk || k0 >= k1) return BURST_ERR_INVALID_ARG;
   if (method == 0) return classify(mk, (int)q0, (int)q1, (int)k0, (int)k1, false);
-  int lo, hi;
-  if (method == 1) {   // query block against a fixed key range
+  // a wave's walk against its own rows of the other axis: tiles as high as the block, or of 64 rows from its first one on
+  if (method < 1 || method > 4) return BURST_ERR_INVALID_ARG;
+  int lo, hi, row0;
+  TileRanges tiles;
+  if (method == 1 || method == 3) {   // query tile against a fixed key range
     range_minmax<false>(mk, (int)k0, (int)k1, lo, hi);
-    BlockClassifier<true> c;
-    c.init(mk, lo, hi, (int)sq, false);
-    return c(mk, (int)q0, (int)q1, false);
-  }
-  if (method == 2) {   // key block against a fixed query range
+    tiles.init(row_intervals<true>(mk, lo, hi, (int)sq, false), (int)sq, method == 1 ? (int)(q1 - q0) : 64);
+    row0 = (int)q0;
+  } else {                            // key tile against a fixed query range
     range_minmax<true>(mk, (int)q0, (int)q1, lo, hi);
-    BlockClassifier<false> c;
-    c.init(mk, lo, hi, (int)sk, false);
-    return c(mk, (int)k0, (int)k1, false);
+    tiles.init(row_intervals<false>(mk, lo, hi, (int)sk, false), (int)sk, method == 2 ? (int)(k1 - k0) : 64);
+    row0 = (int)k0;
   }
-  return BURST_ERR_INVALID_ARG;
+  if (!tiles.some(row0) || tiles.behind(row0)) return TILE_SKIP;
+  return tiles.full(row0) ? TILE_FULL : TILE_PARTIAL;
+}
+
+int burst_attn_visible_rows(const burst_mask_t* mask, int32_t query_axis, int64_t row, int32_t out_lo_hi[2]) {
+  if (!mask || !out_lo_hi || mask->q_nseg < 1 || mask->k_nseg < 1) return BURST_ERR_INVALID_ARG;
+  const int64_t sq = mask->q_nseg * mask->q_seg_len, sk = mask->k_nseg * mask->k_seg_len;
+  MaskDev mk;
+  BURST_TRY(check_mask(mask, sq, sk, &mk));
+  if (row < 0 || row >= (query_axis ? sk : sq)) return BURST_ERR_INVALID_ARG;
+  int lo, hi;
+  if (query_axis) visible_rows<false>(mk, axis_position(axis_of<false>(mk), (int)row), (int)sq, lo, hi);
+  else visible_rows<true>(mk, axis_position(axis_of<true>(mk), (int)row), (int)sk, lo, hi);
+  out_lo_hi[0] = lo;
+  out_lo_hi[1] = hi;
+  return BURST_OK;
 }
 
 int burst_attn_visible_tile_runs(const burst_mask_t* mask, int32_t query_axis, int32_t tile_rows, int64_t r0, int64_t r1,

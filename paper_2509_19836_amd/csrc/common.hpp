@@ -169,25 +169,50 @@ __host__ __device__ __forceinline__ RowIntervals row_intervals(const MaskDev& mk
   return iv;
 }
 
-// The same decisions as classify() for many row blocks of one axis against one fixed position range
-// of the other axis, from the row intervals computed once.
-template <bool Q_AXIS>
-struct BlockClassifier {
-  RowIntervals iv;   // (scalar members: the thresholds must stay in registers)
-
-  __host__ __device__ __forceinline__ void init(const MaskDev& mk, int olo, int ohi, int rows, bool other_empty) {
-    iv = row_intervals<Q_AXIS>(mk, olo, ohi, rows, other_empty);
+// Class of a tile of `bk` rows against a wave's own rows of the other axis, from its first row: nothing visible,
+// all of it visible, or mixed (the per-element mask decides).
+struct TileRanges {
+  int some_lo, full_lo;
+  uint32_t some_len, full_len, end;
+  __host__ __device__ __forceinline__ void init(const RowIntervals& iv, int rows, int bk) {
+    some_lo = iv.some_lo - bk + 1;
+    // (nothing at or behind the last row; an interval that is empty between two rows makes their tile "some", as the
+    // ranges of classify() do: a window can fall between the positions of a stride)
+    some_len = iv.some_lo < rows ? iv.some_hi - some_lo : 0;
+    end = iv.some_hi;
+    full_lo = iv.all_lo;
+    full_len = max(min(iv.all_hi, rows) - bk + 1 - full_lo, 0);
   }
-  // block of rows [r0, r1), r1 > r0, both inside the chunk
-  __host__ __device__ __forceinline__ int operator()(const MaskDev&, int r0, int r1, bool ragged) const {
-    // bitwise logic and selects only: this runs once per tile in every wave, and short-circuit
-    // operators compile to a chain of scalar branches
-    const bool skip = (r1 <= iv.some_lo) | (r0 >= iv.some_hi);
-    const bool full = (r0 >= iv.all_lo) & (r1 <= iv.all_hi) & !ragged;
-    const int cls = full ? TILE_FULL : TILE_PARTIAL;
-    return skip ? TILE_SKIP : cls;
-  }
+  __host__ __device__ __forceinline__ bool some(int row0) const { return (uint32_t)(row0 - some_lo) < some_len; }
+  __host__ __device__ __forceinline__ bool full(int row0) const { return (uint32_t)(row0 - full_lo) < full_len; }
+  // Behind the last tile of which something is visible; so is -1, the end of a walk
+  __host__ __device__ __forceinline__ bool behind(int row0) const { return (uint32_t)row0 >= end; }
 };
+
+// Rows of one axis that a row of the OTHER axis at position `pos` sees / is seen by: [lo, hi), one interval because
+// positions grow with the row.  Per lane, once per work-group; free of divisions for at most two pieces of stride 1.
+template <bool KEYS>   // KEYS: the key rows a query sees; else the query rows that see a key
+__host__ __device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos, int rows, int& lo, int& hi) {
+  lo = 0;
+  hi = rows;
+  if (!mk.causal) return;
+  const AxisMap ax = axis_of<!KEYS>(mk);
+  auto below = [&](int x) {   // rows whose position is below x
+    const int t = max(x, 0) - ax.pos0;
+    if (ax.stride == 1 && ax.nseg <= 2) {
+      const int in_first = min(max(t, 0), ax.seg_len), in_second = ax.nseg == 2 ? min(max(t - ax.period, 0), ax.seg_len) : 0;
+      return ax.nseg == 2 ? in_first + in_second : min(max(t, 0), rows);
+    }
+    return rows_lt(ax, (long long)t + ax.pos0, rows);
+  };
+  if (KEYS) {
+    hi = below(pos + 1);                                            // k <= p
+    if (mk.window != kNoWindow) lo = below(pos - mk.window + 1);    // k > p - window
+  } else {
+    lo = below(pos);                                                                  // p >= k
+    if (mk.window != kNoWindow && pos <= 0x7fffffff - mk.window) hi = below(pos + mk.window);   // p < k + window
+  }
+}
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);

@@ -338,24 +338,6 @@ struct QStream {
   }
 };
 
-// Class of a tile of `bk` rows against a wave's own rows of the other axis, from its first row: nothing visible,
-// all of it visible, or mixed (the per-element mask decides).
-struct TileRanges {
-  int some_lo, full_lo;
-  uint32_t some_len, full_len, end;
-  __device__ __forceinline__ void init(const RowIntervals& iv, int rows, int bk) {
-    some_lo = iv.some_lo - bk + 1;
-    some_len = iv.some_hi > iv.some_lo ? iv.some_hi - some_lo : 0;
-    end = iv.some_hi;
-    full_lo = iv.all_lo;
-    full_len = max(min(iv.all_hi, rows) - bk + 1 - full_lo, 0);
-  }
-  __device__ __forceinline__ bool some(int row0) const { return (uint32_t)(row0 - some_lo) < some_len; }
-  __device__ __forceinline__ bool full(int row0) const { return (uint32_t)(row0 - full_lo) < full_len; }
-  // Behind the last tile of which something is visible; so is -1, the end of a walk
-  __device__ __forceinline__ bool behind(int row0) const { return (uint32_t)row0 >= end; }
-};
-
 // Products with one hook per LDS operand (NB MFMAs): hook(i) holds independent vector work that goes behind
 // them, and the scheduling fence after it keeps it there.  Operands are fetched AHEAD of their use; the first
 // AHEAD ones may have been fetched by the caller (`first`).
@@ -459,31 +441,6 @@ __device__ __forceinline__ void rows_cols_stream(uint32_t kt, uint32_t vt, const
     }
     hook(i);
     __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// Rows of one axis that a row of the OTHER axis at position `pos` sees / is seen by: [lo, hi), one interval because
-// positions grow with the row.  Per lane, once per work-group; free of divisions for at most two pieces of stride 1.
-template <bool KEYS>   // KEYS: the key rows a query sees; else the query rows that see a key
-__device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos, int rows, int& lo, int& hi) {
-  lo = 0;
-  hi = rows;
-  if (!mk.causal) return;
-  const AxisMap ax = axis_of<!KEYS>(mk);
-  auto below = [&](int x) {   // rows whose position is below x
-    const int t = max(x, 0) - ax.pos0;
-    if (ax.stride == 1 && ax.nseg <= 2) {
-      const int in_first = min(max(t, 0), ax.seg_len), in_second = ax.nseg == 2 ? min(max(t - ax.period, 0), ax.seg_len) : 0;
-      return ax.nseg == 2 ? in_first + in_second : min(max(t, 0), rows);
-    }
-    return rows_lt(ax, (long long)t + ax.pos0, rows);
-  };
-  if (KEYS) {
-    hi = below(pos + 1);                                            // k <= p
-    if (mk.window != kNoWindow) lo = below(pos - mk.window + 1);    // k > p - window
-  } else {
-    lo = below(pos);                                                                  // p >= k
-    if (mk.window != kNoWindow && pos <= 0x7fffffff - mk.window) hi = below(pos + mk.window);   // p < k + window
   }
 }
 
