@@ -27,10 +27,7 @@
 
 namespace burst {
 
-#ifndef BURST_DQ_BQ
-#define BURST_DQ_BQ 256
-#endif
-constexpr int kDqBQ = BURST_DQ_BQ;   // query rows per work-group of the dQ kernel: 32 per wave
+constexpr int kDqWaves = 8, kDqBQ = 32 * kDqWaves;   // query rows per work-group of the dQ kernel: 32 per wave
 
 // lse in log2 units, with -inf mapped to +inf so that exp2(x - lse2) = 0 for a dead row
 __device__ __forceinline__ float lse_to_log2(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
@@ -515,7 +512,8 @@ __global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams p, int 
     dkdv_block<D, false, BKV>(*(const BwdParams*)args, smem, blockIdx.x);
   } else {
     asm volatile("" : "+s"(args));
-    dq_block<D, 8, false, 3>(*(const BwdParams*)args, smem, blockIdx.x - n_dkdv);
+    static_assert(kDqWaves * 64 == 512, "both kernels' work-groups have the same size");
+    dq_block<D, kDqWaves, false, 3>(*(const BwdParams*)args, smem, blockIdx.x - n_dkdv);
   }
 }
 
@@ -568,8 +566,8 @@ static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
   const hipError_t e = plan_dq(p, stream);
   const int grid = dq_grid(p);
   if (e != hipSuccess || grid == 0) return e;
-  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, true>), dim3(grid), dim3(2 * kDqBQ), kDqLds<D>, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqBQ / 32, false>), dim3(grid), dim3(2 * kDqBQ), kDqLds<D>, stream, p);
+  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, true>), dim3(grid), dim3(64 * kDqWaves), kDqLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false>), dim3(grid), dim3(64 * kDqWaves), kDqLds<D>, stream, p);
   return hipGetLastError();
 }
 

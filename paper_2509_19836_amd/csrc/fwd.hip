@@ -21,10 +21,7 @@
 
 namespace burst {
 
-#ifndef BURST_FWD_BQ
-#define BURST_FWD_BQ 256
-#endif
-constexpr int kFwdBQ = BURST_FWD_BQ;   // query rows per work-group: 32 per wave
+constexpr int kFwdWaves = 8, kFwdBQ = 32 * kFwdWaves;   // query rows per work-group: 32 per wave
 
 template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdParams p) {
@@ -342,8 +339,8 @@ static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
   }
   if (p.q_runs.total() == 0) return hipSuccess;
   const int grid = mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total());
-  if (p.mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdBQ / 32, true>), dim3(grid), dim3(2 * kFwdBQ), LDS, stream, p);
-  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdBQ / 32, false>), dim3(grid), dim3(2 * kFwdBQ), LDS, stream, p);
+  if (p.mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, true>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
+  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
   return hipGetLastError();
 }
 

@@ -1,6 +1,9 @@
 """Host run of the decisions a wave takes in its walk (class of a tile, rows a lane's row sees) against brute force over
 positions: what the kernels compile, compiled for the CPU."""
 import ctypes as C
+import glob
+import os
+import re
 
 import numpy as np
 import pytest
@@ -83,3 +86,10 @@ def test_visible_rows_rejects_bad_arguments(lib, row):
     assert raw.burst_attn_visible_rows(C.byref(m), 0, row, C.byref(out)) == lib.BURST_ERR_INVALID_ARG
     assert raw.burst_attn_visible_rows(None, 0, 0, C.byref(out)) == lib.BURST_ERR_INVALID_ARG
     assert raw.burst_attn_visible_rows(C.byref(m), 0, 0, None) == lib.BURST_ERR_INVALID_ARG
+
+
+def test_no_build_flag_sets_the_rows_of_a_work_group():
+    """Plans, grids and kernels of a launch, and the two kernels of a joint launch, share one constant."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_19836_amd", "csrc")
+    flags = {name for path in glob.glob(os.path.join(csrc, "*")) for name in re.findall(r"#ifndef (BURST_\w+)", open(path).read())}
+    assert flags == {"BURST_MFMA_PRIO", "BURST_A16"}   # wave priority of MFMA streams, operands fetched ahead
