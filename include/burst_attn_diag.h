@@ -34,8 +34,8 @@ int burst_attn_visible_rows(const burst_mask_t* mask, int32_t query_axis, int64_
 int burst_attn_visible_tile_runs(const burst_mask_t* mask, int32_t query_axis, int32_t tile_rows, int64_t r0, int64_t r1,
                                  int32_t out_start_len[4]);
 
-/* Diagnostic, not part of the attention path: enqueues `iterations` x 4 independent bf16 32x32x16
- * MFMAs per wave on every SIMD (512 work-groups of 256 threads) with constant (0) or pseudo-random
+/* Diagnostic, not part of the attention path: enqueues `iterations` x 8 independent bf16 16x16x32
+ * MFMAs (the kernels' shape) per wave on every SIMD (512 work-groups of 256 threads) with constant (0) or pseudo-random
  * (1) register operands, and stores the flop count of the launch in *flops_out (host, optional).
  * Timed by the caller with events, it gives the matrix-core ceiling of the chip as it is clocked under
  * that load: dense attention tiles are bounded by the random-operand figure.  sink: optional device

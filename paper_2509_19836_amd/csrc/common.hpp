@@ -11,10 +11,7 @@ namespace burst {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -212,10 +209,6 @@ __host__ __device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos
     lo = below(pos);                                                                  // p >= k
     if (mk.window != kNoWindow && pos <= 0x7fffffff - mk.window) hi = below(pos + mk.window);   // p < k + window
   }
-}
-
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 // Wait for every outstanding global load of this wave.  Used once, before a tile loop, after the

@@ -4,6 +4,7 @@
 // whole contiguous head_dim vectors.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma16.hpp"
 
 namespace burst {
 
@@ -205,7 +206,8 @@ hipError_t launch_zero_tensor(const TensorDev& t, int32_t batch, int32_t rows, i
   return hipGetLastError();
 }
 
-// Diagnostic: back-to-back independent bf16 MFMAs from registers, two waves per SIMD on every CU.
+// Diagnostic: back-to-back independent bf16 16x16x32 MFMAs (the kernels' shape) from registers, two waves per SIMD on
+// every CU.
 // With constant operands the chip holds its top clock; with random operands the same instruction
 // stream runs at the clock the power limit allows, which is the ceiling an attention kernel with
 // real data can reach.
@@ -218,34 +220,34 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(float* sink, int iters,
     a[e] = random_operands ? __builtin_bit_cast(__bf16, wa) : (__bf16)1.0f;
     b[e] = random_operands ? __builtin_bit_cast(__bf16, wb) : (__bf16)0.5f;
   }
-  f32x16 c0, c1, c2, c3;
+  constexpr int CHAINS = 8;   // independent accumulators
+  f32x4 c[CHAINS];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) c0[v] = c1[v] = c2[v] = c3[v] = 0.f;
-  for (int i = 0; i < iters; ++i) {
-    c0 = mfma32(a, b, c0);
-    c1 = mfma32(a, b, c1);
-    c2 = mfma32(a, b, c2);
-    c3 = mfma32(a, b, c3);
-    if ((i & 1023) == 1023) {   // keep the accumulators finite
+  for (int j = 0; j < CHAINS; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto iteration = [&]() {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        c0[v] *= 1e-30f;
-        c1[v] *= 1e-30f;
-        c2[v] *= 1e-30f;
-        c3[v] *= 1e-30f;
-      }
+    for (int j = 0; j < CHAINS; ++j) c[j] = mfma16(a, b, c[j]);
+  };
+  for (int i = 0; i < iters / 8; ++i) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) iteration();
+    if ((i & 127) == 127) {   // keep the accumulators finite
+#pragma unroll
+      for (int j = 0; j < CHAINS; ++j) c[j] *= 1e-30f;
     }
   }
-  float s = 0.f;
+  for (int i = 0; i < iters % 8; ++i) iteration();
+  f32x4 s4 = c[0];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) s += c0[v] + c1[v] + c2[v] + c3[v];
+  for (int j = 1; j < CHAINS; ++j) s4 += c[j];
+  const float s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
   if (sink && s == 12345.678f) sink[0] = s;   // never true in practice; keeps the loop alive
 }
 
 hipError_t launch_mfma_probe(float* sink, int iters, int random_operands, int64_t* flops, hipStream_t stream) {
   const int blocks = 512;   // 256 CUs x 2 work-groups x 4 waves
   hipLaunchKernelGGL(mfma_probe_kernel, dim3(blocks), dim3(256), 0, stream, sink, iters, random_operands);
-  if (flops) *flops = (int64_t)blocks * 4 * iters * 4 * 32768;
+  if (flops) *flops = (int64_t)blocks * 4 * iters * 8 * 16384;   // waves, iterations, MFMAs, 2 x 16 x 16 x 32
   return hipGetLastError();
 }
 
