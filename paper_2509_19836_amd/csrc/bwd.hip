@@ -19,8 +19,6 @@
 //    whose A operands are the dO and Q tiles read column-wise from the LDS copies that served
 //    S and dP row-wise.  With grouped-query attention the work-group walks the query heads of its
 //    group, so dK and dV are summed over the group in registers.
-#include <algorithm>
-
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
@@ -39,7 +37,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
   constexpr int TILE = BK * 2 * D, SLOTS = 4;
 
   const int group = p.q_heads / p.kv_heads;
-  const BlockMap bm = map_block<true>(block, p.batch * p.kv_heads, group, p.q_runs.total());
+  const BlockMap bm = map_block<true>(block, p.batch * p.kv_heads, group, p.q_runs.total(), p.q_side_by_side);
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
 
@@ -480,7 +478,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
 
 template <int D, bool BLK, int BKV>
 __device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int block) {   // smem: laid out by DkdvLds, then the open flags
-  const BlockMap bm = map_block<false>(block, p.batch * p.kv_heads, 1, p.k_runs.total());
+  const BlockMap bm = map_block<false>(block, p.batch * p.kv_heads, 1, p.k_runs.total(), p.k_side_by_side);
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -525,18 +523,13 @@ __global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams p, int 
 static bool narrow_key_tiles(const MaskDev& mk, int sq, int sk, int n_keys, const TileRuns& runs128) {
   const int n = n_keys * runs128.total();
   if (mk.blk || n == 0 || n > 256) return false;
-  if (n <= 128) return true;
-  auto walk = [&](int tile) {   // query tiles that see some of the key tile
-    int lo, hi;
-    range_minmax<false>(mk, tile * 128, std::min(tile * 128 + 128, sk), lo, hi);
-    return visible_tiles<true, 64>(mk, lo, hi, sq).len;
-  };
-  return 2 * walk(runs128.tile_of(runs128.total() - 1)) <= walk(runs128.tile_of(0));
+  return n <= 128 || uneven_walks<false>(mk, sq, sk, runs128, 128);
 }
 
 // The work-groups of a kernel: the tiles that see something, and zeros into what gets no work-group under "=".
 static hipError_t plan_dq(BwdParams& p, hipStream_t stream) {
   p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, kDqBQ, true);
+  p.q_side_by_side = side_by_side<true>(p.mask, p.sq, p.sk, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, kDqBQ);
   if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ)
     return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
   return hipSuccess;
@@ -546,6 +539,7 @@ static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
   narrow = narrow_key_tiles(p.mask, p.sq, p.sk, p.batch * p.kv_heads, p.k_runs);
   if (narrow) p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 64, false);
   const int tile = narrow ? 64 : 128;
+  p.k_side_by_side = side_by_side<false>(p.mask, p.sq, p.sk, p.batch * p.kv_heads, 1, p.k_runs, tile);
   hipError_t e = hipSuccess;
   if (p.k_runs.total() < (p.sk + tile - 1) / tile) {
     if (!p.acc_dk) e = launch_zero_tensor(p.dk, p.batch, p.sk, p.kv_heads, p.head_dim, stream);

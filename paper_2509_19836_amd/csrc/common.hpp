@@ -263,17 +263,26 @@ struct NoHook {
 // Heavier tiles start first: under a causal mask a query tile is heavier the higher its rows (HIGH_FIRST), a
 // key tile the lower its rows.  That is also what keeps the work-groups that share an L2 in step: the ones
 // running together then walk the other axis at the same place at the same time, so each tile of it is fetched
-// from HBM once.  The heads of a group take the same tile one after the other.  A launch of few work-groups
-// per CU runs the keys of an XCD side by side, heaviest tiles of all of them first, because there the balance
-// of the last round counts more than the L2 share (16384 rows, 4 keys per XCD, own shard: forward 2228 us key by
-// key, 2165 side by side; 8 x 8 tiles of 64 keys and more: no difference).
+// from HBM once.  The heads of a group take the same tile one after the other.  A launch of few work-groups per CU
+// (kShortLaunch) whose walks are uneven runs the keys of an XCD side by side, heaviest tiles of all of them first,
+// because there the balance of the last round counts more than the L2 share; where all walks are alike there is nothing
+// to balance, and as many streams as keys go through an L2 for nothing.  32 heads, d = 128 (4 keys per XCD), us key by
+// key and side by side:
+//   own shard, causal: forward 8192 rows (128 work-groups per XCD) 618, 605; 12288 (192) 1061, 1025; 16384 (256) 1827,
+//   1835; 18432 (288) 2417, 2376; 32768 (512) 7442, 7520.  dQ 748, 722; 1430, 1415; 2556, 2541; 3235, 3240; 10020,
+//   10070.  dK/dV, whose tiles are half as high, 8192 rows (256) 1011, 991; 12288 (384) 2064, 2082; 16384 3616, 3637.
+//   an earlier shard of the zigzag split, whose keys every query sees: forward 16384 rows 1782, 1777; dQ 2447, 2455; dK/dV,
+//   whose launch is half as long, 8192 rows (128) 942, 955; 12288 (192) 2010, 2089; 16384 (256) 3519, 3911, with
+//   0.95 and 2.59 GB of memory traffic (forward 0.67 and 1.48, dQ 0.81 and 1.62).
+//   block pattern of density 0.25 over 512-token blocks, 16384 rows, forward and backward of a ring: the keys of
+//   its earlier and later shards side by side 21.99 ms, one after the other 22.35.
 struct BlockMap {
   int key, head_in_group, tile;
   bool valid;
 };
 constexpr int kShortLaunch = 256;   // work-groups per XCD (32 CUs)
 template <bool HIGH_FIRST>
-__host__ __device__ __forceinline__ BlockMap map_block(int n, int n_keys, int group, int tiles) {
+__host__ __device__ __forceinline__ BlockMap map_block(int n, int n_keys, int group, int tiles, bool side_by_side) {
   const int per_key = group * tiles, full = n_keys >> 3, rest = n_keys & 7;
   const int rest_items = rest * per_key, rest_blocks = (rest_items + 7) & ~7;
   BlockMap m;
@@ -287,7 +296,7 @@ __host__ __device__ __forceinline__ BlockMap map_block(int n, int n_keys, int gr
   } else {
     const int slot = (n - rest_blocks) >> 3, xcd = n & 7;
     int local_key, in_key;
-    if (full * per_key <= kShortLaunch) {
+    if (side_by_side) {
       const int width = full * group;
       t = slot / width;
       const int w = slot - t * width;
@@ -310,6 +319,7 @@ __host__ __device__ __forceinline__ BlockMap map_block(int n, int n_keys, int gr
 #endif
   return m;
 }
+inline bool short_launch(int n_keys, int group, int tiles) { return (n_keys >> 3) * group * tiles <= kShortLaunch; }
 inline int mapped_grid(int n_keys, int group, int tiles) {
   const int per_key = group * tiles;
   return (((n_keys & 7) * per_key + 7) & ~7) + (n_keys >> 3) * 8 * per_key;

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
 
   const int group = p.q_heads / p.kv_heads;
-  const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total());
+  const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total(), p.q_side_by_side);
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
 
@@ -338,7 +338,9 @@ static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (p.q_runs.total() == 0) return hipSuccess;
-  const int grid = mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total());
+  const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
+  p.q_side_by_side = side_by_side<true>(p.mask, p.sq, p.sk, n_keys, group, p.q_runs, BQ);
+  const int grid = mapped_grid(n_keys, group, p.q_runs.total());
   if (p.mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, true>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
   else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
   return hipGetLastError();

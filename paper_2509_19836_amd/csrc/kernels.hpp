@@ -20,7 +20,8 @@ struct FwdParams {
   int32_t sq, sk;
   float scale;
   MaskDev mask;
-  TileRuns q_runs;      // query tiles with work (filled by the launcher)
+  TileRuns q_runs;      // query tiles with work, and the order of the work-groups (filled by the launcher)
+  int32_t q_side_by_side;
   TensorDev q, k, v;
   TensorDev o_part;     // ptr == nullptr: not requested
   RowvecDev lse_part;
@@ -33,7 +34,8 @@ struct BwdParams {
   int32_t sq, sk;
   float scale;
   MaskDev mask;
-  TileRuns q_runs, k_runs;   // query / key tiles with work (filled by the launcher)
+  TileRuns q_runs, k_runs;   // query / key tiles with work, and the order of the work-groups (filled by the launcher)
+  int32_t q_side_by_side, k_side_by_side;
   TensorDev q, k, v, d_o;
   RowvecDev lse, d;
   TensorDev dq, dk, dv;   // fp32; ptr == nullptr: skip
@@ -75,6 +77,25 @@ inline TileRuns nonempty_runs(const MaskDev& mk, int sq, int sk, int tile_rows, 
     ++tr.len[nruns - 1];
   }
   return tr;
+}
+
+// Whether the walk of the tile that is launched last is at most half as long as that of the first one (heaviest first:
+// map_block), in tiles of 64 rows of the other axis.
+template <bool Q_AXIS>
+inline bool uneven_walks(const MaskDev& mk, int sq, int sk, const TileRuns& runs, int tile_rows) {
+  auto walk = [&](int tile) {
+    const int rows = Q_AXIS ? sq : sk, end = tile * tile_rows + tile_rows;
+    int lo, hi;
+    range_minmax<Q_AXIS>(mk, tile * tile_rows, end < rows ? end : rows, lo, hi);
+    return visible_tiles<!Q_AXIS, 64>(mk, lo, hi, Q_AXIS ? sk : sq).len;
+  };
+  const int n = runs.total();
+  return n > 0 && 2 * walk(runs.tile_of(Q_AXIS ? 0 : n - 1)) <= walk(runs.tile_of(Q_AXIS ? n - 1 : 0));
+}
+// Whether a launch runs the keys of an XCD (of two or more) side by side (map_block).  A block mask makes any walks uneven.
+template <bool Q_AXIS>
+inline bool side_by_side(const MaskDev& mk, int sq, int sk, int n_keys, int group, const TileRuns& runs, int tile_rows) {
+  return n_keys >= 16 && short_launch(n_keys, group, runs.total()) && (mk.blk || uneven_walks<Q_AXIS>(mk, sq, sk, runs, tile_rows));
 }
 
 // ---------------------------------------------------------------------------------------------

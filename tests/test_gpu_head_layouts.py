@@ -116,3 +116,14 @@ def test_gradients_together_and_apart(lib, B, Hq, Hkv, d, sq, sk, causal):
         torch.cuda.synchronize()
         for name, x, y in zip(("dQ", "dK", "dV"), both, apart):
             assert (x - y).abs().max() <= 1e-6 * y.abs().max(), (name, flags)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,sq,sk,causal,q_pos", [
+    (2, 16, 8, 64, 800, 800, True, 0),       # uneven walks: the keys of an XCD side by side
+    (2, 16, 8, 64, 800, 800, False, 0),      # all walks alike: one after the other
+    (1, 19, 19, 128, 530, 700, True, 700),   # an earlier shard: alike, three keys left over
+    (1, 19, 19, 128, 700, 530, True, 100),   # some tiles without keys, uneven
+    (1, 48, 16, 64, 700, 300, True, 200),    # even for the queries' tiles, uneven for the keys'
+])
+def test_order_of_the_keys_of_an_xcd(lib, B, Hq, Hkv, d, sq, sk, causal, q_pos):
+    step_case(lib, B, Hq, Hkv, d, sq, sk, causal, B * 1000 + Hq + sq, q_pos=q_pos)
