@@ -13,7 +13,7 @@
 //    per tile and wave against about 900 clocks of vector work, which the other wave's matrix phase hides.
 //    128K-token ring backward (dQ and dK/dV): 56.3 -> 52.6 ms against the 32x32x16 kernel with register staging.
 //
-//  * dK/dV kernel, key-stationary: a lane owns one key row; K and V rows live in registers as B
+//  * dK/dV kernel, key-stationary: a lane owns two key rows; K and V rows live in registers as B
 //    operands, S = Q K^T and dP = dO V^T come out with the query index in the accumulator registers,
 //    P and dS are packed in place and fed back as B operands of dV^T = dO^T P and dK^T = Q^T dS,
 //    whose A operands are the dO and Q tiles read column-wise from the LDS copies that served
@@ -237,8 +237,12 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 // left a barrier ago; a wave waits for its share of tile t+2 at the end of that phase, two barriers before either
 // role's products read it.  lse or D rows come with a tile into the wave's own LDS, raw, and are brought into the form
 // the accumulators start from in the vector phase before.
-// What bounds it: the matrix pipe under the chip's power limit (64 MFMAs of 16 clocks per wave and tile; the vector
-// phases, 32 exponentials or 32 products and the packing, are shorter and run behind the other wave's MFMAs).
+// What bounds it: not one unit.  The matrix pipe (64 MFMAs of 16 clocks per wave and tile) is 57 % busy at 2.14 GHz, the
+// least of the three kernels and at the highest clock (dQ 70 % at 1.90, forward 62 % at 1.91); waves wait for LDS
+// instructions 0.29 clocks per busy clock of a CU (dQ 0.11, forward 0.08): every operand of a product, the hand-over of P and the
+// row vectors go through the LDS (0.91 instructions per MFMA), and stores_barrier waits for the prefetch of the next phase's first
+// operands together with the stores.  The vector phases, 32 exponentials or 32 products and the packing, are shorter
+// than the matrix phases and run behind the other wave's MFMAs.
 // 128K-token ring backward 52.6 -> 48.7 ms against 32x32x16 MFMAs with tiles staged through registers by the P-waves
 // and the vector work sliced behind each wave's own MFMAs; d = 64, 1500 rows, 4 x 12 heads: 120 -> 95 us per step.
 template <int D>

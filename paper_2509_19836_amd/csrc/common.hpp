@@ -244,7 +244,7 @@ __host__ __device__ __forceinline__ TileRun visible_tiles(const MaskDev& mk, int
 // Scope of a stream of MFMAs: the wave runs at raised issue priority.  A SIMD issues one vector-class
 // instruction at a time and picks the oldest ready wave; without this, a co-resident wave in a
 // dense vector phase (softmax, dS) keeps winning the issue slot and the matrix pipe idles, although
-// an MFMA needs only one slot in eight.
+// an MFMA of 16 clocks needs only one slot in four.
 struct MatrixPhase {
   __device__ __forceinline__ MatrixPhase() { __builtin_amdgcn_s_setprio(BURST_MFMA_PRIO); }
   __device__ __forceinline__ ~MatrixPhase() { __builtin_amdgcn_s_setprio(0); }

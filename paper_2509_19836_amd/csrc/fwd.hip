@@ -11,9 +11,11 @@
 // What bounds it at d = 128: the matrix pipe and the vector unit need about the same time for a tile (64 MFMAs of
 // 16 clocks; 131 vector instructions, of them 32 exponentials, about 1000 clocks for a wave alone), and the chip
 // holds a power limit on top.  So the two waves of a SIMD take the phases in turn, and the products use
-// 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed 2102 against 1772-1874 TFLOP/s).
+// 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed, random operands: 2050-2110 against
+// 1840-1900 TFLOP/s; with operands that change from MFMA to MFMA 1900-1934 against 1786-1817).
 // Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
-// 131072 x 131072 rows x 32 heads: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s); matrix pipe busy 52 -> 61 % at 1.55 GHz.
+// 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one box.  Counters on another: 113 ms,
+// matrix pipe 62 % busy at 1.91 GHz (51 % at 1.64 GHz before).
 // At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -103,7 +105,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // products, 70 so (dQ 121 and 82); a 1024-token window 379 and 367.
   // The last iteration forms a product S nobody reads (of a tile it has): a quarter of a tile's time per work-group,
   // where a second copy of the loop's end cost the registers of the operand prefetch (1 % slower).
-  // Raised priority of the matrix phase: 4-6 % (with both at priority 0 the waves' phases disturb each other).
+  // Raised priority of the matrix phase: 3-6 % (16384 rows x 32 heads 1810 and 1910 us, 32768 rows 7100 and 7430); with both
+  // at priority 0 the waves' phases disturb each other.  dQ 1-3 %, dK/dV 1-6 %.
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
   constexpr int LOADS = KvStream<D, BK, NW, BLK, true>::LOADS, NL = KvStream<D, BK, NW, BLK, true>::N;

@@ -91,8 +91,10 @@ struct LmOperand {
 //    after the first one: their successors of k-tile t + 2 are asked for in phase 2 of t, those of the upper half of
 //    A in phase 1 of t + 1, and every load has two phases until its tile is announced by a barrier, a full phase
 //    before it is read.  The first operands of a phase are therefore fetched in the one before, across the barrier.
-// 8192 tokens, d = 4096, 32000 words, per launch: logits 1.72 ms (1250 TFLOP/s), dH 1.51 (1420), dW 1.69 (1270); with
-// 32x32x16 MFMAs, tiles staged through registers and one barrier per k-tile: 2.10, 1.86, 2.09.  A k-tile takes 1.51 us;
+// 8192 tokens, d = 4096, 32000 words, fastest launch of a run: logits 1.72 ms (1250 TFLOP/s), dH 1.51 (1420), dW 1.69
+// (1270); with 32x32x16 MFMAs, tiles staged through registers and one barrier per k-tile: 2.10, 1.86, 2.09.  (Means of a run, in which
+// the clock falls: 1.78, 1.67, 1.83.  Single launches with counters: 1.81 ms at 68 % busy and 1.66 GHz, 1.81 at 78 % and
+// 1.45, 1.93 at 69 % and 1.54.)  A k-tile takes 1.51 us;
 // the rest of logits and dW (13 and 23 us per output tile) is their fp32 output, which all CUs write at the same time.
 template <bool B_COLS>
 struct LmGemm {
@@ -421,10 +423,10 @@ __global__ __launch_bounds__(256) void lm_dh_sum_kernel(LmHeadParams p, int s0, 
 // 4. dW (+)= dLogits^T H_i, computed as its transpose dW^T = H_i^T dLogits (rows: hidden,
 //    columns: words, contraction: tokens of the tile).  Both factors are stored with the token as
 //    the row, and an operand read column-wise costs twice the LDS instructions of a row-wise one;
-//    the four-fragment A operand is therefore taken from a transposed copy of H_i (a few MB,
-//    written by lm_transpose_h_kernel once per sequence tile), and only the two-fragment B operand
-//    (dLogits) uses the transposing read.  A lane then owns a word: it adds four consecutive
-//    hidden columns of that word's row of dW at a time.
+//    A, of which a wave reads eight operands per k-step (four per phase), is therefore taken from a
+//    transposed copy of H_i (a few MB, written by lm_transpose_h_kernel once per sequence tile), and only
+//    B (dLogits), four operands per k-step that stay in registers for both phases, uses the transposing
+//    read.  A lane then owns a word: it adds four consecutive hidden columns of that word's row of dW at a time.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void lm_transpose_h_kernel(LmHeadParams p, int s0, int n_rows) {
   __shared__ __bf16 tile[64][66];
