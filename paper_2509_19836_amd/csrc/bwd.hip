@@ -237,9 +237,9 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 // left a barrier ago; a wave waits for its share of tile t+2 at the end of that phase, two barriers before either
 // role's products read it.  lse or D rows come with a tile into the wave's own LDS, raw, and are brought into the form
 // the accumulators start from in the vector phase before.
-// What bounds it: not one unit.  The matrix pipe (64 MFMAs of 16 clocks per wave and tile) is 57 % busy at 2.14 GHz, the
-// least of the three kernels and at the highest clock (dQ 70 % at 1.90, forward 62 % at 1.91); waves wait for LDS
-// instructions 0.29 clocks per busy clock of a CU (dQ 0.11, forward 0.08): every operand of a product, the hand-over of P and the
+// What bounds it: not one unit.  The matrix pipe (64 MFMAs of 16 clocks per wave and tile) is 58 % busy at 2.04 GHz, the
+// least of the three kernels and at the highest clock (dQ 70 % at 1.83, forward 63 % at 1.85); waves wait for LDS
+// instructions 0.29 clocks per busy clock of a CU (dQ 0.11, forward 0.07): every operand of a product, the hand-over of P and the
 // row vectors go through the LDS (0.91 instructions per MFMA), and stores_barrier waits for the prefetch of the next phase's first
 // operands together with the stores.  The vector phases, 32 exponentials or 32 products and the packing, are shorter
 // than the matrix phases and run behind the other wave's MFMAs.
