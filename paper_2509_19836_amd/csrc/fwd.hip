@@ -14,7 +14,7 @@
 // 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed, random operands: 2050-2110 against
 // 1840-1900 TFLOP/s; with operands that change from MFMA to MFMA 1900-1934 against 1786-1817).
 // Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
-// 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one box.  Counters on another: 115 ms,
+// 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one card.  Counters on another: 115 ms,
 // matrix pipe 63 % busy at 1.85 GHz.
 // At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
 #include "common.hpp"
