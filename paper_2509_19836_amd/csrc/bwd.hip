@@ -162,33 +162,42 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
       walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
     }
     if (live) {
+      uint32_t kt = k_lds(slot), k1 = k_lds((slot + 1) & 3), v1 = v_lds((slot + 1) & 3);   // slot t mod 4 and the next
+      uint32_t kl = k_lds((slot + 3) & 3), vl = v_lds((slot + 3) & 3);
+      kn = walk.cursor();
+      walk.begin(wave, lane);
       for (;;) {
-        // ---- matrix phase
-        const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
-        const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
-        kn = walk.cursor();
-        walk.begin(wave, lane);
+        // ---- matrix phase; everything else that an iteration computes stands behind its MFMAs or in the vector phase
         bf16x8 first_rows[AHEAD];
         constexpr int NCOLS = MB / 2 * DB;
-        cols_product<D, MB / 2, NB, AHEAD>(k_lds(slot), ad, 0, ds, dq, first, [&](int i) {
+        cols_product<D, MB / 2, NB, AHEAD>(kt, ad, 0, ds, dq, first, [&](int i) {
           if (i < NL) walk.load_v(i, vl, wave);
           if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
           if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
           if (i >= NCOLS - AHEAD) {
             const int f = i - (NCOLS - AHEAD);
-            first_rows[f] = rows_operand<D>(k_lds(slot1), ad, 16 * (f % MB), f / MB);
+            first_rows[f] = rows_operand<D>(k1, ad, 16 * (f % MB), f / MB);
           }
         });
         if (tiles.behind(kb)) break;
-        rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first_rows);
+        rows_product_pair<D, MB, NB, AHEAD>(k1, v1, ad, qreg, doreg, s, dp, first_rows);
         wait_loads_barrier<LOADS>();              // tile t+2
         // ---- vector phase
-        d_scores(kb);
-        slot = slot1;
-        cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
-        phase_barrier();
+        const int tile_k0 = kb;
+        slot = (slot + 1) & 3;
+        vl = kt + TILE;   // (the slot before)
+        kl = kt;
+        kt = k1;
+        k1 = k_lds((slot + 1) & 3);
+        v1 = k1 + TILE;
         kb = kc;
         kc = kn;
+        kn = walk.cursor();
+        walk.begin(wave, lane);
+        pin(slot, kt, k1, v1, kl, vl, kb, kc, kn);
+        d_scores(tile_k0);
+        cols_fetch<D, AHEAD>(kt, ad, 0, first);
+        phase_barrier();
       }
     }
     while (kb >= 0) {   // the rest of the walk is the other waves'
@@ -231,18 +240,19 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 // and a vector phase, a barrier ends every phase, and the dS-waves run one phase behind, so that the two waves of a
 // SIMD hand the matrix pipe to each other.  Iteration t:
 //   P-wave:  matrix: dV^T += dO(t)^T P(t), then S(t+1) from Q(t+1) and -lse      vector: P(t+1), stored to LDS
-//   dS-wave: matrix: dK^T += Q(t)^T dS(t), then dP(t+1) from dO(t+1) and -D      vector: dS(t+1) from P(t+1)
+//   dS-wave: matrix: dK^T -= Q(t)^T dS(t), then D - dP(t+1) from dO(t+1) and D   vector: -dS(t+1) from P(t+1)
 // P(t+1) is stored in the phase before the one that reads it and read a phase before P(t+2) is stored: one copy.
 // Tile t+3 is asked for in the matrix phase of iteration t, into the slot (of four) of tile t-1, which the dS-waves
 // left a barrier ago; a wave waits for its share of tile t+2 at the end of that phase, two barriers before either
-// role's products read it.  lse or D rows come with a tile into the wave's own LDS, raw, and are brought into the form
-// the accumulators start from in the vector phase before.
-// What bounds it: not one unit.  The matrix pipe (64 MFMAs of 16 clocks per wave and tile) is 58 % busy at 2.04 GHz, the
-// least of the three kernels and at the highest clock (dQ 70 % at 1.83, forward 63 % at 1.85); waves wait for LDS
-// instructions 0.29 clocks per busy clock of a CU (dQ 0.11, forward 0.07): every operand of a product, the hand-over of P and the
-// row vectors go through the LDS (0.91 instructions per MFMA), and stores_barrier waits for the prefetch of the next phase's first
-// operands together with the stores.  The vector phases, 32 exponentials or 32 products and the packing, are shorter
-// than the matrix phases and run behind the other wave's MFMAs.
+// role's products read it.  lse or D rows come with a tile into the wave's own LDS, raw; the P-wave brings its rows into the
+// form the accumulators start from in the vector phase before, the dS-wave starts from D as it is.
+// What bounds it: one wave alone on the matrix pipe, and what a phase costs beside its MFMAs.  A wave issues an MFMA of 16 clocks
+// every 18.4 at best, every 20-21 with an operand read for every two (probe); between two barriers lie 1520 (P) and 1870 (dS) clocks of
+// 64 MFMAs while the other role's vector phase, whose instructions take 9 clocks beside MFMAs and its exponentials 15-18, runs
+// for 1460 and 980 (shader clock read at the barriers).  So what stood between the barriers and was neither went: the walk's
+// scalar arithmetic stands behind MFMAs (pin), P is read in one LDS round trip instead of four, the dS-wave needs none for
+// D, the barrier waits for the stores of P and not for the operand prefetch behind them, a direct load waits one state for
+// m0 instead of four.  16384 x 16384 rows, 32 heads, d = 128: 3605 -> 3377 us a step; 8192 rows, d = 64: 621 -> 518.
 // 128K-token ring backward 52.6 -> 48.7 ms against 32x32x16 MFMAs with tiles staged through registers by the P-waves
 // and the vector work sliced behind each wave's own MFMAs; d = 64, 1500 rows, 4 x 12 heads: 120 -> 95 us per step.
 template <int D>
@@ -288,10 +298,10 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
       // few 1e-3 relative, the size of the bf16 rounding P undergoes anyway before the dV product (the paper
       // fixes no precision); only this kernel does it: the forward kernel's Lse is held to 1e-3 absolute and
       // keeps the exact multiply-add.
-      if (ROLE == 0) {
+      // V rows change their sign, which is exact: the dP accumulators then start from D as it comes, and dS and dK^T carry
+      // the sign until the results are written.
 #pragma unroll
-        for (int e = 0; e < 8; ++e) xreg[ks][nb][e] = (__bf16)((float)xreg[ks][nb][e] * c);
-      }
+      for (int e = 0; e < 8; ++e) xreg[ks][nb][e] = ROLE == 0 ? (__bf16)((float)xreg[ks][nb][e] * c) : -xreg[ks][nb][e];
     }
   }
 
@@ -329,23 +339,21 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   bf16x8* const hand = reinterpret_cast<bf16x8*>(smem + L::P_OFF + pair * L::P_PAIR) + lane;
   constexpr int LOADS = QStream<D, BQ, NW, BLK>::LOADS;
 
-  f32x4 s[MB][NB], init[MB];   // S or dP - D of a tile; -lse2 or -D of the lane's rows of it
-  bf16x8 ps[MB / 2][NB];       // P or dS
+  f32x4 s[MB][NB], init[MB];   // S - lse2 or D - dP of a tile; -lse2 or D of the lane's rows of it
+  bf16x8 ps[MB / 2][NB];       // P or -dS
   auto issue = [&](int s_) {
     walk.begin(wave, lane);
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) walk.load(i, q_lds(s_), o_lds(s_), lds0 + row_off(s_), wave);
     walk.advance();
   };
-  // raw row vector -> accumulator start (a dead row's lse of -inf gives P = 0)
-  auto prepare_rows = [&](int s_) {
-    float* x = reinterpret_cast<float*>(smem + row_off(s_)) + lane;
-    *x = ROLE == 0 ? -lse_to_log2(*x) : -*x;
-  };
+  // P-wave: lse of a slot's rows -> accumulator start, in place (a dead row's lse of -inf gives P = 0)
+  auto raw_rows = [&](int s_) { return reinterpret_cast<float*>(smem + row_off(s_)) + lane; };
   auto init_rows = [&](int s_, int mb) { init[mb] = *reinterpret_cast<const f32x4*>(smem + row_off(s_) + 4 * (row0 + 16 * mb + 4 * g)); };
-  // The vector phase, of the tile at query row tile_q0
-  auto vector_phase = [&](int tile_q0) {
+  // The vector phase, of the tile at query row tile_q0.  `next`: the slot whose lse comes next.
+  auto vector_phase = [&](int tile_q0, int next) {
     if (ROLE == 0) {
+      const float raw = *raw_rows(next);   // asked for here, needed behind the exponentials
       const int q0_ = tile_q0 + row0;
       const bool some = tiles.some(q0_);
       if (some && !tiles.full(q0_)) {
@@ -372,25 +380,37 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) ps[ch][nb] = zero_operand();
       }
+      *raw_rows(next) = -lse_to_log2(raw);
 #pragma unroll
       for (int ch = 0; ch < MB / 2; ++ch)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) hand[(ch * NB + nb) * 64] = ps[ch][nb];
+      keep_order();
     } else {
+      bf16x8 pr[MB / 2][NB];   // all of P first: one LDS round trip instead of one per operand
+#pragma unroll
+      for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) pr[ch][nb] = hand[(ch * NB + nb) * 64];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int ch = 0; ch < MB / 2; ++ch)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          const bf16x8 pr = hand[(ch * NB + nb) * 64];
           f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            x[v] *= (float)pr[v];
-            y[v] *= (float)pr[v + 4];
+            x[v] *= (float)pr[ch][nb][v];
+            y[v] *= (float)pr[ch][nb][v + 4];
           }
           ps[ch][nb] = pack_pair(x, y);
         }
     }
+  };
+  // The barrier behind it: P has to be stored, while the AHEAD operands (two LDS reads each) fetched since stay in flight
+  auto vector_barrier = [&]() {
+    if (ROLE == 0) stores_barrier<2 * AHEAD>();
+    else phase_barrier();
   };
 
   if (walk.valid()) {   // uniform over the work-group: all waves take the same number of barriers
@@ -403,46 +423,56 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
     wait_loads_barrier<2 * LOADS>();              // tile 0
     if (ROLE == 1) phase_barrier();
     bf16x8 first[AHEAD];
-    prepare_rows(0);
+    if (ROLE == 0) *raw_rows(0) = -lse_to_log2(*raw_rows(0));
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) init_rows(0, mb);
     rows_fetch<D, MB, AHEAD>(rows_lds(0), ad, 0, first);
     rows_product<D, MB, NB, AHEAD>(rows_lds(0), ad, 0, xreg, s, init, first);
     wait_loads_barrier<LOADS>();                  // tile 1
-    prepare_rows(1);
-    vector_phase(ta);
+    vector_phase(ta, 1);
     cols_fetch<D, AHEAD>(cols_lds(0), ad, 0, first);
-    stores_barrier();
-    int slot = 0;
-    for (;;) {   // iteration t: tb, tc are the first rows of tiles t+1, t+2
-      // ---- matrix phase
-      const int slot1 = (slot + 1) & 3, slot3 = (slot + 3) & 3;
-      const uint32_t ql = q_lds(slot3), ol = o_lds(slot3), rl = lds0 + row_off(slot3);
-      const int tn = walk.cursor();
-      walk.begin(wave, lane);
+    vector_barrier();
+    int slot = 0, tn = walk.cursor();
+    uint32_t ql = q_lds(3), ol = o_lds(3), rl = lds0 + row_off(3), ct = cols_lds(0), rt = rows_lds(1);
+    walk.begin(wave, lane);
+    for (;;) {   // iteration t: tb, tc, tn are the first rows of tiles t+1, t+2, t+3
+      // ---- matrix phase; everything else that an iteration computes stands behind its MFMAs or in the vector phase
       bf16x8 first_rows[AHEAD];
       constexpr int NCOLS = MB / 2 * DB;
       static_assert(LOADS <= NCOLS && MB <= NCOLS && AHEAD <= NCOLS, "a hook per operand");
-      cols_product<D, MB / 2, NB, AHEAD>(cols_lds(slot), ad, 0, ps, acc, first, [&](int i) {
+      cols_product<D, MB / 2, NB, AHEAD>(ct, ad, 0, ps, acc, first, [&](int i) {
         if (i < LOADS) walk.load(i, ql, ol, rl, wave);
-        if (i >= NCOLS - MB) init_rows(slot1, i - (NCOLS - MB));
+        if (!BLK) {
+#pragma unroll
+          for (int part = 0; part < walk.PARTS; ++part)
+            if (i == min(LOADS + part, NCOLS - 1)) walk.end(part);
+        }
+        if (i >= NCOLS - MB) init_rows((slot + 1) & 3, i - (NCOLS - MB));
         if (i >= NCOLS - AHEAD) {
           const int f = i - (NCOLS - AHEAD);
-          first_rows[f] = rows_operand<D>(rows_lds(slot1), ad, 16 * (f % MB), f / MB);
+          first_rows[f] = rows_operand<D>(rt, ad, 16 * (f % MB), f / MB);
         }
       });
       if (tb < 0) break;
-      rows_product<D, MB, NB, AHEAD>(rows_lds(slot1), ad, 0, xreg, s, init, first_rows);
+      rows_product<D, MB, NB, AHEAD>(rt, ad, 0, xreg, s, init, first_rows);
       wait_loads_barrier<LOADS>();                // tile t+2
       // ---- vector phase
-      slot = slot1;
-      walk.advance();
-      prepare_rows((slot + 1) & 3);
-      vector_phase(tb);
-      cols_fetch<D, AHEAD>(cols_lds(slot), ad, 0, first);
-      stores_barrier();
+      if (BLK) walk.advance();
+      ql = q_lds(slot);
+      ol = o_lds(slot);
+      rl = lds0 + row_off(slot);
+      slot = (slot + 1) & 3;
+      ct = cols_lds(slot);
+      rt = rows_lds((slot + 1) & 3);
+      const int tile_q0 = tb;
       tb = tc;
       tc = tn;
+      tn = walk.cursor();
+      walk.begin(wave, lane);
+      pin(slot, ql, ol, rl, ct, rt, tb, tc, tn);
+      vector_phase(tile_q0, (slot + 1) & 3);
+      cols_fetch<D, AHEAD>(ct, ad, 0, first);
+      vector_barrier();
     }
     wait_global_loads();   // tiles past the end of the walk
     if (ROLE == 0) phase_barrier();
@@ -466,7 +496,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
     const int row = k_w0 + 16 * nb + r;
     if (row >= sk) continue;
     const TensorDev& dst = ROLE == 0 ? p.dv : p.dk;
-    const float mul = ROLE == 0 ? 1.f : p.scale;
+    const float mul = ROLE == 0 ? 1.f : -p.scale;   // (dS carried the other sign)
     float* out = (float*)dst.ptr + b * dst.sb + (int64_t)row * dst.ss + hk * dst.sh + 4 * g;
     f32x4 old[DB];
 #pragma unroll

@@ -80,13 +80,14 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 // One direct load: every lane's 16 bytes at base + offset go to LDS at lds + 16 * lane.  Written as an
 // assembly statement because the compiler otherwise waits for all of them before the next LDS read; the
 // kernels wait by count themselves (wait_loads_barrier).  m0 is a reserved register, which the compiler keeps no
-// value in; nothing else in these kernels uses it.
+// value in; nothing else in these kernels uses it.  A load that goes to LDS needs one wait state behind a scalar write of m0;
+// it had four, each up to four clocks between two MFMAs: dQ 2423 -> 2399 us, dK/dV 3428 -> 3377 (16384 rows, 32 heads, d = 128).
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
 // The same with 4 bytes per lane.
 __device__ __forceinline__ void load_dword_to_lds(const char* base, uint32_t offset, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
 // Wait until at most N of this wave's global loads are outstanding, then meet the other waves.  Work-group
 // barrier without the full drain of __syncthreads: loads of later tiles stay in flight.  The scheduling fences
@@ -104,11 +105,41 @@ __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// The same with this wave's LDS stores done, for a phase whose results the other half reads.
+// The same with all but the last N of this wave's LDS instructions done (they complete in order): for a phase whose
+// stores the other half reads, followed by N LDS reads for the next phase, which stay in flight.
+template <int N>
 __device__ __forceinline__ void stores_barrier() {
+  static_assert(N <= 15, "lgkmcnt has four bits");
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
   __builtin_amdgcn_sched_barrier(0);
+}
+// Nothing moves across: the LDS stores that stores_barrier counts on stay in front of the reads it leaves in flight.
+__device__ __forceinline__ void keep_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Keeps the computation of a wave-uniform value where it is written.  The compiler sinks scalar arithmetic to its use, for
+// a loop-carried value the head of the next iteration: there it stood between a barrier and the first MFMA of a matrix
+// phase (35-40 instructions, in which no wave of the SIMD has matrix work) instead of behind MFMAs.  16384 rows, 32 heads,
+// d = 128: dK/dV 3769 -> 3438 us, dQ 2425 -> 2400, forward 1769 -> 1733; in forward, whose vector phase is the longer one, the
+// rest of that work is better off at the head of the matrix phase (moved into the vector phase: 1796).
+template <class T>
+__device__ __forceinline__ void pin(T& x) {
+  asm volatile("" : "+s"(x));
+}
+template <class T, class... Rest>
+__device__ __forceinline__ void pin(T& x, Rest&... rest) {
+  pin(x);
+  pin(rest...);
+}
+
+// All ones where x is negative, else zero: scalar arithmetic in place of conditions, minima and maxima, whose results the
+// compiler keeps in vector registers.
+__device__ __forceinline__ int negative_mask(int x) {
+  pin(x);   // (it would recognise the condition)
+  return x >> 31;
 }
 
 // Direct staging of [ROWS x D] tiles by NW waves: wave w brings 1 KiB pieces w, w + NW, ...  The per-lane part
@@ -187,21 +218,23 @@ struct KvStream {
   __device__ __forceinline__ void load_k(int i, uint32_t lds, int wave) const { stage_k.load_one(k_tile, i, lds, wave); }
   __device__ __forceinline__ void load_v(int i, uint32_t lds, int wave) const { stage_v.load_one(LAG ? v_prev : v_tile, i, lds, wave); }
   // First key row of the cursor's tile, -1 when the walk is over
-  __device__ __forceinline__ int cursor() const { return k0 | (min(left, 1) - 1); }
+  __device__ __forceinline__ int cursor() const { return k0 | negative_mask(left - 1); }
   // After them: the cursor moves to the next tile (and stays on the last one when there is none), in PARTS pieces
-  // of a few scalar instructions that fit between the matrix instructions of a stream.  Arithmetic on 0 / 1
-  // instead of conditions: the compiler keeps selected addresses in vector registers.
+  // of a few scalar instructions that fit between the matrix instructions of a stream.
   static constexpr int PARTS = 3;
-  int move;
+  int move;               // mask: the cursor moves; with a block mask, the number of tiles
   __device__ __forceinline__ void end(int part) {
     if (part == 0) {
       if (LAG) {
         v_prev = v_tile;
         v0 = k0;
       }
-      move = min(max(left - 1, 0), 1);
-      left = max(left - 1, 0);
-      if (BLK) {   // skip tiles that the block mask closes
+      if (!BLK) {
+        move = negative_mask(1 - left);
+        left += negative_mask(-left);
+        k0 += BK & move;
+      } else {
+        left = max(left - 1, 0);   // skip tiles that the block mask closes
         move = 1;
         while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK + move]) == 0) {
           --left;
@@ -209,11 +242,19 @@ struct KvStream {
         }
         move = __builtin_amdgcn_readfirstlane(move * min(left, 1));
         left = __builtin_amdgcn_readfirstlane(left);
+        k0 += move * BK;
       }
-      k0 += move * BK;
+      if (LAG) pin(v_prev, v0);
+      pin(left, k0);
     }
-    if (part == 1) k_tile += BLK ? move * k_step : k_step & -(int64_t)move;
-    if (part == 2) v_tile += BLK ? move * v_step : v_step & -(int64_t)move;
+    if (part == 1) {
+      k_tile += BLK ? move * k_step : k_step & (int64_t)move;
+      pin(k_tile);
+    }
+    if (part == 2) {
+      v_tile += BLK ? move * v_step : v_step & (int64_t)move;
+      pin(v_tile);
+    }
   }
   __device__ __forceinline__ void end() {
     for (int i = 0; i < PARTS; ++i) end(i);
@@ -246,12 +287,11 @@ struct QStream {
   uint32_t row_off;
   int left, heads, q0;    // cursor: tiles left of this head, heads left (0: the walk is over), first row of its tile
   int run_start, run_len, sq;
-  bool clamped;
+  int clamped;            // mask
   const uint8_t* open;    // LDS flags per query tile from a block-wise sparse mask
-  const char *q_head, *o_head, *row_head;   // first tile of the run, at the cursor's head
   const char *q_tile, *o_tile, *row_tile;
-  int64_t q_step, o_step; // bytes per tile
-  int64_t q_next, o_next, row_next;         // bytes per head
+  int64_t q_step, o_step;                   // bytes per tile
+  int64_t q_next, o_next, row_next;         // from the last tile of a head to the first one of the next, bytes
 
   __device__ __forceinline__ void init(const TensorDev& q, const TensorDev& d_o, const RowvecDev& vec, int b, int hq, int group,
                                        TileRun run, int sq_, int wave, int lane, const uint8_t* open_flags) {
@@ -264,25 +304,17 @@ struct QStream {
     q0 = run_start * BQ;
     q_step = 2 * BQ * q.ss;
     o_step = 2 * BQ * d_o.ss;
-    q_next = 2 * q.sh;
-    o_next = 2 * d_o.sh;
-    row_next = 4 * vec.sh;
-    q_head = reinterpret_cast<const char*>((const __bf16*)q.ptr + b * q.sb + hq * q.sh) + run_start * q_step;
-    o_head = reinterpret_cast<const char*>((const __bf16*)d_o.ptr + b * d_o.sb + hq * d_o.sh) + run_start * o_step;
-    row_head = reinterpret_cast<const char*>(vec.ptr + b * vec.sb + hq * vec.sh + q0);
-    first_of_head();
+    q_next = 2 * q.sh - (run_len - 1) * q_step;
+    o_next = 2 * d_o.sh - (run_len - 1) * o_step;
+    row_next = 4 * vec.sh - (run_len - 1) * (int64_t)(4 * BQ);
+    q_tile = reinterpret_cast<const char*>((const __bf16*)q.ptr + b * q.sb + hq * q.sh) + run_start * q_step;
+    o_tile = reinterpret_cast<const char*>((const __bf16*)d_o.ptr + b * d_o.sb + hq * d_o.sh) + run_start * o_step;
+    row_tile = reinterpret_cast<const char*>(vec.ptr + b * vec.sb + hq * vec.sh + q0);
     offsets(BQ, wave, lane);
-    clamped = false;
+    clamped = 0;
     if (BLK) {
       if (heads > 0 && !is_open()) advance();
     }
-  }
-  __device__ __forceinline__ void first_of_head() {
-    left = run_len;
-    q0 = run_start * BQ;
-    q_tile = q_head;
-    o_tile = o_head;
-    row_tile = row_head;
   }
   __device__ __forceinline__ void offsets(int valid, int wave, int lane) {
     stage_q.clamp(q_step / (2 * BQ), valid, wave, lane);
@@ -292,7 +324,7 @@ struct QStream {
   __device__ __forceinline__ bool is_open() const { return __builtin_amdgcn_readfirstlane(open[q0 / BQ]) != 0; }
   __device__ __forceinline__ bool valid() const { return heads > 0; }
   // First row of the cursor's tile, -1 when the walk is over
-  __device__ __forceinline__ int cursor() const { return heads > 0 ? q0 : -1; }
+  __device__ __forceinline__ int cursor() const { return q0 | negative_mask(heads - 1); }
   // Closed tiles from the cursor's on, as far as one read sees (64 tiles, a lane each; left >= 1 of this head).  One
   // read per tile, with its wait, stood in the vector phase of both roles: 16384 rows x 32 heads in blocks of 512,
   // density 0.05: dK/dV 770 -> 409 us a step; density 0.1: 925 -> 570.
@@ -301,32 +333,64 @@ struct QStream {
     const uint64_t some = __ballot(l < left && open[q0 / BQ + min(l, left - 1)] != 0);
     return some ? __builtin_ctzll(some) : 64;
   }
-  // To the next tile; at the end of the walk the cursor stays where it is
+  // To the next tile; at the end of the walk the cursor stays where it is.  Without a block mask in PARTS pieces of a few
+  // scalar instructions that fit between the matrix instructions of a stream, as in KvStream.
+  static constexpr int PARTS = 4;
+  int to_next, to_head;   // masks: the cursor moves on in its head, to the next head
+  __device__ __forceinline__ void end(int part) {
+    if (part == 0) {
+      const int not_over = negative_mask(-heads);
+      to_next = negative_mask(1 - left);
+      to_head = ~to_next & negative_mask(1 - heads);
+      heads += ~to_next & not_over;
+      left += (run_len & to_head) + not_over;        // (over: the last tile of the last head, for good)
+      q0 += (BQ & to_next) - ((run_len - 1) * BQ & to_head);
+      pin(heads, left, q0);
+    }
+    if (part == 1) {
+      q_tile += (q_step & (int64_t)to_next) + (q_next & (int64_t)to_head);
+      pin(q_tile);
+    }
+    if (part == 2) {
+      o_tile += (o_step & (int64_t)to_next) + (o_next & (int64_t)to_head);
+      pin(o_tile);
+    }
+    if (part == 3) {
+      row_tile += ((4 * BQ) & to_next) + (row_next & (int64_t)to_head);
+      pin(row_tile);
+    }
+  }
   __device__ __forceinline__ void advance() {
+    if (!BLK) {
+      for (int i = 0; i < PARTS; ++i) end(i);
+      return;
+    }
     if (heads == 0) return;
     int n = 1;
     do {
       if (left > n) {
         left -= n;
-        q0 += n * BQ;
-        q_tile += n * q_step;
-        o_tile += n * o_step;
-        row_tile += n * 4 * BQ;
       } else {
+        n = left - 1;     // to the last tile of this head, and from there to the next one
         if (--heads == 0) return;
-        q_head += q_next;
-        o_head += o_next;
-        row_head += row_next;
-        first_of_head();
+        left = run_len;
+        q0 -= run_len * BQ - BQ;
+        q_tile += q_next;
+        o_tile += o_next;
+        row_tile += row_next;
       }
-      if (BLK) n = closed_tiles();
-    } while (BLK && n > 0);
+      q0 += n * BQ;
+      q_tile += n * q_step;
+      o_tile += n * o_step;
+      row_tile += n * 4 * BQ;
+      n = closed_tiles();
+    } while (n > 0);
   }
   // Before the loads of a tile: rows past the last one are read as copies of it
   __device__ __forceinline__ void begin(int wave, int lane) {
-    const bool ragged = q0 + BQ > sq;
+    const int ragged = negative_mask(sq - BQ - q0);
     if (ragged != clamped) {
-      offsets(ragged ? sq - q0 : BQ, wave, lane);
+      offsets(min(sq - q0, BQ), wave, lane);
       clamped = ragged;
     }
   }
