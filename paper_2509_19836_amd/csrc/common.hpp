@@ -211,6 +211,22 @@ __host__ __device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos
   }
 }
 
+// Largest of three (a NaN among them is left out, as by fmaxf).  fmaxf is not folded into it: each of its arguments that the
+// compiler cannot prove to be a quiet number costs an instruction that makes it one.  The compiler does not keep an
+// assembly statement away from an MFMA whose result it reads: mfma_results() goes before one that may follow closely.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float m;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+  return m;
+}
+
+// Sixteen wait states: the results of the MFMAs before are in their registers.
+__device__ __forceinline__ void mfma_results() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Wait for every outstanding global load of this wave.  Used once, before a tile loop, after the
 // loop-invariant register operands were fetched: without it the compiler cannot prove on every
 // path that they have landed and re-inserts vmcnt waits inside the loop, which then also wait for
