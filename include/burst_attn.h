@@ -131,6 +131,17 @@ int burst_attn_step_fwd(const burst_shape_t* shape, const burst_mask_t* mask,
                         void* hip_stream);
 
 /*
+ * Consecutive forward steps of one query chunk whose key/value chunks are all at hand (a ring whose shards have arrived, or
+ * are resident): folded into (o_acc, lse_acc) as n_steps calls of burst_attn_step_fwd in this order would, up to rounding,
+ * in as few launches as the steps allow.  shapes, masks, k and v are arrays of n_steps entries; batch, q_heads, head_dim and
+ * sq must fit q and the running state in each.  All steps are checked before the first is enqueued.  At most BURST_MAX_STEPS.
+ */
+#define BURST_MAX_STEPS 1024
+int burst_attn_steps_fwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
+                         const burst_tensor_t* q, const burst_tensor_t* k, const burst_tensor_t* v,
+                         const burst_tensor_t* o_acc, const burst_rowvec_t* lse_acc, void* hip_stream);
+
+/*
  * Online-softmax merge of a step result into the running state (forward algorithm):
  * (o_acc, lse_acc) <- (o_acc, lse_acc) (+) (o_part, lse_part), with exp(-inf) = 0 so that a row
  * whose two Lse are both -inf stays (0, -inf).  o_acc fp32 in/out; o_part fp32 or bf16.
@@ -169,6 +180,17 @@ int burst_attn_step_bwd(const burst_shape_t* shape, const burst_mask_t* mask,
                         const burst_tensor_t* d_o, const burst_rowvec_t* lse, const burst_rowvec_t* d,
                         const burst_tensor_t* dq, const burst_tensor_t* dk, const burst_tensor_t* dv,
                         int32_t accumulate_flags, void* hip_stream);
+
+/*
+ * Consecutive backward steps of one query chunk whose key/value chunks are all at hand: as n_steps calls of
+ * burst_attn_step_bwd, up to rounding, in as few launches as the steps allow.  shapes, masks, k, v, dk and dv are arrays of
+ * n_steps entries (dk and dv NULL to skip them).  dq receives the sum over the steps, on top of its contents with BURST_ACC_DQ.
+ */
+int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
+                         const burst_tensor_t* q, const burst_tensor_t* k, const burst_tensor_t* v,
+                         const burst_tensor_t* d_o, const burst_rowvec_t* lse, const burst_rowvec_t* d,
+                         const burst_tensor_t* dq, const burst_tensor_t* dk, const burst_tensor_t* dv,
+                         int32_t accumulate_flags, void* hip_stream);
 
 /* Host helpers (no GPU involved). */
 

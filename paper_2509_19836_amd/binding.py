@@ -23,6 +23,7 @@ BURST_OK, BURST_ERR_INVALID_ARG, BURST_ERR_UNSUPPORTED, BURST_ERR_HIP, BURST_ERR
 BURST_BF16, BURST_F32 = 0, 1
 BURST_MASK_FULL, BURST_MASK_CAUSAL = 0, 1
 BURST_ACC_DQ, BURST_ACC_DK, BURST_ACC_DV = 1, 2, 4
+BURST_MAX_STEPS = 1024
 
 
 class burst_shape_t(C.Structure):
@@ -59,6 +60,12 @@ _lib.burst_attn_preprocess_bwd.argtypes = [_P(burst_shape_t), _P(burst_tensor_t)
                                            _P(burst_rowvec_t), C.c_void_p]
 _lib.burst_attn_step_bwd.restype = C.c_int
 _lib.burst_attn_step_bwd.argtypes = [_P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
+    _P(burst_rowvec_t)] * 2 + [_P(burst_tensor_t)] * 3 + [C.c_int32, C.c_void_p]
+_lib.burst_attn_steps_fwd.restype = C.c_int
+_lib.burst_attn_steps_fwd.argtypes = [C.c_int32, _P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
+    _P(burst_rowvec_t), C.c_void_p]
+_lib.burst_attn_steps_bwd.restype = C.c_int
+_lib.burst_attn_steps_bwd.argtypes = [C.c_int32, _P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
     _P(burst_rowvec_t)] * 2 + [_P(burst_tensor_t)] * 3 + [C.c_int32, C.c_void_p]
 for _name in ("zigzag", "contiguous", "striped"):
     _f = getattr(_lib, f"burst_attn_fill_{_name}_mask")
@@ -104,7 +111,7 @@ _lib.burst_attn_status_string.argtypes = [C.c_int]
 _lib.burst_attn_last_hip_error.restype = C.c_int
 _lib.burst_attn_version.restype = C.c_char_p
 
-EXPORTS = ["burst_attn_step_fwd", "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
+EXPORTS = ["burst_attn_step_fwd", "burst_attn_steps_fwd", "burst_attn_steps_bwd", "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
            "burst_attn_fill_zigzag_mask", "burst_attn_fill_contiguous_mask", "burst_attn_fill_striped_mask",
            "burst_attn_fill_block_striped_mask",
            "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
@@ -239,6 +246,33 @@ def burst_attn_step_bwd(shp, mask, q, k, v, d_o, lse, d, dq=None, dk=None, dv=No
     _check(_lib.burst_attn_step_bwd(C.byref(shp), _ref(mask), _ref(tensor(q)), _ref(tensor(k)), _ref(tensor(v)),
                                     _ref(tensor(d_o)), _ref(rowvec(lse)), _ref(rowvec(d)), _ref(tensor(dq)),
                                     _ref(tensor(dk)), _ref(tensor(dv)), accumulate_flags, _stream(stream)))
+
+
+def _arrays(shapes, masks, *tensor_lists):
+    n = len(shapes)
+    assert len(masks) == n and all(t is None or len(t) == n for t in tensor_lists)
+    return [(burst_shape_t * n)(*shapes), (burst_mask_t * n)(*masks)] + [
+        None if ts is None else (burst_tensor_t * n)(*map(tensor, ts)) for ts in tensor_lists]
+
+
+def burst_attn_steps_fwd(shapes, masks, q, k, v, o_acc, lse_acc, stream=None):
+    """Consecutive steps of one query chunk: shapes, masks, k and v are lists with an entry for each step."""
+    for i in range(0, len(shapes), BURST_MAX_STEPS):
+        part = slice(i, i + BURST_MAX_STEPS)
+        shp, msk, ks, vs = _arrays(shapes[part], masks[part], k[part], v[part])
+        _check(_lib.burst_attn_steps_fwd(len(shp), shp, msk, _ref(tensor(q)), ks, vs, _ref(tensor(o_acc)), _ref(rowvec(lse_acc)),
+                                         _stream(stream)))
+
+
+def burst_attn_steps_bwd(shapes, masks, q, k, v, d_o, lse, d, dq, dk, dv, accumulate_flags=0, stream=None):
+    """Consecutive steps of one query chunk: shapes, masks, k, v, dk and dv are lists with an entry for each step."""
+    for i in range(0, len(shapes), BURST_MAX_STEPS):
+        part = slice(i, i + BURST_MAX_STEPS)
+        shp, msk, ks, vs, dks, dvs = _arrays(shapes[part], masks[part], k[part], v[part], None if dk is None else dk[part],
+                                             None if dv is None else dv[part])
+        _check(_lib.burst_attn_steps_bwd(len(shp), shp, msk, _ref(tensor(q)), ks, vs, _ref(tensor(d_o)), _ref(rowvec(lse)),
+                                         _ref(rowvec(d)), _ref(tensor(dq)), dks, dvs, accumulate_flags, _stream(stream)))
+        accumulate_flags |= BURST_ACC_DQ
 
 
 def lm_head_shape(n_tokens, d_model, vocab, tile_tokens, grad_scale=1.0):

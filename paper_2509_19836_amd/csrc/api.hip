@@ -205,6 +205,135 @@ int static_scratch_of_current_device(void** out) {
     if (_st != BURST_OK) return _st; \
   } while (0)
 
+// The parts of a forward call's arguments: what a step brings, and what belongs to the query chunk.
+int check_fwd_step(const burst_shape_t* shape, const burst_mask_t* mask, const burst_tensor_t* k, const burst_tensor_t* v,
+                   FwdStep* st) {
+  BURST_TRY(check_shape(shape));
+  std::memset(st, 0, sizeof(*st));
+  BURST_TRY(check_mask(mask, shape->sq, shape->sk, &st->mask));
+  BURST_TRY(check_tensor(k, 1, &st->k));
+  BURST_TRY(check_tensor(v, 1, &st->v));
+  st->sk = (int32_t)shape->sk;
+  return BURST_OK;
+}
+
+int check_fwd(const burst_shape_t* shape, const burst_tensor_t* q, const burst_tensor_t* o_part, const burst_rowvec_t* lse_part,
+              const burst_tensor_t* o_acc, const burst_rowvec_t* lse_acc, FwdParams* p) {
+  std::memset(p, 0, sizeof(*p));
+  BURST_TRY(check_tensor(q, 1, &p->q));
+  const bool want_part = o_part || lse_part, want_acc = o_acc || lse_acc;
+  if (!want_part && !want_acc) return BURST_ERR_INVALID_ARG;
+  if (want_part) {
+    BURST_TRY(check_tensor(o_part, 3, &p->o_part));
+    BURST_TRY(check_rowvec(lse_part, &p->lse_part));
+    BURST_TRY(check_no_overlap(p->o_part, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
+    BURST_TRY(check_rowvec_no_overlap(p->lse_part, shape->batch, shape->q_heads, shape->sq));
+  }
+  if (want_acc) {
+    BURST_TRY(check_tensor(o_acc, 2, &p->o_acc));
+    BURST_TRY(check_rowvec(lse_acc, &p->lse_acc));
+    BURST_TRY(check_no_overlap(p->o_acc, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
+    BURST_TRY(check_rowvec_no_overlap(p->lse_acc, shape->batch, shape->q_heads, shape->sq));
+  }
+  p->batch = shape->batch;
+  p->q_heads = shape->q_heads;
+  p->kv_heads = shape->kv_heads;
+  p->head_dim = shape->head_dim;
+  p->sq = (int32_t)shape->sq;
+  p->scale = shape->scale;
+  return BURST_OK;
+}
+
+// The same for the backward call.
+int check_bwd_step(const burst_shape_t* shape, const burst_mask_t* mask, const burst_tensor_t* k, const burst_tensor_t* v,
+                   const burst_tensor_t* dk, const burst_tensor_t* dv, BwdStep* st) {
+  BURST_TRY(check_shape(shape));
+  std::memset(st, 0, sizeof(*st));
+  BURST_TRY(check_mask(mask, shape->sq, shape->sk, &st->mask));
+  BURST_TRY(check_tensor(k, 1, &st->k));
+  BURST_TRY(check_tensor(v, 1, &st->v));
+  if ((dk == nullptr) != (dv == nullptr)) return BURST_ERR_INVALID_ARG;
+  if (dk) {
+    BURST_TRY(check_tensor(dk, 2, &st->dk));
+    BURST_TRY(check_no_overlap(st->dk, shape->batch, shape->sk, shape->kv_heads, shape->head_dim));
+    BURST_TRY(check_tensor(dv, 2, &st->dv));
+    BURST_TRY(check_no_overlap(st->dv, shape->batch, shape->sk, shape->kv_heads, shape->head_dim));
+  }
+  st->sk = (int32_t)shape->sk;
+  return BURST_OK;
+}
+
+int check_bwd(const burst_shape_t* shape, const burst_tensor_t* q, const burst_tensor_t* d_o, const burst_rowvec_t* lse,
+              const burst_rowvec_t* d, const burst_tensor_t* dq, bool want_dkdv, int32_t accumulate_flags, BwdParams* p) {
+  std::memset(p, 0, sizeof(*p));
+  BURST_TRY(check_tensor(q, 1, &p->q));
+  BURST_TRY(check_tensor(d_o, 1, &p->d_o));
+  BURST_TRY(check_rowvec(lse, &p->lse));
+  BURST_TRY(check_rowvec(d, &p->d));
+  if (!dq && !want_dkdv) return BURST_ERR_INVALID_ARG;
+  if (accumulate_flags & ~(BURST_ACC_DQ | BURST_ACC_DK | BURST_ACC_DV)) return BURST_ERR_INVALID_ARG;
+  if (dq) {
+    BURST_TRY(check_tensor(dq, 2, &p->dq));
+    BURST_TRY(check_no_overlap(p->dq, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
+  }
+  p->acc_dq = (accumulate_flags & BURST_ACC_DQ) != 0;
+  p->acc_dk = (accumulate_flags & BURST_ACC_DK) != 0;
+  p->acc_dv = (accumulate_flags & BURST_ACC_DV) != 0;
+  p->batch = shape->batch;
+  p->q_heads = shape->q_heads;
+  p->kv_heads = shape->kv_heads;
+  p->head_dim = shape->head_dim;
+  p->sq = (int32_t)shape->sq;
+  p->scale = shape->scale;
+  return BURST_OK;
+}
+
+// Steps of one query chunk: those without keys (or queries) contribute nothing, the others run.
+hipError_t run_bwd(const BwdParams& p0, const BwdStep* steps, int n, hipStream_t stream) {
+  BwdParams p = p0;
+  std::vector<BwdStep> run;
+  for (int i = 0; i < n; ++i) {
+    const BwdStep& st = steps[i];
+    if (p.sq > 0 && st.sk > 0) {
+      run.push_back(st);
+      continue;
+    }
+    // "+=" leaves the gradients alone, "=" makes them zero
+    hipError_t e = hipSuccess;
+    if (st.dk.ptr && !p.acc_dk && st.sk > 0) e = launch_zero_tensor(st.dk, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+    if (e == hipSuccess && st.dv.ptr && !p.acc_dv && st.sk > 0)
+      e = launch_zero_tensor(st.dv, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+    if (e != hipSuccess) return e;
+  }
+  if (!run.empty()) return launch_steps_bwd(p, run.data(), (int)run.size(), stream);
+  if (p.dq.ptr && !p.acc_dq && p.sq > 0) return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
+  return hipSuccess;
+}
+
+// Whether two steps of a call can share a launch: the same query side.
+template <class Params, class Step>
+bool same_queries(const Params& p, const Step& s, const Params& p2, const Step& s2) {
+  return p.batch == p2.batch && p.q_heads == p2.q_heads && p.kv_heads == p2.kv_heads && p.head_dim == p2.head_dim && p.sq == p2.sq &&
+         p.scale == p2.scale && s.mask.q_nseg == s2.mask.q_nseg && s.mask.q_seg_len == s2.mask.q_seg_len &&
+         s.mask.q_pos0 == s2.mask.q_pos0 && s.mask.q_period == s2.mask.q_period && s.mask.pos_stride == s2.mask.pos_stride &&
+         !s.mask.blk && !s2.mask.blk;
+}
+
+// Addresses from the first to the last element (empty: begin == end).  Overlapping spans may still name different elements.
+struct Span {
+  uintptr_t begin, end;
+};
+Span span_of(const TensorDev& t, int64_t batch, int64_t rows, int64_t heads, int64_t head_dim) {
+  if (!t.ptr || batch == 0 || rows == 0) return Span{0, 0};
+  const int64_t last = (batch - 1) * t.sb + (rows - 1) * t.ss + (heads - 1) * t.sh + head_dim;
+  return Span{(uintptr_t)t.ptr, (uintptr_t)t.ptr + (uintptr_t)last * (t.is_f32 ? 4 : 2)};
+}
+Span span_of(const RowvecDev& t, int64_t batch, int64_t heads, int64_t rows) {
+  if (!t.ptr || rows == 0) return Span{0, 0};
+  return Span{(uintptr_t)t.ptr, (uintptr_t)t.ptr + (uintptr_t)((batch - 1) * t.sb + (heads - 1) * t.sh + rows) * 4};
+}
+bool overlap(const Span& a, const Span& b) { return a.begin < b.end && b.begin < a.end; }
+
 }  // namespace
 
 extern "C" {
@@ -213,44 +342,52 @@ int burst_attn_step_fwd(const burst_shape_t* shape, const burst_mask_t* mask, co
                         const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* o_part,
                         const burst_rowvec_t* lse_part, const burst_tensor_t* o_acc,
                         const burst_rowvec_t* lse_acc, void* hip_stream) {
-  BURST_TRY(check_shape(shape));
   FwdParams p;
-  std::memset(&p, 0, sizeof(p));
-  BURST_TRY(check_mask(mask, shape->sq, shape->sk, &p.mask));
-  BURST_TRY(check_tensor(q, 1, &p.q));
-  BURST_TRY(check_tensor(k, 1, &p.k));
-  BURST_TRY(check_tensor(v, 1, &p.v));
-  const bool want_part = o_part || lse_part, want_acc = o_acc || lse_acc;
-  if (!want_part && !want_acc) return BURST_ERR_INVALID_ARG;
-  if (want_part) {
-    BURST_TRY(check_tensor(o_part, 3, &p.o_part));
-    BURST_TRY(check_rowvec(lse_part, &p.lse_part));
-    BURST_TRY(check_no_overlap(p.o_part, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
-    BURST_TRY(check_rowvec_no_overlap(p.lse_part, shape->batch, shape->q_heads, shape->sq));
-  }
-  if (want_acc) {
-    BURST_TRY(check_tensor(o_acc, 2, &p.o_acc));
-    BURST_TRY(check_rowvec(lse_acc, &p.lse_acc));
-    BURST_TRY(check_no_overlap(p.o_acc, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
-    BURST_TRY(check_rowvec_no_overlap(p.lse_acc, shape->batch, shape->q_heads, shape->sq));
-  }
-  p.batch = shape->batch;
-  p.q_heads = shape->q_heads;
-  p.kv_heads = shape->kv_heads;
-  p.head_dim = shape->head_dim;
-  p.sq = (int32_t)shape->sq;
-  p.sk = (int32_t)shape->sk;
-  p.scale = shape->scale;
+  FwdStep st;
+  BURST_TRY(check_fwd_step(shape, mask, k, v, &st));
+  BURST_TRY(check_fwd(shape, q, o_part, lse_part, o_acc, lse_acc, &p));
   if (p.sq == 0) return BURST_OK;
   hipStream_t stream = (hipStream_t)hip_stream;
   hipError_t e;
-  if (p.sk == 0) {  // no key: the step result is (0, -inf) and the running state is unchanged
-    if (!want_part) return BURST_OK;
+  if (st.sk == 0) {  // no key: the step result is (0, -inf) and the running state is unchanged
+    if (!p.o_part.ptr) return BURST_OK;
     e = launch_fill_empty_fwd(p, stream);
   } else {
-    e = launch_step_fwd(p, stream);
+    e = launch_steps_fwd(p, &st, 1, stream);
   }
   return e == hipSuccess ? BURST_OK : hip_fail(e);
+}
+
+int burst_attn_steps_fwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks, const burst_tensor_t* q,
+                         const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* o_acc,
+                         const burst_rowvec_t* lse_acc, void* hip_stream) {
+  if (n_steps < 0 || (n_steps > 0 && (!shapes || !masks || !k || !v))) return BURST_ERR_INVALID_ARG;
+  if (n_steps > BURST_MAX_STEPS) return BURST_ERR_UNSUPPORTED;
+  std::vector<FwdParams> p(n_steps);
+  std::vector<FwdStep> st(n_steps);
+  for (int i = 0; i < n_steps; ++i) {
+    BURST_TRY(check_fwd_step(&shapes[i], &masks[i], &k[i], &v[i], &st[i]));
+    BURST_TRY(check_fwd(&shapes[i], q, nullptr, nullptr, o_acc, lse_acc, &p[i]));
+  }
+  for (int i = 0, end; i < n_steps; i = end) {
+    std::vector<FwdStep> run;   // steps that may share launches
+    for (end = i; end < n_steps && (end == i || same_queries(p[i], st[i], p[end], st[end])); ++end)
+      if (st[end].sk > 0) run.push_back(st[end]);
+    if (p[i].sq == 0 || run.empty()) continue;
+    // the state must not be an input of a step that follows
+    const Span state[2] = {span_of(p[i].o_acc, p[i].batch, p[i].sq, p[i].q_heads, p[i].head_dim),
+                           span_of(p[i].lse_acc, p[i].batch, p[i].q_heads, p[i].sq)};
+    bool apart = true;
+    for (const FwdStep& x : run)
+      for (const Span& o : state)
+        apart = apart && !overlap(o, span_of(x.k, p[i].batch, x.sk, p[i].kv_heads, p[i].head_dim)) &&
+                !overlap(o, span_of(x.v, p[i].batch, x.sk, p[i].kv_heads, p[i].head_dim));
+    hipError_t e = hipSuccess;
+    if (apart) e = launch_steps_fwd(p[i], run.data(), (int)run.size(), (hipStream_t)hip_stream);
+    else for (size_t j = 0; j < run.size() && e == hipSuccess; ++j) e = launch_steps_fwd(p[i], &run[j], 1, (hipStream_t)hip_stream);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  return BURST_OK;
 }
 
 int burst_attn_lse_merge(const burst_shape_t* shape, const burst_tensor_t* o_acc, const burst_rowvec_t* lse_acc,
@@ -299,54 +436,56 @@ int burst_attn_step_bwd(const burst_shape_t* shape, const burst_mask_t* mask, co
                         const burst_rowvec_t* lse, const burst_rowvec_t* d, const burst_tensor_t* dq,
                         const burst_tensor_t* dk, const burst_tensor_t* dv, int32_t accumulate_flags,
                         void* hip_stream) {
-  BURST_TRY(check_shape(shape));
   BwdParams p;
-  std::memset(&p, 0, sizeof(p));
-  BURST_TRY(check_mask(mask, shape->sq, shape->sk, &p.mask));
-  BURST_TRY(check_tensor(q, 1, &p.q));
-  BURST_TRY(check_tensor(k, 1, &p.k));
-  BURST_TRY(check_tensor(v, 1, &p.v));
-  BURST_TRY(check_tensor(d_o, 1, &p.d_o));
-  BURST_TRY(check_rowvec(lse, &p.lse));
-  BURST_TRY(check_rowvec(d, &p.d));
-  if (!dq && !dk && !dv) return BURST_ERR_INVALID_ARG;
-  if ((dk == nullptr) != (dv == nullptr)) return BURST_ERR_INVALID_ARG;
-  if (accumulate_flags & ~(BURST_ACC_DQ | BURST_ACC_DK | BURST_ACC_DV)) return BURST_ERR_INVALID_ARG;
-  if (dq) {
-    BURST_TRY(check_tensor(dq, 2, &p.dq));
-    BURST_TRY(check_no_overlap(p.dq, shape->batch, shape->sq, shape->q_heads, shape->head_dim));
-  }
-  if (dk) {
-    BURST_TRY(check_tensor(dk, 2, &p.dk));
-    BURST_TRY(check_no_overlap(p.dk, shape->batch, shape->sk, shape->kv_heads, shape->head_dim));
-  }
-  if (dv) {
-    BURST_TRY(check_tensor(dv, 2, &p.dv));
-    BURST_TRY(check_no_overlap(p.dv, shape->batch, shape->sk, shape->kv_heads, shape->head_dim));
-  }
-  p.acc_dq = (accumulate_flags & BURST_ACC_DQ) != 0;
-  p.acc_dk = (accumulate_flags & BURST_ACC_DK) != 0;
-  p.acc_dv = (accumulate_flags & BURST_ACC_DV) != 0;
-  p.batch = shape->batch;
-  p.q_heads = shape->q_heads;
-  p.kv_heads = shape->kv_heads;
-  p.head_dim = shape->head_dim;
-  p.sq = (int32_t)shape->sq;
-  p.sk = (int32_t)shape->sk;
-  p.scale = shape->scale;
-  hipStream_t stream = (hipStream_t)hip_stream;
-  hipError_t e = hipSuccess;
-  if (p.sq == 0 || p.sk == 0) {
-    // nothing contributes: "+=" leaves the gradients alone, "=" makes them zero
-    if (dq && !p.acc_dq && p.sq > 0) e = launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
-    if (e == hipSuccess && dk && !p.acc_dk && p.sk > 0)
-      e = launch_zero_tensor(p.dk, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
-    if (e == hipSuccess && dv && !p.acc_dv && p.sk > 0)
-      e = launch_zero_tensor(p.dv, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
-  } else {
-    e = launch_step_bwd(p, stream);
-  }
+  BwdStep st;
+  BURST_TRY(check_bwd_step(shape, mask, k, v, dk, dv, &st));
+  BURST_TRY(check_bwd(shape, q, d_o, lse, d, dq, dk != nullptr, accumulate_flags, &p));
+  const hipError_t e = run_bwd(p, &st, 1, (hipStream_t)hip_stream);
   return e == hipSuccess ? BURST_OK : hip_fail(e);
+}
+
+int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks, const burst_tensor_t* q,
+                         const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* d_o, const burst_rowvec_t* lse,
+                         const burst_rowvec_t* d, const burst_tensor_t* dq, const burst_tensor_t* dk, const burst_tensor_t* dv,
+                         int32_t accumulate_flags, void* hip_stream) {
+  if (n_steps < 0 || (n_steps > 0 && (!shapes || !masks || !k || !v))) return BURST_ERR_INVALID_ARG;
+  if (n_steps > BURST_MAX_STEPS) return BURST_ERR_UNSUPPORTED;
+  std::vector<BwdParams> p(n_steps);
+  std::vector<BwdStep> st(n_steps);
+  for (int i = 0; i < n_steps; ++i) {
+    BURST_TRY(check_bwd_step(&shapes[i], &masks[i], &k[i], &v[i], dk ? &dk[i] : nullptr, dv ? &dv[i] : nullptr, &st[i]));
+    BURST_TRY(check_bwd(&shapes[i], q, d_o, lse, d, dq, dk != nullptr, accumulate_flags, &p[i]));
+  }
+  for (int i = 0, end; i < n_steps; i = end) {
+    for (end = i + 1; end < n_steps && same_queries(p[i], st[i], p[end], st[end]);) ++end;
+    if (i > 0) p[i].acc_dq = 1;
+    // What a step writes must be nothing that another one reads or writes
+    bool apart = true;
+    for (int x = i; x < end && apart; ++x)
+      for (int y = i; y < end && apart; ++y) {
+        if (x == y) continue;
+        const Span writes[3] = {span_of(st[x].dk, p[i].batch, st[x].sk, p[i].kv_heads, p[i].head_dim),
+                                span_of(st[x].dv, p[i].batch, st[x].sk, p[i].kv_heads, p[i].head_dim),
+                                span_of(p[i].dq, p[i].batch, p[i].sq, p[i].q_heads, p[i].head_dim)};
+        const Span others[4] = {span_of(st[y].dk, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
+                                span_of(st[y].dv, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
+                                span_of(st[y].k, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
+                                span_of(st[y].v, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim)};
+        for (const Span& w : writes)
+          for (const Span& o : others) apart = apart && !overlap(w, o);
+      }
+    hipError_t e = hipSuccess;
+    if (apart) {
+      e = run_bwd(p[i], &st[i], end - i, (hipStream_t)hip_stream);
+    } else {
+      for (int j = i; j < end && e == hipSuccess; ++j) {
+        e = run_bwd(p[i], &st[j], 1, (hipStream_t)hip_stream);
+        p[i].acc_dq = 1;
+      }
+    }
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  return BURST_OK;
 }
 
 static int fill_common(int32_t dev_i, int32_t shard_j, int32_t G, int64_t N, burst_mask_t* out) {

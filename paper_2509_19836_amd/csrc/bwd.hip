@@ -31,7 +31,7 @@ constexpr int kDqWaves = 8, kDqBQ = 32 * kDqWaves;   // query rows per work-grou
 __device__ __forceinline__ float lse_to_log2(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int NW, bool BLK, int AHEAD>   // BLK: with a block-wise sparse mask
+template <int D, int NW, bool BLK, bool MULTI, int AHEAD>   // BLK: with a block-wise sparse mask; MULTI: more than one step
 __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int block) {   // smem: [SLOTS][K tile, V tile], open flags
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
   constexpr int TILE = BK * 2 * D, SLOTS = 4;
@@ -43,19 +43,19 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: everything derived from it stays wave-uniform
-  const int sq = p.sq, sk = p.sk;
-  const MaskDev mk = p.mask;
+  const int sq = p.sq, n_steps = MULTI ? p.n_steps : 1;
+  const MaskDev q_side = p.step[0].mask;   // all steps have the same
   const int q_blk0 = p.q_runs.tile_of(bm.tile) * BQ, q_blk1 = min(q_blk0 + BQ, sq);
   const int q_w0 = q_blk0 + wave * 32, q_w1 = min(q_w0 + 32, sq);
 
   // Q and dO as B operands: lane holds rows q_w0 + 16 nb + r, columns 32 ks + 8g .. +7
   bf16x8 qreg[DK][NB], doreg[DK][NB];
-  int klo[NB], khi[NB];   // key rows that the lane's query rows see
+  int q_pos[NB], klo[NB], khi[NB];   // positions of the lane's query rows, the key rows they see of a step
   float lse2[NB], dval[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int row = min(q_w0 + 16 * nb + r, sq - 1);
-    visible_rows<true>(mk, axis_position(axis_of<true>(mk), row), sk, klo[nb], khi[nb]);
+    q_pos[nb] = axis_position(axis_of<true>(q_side), row);
     const __bf16* qs = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * g;
     const __bf16* gs = (const __bf16*)p.d_o.ptr + b * p.d_o.sb + hq * p.d_o.sh + (int64_t)row * p.d_o.ss + 8 * g;
 #pragma unroll
@@ -74,26 +74,23 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) dq[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Key tiles the work-group can see, and the class of each against this wave's 32 query rows
+  // Positions of the work-group's and the wave's query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
-  range_minmax<true>(mk, q_blk0, q_blk1, qlo_blk, qhi_blk);
-  if (q_w0 < q_w1) range_minmax<true>(mk, q_w0, q_w1, qlo_w, qhi_w);
-  TileRanges tiles;
-  tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
+  range_minmax<true>(q_side, q_blk0, q_blk1, qlo_blk, qhi_blk);
+  if (q_w0 < q_w1) range_minmax<true>(q_side, q_w0, q_w1, qlo_w, qhi_w);
 
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
   if (BLK) {
     open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE);
-    fill_open_flags<true, BK>(mk, open_flags, q_blk0, sk, tid, NT);
+    fill_open_flags<true, BK>(q_side, open_flags, q_blk0, p.step[0].sk, tid, NT);
     __syncthreads();
   }
   OperandAddr<D> ad;
   ad.init(lane);
-  KvStream<D, BK, NW, BLK, false> walk;
-  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
-  wait_global_loads();
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+  TileRanges tiles;   // class of a step's key tiles against this wave's 32 query rows
+  bool windowed;
+  uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
 
   // The two waves of a SIMD take a tile's matrix phase and its vector phase in turn, as in the forward kernel:
   // waves 4-7 run one barrier behind waves 0-3.  Iteration t, tile t in slot t mod 4:
@@ -107,110 +104,152 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
   constexpr int LOADS = KvStream<D, BK, NW, BLK, false>::LOADS, NL = KvStream<D, BK, NW, BLK, false>::N;
-  f32x4 s[MB][NB], dp[MB][NB];
-  bf16x8 ds[MB / 2][NB];
-  // dS of the tile at key row k0_, of which the wave sees something, from its scores and dP
-  auto d_scores = [&](int k0_) {
-    if (!tiles.full(k0_)) {
+  // The steps one after the other; dQ stays in registers
+#pragma clang loop unroll(disable)
+  for (int step = 0; step < n_steps; ++step) {
+    const BwdStep& st = p.step[MULTI ? step : 0];
+    const MaskDev mk = st.mask;
+    const int sk = st.sk;
+    windowed = mk.window != kNoWindow;
 #pragma unroll
-      for (int half = 0; half < MB / 2; ++half)
-        mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
-    }
+    for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
+    tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
+    KvStream<D, BK, NW, BLK, false> walk;
+    walk.init(mk, st.k, st.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
+    wait_global_loads();
+    if (step > 0) __syncthreads();   // the later half may still read the last tile of the step before
+    pin(lds0);   // (LDS addresses worked out once for all steps would cost the registers)
+    bf16x8 ds[MB / 2][NB];
+    // dS of the tile at key row k0_, of which the wave sees something, for the query rows nb: from their scores and dP
+    auto d_scores = [&](int k0_, int nb, auto&& score, auto&& d_p) {   // score(mb), d_p(mb): f32x4
+      if (!tiles.full(k0_)) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+        for (int half = 0; half < MB / 2; ++half)
+          mask_rows32(score(2 * half), score(2 * half + 1), k0_ + 32 * half, g, klo[nb], khi[nb], windowed);
+      }
 #pragma unroll
       for (int ch = 0; ch < MB / 2; ++ch) {
-        f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+        f32x4 &x = score(2 * ch), &y = score(2 * ch + 1);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (dp[2 * ch][nb][v] - dval[nb]);
-          y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (dp[2 * ch + 1][nb][v] - dval[nb]);
+          x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (d_p(2 * ch)[v] - dval[nb]);
+          y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (d_p(2 * ch + 1)[v] - dval[nb]);
         }
         ds[ch][nb] = pack_pair(x, y);
       }
-  };
-  if (walk.valid()) {
-    int kb = walk.k0;   // iteration t: kb, kc are the first rows of tiles t+1, t+2
-    walk.issue(k_lds(0), v_lds(0), wave, lane);
-    int kc = walk.cursor();
-    walk.issue(k_lds(1), v_lds(1), wave, lane);
-    int kn = walk.cursor();
-    walk.issue(k_lds(2), v_lds(2), wave, lane);
-    wait_loads_barrier<2 * LOADS>();              // tile 0
-    if (wave >= NW / 2) phase_barrier();
-    int slot = 3;
-    bool live;
-    bf16x8 first[AHEAD];
-    for (;;) {   // iterations -1 .., up to the wave's first tile
-      const int slot1 = (slot + 1) & 3;
-      live = tiles.some(kb);
-      if (live) {
-        rows_fetch<D, MB, AHEAD>(k_lds(slot1), ad, 0, first);
-        rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first);
-      }
-      wait_loads_barrier<LOADS>();                // tile t+2
-      slot = slot1;
-      if (live) {
-        d_scores(kb);
-        cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
-      }
-      phase_barrier();
-      kb = kc;
-      kc = kn;
-      if (live || kb < 0) break;
-      kn = walk.cursor();
-      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
-    }
-    if (live) {
-      uint32_t kt = k_lds(slot), k1 = k_lds((slot + 1) & 3), v1 = v_lds((slot + 1) & 3);   // slot t mod 4 and the next
-      uint32_t kl = k_lds((slot + 3) & 3), vl = v_lds((slot + 3) & 3);
-      kn = walk.cursor();
-      walk.begin(wave, lane);
-      for (;;) {
-        // ---- matrix phase; everything else that an iteration computes stands behind its MFMAs or in the vector phase
-        bf16x8 first_rows[AHEAD];
-        constexpr int NCOLS = MB / 2 * DB;
-        cols_product<D, MB / 2, NB, AHEAD>(kt, ad, 0, ds, dq, first, [&](int i) {
-          if (i < NL) walk.load_v(i, vl, wave);
-          if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
-          if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
-          if (i >= NCOLS - AHEAD) {
-            const int f = i - (NCOLS - AHEAD);
-            first_rows[f] = rows_operand<D>(k1, ad, 16 * (f % MB), f / MB);
+    };
+    if (walk.valid()) {
+      int kb = walk.k0;   // iteration t: kb, kc are the first rows of tiles t+1, t+2
+      walk.issue(k_lds(0), v_lds(0), wave, lane);
+      int kc = walk.cursor();
+      walk.issue(k_lds(1), v_lds(1), wave, lane);
+      int kn = walk.cursor();
+      walk.issue(k_lds(2), v_lds(2), wave, lane);
+      wait_loads_barrier<2 * LOADS>();              // tile 0
+      if (wave >= NW / 2) phase_barrier();
+      int slot = 3;
+      bool live;
+      bf16x8 first[AHEAD];
+      // The first tile of several steps at d = 128: dQ of the steps before, both products of 32 query rows and their operands do
+      // not fit the registers, so the rows go 16 after the other, each through its vector work (elsewhere that would be one
+      // vector phase more before the later half's first products, 0.5 us of a step)
+      constexpr bool WHOLE = !(MULTI && D == 128);
+      any_value(ds);
+      any_value(first);
+      for (;;) {   // iterations -1 .., up to the wave's first tile
+        const int slot1 = (slot + 1) & 3;
+        live = tiles.some(kb);
+        f32x4 s[MB][NB], dp[MB][NB];
+        auto scores = [&]() {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            d_scores(kb, nb, [&](int mb) -> f32x4& { return s[mb][nb]; }, [&](int mb) -> f32x4& { return dp[mb][nb]; });
+        };
+        if (live && WHOLE) {
+          rows_fetch<D, MB, AHEAD>(k_lds(slot1), ad, 0, first);
+          rows_product_pair<D, MB, NB, AHEAD>(k_lds(slot1), v_lds(slot1), ad, qreg, doreg, s, dp, first);
+        } else if (live) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            f32x4 s1[MB][1], dp1[MB][1];
+            bf16x8 q1[DK][1], do1[DK][1], ahead[2];
+#pragma unroll
+            for (int ks = 0; ks < DK; ++ks) {
+              q1[ks][0] = qreg[ks][nb];
+              do1[ks][0] = doreg[ks][nb];
+            }
+            rows_fetch<D, MB, 2>(k_lds(slot1), ad, 0, ahead);
+            rows_product_pair<D, MB, 1, 2>(k_lds(slot1), v_lds(slot1), ad, q1, do1, s1, dp1, ahead);
+            d_scores(kb, nb, [&](int mb) -> f32x4& { return s1[mb][0]; }, [&](int mb) -> f32x4& { return dp1[mb][0]; });
           }
-        });
-        if (tiles.behind(kb)) break;
-        rows_product_pair<D, MB, NB, AHEAD>(k1, v1, ad, qreg, doreg, s, dp, first_rows);
-        wait_loads_barrier<LOADS>();              // tile t+2
-        // ---- vector phase
-        const int tile_k0 = kb;
+        }
+        wait_loads_barrier<LOADS>();                // tile t+2
+        slot = slot1;
+        if (live) {
+          if (WHOLE) scores();
+          cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+        }
+        phase_barrier();
+        kb = kc;
+        kc = kn;
+        if (live || kb < 0) break;
+        kn = walk.cursor();
+        walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
+      }
+      if (live) {
+        uint32_t kt = k_lds(slot), k1 = k_lds((slot + 1) & 3), v1 = v_lds((slot + 1) & 3);   // slot t mod 4 and the next
+        uint32_t kl = k_lds((slot + 3) & 3), vl = v_lds((slot + 3) & 3);
+        kn = walk.cursor();
+        walk.begin(wave, lane);
+        for (;;) {
+          // ---- matrix phase; everything else that an iteration computes stands behind its MFMAs or in the vector phase
+          f32x4 s[MB][NB], dp[MB][NB];
+          bf16x8 first_rows[AHEAD];
+          constexpr int NCOLS = MB / 2 * DB;
+          cols_product<D, MB / 2, NB, AHEAD>(kt, ad, 0, ds, dq, first, [&](int i) {
+            if (i < NL) walk.load_v(i, vl, wave);
+            if (i >= NL && i < 2 * NL) walk.load_k(i - NL, kl, wave);
+            if (i >= 2 * NL && i < 2 * NL + walk.PARTS) walk.end(i - 2 * NL);
+            if (i >= NCOLS - AHEAD) {
+              const int f = i - (NCOLS - AHEAD);
+              first_rows[f] = rows_operand<D>(k1, ad, 16 * (f % MB), f / MB);
+            }
+          });
+          if (tiles.behind(kb)) break;
+          rows_product_pair<D, MB, NB, AHEAD>(k1, v1, ad, qreg, doreg, s, dp, first_rows);
+          wait_loads_barrier<LOADS>();              // tile t+2
+          // ---- vector phase
+          const int tile_k0 = kb;
+          slot = (slot + 1) & 3;
+          vl = kt + TILE;   // (the slot before)
+          kl = kt;
+          kt = k1;
+          k1 = k_lds((slot + 1) & 3);
+          v1 = k1 + TILE;
+          kb = kc;
+          kc = kn;
+          kn = walk.cursor();
+          walk.begin(wave, lane);
+          pin(slot, kt, k1, v1, kl, vl, kb, kc, kn);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            d_scores(tile_k0, nb, [&](int mb) -> f32x4& { return s[mb][nb]; }, [&](int mb) -> f32x4& { return dp[mb][nb]; });
+          cols_fetch<D, AHEAD>(kt, ad, 0, first);
+          phase_barrier();
+        }
+      }
+      while (kb >= 0) {   // the rest of the walk is the other waves'
+        wait_loads_barrier<LOADS>();
         slot = (slot + 1) & 3;
-        vl = kt + TILE;   // (the slot before)
-        kl = kt;
-        kt = k1;
-        k1 = k_lds((slot + 1) & 3);
-        v1 = k1 + TILE;
+        phase_barrier();
         kb = kc;
         kc = kn;
         kn = walk.cursor();
-        walk.begin(wave, lane);
-        pin(slot, kt, k1, v1, kl, vl, kb, kc, kn);
-        d_scores(tile_k0);
-        cols_fetch<D, AHEAD>(kt, ad, 0, first);
-        phase_barrier();
+        walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
       }
+      wait_global_loads();   // tiles past the end of the walk
+      if (wave < NW / 2) phase_barrier();
     }
-    while (kb >= 0) {   // the rest of the walk is the other waves'
-      wait_loads_barrier<LOADS>();
-      slot = (slot + 1) & 3;
-      phase_barrier();
-      kb = kc;
-      kc = kn;
-      kn = walk.cursor();
-      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
-    }
-    wait_global_loads();   // tiles past the end of the walk
-    if (wave < NW / 2) phase_barrier();
   }
 
 #pragma unroll
@@ -268,15 +307,15 @@ struct DkdvLds {
 // with too few key tiles to fill the CUs: two pairs share 32 key rows, each runs through 32 of the 64 query rows (the
 // same operand reads per MFMA, half the MFMAs per phase), and the second one's sums are added through LDS at the end.
 template <int D, int ROLE, bool BLK, int BKV>
-__device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b, int hk, int kv_tile, int wave) {
+__device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st, char* smem, int b, int hk, int kv_tile, int wave) {
   constexpr int BQ = 64, QS = 128 / BKV, ROWS = BQ / QS, MB = ROWS / 16, NB = 2, DK = D / 32, DB = D / 16, NW = 8, AHEAD = kAhead16;
   using L = DkdvLds<D>;
 
   const int group = p.q_heads / p.kv_heads;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4, pair = wave & 3;
-  const int sq = p.sq, sk = p.sk;
-  const MaskDev mk = p.mask;
-  const int k_blk0 = p.k_runs.tile_of(kv_tile) * BKV, k_blk1 = min(k_blk0 + BKV, sk);
+  const int sq = p.sq, sk = st.sk;
+  const MaskDev mk = st.mask;
+  const int k_blk0 = st.k_runs.tile_of(kv_tile) * BKV, k_blk1 = min(k_blk0 + BKV, sk);
   const int k_w0 = k_blk0 + (QS == 1 ? pair : pair & 1) * 32, k_w1 = min(k_w0 + 32, sk);
   const int row0 = QS == 1 ? 0 : (pair >> 1) * ROWS;   // first row of the wave's part of a query tile
   const float c = p.scale * kLog2e;
@@ -288,7 +327,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   for (int nb = 0; nb < NB; ++nb) {
     const int row = min(k_w0 + 16 * nb + r, sk - 1);
     if (ROLE == 0) visible_rows<false>(mk, axis_position(axis_of<false>(mk), row), sq, qlo[nb], qhi[nb]);
-    const TensorDev& src = ROLE == 0 ? p.k : p.v;
+    const TensorDev& src = ROLE == 0 ? st.k : st.v;
     const __bf16* x = (const __bf16*)src.ptr + b * src.sb + hk * src.sh + (int64_t)row * src.ss + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) {
@@ -359,7 +398,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
       if (some && !tiles.full(q0_)) {
 #pragma unroll
         for (int half = 0; half < MB / 2; ++half)
-          mask_rows32<NB>(s[2 * half], s[2 * half + 1], q0_ + 32 * half, g, qlo, qhi, true);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) mask_rows32(s[2 * half][nb], s[2 * half + 1][nb], q0_ + 32 * half, g, qlo[nb], qhi[nb], true);
       }
       if (some) {
 #pragma unroll
@@ -495,7 +535,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   for (int nb = 0; nb < NB; ++nb) {
     const int row = k_w0 + 16 * nb + r;
     if (row >= sk) continue;
-    const TensorDev& dst = ROLE == 0 ? p.dv : p.dk;
+    const TensorDev& dst = ROLE == 0 ? st.dv : st.dk;
     const float mul = ROLE == 0 ? 1.f : -p.scale;   // (dS carried the other sign)
     float* out = (float*)dst.ptr + b * dst.sb + (int64_t)row * dst.ss + hk * dst.sh + 4 * g;
     f32x4 old[DB];
@@ -510,42 +550,55 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, char* smem, int b,
   }
 }
 
-template <int D, bool BLK, int BKV>
+template <int D, bool BLK, bool MULTI, int BKV>
 __device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int block) {   // smem: laid out by DkdvLds, then the open flags
-  const BlockMap bm = map_block<false>(block, p.batch * p.kv_heads, 1, p.k_runs.total(), p.k_side_by_side);
+  int step = 0;   // the steps' work-groups one after the other
+  while (MULTI && step + 1 < p.n_steps && block >= p.step[step + 1].first_block) ++step;
+  const BwdStep& st = p.step[MULTI ? step : 0];
+  const BlockMap bm = map_block<false>(block - st.first_block, p.batch * p.kv_heads, 1, st.k_runs.total(), st.k_side_by_side);
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 4) dkdv_role<D, 0, BLK, BKV>(p, smem, b, hk, bm.tile, wave);
-  else dkdv_role<D, 1, BLK, BKV>(p, smem, b, hk, bm.tile, wave);
+  if (wave < 4) dkdv_role<D, 0, BLK, BKV>(p, st, smem, b, hk, bm.tile, wave);
+  else dkdv_role<D, 1, BLK, BKV>(p, st, smem, b, hk, bm.tile, wave);
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int NW, bool BLK>
+// A kernel argument indexed with a variable would be copied to scratch memory: several steps are read through the argument
+// pointer, a single one (MULTI false) directly, all at once at the start.
+__device__ __forceinline__ const BwdParams& launch_args() {
+  typedef const __attribute__((address_space(4))) BwdParams* args_ptr;
+  return *(const BwdParams*)(args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+template <int D, int NW, bool BLK, bool MULTI>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  dq_block<D, NW, BLK, BLK ? 3 : kAhead16>(p, smem, blockIdx.x);   // (the block flags take the registers of one operand)
+  constexpr int AHEAD = BLK ? 3 : kAhead16;   // (the block flags take the registers of one operand)
+  if constexpr (MULTI) dq_block<D, NW, BLK, true, AHEAD>(launch_args(), smem, blockIdx.x);
+  else dq_block<D, NW, BLK, false, AHEAD>(p, smem, blockIdx.x);
 }
-template <int D, bool BLK, int BKV>
+template <int D, bool BLK, bool MULTI, int BKV>
 __global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  dkdv_block<D, BLK, BKV>(p, smem, blockIdx.x);
+  if constexpr (MULTI) dkdv_block<D, BLK, true, BKV>(launch_args(), smem, blockIdx.x);
+  else dkdv_block<D, BLK, false, BKV>(p, smem, blockIdx.x);
 }
-// Both in one launch (they share nothing but inputs): work-groups 0 .. n_dkdv - 1 (a multiple of 8, as the mapping to
-// XCDs needs) are the dK/dV kernel's, whose walks are the longer ones, the others the dQ kernel's.
-template <int D, int BKV>
-__global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams p, int n_dkdv) {
+// Both in one launch (they share nothing but inputs): the first n_first work-groups (a multiple of 8, as the mapping to
+// XCDs needs) are those of the kernel whose walks are the longer ones.
+template <int D, bool MULTI, int BKV>
+__global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams, int n_first, int dq_first) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // each side reads its own arguments: loaded for both at the start they would not fit the scalar registers
   typedef const __attribute__((address_space(4))) BwdParams* args_ptr;
   args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-  if ((int)blockIdx.x < n_dkdv) {
+  const int in_first = (int)blockIdx.x < n_first, block = blockIdx.x - (in_first ? 0 : n_first);
+  if (in_first != dq_first) {
     asm volatile("" : "+s"(args));
-    dkdv_block<D, false, BKV>(*(const BwdParams*)args, smem, blockIdx.x);
+    dkdv_block<D, false, MULTI, BKV>(*(const BwdParams*)args, smem, block);
   } else {
     asm volatile("" : "+s"(args));
     static_assert(kDqWaves * 64 == 512, "both kernels' work-groups have the same size");
-    dq_block<D, kDqWaves, false, 3>(*(const BwdParams*)args, smem, blockIdx.x - n_dkdv);
+    dq_block<D, kDqWaves, false, MULTI, 3>(*(const BwdParams*)args, smem, block);
   }
 }
 
@@ -554,35 +607,61 @@ __global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams p, int 
 // are uneven, as the mask makes them, and the longest one decides.  One step, full mask, tiles of 128: 64 of them 61 us
 // against 45 with tiles of 64, 128 (16/2 heads, 8192 rows) 1556 against 1125, but 160 258 against 332, 256 68 against
 // 82.  Own shard, causal: 160 252 against 169, 256 63 against 53, 288 87 against 81, 384 48 against 54.
-static bool narrow_key_tiles(const MaskDev& mk, int sq, int sk, int n_keys, const TileRuns& runs128) {
-  const int n = n_keys * runs128.total();
-  if (mk.blk || n == 0 || n > 256) return false;
-  return n <= 128 || uneven_walks<false>(mk, sq, sk, runs128, 128);
+static bool narrow_key_tiles(const BwdParams& p) {
+  int n = 0;
+  bool uneven = false;
+  for (int i = 0; i < p.n_steps; ++i) {
+    const BwdStep& st = p.step[i];
+    n += p.batch * p.kv_heads * st.k_runs.total();
+    uneven |= uneven_k_walks(st.mask, p.sq, st.sk, st.k_runs, 128);
+  }
+  if (p.step[0].mask.blk || n == 0 || n > 256) return false;
+  return n <= 128 || uneven;
 }
 
 // The work-groups of a kernel: the tiles that see something, and zeros into what gets no work-group under "=".
 static hipError_t plan_dq(BwdParams& p, hipStream_t stream) {
-  p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, kDqBQ, true);
-  p.q_side_by_side = side_by_side<true>(p.mask, p.sq, p.sk, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, kDqBQ);
+  p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, kDqBQ);
+  p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, kDqBQ);
   if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ)
     return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
   return hipSuccess;
 }
 static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
-  p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 128, false);
-  narrow = narrow_key_tiles(p.mask, p.sq, p.sk, p.batch * p.kv_heads, p.k_runs);
-  if (narrow) p.k_runs = nonempty_runs(p.mask, p.sq, p.sk, 64, false);
+  const int n_keys = p.batch * p.kv_heads;
+  for (int i = 0; i < p.n_steps; ++i) p.step[i].k_runs = nonempty_k_runs(p.step[i].mask, p.sq, p.step[i].sk, 128);
+  narrow = narrow_key_tiles(p);
   const int tile = narrow ? 64 : 128;
-  p.k_side_by_side = side_by_side<false>(p.mask, p.sq, p.sk, p.batch * p.kv_heads, 1, p.k_runs, tile);
-  hipError_t e = hipSuccess;
-  if (p.k_runs.total() < (p.sk + tile - 1) / tile) {
-    if (!p.acc_dk) e = launch_zero_tensor(p.dk, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
-    if (e == hipSuccess && !p.acc_dv) e = launch_zero_tensor(p.dv, p.batch, p.sk, p.kv_heads, p.head_dim, stream);
+  for (int i = 0; i < p.n_steps; ++i) {
+    BwdStep& st = p.step[i];
+    if (narrow) st.k_runs = nonempty_k_runs(st.mask, p.sq, st.sk, 64);
+    st.k_side_by_side = k_side_by_side(st.mask, p.sq, st.sk, n_keys, st.k_runs, tile);
+    if (st.k_runs.total() < (st.sk + tile - 1) / tile) {
+      hipError_t e = hipSuccess;
+      if (!p.acc_dk) e = launch_zero_tensor(st.dk, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+      if (e == hipSuccess && !p.acc_dv) e = launch_zero_tensor(st.dv, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+      if (e != hipSuccess) return e;
+    }
   }
-  return e;
+  // heaviest first among the steps, too
+  if (p.n_steps > 1) {
+    auto longest = [&](const BwdStep& st) {
+      return st.k_runs.total() ? k_tile_walk(st.mask, p.sq, st.sk, st.k_runs.tile_of(0), tile) : 0;
+    };
+    std::stable_sort(p.step, p.step + p.n_steps, [&](const BwdStep& x, const BwdStep& y) { return longest(x) > longest(y); });
+  }
+  int block = 0;
+  for (int i = 0; i < p.n_steps; ++i) {
+    p.step[i].first_block = block;
+    block += mapped_grid(n_keys, 1, p.step[i].k_runs.total());
+  }
+  return hipSuccess;
 }
 static int dq_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total()); }
-static int dkdv_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, 1, p.k_runs.total()); }
+static int dkdv_grid(const BwdParams& p) {
+  const BwdStep& last = p.step[p.n_steps - 1];
+  return last.first_block + mapped_grid(p.batch * p.kv_heads, 1, last.k_runs.total());
+}
 
 template <int D>
 constexpr int kDqLds = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
@@ -590,25 +669,30 @@ template <int D>
 constexpr int kDkdvLds = DkdvLds<D>::BYTES + kMaxBlockCacheTiles;
 
 template <int D>
-static hipError_t launch_dq_t(BwdParams p, hipStream_t stream) {
+static hipError_t launch_dq_t(BwdParams& p, hipStream_t stream) {
   const hipError_t e = plan_dq(p, stream);
   const int grid = dq_grid(p);
   if (e != hipSuccess || grid == 0) return e;
-  if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, true>), dim3(grid), dim3(64 * kDqWaves), kDqLds<D>, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false>), dim3(grid), dim3(64 * kDqWaves), kDqLds<D>, stream, p);
+  constexpr int NT = 64 * kDqWaves;
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, true, false>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
+  else if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false, true>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false, false>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
+static hipError_t launch_dkdv_t(BwdParams& p, hipStream_t stream) {
   static_assert(kDkdvLds<D> <= 160 * 1024, "LDS of a CU");
   bool narrow = false;
   const hipError_t e = plan_dkdv(p, narrow, stream);
   const int grid = dkdv_grid(p);
   if (e != hipSuccess || grid == 0) return e;
-  if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else if (p.mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  const bool multi = p.n_steps > 1;
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else if (narrow && multi) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, true, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, false, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else if (multi) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, true, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
   return hipGetLastError();
 }
 
@@ -616,69 +700,114 @@ static hipError_t launch_dkdv_t(BwdParams p, hipStream_t stream) {
 // second one's work-groups then fill the CUs that the last round of the first leaves idle, and there is one start
 // less.  One step, d = 128, two launches against one: 6 work-groups 33 -> 21 us, 4 heads x 2048 rows (96) 115 -> 78,
 // 12 heads x 3000 (432) 262 -> 189, 48 x 1500 (864) 260 -> 217, causal 16 x 6000 (1136) 479 -> 446; alike from 32 x 4096
-// (1536) on, 772 and 770, causal 422 and 428.
+// (1536) on, 772 and 770, causal 422 and 428.  Several steps, twice as many: they go from longer to shorter walks, which a
+// part-empty round costs more.  Apart, dK/dV's first, dQ's first: 3 steps of 48 x 1500 rows, d = 64 (2016) 365, 334, 295 us;
+// 8 of 16/2 heads x 8192 (1344), whose key tiles walk 8 heads, 5861, 5771, 5947; 4 of 32 x 4096 (3584) 1591, 1583, 1636.
 constexpr int kBothLaunch = 1280;
 
-// One launch for a short step; `done` says whether it was taken.
+// One launch of both kernels; `done` says whether it was taken.
 template <int D>
-static hipError_t launch_both_t(BwdParams p, bool& done, hipStream_t stream) {
+static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  const int64_t most = (int64_t)n_keys * group * ((p.sq + kDqBQ - 1) / kDqBQ) + (int64_t)n_keys * ((p.sk + 127) / 128);
-  done = !p.mask.blk && p.sq <= chunk_rows() && p.sk <= chunk_rows() && most <= kBothLaunch;
+  int64_t most = (int64_t)n_keys * group * ((p.sq + kDqBQ - 1) / kDqBQ);
+  for (int i = 0; i < p.n_steps; ++i) most += (int64_t)n_keys * ((p.step[i].sk + 127) / 128);
+  done = most <= (p.n_steps > 1 ? 2 : 1) * kBothLaunch;
   if (!done) return hipSuccess;
   bool narrow = false;
   hipError_t e = plan_dq(p, stream);
   if (e == hipSuccess) e = plan_dkdv(p, narrow, stream);
-  const int n_dkdv = dkdv_grid(p), grid = n_dkdv + dq_grid(p);
+  const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
   if (e != hipSuccess || grid == 0) return e;
   constexpr int LDS = kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>;
-  if (narrow) hipLaunchKernelGGL((step_bwd_both_kernel<D, 64>), dim3(grid), dim3(512), LDS, stream, p, n_dkdv);
-  else hipLaunchKernelGGL((step_bwd_both_kernel<D, 128>), dim3(grid), dim3(512), LDS, stream, p, n_dkdv);
+  // a dQ work-group walks every step (three products a tile against two), a dK/dV one the heads of its group
+    const int dq_first = p.n_steps > 1 && 3 * p.n_steps > 4 * group, n_first = dq_first ? n_dq : n_dkdv;
+  const bool multi = p.n_steps > 1;
+  if (narrow && multi) hipLaunchKernelGGL((step_bwd_both_kernel<D, true, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
+  else if (narrow) hipLaunchKernelGGL((step_bwd_both_kernel<D, false, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
+  else if (multi) hipLaunchKernelGGL((step_bwd_both_kernel<D, true, 128>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
+  else hipLaunchKernelGGL((step_bwd_both_kernel<D, false, 128>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_bwd_t(const BwdParams& p0, hipStream_t stream) {
+static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, int n, hipStream_t stream) {
+  BwdParams p = p0;
+  const bool dkdv = steps[0].dk.ptr != nullptr;
   hipError_t e = hipSuccess;
-  if (p0.dq.ptr && p0.dk.ptr) {
+  std::vector<BwdStep> whole;   // the steps of which some query row sees something
+  for (int i = 0; i < n; ++i) {
+    const BwdStep& st = steps[i];
+    if (classify(st.mask, 0, p.sq, 0, st.sk, false) != TILE_SKIP) {
+      whole.push_back(st);
+      continue;
+    }
+    if (dkdv && !p.acc_dk) e = launch_zero_tensor(st.dk, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+    if (e == hipSuccess && dkdv && !p.acc_dv) e = launch_zero_tensor(st.dv, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
+    if (e != hipSuccess) return e;
+  }
+  n = (int)whole.size();
+  if (n == 0) return p.dq.ptr && !p.acc_dq ? launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream) : hipSuccess;
+  bool together = p.dq.ptr && dkdv && p.sq <= chunk_rows();
+  for (const BwdStep& st : whole) together = together && !st.mask.blk && st.sk <= chunk_rows();
+  auto put = [&](const std::vector<BwdStep>& from, int first, int end) {
+    p.n_steps = end - first;
+    std::copy(from.begin() + first, from.begin() + end, p.step);
+  };
+  if (together && n <= kMaxSteps) {
     bool done = false;
-    e = launch_both_t<D>(p0, done, stream);
+    put(whole, 0, n);
+    e = launch_both_t<D>(p, done, stream);
     if (done) return e;
   }
   if (p0.dq.ptr) {   // the dQ kernel streams the key axis
-    const std::vector<RowRange> ranges = chunk_ranges(p0.mask.k_nseg, p0.mask.k_seg_len, p0.sk, p0.mask.blk ? p0.mask.blk_k : 0);
-    bool first = true;
-    for (const RowRange& rg : ranges) {
-      BwdParams p = p0;
-      if (ranges.size() > 1) {
-        p.mask = sub_mask<false>(p0.mask, rg.r0, rg.r1);
-        p.sk = rg.r1 - rg.r0;
-        offset_rows(p.k, rg.r0);
-        offset_rows(p.v, rg.r0);
-        if (!first) p.acc_dq = 1;
+    std::vector<BwdStep> parts;
+    for (const BwdStep& step : whole) {
+      const MaskDev& mk = step.mask;
+      const std::vector<RowRange> ranges = chunk_ranges(mk.k_nseg, mk.k_seg_len, step.sk, mk.blk ? mk.blk_k : 0);
+      for (const RowRange& rg : ranges) {
+        BwdStep st = step;
+        if (ranges.size() > 1) {
+          st.mask = sub_mask<false>(mk, rg.r0, rg.r1);
+          st.sk = rg.r1 - rg.r0;
+          offset_rows(st.k, rg.r0);
+          offset_rows(st.v, rg.r0);
+        }
+        parts.push_back(st);
       }
-      e = launch_dq_t<D>(p, stream);
-      if (e != hipSuccess) return e;
-      first = false;
     }
+    bool any = false;
+    e = for_step_groups(parts, p.sq, p.batch * p.q_heads, [&](int first, int end) {
+      put(parts, first, end);
+      const hipError_t err = launch_dq_t<D>(p, stream);
+      p.acc_dq = 1;
+      any = true;
+      return err;
+    });
+    if (e == hipSuccess && !any && !p0.acc_dq) e = launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
+    if (e != hipSuccess) return e;
   }
-  if (p0.dk.ptr) {   // the dK/dV kernel streams the query axis
-    const std::vector<RowRange> ranges = chunk_ranges(p0.mask.q_nseg, p0.mask.q_seg_len, p0.sq, p0.mask.blk ? p0.mask.blk_q : 0);
-    bool first = true;
+  if (dkdv) {   // the dK/dV kernel streams the query axis
+    const MaskDev mk = whole[0].mask;   // all steps have the same query side
+    const std::vector<RowRange> ranges = chunk_ranges(mk.q_nseg, mk.q_seg_len, p0.sq, mk.blk ? mk.blk_q : 0);
     for (const RowRange& rg : ranges) {
-      BwdParams p = p0;
+      p = p0;
+      std::vector<BwdStep> parts = whole;
       if (ranges.size() > 1) {
-        p.mask = sub_mask<true>(p0.mask, rg.r0, rg.r1);
+        for (BwdStep& st : parts) st.mask = sub_mask<true>(st.mask, rg.r0, rg.r1);
         p.sq = rg.r1 - rg.r0;
         offset_rows(p.q, rg.r0);
         offset_rows(p.d_o, rg.r0);
         p.lse.ptr += rg.r0;
         p.d.ptr += rg.r0;
-        if (!first) p.acc_dk = p.acc_dv = 1;
+        if (&rg != &ranges.front()) p.acc_dk = p.acc_dv = 1;
       }
-      e = launch_dkdv_t<D>(p, stream);
-      if (e != hipSuccess) return e;
-      first = false;
+      auto share = [&](const BwdStep& st) { return !st.mask.blk && share_launch(p.batch * p.kv_heads, st.sk); };
+      for (int first = 0, end; first < n; first = end) {
+        for (end = first + 1; end < n && end - first < kMaxSteps && share(parts[first]) && share(parts[end]);) ++end;
+        put(parts, first, end);
+        e = launch_dkdv_t<D>(p, stream);
+        if (e != hipSuccess) return e;
+      }
     }
   }
   return hipSuccess;
@@ -705,9 +834,9 @@ int chunk_plan(const MaskDev& mk, int sq, int sk, bool query_axis, int max_range
   return (int)ranges.size();
 }
 
-hipError_t launch_step_bwd(const BwdParams& p, hipStream_t stream) {
-  if (p.head_dim == 128) return launch_bwd_t<128>(p, stream);
-  return launch_bwd_t<64>(p, stream);
+hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream) {
+  if (p.head_dim == 128) return launch_bwd_groups<128>(p, steps, n, stream);
+  return launch_bwd_groups<64>(p, steps, n, stream);
 }
 
 }  // namespace burst

@@ -25,12 +25,17 @@ namespace burst {
 
 constexpr int kFwdWaves = 8, kFwdBQ = 32 * kFwdWaves;   // query rows per work-group: 32 per wave
 
-template <int D, int NW, bool BLK>   // BLK: with a block-wise sparse mask
+// BLK: with a block-wise sparse mask; MULTI: more than one step.  (Kernel arguments lie in host memory: what a single step needs
+// is asked for at once at the start, where steps picked by a variable are a second round trip, 1-2 us of a launch.)
+template <int D, int NW, bool BLK, bool MULTI>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdParams p) {
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
   constexpr int TILE = BK * 2 * D, SLOTS = 4, AHEAD = kAhead16;
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
 
+  // (a kernel argument indexed with a variable would be copied to scratch memory: read through the argument pointer)
+  typedef const __attribute__((address_space(4))) FwdParams* args_ptr;
+  const FwdParams& args = *(const FwdParams*)(args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   const int group = p.q_heads / p.kv_heads;
   const BlockMap bm = map_block<true>(blockIdx.x, p.batch * p.kv_heads, group, p.q_runs.total(), p.q_side_by_side);
   if (!bm.valid) return;
@@ -38,8 +43,9 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
 
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: everything derived from it stays wave-uniform
-  const int sq = p.sq, sk = p.sk;
-  const MaskDev mk = p.mask;
+  const int sq = p.sq;
+  const int n_steps = MULTI ? p.n_steps : 1;
+  const MaskDev q_side = p.step[0].mask;   // all steps have the same
   const int q_blk0 = p.q_runs.tile_of(bm.tile) * BQ;     // first row of the work-group
   const int q_blk1 = min(q_blk0 + BQ, sq);
   const int q_w0 = q_blk0 + wave * 32;                   // first row of the wave
@@ -47,11 +53,11 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
 
   // Q as the B operand of S^T = K Q^T: lane holds rows q_w0 + 16 nb + r, columns 32 ks + 8g .. +7
   bf16x8 qreg[DK][NB];
-  int klo[NB], khi[NB];   // key rows that the lane's query rows see
+  int q_pos[NB], klo[NB], khi[NB];   // positions of the lane's query rows, the key rows they see of a step
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int row = min(q_w0 + 16 * nb + r, sq - 1);
-    visible_rows<true>(mk, axis_position(axis_of<true>(mk), row), sk, klo[nb], khi[nb]);
+    q_pos[nb] = axis_position(axis_of<true>(q_side), row);
     const __bf16* src = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) qreg[ks][nb] = *reinterpret_cast<const bf16x8*>(src + ks * 32);
@@ -67,26 +73,23 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   float m_run[NB] = {-INFINITY, -INFINITY}, limit[NB] = {-INFINITY, -INFINITY}, msub[NB] = {0.f, 0.f};
   f32x4 l_run[NB] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // four independent chains
 
-  // Key tiles the work-group can see, and the class of each against this wave's 32 query rows
+  // Positions of the work-group's and the wave's query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
-  range_minmax<true>(mk, q_blk0, q_blk1, qlo_blk, qhi_blk);
-  if (q_w0 < q_w1) range_minmax<true>(mk, q_w0, q_w1, qlo_w, qhi_w);
-  TileRanges tiles;
-  tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
+  range_minmax<true>(q_side, q_blk0, q_blk1, qlo_blk, qhi_blk);
+  if (q_w0 < q_w1) range_minmax<true>(q_side, q_w0, q_w1, qlo_w, qhi_w);
 
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
   if (BLK) {
     open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE);
-    fill_open_flags<true, BK>(mk, open_flags, q_blk0, sk, tid, NT);
+    fill_open_flags<true, BK>(q_side, open_flags, q_blk0, p.step[0].sk, tid, NT);
     __syncthreads();
   }
   OperandAddr<D> ad;
   ad.init(lane);
-  KvStream<D, BK, NW, BLK, true> walk;
-  walk.init(mk, p.k, p.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
-  wait_global_loads();
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+  TileRanges tiles;   // class of a step's key tiles against this wave's 32 query rows
+  bool windowed;
+  uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
 
   // A wave's work on a tile is a matrix phase and a vector phase of about the same length, and the two waves of
   // a SIMD take them in turn: while waves 0-3 run iteration t's products, waves 4-7 (one barrier behind) run
@@ -110,140 +113,160 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
   constexpr int LOADS = KvStream<D, BK, NW, BLK, true>::LOADS, NL = KvStream<D, BK, NW, BLK, true>::N;
-  f32x4 s[MB][NB];
-  bf16x8 pp[MB / 2][NB];
-  // P of the tile at key row k0_, of which the wave sees something, from its scores
-  auto softmax = [&](int k0_) {
-    if (!tiles.full(k0_)) {
+  // The steps one after the other; the state stays in registers
+#pragma clang loop unroll(disable)
+  for (int step = 0; step < n_steps; ++step) {
+    const FwdStep& st = MULTI ? args.step[step] : p.step[0];
+    const MaskDev mk = st.mask;
+    const int sk = st.sk;
+    windowed = mk.window != kNoWindow;
 #pragma unroll
-      for (int half = 0; half < MB / 2; ++half)
-        mask_rows32<NB>(s[2 * half], s[2 * half + 1], k0_ + 32 * half, g, klo, khi, mk.window != kNoWindow);
-    }
-    // Largest score among this lane's keys of the tile (a query row's keys are spread over four lanes).
-    // Rescale lazily: keep a stale maximum while no row of the wave has grown by more than
-    // 2^kLazyLog2 (any common per-row offset gives the same result; fp32 has the headroom).  A row has
-    // grown exactly if one of its four lanes has, and the vote runs over the whole wave, so the lanes
-    // of a row exchange their maxima only when a rescale happens: the steady state has no cross-lane
-    // traffic (the exchange goes through LDS and costs a round trip the wave cannot fill).
-    float mx[NB];
-    bool grow = false;
+    for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
+    tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
+    KvStream<D, BK, NW, BLK, true> walk;
+    walk.init(mk, st.k, st.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
+    wait_global_loads();
+    if (step > 0) __syncthreads();   // the later half may still read the last tiles of the step before
+    pin(lds0);   // (LDS addresses worked out once for all steps would cost the registers)
+    f32x4 s[MB][NB];
+    bf16x8 pp[MB / 2][NB];
+    // P of the tile at key row k0_, of which the wave sees something, from its scores
+    auto softmax = [&](int k0_) {
+      if (!tiles.full(k0_)) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      float m5[5];   // eight v_max3_f32 for sixteen scores (fifteen with fmaxf: 1795 and 1769 us at 16384 rows, 32 heads, d = 128)
+        for (int half = 0; half < MB / 2; ++half)
 #pragma unroll
-      for (int i = 0; i < 5; ++i)
-        m5[i] = max3(s[3 * i / 4][nb][3 * i % 4], s[(3 * i + 1) / 4][nb][(3 * i + 1) % 4], s[(3 * i + 2) / 4][nb][(3 * i + 2) % 4]);
-      mx[nb] = max3(max3(m5[0], m5[1], m5[2]), max3(m5[3], m5[4], s[3][nb][3]), -INFINITY);
-      grow |= mx[nb] > limit[nb];
-    }
-    if (__any(grow)) {
+          for (int nb = 0; nb < NB; ++nb) mask_rows32(s[2 * half][nb], s[2 * half + 1][nb], k0_ + 32 * half, g, klo[nb], khi[nb], windowed);
+      }
+      // Largest score among this lane's keys of the tile (a query row's keys are spread over four lanes).
+      // Rescale lazily: keep a stale maximum while no row of the wave has grown by more than
+      // 2^kLazyLog2 (any common per-row offset gives the same result; fp32 has the headroom).  A row has
+      // grown exactly if one of its four lanes has, and the vote runs over the whole wave, so the lanes
+      // of a row exchange their maxima only when a rescale happens: the steady state has no cross-lane
+      // traffic (the exchange goes through LDS and costs a round trip the wave cannot fill).
+      float mx[NB];
+      bool grow = false;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        float m_new = fmaxf(mx[nb], __shfl_xor(mx[nb], 16, 64));
-        m_new = fmaxf(m_run[nb], fmaxf(m_new, __shfl_xor(m_new, 32, 64)));
-        const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run[nb] - m_new));
-        m_run[nb] = m_new;
-        limit[nb] = m_new + slack;
-        msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
-        l_run[nb] *= alpha;
+        float m5[5];   // eight v_max3_f32 for sixteen scores (fifteen with fmaxf: 1795 and 1769 us at 16384 rows, 32 heads, d = 128)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) o[db][nb][v] *= alpha;
+        for (int i = 0; i < 5; ++i)
+          m5[i] = max3(s[3 * i / 4][nb][3 * i % 4], s[(3 * i + 1) / 4][nb][(3 * i + 1) % 4], s[(3 * i + 2) / 4][nb][(3 * i + 2) % 4]);
+        mx[nb] = max3(max3(m5[0], m5[1], m5[2]), max3(m5[3], m5[4], s[3][nb][3]), -INFINITY);
+        grow |= mx[nb] > limit[nb];
       }
-    }
-    // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
-    // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
-    // exponential, few enough to keep the intermediate values out of the register budget.  The fence keeps the
-    // groups apart: with the 32 exponentials in a row the d = 64 kernel is 2-3 % slower (12 heads x 12000 rows 665, 636 us).
+      if (__any(grow)) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb) {
+          float m_new = fmaxf(mx[nb], __shfl_xor(mx[nb], 16, 64));
+          m_new = fmaxf(m_run[nb], fmaxf(m_new, __shfl_xor(m_new, 32, 64)));
+          const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run[nb] - m_new));
+          m_run[nb] = m_new;
+          limit[nb] = m_new + slack;
+          msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
+          l_run[nb] *= alpha;
 #pragma unroll
-      for (int ch = 0; ch < MB / 2; ++ch) {
-        f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+          for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          x[v] = __builtin_amdgcn_exp2f(c * x[v] - msub[nb]);
-          y[v] = __builtin_amdgcn_exp2f(c * y[v] - msub[nb]);
+            for (int v = 0; v < 4; ++v) o[db][nb][v] *= alpha;
         }
-        l_run[nb] += x + y;
-        pp[ch][nb] = pack_pair(x, y);
-        __builtin_amdgcn_sched_barrier(0);
       }
-  };
-  if (walk.valid()) {
-    int kb = walk.k0;   // iteration t: kb, kc, kd are the first rows of tiles t+1, t+2, t+3
-    walk.issue(k_lds(3), v_lds(3), wave, lane);   // set -1
-    int kc = walk.cursor();
-    walk.issue(k_lds(0), v_lds(0), wave, lane);   // set 0
-    int kd = walk.cursor();
-    walk.issue(k_lds(1), v_lds(1), wave, lane);   // set 1
-    int kn = walk.cursor();
-    walk.issue(k_lds(2), v_lds(2), wave, lane);   // set 2
-    wait_loads_barrier<3 * LOADS>();              // set -1
-    if (wave >= NW / 2) wait_loads_barrier<2 * LOADS>();   // set 0: the first half's first vector phase reads its K
-    int slot = 3;
-    bool live;
-    bf16x8 first[AHEAD];
-    for (;;) {   // iterations -1 .., up to the wave's first tile
-      live = tiles.some(kb);
-      if (live) {
-        const f32x4 zero[MB] = {};
-        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
-        rows_product<D, MB, NB, AHEAD>(k_lds(slot), ad, 0, qreg, s, zero, first);
-      }
-      wait_loads_barrier<2 * LOADS>();            // set 0 (later ones have been waited for)
-      slot = (slot + 1) & 3;
-      if (live) {
-        mfma_results();   // (in the loop below the products of P stand between)
-        softmax(kb);
-        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
-      }
-      wait_loads_barrier<LOADS>();
-      kb = kc;
-      kc = kd;
-      kd = kn;
-      if (live || kb < 0) break;
-      kn = walk.cursor();
-      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
-    }
-    if (live) {
-      for (;;) {
-        const uint32_t kt = k_lds(slot), vt = v_lds(slot);
-        // ---- matrix phase
-        kn = walk.cursor();
-        walk.begin(wave, lane);
-        const int slot3 = (slot + 3) & 3;
-        const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
-        rows_cols_stream<D, MB, NB, AHEAD>(kt, vt, ad, qreg, s, pp, o, first, [&](int i) {
-          if (i >= 1 && i < 1 + NL) walk.load_v(i - 1, vl, wave);
-          if (i >= 1 + NL && i < 1 + 2 * NL) walk.load_k(i - 1 - NL, kl, wave);
-          if (i >= 1 + 2 * NL && i < 1 + 2 * NL + walk.PARTS) walk.end(i - 1 - 2 * NL);
-        });
-        if (tiles.behind(kb)) break;
-        phase_barrier();
-        // ---- vector phase
-        softmax(kb);
+      // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
+      // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
+      // exponential, few enough to keep the intermediate values out of the register budget.  The fence keeps the
+      // groups apart: with the 32 exponentials in a row the d = 64 kernel is 2-3 % slower (12 heads x 12000 rows 665, 636 us).
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int ch = 0; ch < MB / 2; ++ch) {
+          f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            x[v] = __builtin_amdgcn_exp2f(c * x[v] - msub[nb]);
+            y[v] = __builtin_amdgcn_exp2f(c * y[v] - msub[nb]);
+          }
+          l_run[nb] += x + y;
+          pp[ch][nb] = pack_pair(x, y);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (walk.valid()) {
+      int kb = walk.k0;   // iteration t: kb, kc, kd are the first rows of tiles t+1, t+2, t+3
+      walk.issue(k_lds(3), v_lds(3), wave, lane);   // set -1
+      int kc = walk.cursor();
+      walk.issue(k_lds(0), v_lds(0), wave, lane);   // set 0
+      int kd = walk.cursor();
+      walk.issue(k_lds(1), v_lds(1), wave, lane);   // set 1
+      int kn = walk.cursor();
+      walk.issue(k_lds(2), v_lds(2), wave, lane);   // set 2
+      wait_loads_barrier<3 * LOADS>();              // set -1
+      if (wave >= NW / 2) wait_loads_barrier<2 * LOADS>();   // set 0: the first half's first vector phase reads its K
+      int slot = 3;
+      bool live;
+      bf16x8 first[AHEAD];
+      any_value(s);
+      any_value(pp);
+      any_value(first);
+      for (;;) {   // iterations -1 .., up to the wave's first tile
+        live = tiles.some(kb);
+        if (live) {
+          const f32x4 zero[MB] = {};
+          rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+          rows_product<D, MB, NB, AHEAD>(k_lds(slot), ad, 0, qreg, s, zero, first);
+        }
+        wait_loads_barrier<2 * LOADS>();            // set 0 (later ones have been waited for)
         slot = (slot + 1) & 3;
-        rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+        if (live) {
+          mfma_results();   // (in the loop below the products of P stand between)
+          softmax(kb);
+          rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+        }
         wait_loads_barrier<LOADS>();
         kb = kc;
         kc = kd;
         kd = kn;
+        if (live || kb < 0) break;
+        kn = walk.cursor();
+        walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
       }
+      if (live) {
+        for (;;) {
+          const uint32_t kt = k_lds(slot), vt = v_lds(slot);
+          // ---- matrix phase
+          kn = walk.cursor();
+          walk.begin(wave, lane);
+          const int slot3 = (slot + 3) & 3;
+          const uint32_t kl = k_lds(slot3), vl = v_lds(slot3);
+          rows_cols_stream<D, MB, NB, AHEAD>(kt, vt, ad, qreg, s, pp, o, first, [&](int i) {
+            if (i >= 1 && i < 1 + NL) walk.load_v(i - 1, vl, wave);
+            if (i >= 1 + NL && i < 1 + 2 * NL) walk.load_k(i - 1 - NL, kl, wave);
+            if (i >= 1 + 2 * NL && i < 1 + 2 * NL + walk.PARTS) walk.end(i - 1 - 2 * NL);
+          });
+          if (tiles.behind(kb)) break;
+          phase_barrier();
+          // ---- vector phase
+          softmax(kb);
+          slot = (slot + 1) & 3;
+          rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+          wait_loads_barrier<LOADS>();
+          kb = kc;
+          kc = kd;
+          kd = kn;
+        }
+      }
+      while (kb >= 0) {   // the rest of the walk is the other waves'
+        phase_barrier();
+        slot = (slot + 1) & 3;
+        wait_loads_barrier<LOADS>();
+        kb = kc;
+        kc = kd;
+        kd = kn;
+        kn = walk.cursor();
+        walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
+      }
+      wait_global_loads();   // sets past the end of the walk
+      if (wave < NW / 2) phase_barrier();
     }
-    while (kb >= 0) {   // the rest of the walk is the other waves'
-      phase_barrier();
-      slot = (slot + 1) & 3;
-      wait_loads_barrier<LOADS>();
-      kb = kc;
-      kc = kd;
-      kd = kn;
-      kn = walk.cursor();
-      walk.issue(k_lds((slot + 3) & 3), v_lds((slot + 3) & 3), wave, lane);
-    }
-    wait_global_loads();   // sets past the end of the walk
-    if (wave < NW / 2) phase_barrier();
   }
 
   // Epilogue: normalise, Lse in natural-log units, optional online-softmax merge.
@@ -254,7 +277,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     l_tot += __shfl_xor(l_tot, 32, 64);
     const int orow = q_w0 + 16 * nb + r;
     if (orow >= sq) continue;
-    const bool alive = l_tot > 0.f;
+    const bool alive = l_tot != 0.f;   // (zero: no key seen; NaN is seen)
     const float inv = alive ? 1.f / l_tot : 0.f;
     const float lse_cur = alive ? (c * m_run[nb] + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
     if (p.o_part.ptr) {
@@ -326,10 +349,10 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p) {
 }
 
 template <int D>
-static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
+static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
   constexpr int BQ = kFwdBQ;
   constexpr int LDS = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
-  p.q_runs = nonempty_runs(p.mask, p.sq, p.sk, BQ, true);
+  p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {
     const int64_t total = (int64_t)p.batch * p.sq * p.q_heads * (p.head_dim / 4);
@@ -340,37 +363,51 @@ static hipError_t launch_fwd_t(FwdParams p, hipStream_t stream) {
   }
   if (p.q_runs.total() == 0) return hipSuccess;
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  p.q_side_by_side = side_by_side<true>(p.mask, p.sq, p.sk, n_keys, group, p.q_runs, BQ);
+  p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, n_keys, group, p.q_runs, BQ);
   const int grid = mapped_grid(n_keys, group, p.q_runs.total());
-  if (p.mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, true>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
-  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false>), dim3(grid), dim3(64 * kFwdWaves), LDS, stream, p);
+  constexpr int NT = 64 * kFwdWaves;
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, true, false>), dim3(grid), dim3(NT), LDS, stream, p);
+  else if (p.n_steps > 1) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false, true>), dim3(grid), dim3(NT), LDS, stream, p);
+  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false, false>), dim3(grid), dim3(NT), LDS, stream, p);
   return hipGetLastError();
 }
 
-// With the fused merge and no separate step result, a key axis longer than two ranges is cut into ranges, one
-// launch per range, each folding its part into the running (O, Lse): the same online-softmax merge the ring
-// applies from step to step, so the result is the step's up to rounding.  The step result itself (o_part,
-// lse_part) cannot be cut this way and is always one launch.
+// With the fused merge and no separate step result, a key axis longer than two ranges is cut into ranges, each walked as
+// a step of its own: the same online-softmax merge the ring applies from step to step, so the result is the step's up to
+// rounding.  The step result itself (o_part, lse_part) cannot be cut this way and is always one launch.
 template <int D>
-static hipError_t launch_fwd_chunked(const FwdParams& p0, hipStream_t stream) {
-  if (!p0.o_acc.ptr || p0.o_part.ptr) return launch_fwd_t<D>(p0, stream);
-  const std::vector<RowRange> ranges = chunk_ranges(p0.mask.k_nseg, p0.mask.k_seg_len, p0.sk, p0.mask.blk ? p0.mask.blk_k : 0);
-  if (ranges.size() == 1) return launch_fwd_t<D>(p0, stream);
-  for (const RowRange& rg : ranges) {
-    FwdParams p = p0;
-    p.mask = sub_mask<false>(p0.mask, rg.r0, rg.r1);
-    p.sk = rg.r1 - rg.r0;
-    offset_rows(p.k, rg.r0);
-    offset_rows(p.v, rg.r0);
-    hipError_t e = launch_fwd_t<D>(p, stream);
-    if (e != hipSuccess) return e;
+static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, int n, hipStream_t stream) {
+  FwdParams p = p0;
+  if (!p.o_acc.ptr || p.o_part.ptr) {
+    p.n_steps = 1;
+    p.step[0] = steps[0];
+    return launch_fwd_t<D>(p, stream);
   }
-  return hipSuccess;
+  std::vector<FwdStep> parts;
+  for (int i = 0; i < n; ++i) {
+    const MaskDev& mk = steps[i].mask;
+    const std::vector<RowRange> ranges = chunk_ranges(mk.k_nseg, mk.k_seg_len, steps[i].sk, mk.blk ? mk.blk_k : 0);
+    for (const RowRange& rg : ranges) {
+      FwdStep st = steps[i];
+      if (ranges.size() > 1) {
+        st.mask = sub_mask<false>(mk, rg.r0, rg.r1);
+        st.sk = rg.r1 - rg.r0;
+        offset_rows(st.k, rg.r0);
+        offset_rows(st.v, rg.r0);
+      }
+      parts.push_back(st);
+    }
+  }
+  return for_step_groups(parts, p.sq, p.batch * p.q_heads, [&](int first, int end) {
+    p.n_steps = end - first;
+    std::copy(parts.begin() + first, parts.begin() + end, p.step);
+    return launch_fwd_t<D>(p, stream);
+  });
 }
 
-hipError_t launch_step_fwd(const FwdParams& p, hipStream_t stream) {
-  if (p.head_dim == 128) return launch_fwd_chunked<128>(p, stream);
-  return launch_fwd_chunked<64>(p, stream);
+hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream) {
+  if (p.head_dim == 128) return launch_fwd_groups<128>(p, steps, n, stream);
+  return launch_fwd_groups<64>(p, steps, n, stream);
 }
 
 }  // namespace burst

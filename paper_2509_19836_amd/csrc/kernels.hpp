@@ -1,5 +1,6 @@
 // Kernel parameter blocks and host-side launchers shared between the C-ABI layer and the kernels.
 #pragma once
+#include <algorithm>
 #include <vector>
 
 #include "common.hpp"
@@ -15,31 +16,49 @@ constexpr float kLazyLog2 = 6.0f;
 #endif
 constexpr int kAhead16 = BURST_A16;
 
+// What a launch walks: the key/value chunks of up to kMaxSteps ring steps of one query chunk, one after the other (a step
+// whose key axis is cut into ranges is one for each).  All have the same query side; only a single one may have a
+// block mask.
+constexpr int kMaxSteps = 8;
+struct FwdStep {
+  MaskDev mask;
+  int32_t sk;
+  TensorDev k, v;
+};
+
 struct FwdParams {
   int32_t batch, q_heads, kv_heads, head_dim;
-  int32_t sq, sk;
+  int32_t sq, n_steps;
   float scale;
-  MaskDev mask;
   TileRuns q_runs;      // query tiles with work, and the order of the work-groups (filled by the launcher)
   int32_t q_side_by_side;
-  TensorDev q, k, v;
+  TensorDev q;
   TensorDev o_part;     // ptr == nullptr: not requested
   RowvecDev lse_part;
   TensorDev o_acc;      // ptr == nullptr: no fused merge
   RowvecDev lse_acc;
+  FwdStep step[kMaxSteps];
+};
+
+struct BwdStep {
+  MaskDev mask;
+  int32_t sk;
+  TensorDev k, v, dk, dv;   // dk, dv: fp32; ptr == nullptr: skip
+  TileRuns k_runs;          // key tiles with work, the order of the work-groups and the first of them (filled by the launcher)
+  int32_t k_side_by_side, first_block;
 };
 
 struct BwdParams {
   int32_t batch, q_heads, kv_heads, head_dim;
-  int32_t sq, sk;
+  int32_t sq, n_steps;
   float scale;
-  MaskDev mask;
-  TileRuns q_runs, k_runs;   // query / key tiles with work, and the order of the work-groups (filled by the launcher)
-  int32_t q_side_by_side, k_side_by_side;
-  TensorDev q, k, v, d_o;
+  TileRuns q_runs;          // query tiles with work, and the order of the work-groups (filled by the launcher)
+  int32_t q_side_by_side;
+  TensorDev q, d_o;
   RowvecDev lse, d;
-  TensorDev dq, dk, dv;   // fp32; ptr == nullptr: skip
+  TensorDev dq;             // fp32; ptr == nullptr: skip
   int32_t acc_dq, acc_dk, acc_dv;
+  BwdStep step[kMaxSteps];
 };
 
 struct MergeParams {
@@ -54,18 +73,14 @@ struct PreParams {
   RowvecDev d;
 };
 
-// Runs of non-empty tiles along the query axis (each tile against the whole key chunk) or along
-// the key axis (each tile against the whole query chunk); the same classification the kernels use.
-inline TileRuns nonempty_runs(const MaskDev& mk, int sq, int sk, int tile_rows, bool q_axis) {
-  const int rows = q_axis ? sq : sk;
-  const int n = (rows + tile_rows - 1) / tile_rows;
+// Runs of tiles, of `n`, for which nonempty(tile) holds.
+template <class Nonempty>
+inline TileRuns tile_runs(int n, Nonempty&& nonempty) {
   TileRuns tr{{0, 0}, {0, 0}};
   int nruns = 0;
   bool in_run = false;
   for (int t = 0; t < n; ++t) {
-    const int r0 = t * tile_rows, r1 = r0 + tile_rows < rows ? r0 + tile_rows : rows;
-    const int cls = q_axis ? classify(mk, r0, r1, 0, sk, false) : classify(mk, 0, sq, r0, r1, false);
-    if (cls == TILE_SKIP) {
+    if (!nonempty(t)) {
       in_run = false;
       continue;
     }
@@ -78,24 +93,60 @@ inline TileRuns nonempty_runs(const MaskDev& mk, int sq, int sk, int tile_rows, 
   }
   return tr;
 }
+// Query tiles that see something of any of the steps' key chunks; key tiles of which the query chunk sees something.  The
+// same classification the kernels use.
+template <class Step>
+inline TileRuns nonempty_q_runs(const Step* steps, int n_steps, int sq, int tile_rows) {
+  return tile_runs((sq + tile_rows - 1) / tile_rows, [&](int t) {
+    const int r0 = t * tile_rows, r1 = r0 + tile_rows < sq ? r0 + tile_rows : sq;
+    for (int i = 0; i < n_steps; ++i)
+      if (classify(steps[i].mask, r0, r1, 0, steps[i].sk, false) != TILE_SKIP) return true;
+    return false;
+  });
+}
+inline TileRuns nonempty_k_runs(const MaskDev& mk, int sq, int sk, int tile_rows) {
+  return tile_runs((sk + tile_rows - 1) / tile_rows, [&](int t) {
+    const int r0 = t * tile_rows, r1 = r0 + tile_rows < sk ? r0 + tile_rows : sk;
+    return classify(mk, 0, sq, r0, r1, false) != TILE_SKIP;
+  });
+}
 
-// Whether the walk of the tile that is launched last is at most half as long as that of the first one (heaviest first:
-// map_block), in tiles of 64 rows of the other axis.
-template <bool Q_AXIS>
-inline bool uneven_walks(const MaskDev& mk, int sq, int sk, const TileRuns& runs, int tile_rows) {
-  auto walk = [&](int tile) {
-    const int rows = Q_AXIS ? sq : sk, end = tile * tile_rows + tile_rows;
-    int lo, hi;
-    range_minmax<Q_AXIS>(mk, tile * tile_rows, end < rows ? end : rows, lo, hi);
-    return visible_tiles<!Q_AXIS, 64>(mk, lo, hi, Q_AXIS ? sk : sq).len;
-  };
+// Walk of the tile that is launched first (heaviest first: map_block) or last, in tiles of 64 rows of the other axis.
+inline int q_tile_walk(const MaskDev& mk, int sq, int sk, int tile, int tile_rows) {
+  const int end = tile * tile_rows + tile_rows;
+  int lo, hi;
+  range_minmax<true>(mk, tile * tile_rows, end < sq ? end : sq, lo, hi);
+  return visible_tiles<false, 64>(mk, lo, hi, sk).len;
+}
+inline int k_tile_walk(const MaskDev& mk, int sq, int sk, int tile, int tile_rows) {
+  const int end = tile * tile_rows + tile_rows;
+  int lo, hi;
+  range_minmax<false>(mk, tile * tile_rows, end < sk ? end : sk, lo, hi);
+  return visible_tiles<true, 64>(mk, lo, hi, sq).len;
+}
+// Whether the walk of the tile that is launched last is at most half as long as that of the first one.
+template <class Step>
+inline bool uneven_q_walks(const Step* steps, int n_steps, int sq, const TileRuns& runs, int tile_rows) {
   const int n = runs.total();
-  return n > 0 && 2 * walk(runs.tile_of(Q_AXIS ? 0 : n - 1)) <= walk(runs.tile_of(Q_AXIS ? n - 1 : 0));
+  int first = 0, last = 0;
+  for (int i = 0; i < n_steps && n > 0; ++i) {
+    first += q_tile_walk(steps[i].mask, sq, steps[i].sk, runs.tile_of(n - 1), tile_rows);
+    last += q_tile_walk(steps[i].mask, sq, steps[i].sk, runs.tile_of(0), tile_rows);
+  }
+  return n > 0 && 2 * last <= first;
+}
+inline bool uneven_k_walks(const MaskDev& mk, int sq, int sk, const TileRuns& runs, int tile_rows) {
+  const int n = runs.total();
+  return n > 0 && 2 * k_tile_walk(mk, sq, sk, runs.tile_of(n - 1), tile_rows) <= k_tile_walk(mk, sq, sk, runs.tile_of(0), tile_rows);
 }
 // Whether a launch runs the keys of an XCD (of two or more) side by side (map_block).  A block mask makes any walks uneven.
-template <bool Q_AXIS>
-inline bool side_by_side(const MaskDev& mk, int sq, int sk, int n_keys, int group, const TileRuns& runs, int tile_rows) {
-  return n_keys >= 16 && short_launch(n_keys, group, runs.total()) && (mk.blk || uneven_walks<Q_AXIS>(mk, sq, sk, runs, tile_rows));
+template <class Step>
+inline bool q_side_by_side(const Step* steps, int n_steps, int sq, int n_keys, int group, const TileRuns& runs, int tile_rows) {
+  return n_keys >= 16 && short_launch(n_keys, group, runs.total()) &&
+         (steps[0].mask.blk || uneven_q_walks(steps, n_steps, sq, runs, tile_rows));
+}
+inline bool k_side_by_side(const MaskDev& mk, int sq, int sk, int n_keys, const TileRuns& runs, int tile_rows) {
+  return n_keys >= 16 && short_launch(n_keys, 1, runs.total()) && (mk.blk || uneven_k_walks(mk, sq, sk, runs, tile_rows));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -161,6 +212,38 @@ inline MaskDev sub_mask(const MaskDev& mk, int r0, int r1) {
 }
 inline void offset_rows(TensorDev& t, int r0) { t.ptr = (char*)t.ptr + (int64_t)r0 * t.ss * (t.is_f32 ? 4 : 2); }
 
+// Steps that one launch walks.  Consecutive steps of a ring whose shards are all there share a launch (they have the same
+// query side): a query tile keeps its state in registers from shard to shard, and there is one last, part-empty round of
+// work-groups instead of one for each.  A ring, d = 128, us step by step and shared: 8 shards of 8192 rows, 16/2 heads:
+// forward 1826, 1706, dQ 2500, 2357, dK/dV 5446, 3657; 4 shards of 4096 rows, 32 heads: dQ 696, 613, dK/dV 1003, 961; 4
+// of 1500 rows, 48 heads, d = 64: forward 181, 160, dQ 195, 176, dK/dV 238, 193; 4 of 8192 rows, 32 heads: 1891, 1823, 2542, 2427,
+// 3621, 3579.  Beyond kShareLaunch tiles of 256 rows a step (4 per CU; key tiles of 128 rows are twice as many) there is
+// nothing to gain: 8 shards of 16384 rows, 32 heads, zigzag: forward 13753, 13778, dQ 18904, 18828, dK/dV 26695, 27106,
+// striped: 14816, 15190, 20535, 20615, 29172, 29317.
+// A step with a block mask goes alone, and a launch's walk is bounded by what stays in step in an L2, two ranges.  Steps of
+// which no query row sees anything are left out.  launch(first, end): steps [first, end) of `parts`.
+constexpr int kShareLaunch = 1024;
+inline bool share_launch(int heads, int rows) { return (int64_t)heads * ((rows + 255) / 256) <= kShareLaunch; }
+template <class Step, class Launch>
+inline hipError_t for_step_groups(std::vector<Step>& parts, int sq, int heads, Launch&& launch) {
+  parts.erase(std::remove_if(parts.begin(), parts.end(),
+                             [&](const Step& st) { return classify(st.mask, 0, sq, 0, st.sk, false) == TILE_SKIP; }), parts.end());
+  const int n = (int)parts.size();
+  const bool share = share_launch(heads, sq);
+  for (int first = 0, end = 0; first < n; first = end) {
+    int64_t rows = 0;
+    for (; end < n; ++end) {
+      if (end > first && (!share || parts[end].mask.blk || parts[first].mask.blk || end - first == kMaxSteps ||
+                          rows + parts[end].sk > 2ll * chunk_rows()))
+        break;
+      rows += parts[end].sk;
+    }
+    const hipError_t e = launch(first, end);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Fused LM head + cross-entropy (Alg. 3).  Sizes are validated on the host; the workspace is carved up there.
 struct LmHeadParams {
   int32_t n_tokens, d_model, vocab, tile_tokens;
@@ -186,8 +269,9 @@ struct LmHeadParams {
 int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_model);
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream);
 
-hipError_t launch_step_fwd(const FwdParams& p, hipStream_t stream);
-hipError_t launch_step_bwd(const BwdParams& p, hipStream_t stream);
+// n steps of the query chunk that `p` describes (its own step array is not read).  More than one only without o_part.
+hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream);
+hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream);
 // rows of the streamed axis per launch of a step kernel (longer axes are cut into several launches)
 void set_chunk_rows(int rows);
 int chunk_plan(const MaskDev& mk, int sq, int sk, bool query_axis, int max_ranges, int64_t* out);

@@ -135,6 +135,19 @@ __device__ __forceinline__ void pin(T& x, Rest&... rest) {
   pin(rest...);
 }
 
+// Any value.  Registers that a walk fills before it reads them, on paths the compiler cannot tell, are otherwise carried
+// around the loop over the steps as values it might need (a hundred of them in the dQ kernel, which then spilled).
+template <class T, int M, int N>
+__device__ __forceinline__ void any_value(T (&x)[M][N]) {
+#pragma unroll
+  for (int i = 0; i < M * N; ++i) asm volatile("" : "=v"(x[i / N][i % N]));
+}
+template <class T, int N>
+__device__ __forceinline__ void any_value(T (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "=v"(x[i]));
+}
+
 // All ones where x is negative, else zero: scalar arithmetic in place of conditions, minima and maxima, whose results the
 // compiler keeps in vector registers.
 __device__ __forceinline__ int negative_mask(int x) {
@@ -508,30 +521,25 @@ __device__ __forceinline__ void rows_cols_stream(uint32_t kt, uint32_t vt, const
   }
 }
 
-// Per-element mask of two accumulator tiles, rows base_row .. base_row + 31 (wave-uniform): a lane's own row nb keeps
-// the entries of rows [lo[nb], hi[nb]); the others become -inf.  Compares with constants and selects only.
-template <int NB>
-__device__ __forceinline__ void mask_rows32(f32x4 (&s0)[NB], f32x4 (&s1)[NB], int base_row, int g, const int (&lo)[NB],
-                                            const int (&hi)[NB], bool check_lo) {
+// Per-element mask of two accumulator tiles, rows base_row .. base_row + 31 (wave-uniform): the lane keeps the entries of
+// rows [lo, hi); the others become -inf.  Compares with constants and selects only.
+__device__ __forceinline__ void mask_rows32(f32x4& s0, f32x4& s1, int base_row, int g, int lo, int hi, bool check_lo) {
+  const int h = hi - base_row - 4 * g, l = lo - base_row - 4 * g;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int h = hi[nb] - base_row - 4 * g, l = lo[nb] - base_row - 4 * g;
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      f32x4& s = a == 0 ? s0 : s1;
+      s[v] = 16 * a + v < h ? s[v] : -INFINITY;
+    }
+  if (check_lo) {   // wave-uniform
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        f32x4& s = a == 0 ? s0[nb] : s1[nb];
-        s[v] = 16 * a + v < h ? s[v] : -INFINITY;
+        f32x4& s = a == 0 ? s0 : s1;
+        s[v] = 16 * a + v >= l ? s[v] : -INFINITY;
       }
-    if (check_lo) {   // wave-uniform
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          f32x4& s = a == 0 ? s0[nb] : s1[nb];
-          s[v] = 16 * a + v >= l ? s[v] : -INFINITY;
-        }
-    }
   }
 }
 

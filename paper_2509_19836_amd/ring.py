@@ -3,8 +3,9 @@
 On one GPU the ring is simulated: every KV shard already sits in HBM and device i visits them in
 ring order, its own shard first and then j = (i - t) mod G (Sec. 3.4; forward algorithm lines
 3-12; Alg. 1 for the backward order used here: Q_i, dO_i, Lse_i, D_i stay and dQ_i accumulates
-locally while dK_j, dV_j of the visiting shard accumulate).  Nothing here computes: each step is
-one call into the C ABI.
+locally while dK_j, dV_j of the visiting shard accumulate).  Nothing here computes: the steps of a
+direction are one call into the C ABI, since all shards are there (a loop that waits for them calls
+burst_attn_step_fwd and burst_attn_step_bwd shard by shard).
 """
 from . import binding as lib
 
@@ -43,27 +44,33 @@ def mask_positions(mask, side):
                            for s in range(nseg)])
 
 
+def _steps(i, G, N, kind, scale, q_i, k_shards, v_shards, window, N_blk):
+    """Order, shapes, masks, K and V of the ring's steps."""
+    B, n, Hq, d = q_i.shape
+    order = ring_order(i, G)
+    k, v = [k_shards[j] for j in order], [v_shards[j] for j in order]
+    shapes = [lib.shape(B, Hq, k_j.shape[2], d, n, k_j.shape[1], scale) for k_j in k]
+    return order, shapes, [fill_mask(kind, i, j, G, N, window, N_blk) for j in order], k, v
+
+
 def ring_forward(i, G, N, kind, scale, q_i, k_shards, v_shards, o_acc, lse_acc, stream=None, window=0, N_blk=0):
     """o_acc / lse_acc must hold (0, -inf) on entry; they hold (O_i, Lse_i) on return."""
-    B, n, Hq, d = q_i.shape
-    for j in ring_order(i, G):
-        k_j, v_j = k_shards[j], v_shards[j]
-        shp = lib.shape(B, Hq, k_j.shape[2], d, n, k_j.shape[1], scale)
-        lib.burst_attn_step_fwd(shp, fill_mask(kind, i, j, G, N, window, N_blk), q_i, k_j, v_j,
-                                o_acc=o_acc, lse_acc=lse_acc, stream=stream)
+    _, shapes, masks, k, v = _steps(i, G, N, kind, scale, q_i, k_shards, v_shards, window, N_blk)
+    lib.burst_attn_steps_fwd(shapes, masks, q_i, k, v, o_acc, lse_acc, stream=stream)
 
 
 def ring_backward(i, G, N, kind, scale, q_i, do_i, o_i, lse_i, d_i, k_shards, v_shards, dq_i, dk_shards,
                   dv_shards, stream=None, window=0, N_blk=0):
-    """D_i once, then one backward step per shard; dq_i, dk_shards[j], dv_shards[j] are fp32
-    accumulators ("+=")."""
+    """D_i once, then the backward steps; dq_i, dk_shards[j], dv_shards[j] are fp32 accumulators ("+=")."""
     B, n, Hq, d = q_i.shape
     shp0 = lib.shape(B, Hq, k_shards[0].shape[2], d, n, n, scale)
     lib.burst_attn_preprocess_bwd(shp0, o_i, do_i, d_i, stream=stream)
+    order, shapes, masks, k, v = _steps(i, G, N, kind, scale, q_i, k_shards, v_shards, window, N_blk)
+    dk, dv = [dk_shards[j] for j in order], [dv_shards[j] for j in order]
     flags = lib.BURST_ACC_DQ | lib.BURST_ACC_DK | lib.BURST_ACC_DV
-    for j in ring_order(i, G):
-        k_j, v_j = k_shards[j], v_shards[j]
-        shp = lib.shape(B, Hq, k_j.shape[2], d, n, k_j.shape[1], scale)
-        lib.burst_attn_step_bwd(shp, fill_mask(kind, i, j, G, N, window, N_blk), q_i, k_j, v_j, do_i, lse_i, d_i,
-                                dq=dq_i, dk=dk_shards[j], dv=dv_shards[j], accumulate_flags=flags,
-                                stream=stream)
+    if any(t is None for t in dk + dv):     # shards whose gradients are not asked for
+        for t in range(G):
+            lib.burst_attn_step_bwd(shapes[t], masks[t], q_i, k[t], v[t], do_i, lse_i, d_i, dq=dq_i, dk=dk[t], dv=dv[t],
+                                    accumulate_flags=flags, stream=stream)
+        return
+    lib.burst_attn_steps_bwd(shapes, masks, q_i, k, v, do_i, lse_i, d_i, dq_i, dk, dv, accumulate_flags=flags, stream=stream)

@@ -497,3 +497,34 @@ def test_backward_chunk_plan_covers_the_axis_with_the_same_positions(lib, chunk_
         assert len(lib.burst_attn_chunk_plan(hp.fill_mask(lib, "causal", 1, 2, G, 4 * 2 * chunk_rows), 1)) == 1
     finally:
         lib.burst_attn_set_chunk_rows(32768)
+
+
+def test_calls_of_several_steps_check_every_step_before_anything_runs(lib):
+    raw, n = lib.raw(), 3
+    good = lib.burst_tensor_t(4096, lib.BURST_BF16, 0, 64 * 2 * 64, 2 * 64, 64)
+    f32 = lib.burst_tensor_t(4096, lib.BURST_F32, 0, 64 * 2 * 64, 2 * 64, 64)
+    vec = lib.burst_rowvec_t(4096, 128, 64)
+    off = lib.burst_tensor_t(4098, lib.BURST_BF16, 0, 64 * 2 * 64, 2 * 64, 64)   # not 16-byte aligned
+
+    def call(count=n, k=None, mask=None, shape=None, dk=True):
+        shapes = (lib.burst_shape_t * n)(*[lib.shape(1, 2, 2, 64, 64, 64, 0.125) for _ in range(n)])
+        masks = (lib.burst_mask_t * n)(*[hp.fill_mask(lib, "causal", 2, j, n, 64 * n) for j in range(n)])
+        ks, fs = (lib.burst_tensor_t * n)(good, good, good), (lib.burst_tensor_t * n)(f32, f32, f32)
+        if k is not None:
+            ks[2] = k
+        if mask is not None:
+            masks[2].q_seg_len = mask
+        if shape is not None:
+            shapes[2].head_dim = shape
+        vs = (lib.burst_tensor_t * n)(good, good, good)
+        return (raw.burst_attn_steps_fwd(count, shapes, masks, C.byref(good), ks, vs, C.byref(f32), C.byref(vec), None),
+                raw.burst_attn_steps_bwd(count, shapes, masks, C.byref(good), ks, vs, C.byref(good), C.byref(vec), C.byref(vec),
+                                         C.byref(f32), fs if dk else None, fs, 7, None))
+
+    assert call(count=0) == (lib.BURST_OK, lib.BURST_OK)
+    assert call(count=-1) == (lib.BURST_ERR_INVALID_ARG,) * 2
+    assert call(count=lib.BURST_MAX_STEPS + 1) == (lib.BURST_ERR_UNSUPPORTED,) * 2
+    assert call(k=off) == (lib.BURST_ERR_INVALID_ARG,) * 2
+    assert call(mask=63) == (lib.BURST_ERR_INVALID_ARG,) * 2
+    assert call(shape=96) == (lib.BURST_ERR_UNSUPPORTED,) * 2
+    assert call(k=off, dk=False)[1] == lib.BURST_ERR_INVALID_ARG

@@ -1,0 +1,189 @@
+"""Several steps in one call (burst_attn_steps_fwd, burst_attn_steps_bwd) against the same steps one by one.
+
+The one-by-one calls are held against the oracle elsewhere.  What may differ: forward rounds P to bf16 against another running
+maximum (a relative 2^-9 of a score's share, so a relative 2-norm of O below 2^-8 = 4e-3) and merges in fp32; backward
+forms the same P and dS and only adds them up in another order (fp32: 1e-5)."""
+import math
+
+import numpy as np
+import pytest
+
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+
+# name: (kind, G, device, rows, window, N_blk), heads (q, kv), head_dim, batch, rows of the ranges
+CASES = {
+    "ragged tiles": (("causal", 4, 2, 333, 0, 0), (3, 3), 64, 2, 32768),
+    "more steps than a launch takes": (("zigzag", 10, 9, 130, 0, 0), (2, 1), 128, 1, 32768),
+    "walks over more than one launch": (("zigzag", 5, 1, 514, 0, 0), (2, 2), 128, 1, 512),
+    "ranges of a step and steps together": (("striped", 3, 2, 700, 0, 0), (4, 2), 128, 1, 256),
+    "window that leaves shards behind": (("striped", 4, 3, 300, 90, 0), (2, 2), 64, 1, 32768),
+    "window over contiguous shards": (("causal", 6, 5, 200, 150, 0), (8, 1), 128, 1, 32768),
+    "many pieces": (("block_striped", 4, 1, 256, 0, 256), (2, 2), 128, 2, 256),
+    "nothing masked, one row": (("full", 3, 0, 1, 0, 0), (2, 2), 128, 1, 32768),
+    "separate launches of dQ and dK/dV": (("zigzag", 4, 2, 600, 0, 0), (128, 128), 64, 2, 32768),
+}
+
+
+def _state(lib, case):
+    import torch
+    (kind, G, dev, n, window, N_blk), (Hq, Hkv), d, B, _ = case
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    draw = lambda h: torch.randn(B, n, h, d, device="cuda", generator=gen).to(torch.bfloat16)
+    order = [(dev - t) % G for t in range(G)]
+    s = dict(q=draw(Hq), do=draw(Hq), k=[draw(Hkv) for _ in order], v=[draw(Hkv) for _ in order],
+             masks=[hp.fill_mask(lib, kind, dev, j, G, n * G, window, N_blk) for j in order],
+             shapes=[lib.shape(B, Hq, Hkv, d, n, n, d ** -0.5) for _ in order],
+             lse=math.log(n * G) + 0.2 * torch.randn(B, Hq, n, device="cuda", generator=gen),
+             d=0.1 * torch.randn(B, Hq, n, device="cuda", generator=gen))
+    s["new"] = lambda h, fill=0.0: torch.full((B, n, h, d), fill, device="cuda", dtype=torch.float32)
+    return s
+
+
+def _close(got, ref, tol):
+    if not ref.any():
+        assert not got.any()
+        return
+    assert float((got - ref).norm() / ref.norm()) <= tol
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_steps_in_one_call_equal_steps_one_by_one(lib, name):
+    import torch
+    case = CASES[name]
+    (_, G, _, n, _, _), (Hq, Hkv), d, B, chunk = case
+    print(name, flush=True)
+    s = _state(lib, case)
+    lib.burst_attn_set_chunk_rows(chunk)
+    try:
+        for live in (False, True):   # a fresh running state, one that holds something
+            o, lse = ([s["new"](Hq, 0.5 if live else 0.0) for _ in range(2)],
+                      [torch.full((B, Hq, n), 1.0 if live else -math.inf, device="cuda") for _ in range(2)])
+            lib.burst_attn_steps_fwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], o[0], lse[0])
+            for t in range(G):
+                lib.burst_attn_step_fwd(s["shapes"][t], s["masks"][t], s["q"], s["k"][t], s["v"][t], o_acc=o[1], lse_acc=lse[1])
+            torch.cuda.synchronize()
+            _close(o[0], o[1], 4e-3)
+            dead = torch.isinf(lse[1])
+            assert torch.equal(dead, torch.isinf(lse[0]))
+            assert float((lse[0] - lse[1])[~dead].abs().max()) <= 1e-5 * max(1.0, float(lse[1][~dead].abs().max()))
+        for flags in (0, lib.BURST_ACC_DQ | lib.BURST_ACC_DV, lib.BURST_ACC_DK, 7):
+            g = [dict(dq=s["new"](Hq, 1.0), dk=[s["new"](Hkv, 2.0) for _ in range(G)], dv=[s["new"](Hkv, 3.0) for _ in range(G)])
+                 for _ in range(2)]
+            lib.burst_attn_steps_bwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], s["do"], s["lse"], s["d"], g[0]["dq"],
+                                     g[0]["dk"], g[0]["dv"], accumulate_flags=flags)
+            for t in range(G):   # dq: the sum over the steps
+                lib.burst_attn_step_bwd(s["shapes"][t], s["masks"][t], s["q"], s["k"][t], s["v"][t], s["do"], s["lse"], s["d"],
+                                        dq=g[1]["dq"], dk=g[1]["dk"][t], dv=g[1]["dv"][t],
+                                        accumulate_flags=flags | (lib.BURST_ACC_DQ if t else 0))
+            torch.cuda.synchronize()
+            _close(g[0]["dq"], g[1]["dq"], 1e-5)
+            for t in range(G):
+                _close(g[0]["dk"][t], g[1]["dk"][t], 1e-5)
+                _close(g[0]["dv"][t], g[1]["dv"][t], 1e-5)
+        dq = s["new"](Hq)            # dQ alone, dK and dV alone
+        lib.burst_attn_steps_bwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], s["do"], s["lse"], s["d"], dq, None, None)
+        dk, dv = ([s["new"](Hkv) for _ in range(G)] for _ in range(2))
+        lib.burst_attn_steps_bwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], s["do"], s["lse"], s["d"], None, dk, dv,
+                                 accumulate_flags=7)
+        torch.cuda.synchronize()
+        _close(dq, g[1]["dq"] - 1.0, 1e-4)   # (the last ones above stand on ones, twos and threes: rounded at 1e-7 of those)
+        for t in range(G):
+            _close(dk[t] + 2.0, g[1]["dk"][t], 1e-5)
+            _close(dv[t] + 3.0, g[1]["dv"][t], 1e-5)
+    finally:
+        lib.burst_attn_set_chunk_rows(32768)
+
+
+def test_steps_that_share_buffers_run_in_order(lib):
+    """A gradient buffer that two steps add to, and gradients interleaved in one array."""
+    import torch
+    case = (("zigzag", 4, 3, 128, 0, 0), (2, 2), 64, 1, 32768)
+    s = _state(lib, case)
+    args = (s["shapes"], s["masks"], s["q"], s["k"], s["v"], s["do"], s["lse"], s["d"])
+    ref_k, ref_v, ref_q = [s["new"](2) for _ in range(4)], [s["new"](2) for _ in range(4)], s["new"](2)
+    lib.burst_attn_steps_bwd(*args, ref_q, ref_k, ref_v, accumulate_flags=7)
+    one_k, one_v, dq = s["new"](2), s["new"](2), s["new"](2)
+    lib.burst_attn_steps_bwd(*args, dq, [one_k] * 4, [one_v] * 4, accumulate_flags=7)
+    both = torch.zeros(1, 128, 4, 2, 2, 64, device="cuda")     # step and dK / dV between rows and heads
+    dq2 = s["new"](2)
+    lib.burst_attn_steps_bwd(*args, dq2, [both[:, :, t, 0] for t in range(4)], [both[:, :, t, 1] for t in range(4)], accumulate_flags=7)
+    torch.cuda.synchronize()
+    _close(one_k, sum(ref_k), 1e-5)
+    _close(one_v, sum(ref_v), 1e-5)
+    for x in (dq, dq2):
+        _close(x, ref_q, 1e-5)
+    for t in range(4):
+        _close(both[:, :, t, 0], ref_k[t], 1e-5)
+        _close(both[:, :, t, 1], ref_v[t], 1e-5)
+
+
+def test_chunks_without_keys_and_of_other_lengths(lib):
+    import torch
+    B, H, d, n = 1, 2, 128, 300
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    draw = lambda rows: torch.randn(B, rows, H, d, device="cuda", generator=gen).to(torch.bfloat16)
+    rows = [77, 0, 512, 1]
+    q, k, v = draw(n), [draw(max(r, 1))[:, :r] for r in rows], [draw(max(r, 1))[:, :r] for r in rows]
+    masks = []
+    for r in rows:
+        m = lib.burst_mask_t()
+        m.mode, m.pos_stride, m.q_nseg, m.k_nseg, m.q_seg_len, m.k_seg_len = lib.BURST_MASK_FULL, 1, 1, 1, n, r
+        masks.append(m)
+    # (torch gives an empty view no address of its own: the library asks for one)
+    k[1], v[1] = draw(1), draw(1)
+    shapes = [lib.shape(B, H, H, d, n, r, d ** -0.5) for r in rows]
+    o, lse = torch.zeros(B, n, H, d, device="cuda"), torch.full((B, H, n), -math.inf, device="cuda")
+    lib.burst_attn_steps_fwd(shapes, masks, q, k, v, o, lse)
+    ks, vs = (torch.cat([t[:, :r] for t, r in zip(x, rows)], 1).double().cpu() for x in (k, v))
+    s = torch.matmul(q.double().cpu().transpose(1, 2), ks.permute(0, 2, 3, 1).contiguous()) * d ** -0.5
+    ref = torch.matmul(s.softmax(-1), vs.transpose(1, 2).contiguous()).transpose(1, 2)
+    assert hp.rel_err(o.cpu().numpy(), ref.numpy()) <= hp.REL_TOL
+    assert hp.lse_err(lse.cpu().numpy(), s.logsumexp(-1).numpy()) <= hp.LSE_TOL
+
+
+def test_a_nan_key_reaches_the_rows_that_see_it_in_any_step(lib):
+    import torch
+    case = (("causal", 3, 2, 64, 0, 0), (1, 1), 64, 1, 32768)
+    s = _state(lib, case)
+    s["k"][1][0, 5] = math.nan
+    o, lse = s["new"](1), torch.full((1, 1, 64), -math.inf, device="cuda")
+    lib.burst_attn_steps_fwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], o, lse)
+    o1, lse1 = s["new"](1), torch.full((1, 1, 64), -math.inf, device="cuda")
+    for t in range(3):
+        lib.burst_attn_step_fwd(s["shapes"][t], s["masks"][t], s["q"], s["k"][t], s["v"][t], o_acc=o1, lse_acc=lse1)
+    torch.cuda.synchronize()
+    for x in (o, lse, o1, lse1):
+        assert bool(torch.isnan(x).all())
+
+
+def test_a_captured_call_replays(lib):
+    import torch
+    case = CASES["ragged tiles"]
+    s = _state(lib, case)
+    o, lse, dq = s["new"](3), torch.empty(2, 3, 333, device="cuda"), s["new"](3)
+    dk, dv = ([s["new"](3) for _ in range(4)] for _ in range(2))
+
+    def run():
+        o.zero_()
+        lse.fill_(-math.inf)
+        lib.burst_attn_steps_fwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], o, lse)
+        lib.burst_attn_steps_bwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], s["do"], s["lse"], s["d"], dq, dk, dv)
+
+    run()
+    torch.cuda.synchronize()
+    ref = [x.clone() for x in (o, lse, dq, *dk, *dv)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        for x in (o, lse, dq, *dk, *dv):
+            x.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip((o, lse, dq, *dk, *dv), ref):
+            assert torch.equal(x, y)
