@@ -67,12 +67,16 @@ int burst_lm_head_loss(const burst_lm_head_shape_t* shape, const void* h_last, i
  * The same computation for callers that cannot allocate device memory or hand over a workspace of
  * their own: code running under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Arguments, results and errors are those of burst_lm_head_loss without the workspace
- * pair: the scratch memory is an array built into the library's code object, 64 MiB per GPU
- * (burst_lm_head_static_scratch_bytes()), present from the moment the library is loaded until the
- * process ends.  The call allocates nothing and frees nothing, on the host or on the device.
- *   - A shape whose burst_lm_head_workspace_bytes() exceeds that size is refused with
- *     BURST_ERR_SCRATCH and nothing is enqueued (64 MiB holds e.g. tile_tokens = 256 with a
- *     32000-word vocabulary and d = 4096); choose a smaller tile_tokens or use burst_lm_head_loss.
+ * pair: the scratch memory is an array built into the library's code object, 256 MiB per GPU, present
+ * from the moment the library is loaded until the process ends.  The call allocates nothing and
+ * frees nothing, on the host or on the device.
+ *   - A shape whose burst_lm_head_workspace_bytes() exceeds 64 MiB
+ *     (burst_lm_head_static_scratch_bytes()) is refused with BURST_ERR_SCRATCH and nothing is enqueued
+ *     (64 MiB holds e.g. tile_tokens = 256 with a 32000-word vocabulary and d = 4096); choose a
+ *     smaller tile_tokens or use burst_lm_head_loss.
+ *   - Sequence tiles of 256 tokens are joined as far as the array reaches, which changes the order in
+ *     which the fp32 sums of dW (and of a dH whose contraction is split) are taken; longer tiles give the
+ *     bits of burst_lm_head_loss.
  *   - The array used is that of the GPU that is current on the calling thread when the call is
  *     made; the stream must belong to that GPU.
  *   - Every call on a GPU shares that GPU's array, which keeps whatever the last call left in it
