@@ -181,6 +181,32 @@ struct DirectStager {
   }
 };
 
+// The tiles of the walked axis that a block-wise sparse mask leaves open, in order: the flags of 64 tiles at a time as bits
+// of a scalar register, one LDS read for each 64 tiles of the axis.
+struct OpenTiles {
+  const uint8_t* flags;   // LDS, kMaxBlockCacheTiles of them
+  uint64_t bits;          // of tiles base .. base + 63: open and not handed out yet
+  int base;
+  __device__ __forceinline__ void read() { bits = __ballot(flags[base + (threadIdx.x & 63)] != 0); }
+  // From `tile` on
+  __device__ __forceinline__ void start(int tile) {
+    base = tile & ~63;
+    read();
+    bits &= ~0ull << (tile & 63);
+  }
+  // The next open tile below `end` (at most kMaxBlockCacheTiles), -1 when there is none
+  __device__ __forceinline__ int next(int end) {
+    while (bits == 0) {
+      base += 64;
+      if (base >= end) return -1;
+      read();
+    }
+    const int tile = base + __builtin_ctzll(bits);
+    bits &= bits - 1;
+    return __builtin_amdgcn_readfirstlane(tile < end ? tile : -1);
+  }
+};
+
 // Walk of a query block over the key tiles (BK rows) it can see.  The visible tiles are one run of consecutive
 // tiles, so the cursor and the tile addresses move by adding constants.  Tiles are brought in sets:
 // {K of tile t + 1, V of tile t} with LAG, the two that one pipelined iteration of the forward kernel reads,
@@ -192,20 +218,31 @@ struct KvStream {
   using Stager = DirectStager<D, BK, NW>;
   static constexpr int N = Stager::N, LOADS = 2 * N;   // per wave: one tile, one set
   Stager stage_k, stage_v;
-  int left, k0;           // cursor: tiles left in the run (0: the walk is over), first key row of its tile
+  int left, k0;           // cursor: tiles left in the run (with a block mask 1; 0: the walk is over), first key row of its tile
   int v0;                 // LAG: first key row of the tile whose V comes with the next set
   int sk;
-  const uint8_t* open;    // LDS flags per key tile from a block-wise sparse mask, or nullptr
+  OpenTiles open;         // with a block mask, and the end of the run in tiles
+  int run_end;
   const char *k_tile, *v_tile, *v_prev;
   int64_t k_step, v_step; // bytes per tile
 
   __device__ __forceinline__ void init(const MaskDev& mk, const TensorDev& k, const TensorDev& v, int b, int hk, int sk_,
                                        int q_lo, int q_hi, int wave, int lane, const uint8_t* open_flags) {
     sk = sk_;
-    if (BLK) open = open_flags;
     TileRun run = visible_tiles<false, BK>(mk, q_lo, q_hi, sk);
     run.start = __builtin_amdgcn_readfirstlane(run.start);   // (results of divisions: keeps what follows scalar)
     left = __builtin_amdgcn_readfirstlane(run.len);
+    if (BLK) {
+      open.flags = open_flags;
+      run_end = run.start + left;
+      if (left > 0) {
+        open.start(run.start);
+        const int tile = open.next(run_end);
+        left = tile >= 0;
+        run.start = max(tile, 0);
+      }
+      left = __builtin_amdgcn_readfirstlane(left);
+    }
     k0 = run.start * BK;
     k_step = 2 * BK * k.ss;
     v_step = 2 * BK * v.ss;
@@ -213,9 +250,6 @@ struct KvStream {
     v_tile = reinterpret_cast<const char*>((const __bf16*)v.ptr + b * v.sb + hk * v.sh) + run.start * v_step;
     stage_k.init(k.ss, wave, lane);
     stage_v.init(v.ss, wave, lane);
-    if (BLK) {   // skip tiles that the block mask closes
-      while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK]) == 0) step();
-    }
     v_prev = v_tile;
     v0 = k0;
   }
@@ -247,13 +281,13 @@ struct KvStream {
         left += negative_mask(-left);
         k0 += BK & move;
       } else {
-        left = max(left - 1, 0);   // skip tiles that the block mask closes
-        move = 1;
-        while (left > 0 && __builtin_amdgcn_readfirstlane(open[k0 / BK + move]) == 0) {
-          --left;
-          ++move;
+        move = 0;
+        if (left > 0) {
+          const int tile = open.next(run_end);
+          left = tile >= 0;
+          if (left) move = tile - k0 / BK;
         }
-        move = __builtin_amdgcn_readfirstlane(move * min(left, 1));
+        move = __builtin_amdgcn_readfirstlane(move);
         left = __builtin_amdgcn_readfirstlane(left);
         k0 += move * BK;
       }
@@ -280,12 +314,6 @@ struct KvStream {
     for (int i = 0; i < N; ++i) load_k(i, k_lds, wave);
     end();
   }
-  __device__ __forceinline__ void step() {
-    --left;
-    k0 += BK;
-    k_tile += k_step;
-    v_tile += v_step;
-  }
 };
 
 // Walk of a key block over (query head of its group, query tile of BQ rows that can see it): per tile the Q and dO
@@ -301,7 +329,7 @@ struct QStream {
   int left, heads, q0;    // cursor: tiles left of this head, heads left (0: the walk is over), first row of its tile
   int run_start, run_len, sq;
   int clamped;            // mask
-  const uint8_t* open;    // LDS flags per query tile from a block-wise sparse mask
+  OpenTiles open;         // with a block mask
   const char *q_tile, *o_tile, *row_tile;
   int64_t q_step, o_step;                   // bytes per tile
   int64_t q_next, o_next, row_next;         // from the last tile of a head to the first one of the next, bytes
@@ -309,7 +337,6 @@ struct QStream {
   __device__ __forceinline__ void init(const TensorDev& q, const TensorDev& d_o, const RowvecDev& vec, int b, int hq, int group,
                                        TileRun run, int sq_, int wave, int lane, const uint8_t* open_flags) {
     sq = sq_;
-    if (BLK) open = open_flags;
     run_start = __builtin_amdgcn_readfirstlane(run.start);   // (results of divisions: keeps what follows scalar)
     run_len = __builtin_amdgcn_readfirstlane(run.len);
     heads = run_len > 0 ? group : 0;
@@ -326,7 +353,14 @@ struct QStream {
     offsets(BQ, wave, lane);
     clamped = 0;
     if (BLK) {
-      if (heads > 0 && !is_open()) advance();
+      open.flags = open_flags;
+      if (heads > 0) {
+        open.start(run_start);
+        const int first = open.next(run_start + run_len);
+        if (first >= 0) to_tile(first);
+        else heads = 0;
+      }
+      heads = __builtin_amdgcn_readfirstlane(heads);
     }
   }
   __device__ __forceinline__ void offsets(int valid, int wave, int lane) {
@@ -334,17 +368,16 @@ struct QStream {
     stage_o.clamp(o_step / (2 * BQ), valid, wave, lane);
     row_off = 4 * min(lane, valid - 1);
   }
-  __device__ __forceinline__ bool is_open() const { return __builtin_amdgcn_readfirstlane(open[q0 / BQ]) != 0; }
   __device__ __forceinline__ bool valid() const { return heads > 0; }
   // First row of the cursor's tile, -1 when the walk is over
   __device__ __forceinline__ int cursor() const { return q0 | negative_mask(heads - 1); }
-  // Closed tiles from the cursor's on, as far as one read sees (64 tiles, a lane each; left >= 1 of this head).  One
-  // read per tile, with its wait, stood in the vector phase of both roles: 16384 rows x 32 heads in blocks of 512,
-  // density 0.05: dK/dV 770 -> 409 us a step; density 0.1: 925 -> 570.
-  __device__ __forceinline__ int closed_tiles() const {
-    const int l = threadIdx.x & 63;
-    const uint64_t some = __ballot(l < left && open[q0 / BQ + min(l, left - 1)] != 0);
-    return some ? __builtin_ctzll(some) : 64;
+  // To another tile of the cursor's head
+  __device__ __forceinline__ void to_tile(int tile) {
+    const int n = __builtin_amdgcn_readfirstlane(tile - q0 / BQ);
+    q0 += n * BQ;
+    q_tile += n * q_step;
+    o_tile += n * o_step;
+    row_tile += n * 4 * BQ;
   }
   // To the next tile; at the end of the walk the cursor stays where it is.  Without a block mask in PARTS pieces of a few
   // scalar instructions that fit between the matrix instructions of a stream, as in KvStream.
@@ -379,25 +412,22 @@ struct QStream {
       return;
     }
     if (heads == 0) return;
-    int n = 1;
-    do {
-      if (left > n) {
-        left -= n;
-      } else {
-        n = left - 1;     // to the last tile of this head, and from there to the next one
-        if (--heads == 0) return;
-        left = run_len;
-        q0 -= run_len * BQ - BQ;
-        q_tile += q_next;
-        o_tile += o_next;
-        row_tile += row_next;
+    int tile = open.next(run_start + run_len);
+    if (tile < 0) {   // the same tiles of the next head
+      if (heads == 1) {
+        heads = 0;
+        return;
       }
-      q0 += n * BQ;
-      q_tile += n * q_step;
-      o_tile += n * o_step;
-      row_tile += n * 4 * BQ;
-      n = closed_tiles();
-    } while (n > 0);
+      --heads;
+      to_tile(run_start + run_len - 1);
+      q0 -= (run_len - 1) * BQ;
+      q_tile += q_next;
+      o_tile += o_next;
+      row_tile += row_next;
+      open.start(run_start);
+      tile = open.next(run_start + run_len);
+    }
+    to_tile(tile);
   }
   // Before the loads of a tile: rows past the last one are read as copies of it
   __device__ __forceinline__ void begin(int wave, int lane) {
