@@ -216,6 +216,12 @@ int burst_attn_fill_striped_mask(int32_t dev_i, int32_t shard_j, int32_t G, int6
 int burst_attn_fill_block_striped_mask(int32_t dev_i, int32_t shard_j, int32_t G, int64_t N, int64_t N_blk,
                                        int32_t causal, burst_mask_t* out);
 
+/* Masks of a whole ring of device dev_i in ring order (its own shard first, then (dev_i - t) mod G): out has G entries.
+ * partition 0: full (contiguous split, every pair visible), 1: contiguous, 2: zigzag, 3: striped, 4: block-striped (N_blk); 1-4
+ * causal, with a window if window > 0. */
+int burst_attn_fill_ring_masks(int32_t partition, int32_t dev_i, int32_t G, int64_t N, int64_t N_blk, int64_t window,
+                               burst_mask_t* out);
+
 /* Number of visible (query row, key row) pairs of a step per (batch, head): the benchmark's work
  * unit (4*head_dim flop forward, 10*head_dim backward).  Returns -1 on an invalid mask.  The
  * count is that of the mode and window alone: block_mask lives in device memory and is not read

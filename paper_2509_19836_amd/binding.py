@@ -7,6 +7,7 @@ not been built, importing this module raises.
 """
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -62,11 +63,15 @@ _lib.burst_attn_step_bwd.restype = C.c_int
 _lib.burst_attn_step_bwd.argtypes = [_P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
     _P(burst_rowvec_t)] * 2 + [_P(burst_tensor_t)] * 3 + [C.c_int32, C.c_void_p]
 _lib.burst_attn_steps_fwd.restype = C.c_int
-_lib.burst_attn_steps_fwd.argtypes = [C.c_int32, _P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
-    _P(burst_rowvec_t), C.c_void_p]
+# (arrays of structs go in as the bytes they consist of)
+_lib.burst_attn_steps_fwd.argtypes = [C.c_int32, C.c_char_p, _P(burst_mask_t), _P(burst_tensor_t), C.c_char_p, C.c_char_p,
+                                      _P(burst_tensor_t), _P(burst_rowvec_t), C.c_void_p]
 _lib.burst_attn_steps_bwd.restype = C.c_int
-_lib.burst_attn_steps_bwd.argtypes = [C.c_int32, _P(burst_shape_t), _P(burst_mask_t)] + [_P(burst_tensor_t)] * 4 + [
-    _P(burst_rowvec_t)] * 2 + [_P(burst_tensor_t)] * 3 + [C.c_int32, C.c_void_p]
+_lib.burst_attn_steps_bwd.argtypes = [C.c_int32, C.c_char_p, _P(burst_mask_t), _P(burst_tensor_t), C.c_char_p, C.c_char_p,
+                                      _P(burst_tensor_t), _P(burst_rowvec_t), _P(burst_rowvec_t), _P(burst_tensor_t),
+                                      C.c_char_p, C.c_char_p, C.c_int32, C.c_void_p]
+_lib.burst_attn_fill_ring_masks.restype = C.c_int
+_lib.burst_attn_fill_ring_masks.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int64, C.c_int64, C.c_int64, _P(burst_mask_t)]
 for _name in ("zigzag", "contiguous", "striped"):
     _f = getattr(_lib, f"burst_attn_fill_{_name}_mask")
     _f.restype = C.c_int
@@ -111,7 +116,8 @@ _lib.burst_attn_status_string.argtypes = [C.c_int]
 _lib.burst_attn_last_hip_error.restype = C.c_int
 _lib.burst_attn_version.restype = C.c_char_p
 
-EXPORTS = ["burst_attn_step_fwd", "burst_attn_steps_fwd", "burst_attn_steps_bwd", "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
+EXPORTS = ["burst_attn_step_fwd", "burst_attn_steps_fwd", "burst_attn_steps_bwd", "burst_attn_fill_ring_masks",
+           "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
            "burst_attn_fill_zigzag_mask", "burst_attn_fill_contiguous_mask", "burst_attn_fill_striped_mask",
            "burst_attn_fill_block_striped_mask",
            "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
@@ -141,17 +147,25 @@ def tensor(t):
     """Describe a [batch, seq, heads, head_dim] torch tensor (bf16 or fp32, last dim contiguous)."""
     if t is None:
         return None
-    assert t.dim() == 4 and t.stride(3) == 1, "expected [batch, seq, heads, head_dim] with contiguous head_dim"
-    dt = {torch.bfloat16: BURST_BF16, torch.float32: BURST_F32}[t.dtype]
-    return burst_tensor_t(t.data_ptr(), dt, 0, t.stride(0), t.stride(1), t.stride(2))
+    return burst_tensor_t(*_described(t))
+
+
+_DTYPES = {torch.bfloat16: BURST_BF16, torch.float32: BURST_F32}
+
+
+def _described(t):
+    stride = t.stride()
+    assert len(stride) == 4 and stride[3] == 1, "expected [batch, seq, heads, head_dim] with contiguous head_dim"
+    return t.data_ptr(), _DTYPES[t.dtype], 0, stride[0], stride[1], stride[2]
 
 
 def rowvec(t):
     """Describe a [batch, heads, seq] fp32 torch tensor (seq contiguous)."""
     if t is None:
         return None
-    assert t.dim() == 3 and t.stride(2) == 1 and t.dtype == torch.float32
-    return burst_rowvec_t(t.data_ptr(), t.stride(0), t.stride(1))
+    stride = t.stride()
+    assert len(stride) == 3 and stride[2] == 1 and t.dtype == torch.float32
+    return burst_rowvec_t(t.data_ptr(), stride[0], stride[1])
 
 
 def _ref(x):
@@ -186,6 +200,18 @@ def burst_attn_fill_block_striped_mask(dev_i, shard_j, G, N, N_blk, causal=True)
     m = burst_mask_t()
     _check(_lib.burst_attn_fill_block_striped_mask(dev_i, shard_j, G, N, N_blk, int(causal), C.byref(m)))
     return m
+
+
+_PARTITIONS = {"full": 0, "causal": 1, "zigzag": 2, "striped": 3, "block_striped": 4}
+
+
+def burst_attn_fill_ring_masks(partition, dev_i, G, N, N_blk=0, window=0):
+    """Masks of device dev_i's ring in ring order (its own shard first, then (dev_i - t) mod G): an array of G burst_mask_t."""
+    if partition not in _PARTITIONS:
+        raise ValueError(partition)
+    masks = (burst_mask_t * G)()
+    _check(_lib.burst_attn_fill_ring_masks(_PARTITIONS[partition], dev_i, G, N, N_blk, window, masks))
+    return masks
 
 
 def set_block_mask(mask, block_mask, q_block_rows, k_block_rows):
@@ -248,30 +274,42 @@ def burst_attn_step_bwd(shp, mask, q, k, v, d_o, lse, d, dq=None, dk=None, dv=No
                                     _ref(tensor(dk)), _ref(tensor(dv)), accumulate_flags, _stream(stream)))
 
 
-def _arrays(shapes, masks, *tensor_lists):
-    n = len(shapes)
-    assert len(masks) == n and all(t is None or len(t) == n for t in tensor_lists)
-    return [(burst_shape_t * n)(*shapes), (burst_mask_t * n)(*masks)] + [
-        None if ts is None else (burst_tensor_t * n)(*map(tensor, ts)) for ts in tensor_lists]
+def _tensor_array(tensors):
+    """The bytes of an array of burst_tensor_t."""
+    if tensors is None:
+        return None
+    values = []
+    for t in tensors:
+        values.extend(_described(t))
+    return struct.pack("=" + "Qiiqqq" * len(tensors), *values)
+
+
+def _mask_array(masks):
+    return masks if isinstance(masks, C.Array) else (burst_mask_t * len(masks))(*masks)
 
 
 def burst_attn_steps_fwd(shapes, masks, q, k, v, o_acc, lse_acc, stream=None):
-    """Consecutive steps of one query chunk: shapes, masks, k and v are lists with an entry for each step."""
-    for i in range(0, len(shapes), BURST_MAX_STEPS):
+    """Consecutive steps of one query chunk: shapes, masks, k and v have an entry for each step."""
+    n = len(shapes)
+    assert len(masks) == n and len(k) == n and len(v) == n
+    for i in range(0, n, BURST_MAX_STEPS):
         part = slice(i, i + BURST_MAX_STEPS)
-        shp, msk, ks, vs = _arrays(shapes[part], masks[part], k[part], v[part])
-        _check(_lib.burst_attn_steps_fwd(len(shp), shp, msk, _ref(tensor(q)), ks, vs, _ref(tensor(o_acc)), _ref(rowvec(lse_acc)),
-                                         _stream(stream)))
+        _check(_lib.burst_attn_steps_fwd(len(shapes[part]), b"".join(shapes[part]), _mask_array(masks if n <= BURST_MAX_STEPS else masks[part]),
+                                         _ref(tensor(q)), _tensor_array(k[part]), _tensor_array(v[part]), _ref(tensor(o_acc)),
+                                         _ref(rowvec(lse_acc)), _stream(stream)))
 
 
 def burst_attn_steps_bwd(shapes, masks, q, k, v, d_o, lse, d, dq, dk, dv, accumulate_flags=0, stream=None):
-    """Consecutive steps of one query chunk: shapes, masks, k, v, dk and dv are lists with an entry for each step."""
-    for i in range(0, len(shapes), BURST_MAX_STEPS):
+    """Consecutive steps of one query chunk: shapes, masks, k, v, dk and dv have an entry for each step."""
+    n = len(shapes)
+    assert len(masks) == n and len(k) == n and len(v) == n and all(t is None or len(t) == n for t in (dk, dv))
+    for i in range(0, n, BURST_MAX_STEPS):
         part = slice(i, i + BURST_MAX_STEPS)
-        shp, msk, ks, vs, dks, dvs = _arrays(shapes[part], masks[part], k[part], v[part], None if dk is None else dk[part],
-                                             None if dv is None else dv[part])
-        _check(_lib.burst_attn_steps_bwd(len(shp), shp, msk, _ref(tensor(q)), ks, vs, _ref(tensor(d_o)), _ref(rowvec(lse)),
-                                         _ref(rowvec(d)), _ref(tensor(dq)), dks, dvs, accumulate_flags, _stream(stream)))
+        _check(_lib.burst_attn_steps_bwd(len(shapes[part]), b"".join(shapes[part]), _mask_array(masks if n <= BURST_MAX_STEPS else masks[part]),
+                                         _ref(tensor(q)), _tensor_array(k[part]), _tensor_array(v[part]), _ref(tensor(d_o)),
+                                         _ref(rowvec(lse)), _ref(rowvec(d)), _ref(tensor(dq)),
+                                         _tensor_array(dk and dk[part]), _tensor_array(dv and dv[part]), accumulate_flags,
+                                         _stream(stream)))
         accumulate_flags |= BURST_ACC_DQ
 
 

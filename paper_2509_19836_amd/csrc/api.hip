@@ -556,6 +556,21 @@ int burst_attn_fill_block_striped_mask(int32_t dev_i, int32_t shard_j, int32_t G
   return BURST_OK;
 }
 
+int burst_attn_fill_ring_masks(int32_t partition, int32_t dev_i, int32_t G, int64_t N, int64_t N_blk, int64_t window,
+                               burst_mask_t* out) {
+  if (!out || partition < 0 || partition > 4 || G < 1) return BURST_ERR_INVALID_ARG;
+  for (int32_t t = 0; t < G; ++t) {
+    const int32_t j = (int32_t)(((int64_t)dev_i - t + G) % G);
+    burst_mask_t* m = out + t;
+    if (partition <= 1) BURST_TRY(burst_attn_fill_contiguous_mask(dev_i, j, G, N, partition, m));
+    else if (partition == 2) BURST_TRY(burst_attn_fill_zigzag_mask(dev_i, j, G, N, 1, m));
+    else if (partition == 3) BURST_TRY(burst_attn_fill_striped_mask(dev_i, j, G, N, 1, m));
+    else BURST_TRY(burst_attn_fill_block_striped_mask(dev_i, j, G, N, N_blk, 1, m));
+    m->window = window;
+  }
+  return BURST_OK;
+}
+
 int64_t burst_attn_visible_pairs(const burst_mask_t* m) {
   if (!m) return -1;
   if (m->q_nseg < 1 || m->k_nseg < 1 || m->q_seg_len < 0 || m->k_seg_len < 0 || m->q_seg_len > kMaxRows ||

@@ -49,8 +49,13 @@ def _steps(i, G, N, kind, scale, q_i, k_shards, v_shards, window, N_blk):
     B, n, Hq, d = q_i.shape
     order = ring_order(i, G)
     k, v = [k_shards[j] for j in order], [v_shards[j] for j in order]
-    shapes = [lib.shape(B, Hq, k_j.shape[2], d, n, k_j.shape[1], scale) for k_j in k]
-    return order, shapes, [fill_mask(kind, i, j, G, N, window, N_blk) for j in order], k, v
+    shapes, last = [], None
+    for k_j in k:
+        size = k_j.shape
+        if size != last:
+            shp, last = lib.shape(B, Hq, size[2], d, n, size[1], scale), size
+        shapes.append(shp)
+    return order, shapes, lib.burst_attn_fill_ring_masks(kind, i, G, N, N_blk, window), k, v
 
 
 def ring_forward(i, G, N, kind, scale, q_i, k_shards, v_shards, o_acc, lse_acc, stream=None, window=0, N_blk=0):

@@ -517,6 +517,7 @@ def test_calls_of_several_steps_check_every_step_before_anything_runs(lib):
         if shape is not None:
             shapes[2].head_dim = shape
         vs = (lib.burst_tensor_t * n)(good, good, good)
+        shapes, ks, vs, fs = (bytes(x) for x in (shapes, ks, vs, fs))
         return (raw.burst_attn_steps_fwd(count, shapes, masks, C.byref(good), ks, vs, C.byref(f32), C.byref(vec), None),
                 raw.burst_attn_steps_bwd(count, shapes, masks, C.byref(good), ks, vs, C.byref(good), C.byref(vec), C.byref(vec),
                                          C.byref(f32), fs if dk else None, fs, 7, None))
@@ -528,3 +529,17 @@ def test_calls_of_several_steps_check_every_step_before_anything_runs(lib):
     assert call(mask=63) == (lib.BURST_ERR_INVALID_ARG,) * 2
     assert call(shape=96) == (lib.BURST_ERR_UNSUPPORTED,) * 2
     assert call(k=off, dk=False)[1] == lib.BURST_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("kind", ["full", "causal", "zigzag", "striped", "block_striped"])
+def test_ring_masks_are_the_masks_of_the_steps_in_ring_order(lib, kind):
+    G, N = 4, 4 * 2 * 96
+    for i in range(G):
+        for window in (0, 50) if kind != "full" else (0,):
+            masks = lib.burst_attn_fill_ring_masks(kind, i, G, N, 96, window)
+            for t in range(G):
+                assert bytes(masks[t]) == bytes(hp.fill_mask(lib, kind, i, (i - t) % G, G, N, window, 96))
+    with pytest.raises(lib.BurstError):
+        lib.burst_attn_fill_ring_masks("zigzag", 0, G, N + 1)
+    with pytest.raises(lib.BurstError):
+        lib.burst_attn_fill_ring_masks("causal", G, G, N)
