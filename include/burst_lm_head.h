@@ -74,9 +74,9 @@ int burst_lm_head_loss(const burst_lm_head_shape_t* shape, const void* h_last, i
  *     (burst_lm_head_static_scratch_bytes()) is refused with BURST_ERR_SCRATCH and nothing is enqueued
  *     (64 MiB holds e.g. tile_tokens = 256 with a 32000-word vocabulary and d = 4096); choose a
  *     smaller tile_tokens or use burst_lm_head_loss.
- *   - Sequence tiles of 256 tokens are joined as far as the array reaches, which changes the order in
- *     which the fp32 sums of dW (and of a dH whose contraction is split) are taken; longer tiles give the
- *     bits of burst_lm_head_loss.
+ *   - Sequence tiles of 256 tokens get what the array holds: they are joined, and contractions are split
+ *     where few work-groups would run, which changes the order in which fp32 sums are taken; longer tiles
+ *     give the bits of burst_lm_head_loss.
  *   - The array used is that of the GPU that is current on the calling thread when the call is
  *     made; the stream must belong to that GPU.
  *   - Every call on a GPU shares that GPU's array, which keeps whatever the last call left in it

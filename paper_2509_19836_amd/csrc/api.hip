@@ -770,9 +770,10 @@ int64_t burst_lm_head_static_scratch_bytes(void) { return kStaticScratchBytes; }
 constexpr int64_t kLmShortTile = 512;
 static int64_t lm_joined_tile(const burst_lm_head_shape_t* s) {
   const int64_t asked = s->tile_tokens, n = s->n_tokens;
-  if (asked >= kLmShortTile || n <= asked) return asked;
-  int64_t most = asked;
-  while (most < n && lm_head_workspace_bytes(most + 256, s->vocab, s->d_model) <= kStaticArrayBytes) most += 256;
+  if (asked >= kLmShortTile) return asked;
+  int64_t most = asked;   // (up to four times the tokens: room for partial logits, lm_logit_splits)
+  while (most < 4 * n && lm_head_workspace_bytes(most + 256, s->vocab, s->d_model) <= kStaticArrayBytes) most += 256;
+  if (n <= most) return most;
   const int64_t tiles = (n + most - 1) / most;
   return ((n + tiles - 1) / tiles + 255) / 256 * 256;
 }

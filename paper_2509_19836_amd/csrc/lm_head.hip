@@ -237,6 +237,20 @@ int lm_dh_splits(const LmHeadParams& p, int TM, int TN) {
   return (int)std::max<int64_t>(s, 1);
 }
 
+// The logits contract over the hidden dimension and have few output tiles when the sequence tile or the vocabulary is short:
+// the k-tiles are then dealt to as many work-groups per output tile as fill the CUs, which leave partial logits, one
+// array of the tile's rows (up to a multiple of 256) behind the other in the logits buffer, for lm_loss_dlogits_kernel to add
+// up.  Bounds: that buffer, 16 k-tiles a part, and kLmSplitWords words times parts, beyond which the parts ask for W faster
+// than memory gives it (a part's k-tile takes 1.5 us, its 32 KiB of W at 5 TB/s over all of them as long).  The whole call, us,
+// without and with: d = 4096, 100 tokens: 8000 words (4 parts) 150, 108, 32000 (2, against the bound) 353, 366; 300 x 16000 (2)
+// 261, 241; 700 x 8000, d = 5120 (2) 259, 230; 64 x 20000, d = 2048 (2) 131, 119; 70 x 30000 (2) 368, 342; without a workspace
+// 200 x 20000 (3) 315, 248, 500 x 10000 (3) 255, 189.
+constexpr int kLmSplitWords = 60000;
+int lm_logit_splits(const LmHeadParams& p, int TM, int TN) {
+  const int64_t s = std::min<int64_t>({kLmOneRound / (TM * TN), p.tile_tokens / (TN * kLmBN), p.d_model / (16 * kLmBK), kLmSplitWords / p.vocab});
+  return (int)std::max<int64_t>(s, 1);
+}
+
 // (max, sum of exp(x - max)) pairs combine like the log-sum-exp merge of the attention forward.
 __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l2) {
   const float mm = fmaxf(m, m2);
@@ -247,22 +261,32 @@ __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l
 // ---------------------------------------------------------------------------------------------
 // 1. Logits^T tile (rows: words, columns: tokens of the sequence tile), Alg. 3 forward sweep.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN) {
+__global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
   using G = LmGemm<false>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn, split;
-  if (!lm_tile(blockIdx.x, TM, TN, 1, tm, tn, split)) return;
+  if (!lm_tile(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = p.d_model / kLmBK;
+  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk_all = p.d_model / kLmBK;
+  const int kt0 = nk_all * split / splits, nk = nk_all * (split + 1) / splits - kt0, k0 = kt0 * kLmBK;
   G::OpA a;
   G::OpB b;
-  a.init(p.w, p.ld_w, p.vocab, m0, nk, wave, lane);
-  b.init(p.h + (int64_t)s0 * p.ld_h, p.ld_h, n_rows, n0, nk, wave, lane);
+  a.init(p.w + k0, p.ld_w, p.vocab, m0, nk, wave, lane);
+  b.init(p.h + (int64_t)s0 * p.ld_h + k0, p.ld_h, n_rows, n0, nk, wave, lane);
   G gemm;
   gemm.run(smem, a, b, nk, wm, wn, wave, lane);
 
   const int word0 = m0 + wm * 64 + 4 * g;              // first word of the lane
+  if (splits > 1) {
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      float* dst = p.logits + ((int64_t)split * TN * kLmBN + n0 + wn * 64 + 16 * nb + r) * p.v_pad + word0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb];
+    }
+    return;
+  }
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) {
     const int token = n0 + wn * 64 + 16 * nb + r;      // < tile_tokens: the tile count covers n_rows only
@@ -302,20 +326,50 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p
 //    two lines of the backward sweep).  Rows n_rows .. gridDim.x-1 are zero-filled: they pad the
 //    contraction of the dW GEMM.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void lm_loss_dlogits_kernel(LmHeadParams p, int s0, int n_rows, int want_grad) {
-  __shared__ float red_m[4], red_l[4];
+// SPLIT: the logits come as `splits` partial sums, `part` rows apart; their sum goes where the first of them was.
+constexpr int lm_loss_threads(bool split) { return split ? 1024 : 256; }   // (few tokens: more of a row's loads in flight)
+template <bool SPLIT>
+__global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel(LmHeadParams p, int s0, int n_rows, int want_grad, int splits, int part) {
+  constexpr int NT = lm_loss_threads(SPLIT), STEP = 8 * NT;
+  __shared__ float red_m[NT / 64], red_l[NT / 64], target;
   const int i = blockIdx.x, tid = threadIdx.x;
   __bf16* drow = p.dlogits + (int64_t)i * p.v_pad;
   const bf16x8 zero8 = {(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
   if (i >= n_rows) {
-    for (int j = tid * 8; j < p.v_pad; j += 2048) *reinterpret_cast<bf16x8*>(drow + j) = zero8;
+    for (int j = tid * 8; j < p.v_pad; j += STEP) *reinterpret_cast<bf16x8*>(drow + j) = zero8;
     return;
   }
   float m = -INFINITY, l = 0.f;
-  const int n_part = p.v_pad / 128;
-  for (int pp = tid; pp < n_part; pp += 256) {
-    const float2 x = p.part[(int64_t)pp * p.tile_tokens + i];
-    lm_combine(m, l, x.x, x.y);
+  float* lrow = p.logits + (int64_t)i * p.v_pad;
+  const int64_t y = p.y[s0 + i];
+  const bool ok = y >= 0 && y < p.vocab;
+  if (SPLIT) {
+    for (int j = tid * 8; j < p.v_pad; j += STEP) {
+      f32x4 x[2] = {*reinterpret_cast<const f32x4*>(lrow + j), *reinterpret_cast<const f32x4*>(lrow + j + 4)};
+      for (int s = 1; s < splits; ++s) {
+        const float* other = lrow + (int64_t)s * part * p.v_pad + j;
+        x[0] += *reinterpret_cast<const f32x4*>(other);
+        x[1] += *reinterpret_cast<const f32x4*>(other + 4);
+      }
+      *reinterpret_cast<f32x4*>(lrow + j) = x[0];
+      *reinterpret_cast<f32x4*>(lrow + j + 4) = x[1];
+      float mx = -INFINITY, sum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (j + e == y) target = x[e / 4][e % 4];
+        if (j + e < p.vocab) mx = fmaxf(mx, x[e / 4][e % 4]);   // padding words stay out of Lse
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (j + e < p.vocab) sum += __expf(x[e / 4][e % 4] - mx);
+      if (j < p.vocab) lm_combine(m, l, mx, sum);
+    }
+  } else {
+    const int n_part = p.v_pad / 128;
+    for (int pp = tid; pp < n_part; pp += NT) {
+      const float2 x = p.part[(int64_t)pp * p.tile_tokens + i];
+      lm_combine(m, l, x.x, x.y);
+    }
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) lm_combine(m, l, __shfl_xor(m, off), __shfl_xor(l, off));
@@ -327,23 +381,20 @@ __global__ __launch_bounds__(256) void lm_loss_dlogits_kernel(LmHeadParams p, in
   m = red_m[0];
   l = red_l[0];
 #pragma unroll
-  for (int w = 1; w < 4; ++w) lm_combine(m, l, red_m[w], red_l[w]);
+  for (int w = 1; w < NT / 64; ++w) lm_combine(m, l, red_m[w], red_l[w]);
   const float lse = m + __logf(l);
-  const int64_t y = p.y[s0 + i];
-  const bool ok = y >= 0 && y < p.vocab;
-  const float* lrow = p.logits + (int64_t)i * p.v_pad;
   if (tid == 0) {
-    p.loss[s0 + i] = ok ? lse - lrow[ok ? y : 0] : 0.f;
+    p.loss[s0 + i] = ok ? lse - (SPLIT ? target : lrow[ok ? y : 0]) : 0.f;
     if (p.lse) p.lse[s0 + i] = lse;
   }
   if (!want_grad) return;
   if (!ok) {
-    for (int j = tid * 8; j < p.v_pad; j += 2048) *reinterpret_cast<bf16x8*>(drow + j) = zero8;
+    for (int j = tid * 8; j < p.v_pad; j += STEP) *reinterpret_cast<bf16x8*>(drow + j) = zero8;
     return;
   }
   const int yi = (int)y;
   const float gs = p.grad_scale;
-  for (int j = tid * 8; j < p.v_pad; j += 2048) {
+  for (int j = tid * 8; j < p.v_pad; j += STEP) {
     const f32x4 x0 = *reinterpret_cast<const f32x4*>(lrow + j), x1 = *reinterpret_cast<const f32x4*>(lrow + j + 4);
     bf16x8 out;
 #pragma unroll
@@ -504,9 +555,14 @@ hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {
   for (int s0 = 0; s0 < p.n_tokens; s0 += p.tile_tokens) {
     const int n_rows = p.n_tokens - s0 < p.tile_tokens ? p.n_tokens - s0 : p.tile_tokens;
     const int TT = (n_rows + kLmBM - 1) / kLmBM, TTn = (n_rows + kLmBN - 1) / kLmBN, k_rows = (n_rows + 63) / 64 * 64;
-    hipLaunchKernelGGL(lm_logits_kernel, dim3(lm_grid(TV, TTn)), dim3(kLmThreads), kLdsLogits, stream, p, s0,
-                       n_rows, TV, TTn);
-    hipLaunchKernelGGL(lm_loss_dlogits_kernel, dim3(want_grad ? k_rows : n_rows), dim3(256), 0, stream, p, s0, n_rows, want_grad);
+    const int parts = lm_logit_splits(p, TV, TTn);
+    hipLaunchKernelGGL(lm_logits_kernel, dim3(lm_grid(TV, TTn, parts)), dim3(kLmThreads), kLdsLogits, stream, p, s0,
+                       n_rows, TV, TTn, parts);
+    const dim3 loss_grid(want_grad ? k_rows : n_rows);
+    if (parts > 1)
+      hipLaunchKernelGGL((lm_loss_dlogits_kernel<true>), loss_grid, dim3(lm_loss_threads(true)), 0, stream, p, s0, n_rows, want_grad, parts, TTn * kLmBN);
+    else
+      hipLaunchKernelGGL((lm_loss_dlogits_kernel<false>), loss_grid, dim3(lm_loss_threads(false)), 0, stream, p, s0, n_rows, want_grad, 1, 0);
     if (p.dh) {
       const int splits = lm_dh_splits(p, TT, TD);
       hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD, splits)), dim3(kLmThreads), kLdsGrad, stream, p, s0, n_rows, TT, TD,
