@@ -2,20 +2,21 @@
 // optionally folded into the running (O_i, Lse_i) in the epilogue (forward algorithm).
 //
 // One work-group = 8 waves = 256 query rows of one (batch, head); wave w owns rows [32w, 32w+32), two waves per
-// SIMD.  The key/value chunk streams through LDS in tiles of 64 rows.  Everything is computed transposed so that a
-// lane always owns query rows (two of them):
+// SIMD.  The key/value chunk (or several, of consecutive ring steps) streams through LDS in tiles of 64 rows.  Everything is
+// computed transposed so that a lane always owns query rows (two of them):
 //   S^T = K Q^T   (A = K rows from LDS, B = Q held in registers),
 //   P^T = exp2(..) in the accumulator registers, packed to bf16 and fed straight back as the B operand of
 //   O^T = V^T P^T (A = V columns via transposing LDS reads).
 //
 // What bounds it at d = 128: the matrix pipe and the vector unit need about the same time for a tile (64 MFMAs of
-// 16 clocks; 131 vector instructions, of them 32 exponentials, about 1000 clocks for a wave alone), and the chip
+// 16 clocks; 117 vector instructions, of them 32 exponentials, about 900 clocks for a wave alone), and the chip
 // holds a power limit on top.  So the two waves of a SIMD take the phases in turn, and the products use
 // 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed, random operands: 2050-2110 against
 // 1840-1900 TFLOP/s; with operands that change from MFMA to MFMA 1900-1934 against 1786-1817).
 // Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
-// 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one card.  Counters on another: 115 ms,
-// matrix pipe 63 % busy at 1.85 GHz.
+// 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one card.  Counters: matrix pipe 66 % busy
+// at 1.86 GHz.  What is left, 16384 x 16384 rows, 1727 us: with half the LDS operand reads 1649, without exponentials 1666,
+// without any vector work 1614, with both halves of that gone 1482; on zeros, which draw less, 1456.
 // At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -25,8 +26,8 @@ namespace burst {
 
 constexpr int kFwdWaves = 8, kFwdBQ = 32 * kFwdWaves;   // query rows per work-group: 32 per wave
 
-// BLK: with a block-wise sparse mask; MULTI: more than one step.  (Kernel arguments lie in host memory: what a single step needs
-// is asked for at once at the start, where steps picked by a variable are a second round trip, 1-2 us of a launch.)
+// BLK: with a block-wise sparse mask; MULTI: more than one step.  (A single step's arguments are asked for at once at the start;
+// steps picked by a variable are a second round trip, 1-2 us of a launch: dK/dV of three steps of 1500 rows 241, 246 us.)
 template <int D, int NW, bool BLK, bool MULTI>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdParams p) {
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
@@ -72,6 +73,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // running maximum, what a score must exceed for a rescale, c * maximum (0 while there is none), running sum
   float m_run[NB] = {-INFINITY, -INFINITY}, limit[NB] = {-INFINITY, -INFINITY}, msub[NB] = {0.f, 0.f};
   f32x4 l_run[NB] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // four independent chains
+  float m_top[NB] = {-INFINITY, -INFINITY};   // MULTI: largest maximum of the steps so far
 
   // Positions of the work-group's and the wave's query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
@@ -120,6 +122,10 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     const MaskDev mk = st.mask;
     const int sk = st.sk;
     windowed = mk.window != kNoWindow;
+    if (step > 0) {   // a step's maximum is its own (see softmax)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) limit[nb] = -INFINITY;
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
     tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
@@ -159,10 +165,23 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
           float m_new = fmaxf(mx[nb], __shfl_xor(mx[nb], 16, 64));
-          m_new = fmaxf(m_run[nb], fmaxf(m_new, __shfl_xor(m_new, 32, 64)));
+          m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
+          bool fresh = false;   // the row has seen no key of this step, and sees none in this tile
+          if (MULTI) {
+            // A row's P at its maximum is one and rounds to bf16 exactly.  A step that kept the maximum of the steps
+            // before would lose that: 8 steps of 512 rows, window 700, error of O against 64 bits 1.64e-3 so, 1.17e-3
+            // with a maximum for each step.  It is let down to 2^-12 of the largest at most: a step below that weighs little, and
+            // fp32 keeps its headroom (with 2^-6 heads scaled by 0.5 to 2 had 1 % more error).
+            m_top[nb] = fmaxf(m_top[nb], m_new);
+            const bool first = limit[nb] == -INFINITY;
+            fresh = first && m_new == -INFINITY;
+            m_new = fresh ? m_run[nb] : fmaxf(m_new, first ? m_top[nb] - 2.f * slack : m_run[nb]);
+          } else {
+            m_new = fmaxf(m_run[nb], m_new);
+          }
           const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run[nb] - m_new));
           m_run[nb] = m_new;
-          limit[nb] = m_new + slack;
+          limit[nb] = fresh ? -INFINITY : m_new + slack;
           msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
           l_run[nb] *= alpha;
 #pragma unroll
