@@ -29,8 +29,8 @@ PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA: 256 CU x 4 SIMD x 1024 flo
 # process, so the figure is the profiled one: it is reported with the profile it came from and its date,
 # and only for the workload that was profiled.
 PROFILED_TRAFFIC = {
-    2: {"bytes": 1.685e+09, "profile": "profiles/bench_config2_pmc_hbm_traffic.md", "taken": "with the kernels and launch plan as committed (direct LDS loads, 32768-row ranges)"},
-    5: {"bytes": 5.776e+10, "profile": "profiles/bench_config5_pmc_hbm_traffic.md", "taken": "with the kernels and launch plan as committed (direct LDS loads, 32768-row ranges)"},
+    2: {"bytes": 1.675e+09, "profile": "profiles/bench_config2_pmc_hbm_traffic.md", "taken": "with the kernels and launch plan as committed (direct LDS loads, 32768-row ranges)"},
+    5: {"bytes": 5.756e+10, "profile": "profiles/bench_config5_pmc_hbm_traffic.md", "taken": "with the kernels and launch plan as committed (direct LDS loads, 32768-row ranges)"},
 }
 # --lm-head, default shape: bytes per call over all its launches (profiles/bench_lm_head_kernel_trace_and_counters.md)
 PROFILED_LM_HEAD_TRAFFIC_BYTES = 2.75e+10
