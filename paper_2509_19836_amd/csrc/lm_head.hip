@@ -359,9 +359,12 @@ __global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel
         if (j + e == y) target = x[e / 4][e % 4];
         if (j + e < p.vocab) mx = fmaxf(mx, x[e / 4][e % 4]);   // padding words stay out of Lse
       }
+      // eight words at -inf (masked, or past the fp32 range) have no share: from zero their exponentials are zero, and a NaN
+      // among them, which the maximum leaves out, stays one
+      const float from = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (j + e < p.vocab) sum += __expf(x[e / 4][e % 4] - mx);
+        if (j + e < p.vocab) sum += __expf(x[e / 4][e % 4] - from);
       if (j < p.vocab) lm_combine(m, l, mx, sum);
     }
   } else {
