@@ -80,8 +80,13 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 // One direct load: every lane's 16 bytes at base + offset go to LDS at lds + 16 * lane.  Written as an
 // assembly statement because the compiler otherwise waits for all of them before the next LDS read; the
 // kernels wait by count themselves (wait_loads_barrier).  m0 is a reserved register, which the compiler keeps no
-// value in; nothing else in these kernels uses it.  A load that goes to LDS needs one wait state behind a scalar write of m0;
-// it had four, each up to four clocks between two MFMAs: dQ 2423 -> 2399 us, dK/dV 3428 -> 3377 (16384 rows, 32 heads, d = 128).
+// value in; nothing else in these kernels uses it.
+// The compiler does not look for hazards inside the statement.  A load that goes to LDS needs one wait state behind a scalar
+// write of m0, the s_nop (with four, each up to four clocks between two MFMAs: dQ 2423 us instead of 2399, dK/dV 3428 instead of
+// 3377; 16384 rows, 32 heads, d = 128).  And it must stay five behind a vector instruction that wrote its address, as
+// v_readfirstlane_b32 or the return of a spilled scalar register from a lane do; the statement has two.  The addresses come from
+// scalar arithmetic, and the build refuses a kernel in which one does not (build.check_load_addresses).  A scalar copy of the
+// address in place of the s_nop would do without the check, at 0.5 % of every case.
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
