@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <atomic>
+#include <exception>
 #include <mutex>
 
 #include "../../include/burst_attn.h"
@@ -206,6 +207,10 @@ int static_scratch_of_current_device(void** out) {
     if (_st != BURST_OK) return _st; \
   } while (0)
 
+// Entry points that keep lists of steps or ranges: no exception leaves them (lists are all that can throw).
+#define BURST_NO_THROW \
+  catch (const std::exception&) { return hip_fail(hipErrorOutOfMemory); }
+
 // The parts of a forward call's arguments: what a step brings, and what belongs to the query chunk.
 int check_fwd_step(const burst_shape_t* shape, const burst_mask_t* mask, const burst_tensor_t* k, const burst_tensor_t* v,
                    FwdStep* st) {
@@ -342,7 +347,7 @@ extern "C" {
 int burst_attn_step_fwd(const burst_shape_t* shape, const burst_mask_t* mask, const burst_tensor_t* q,
                         const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* o_part,
                         const burst_rowvec_t* lse_part, const burst_tensor_t* o_acc,
-                        const burst_rowvec_t* lse_acc, void* hip_stream) {
+                        const burst_rowvec_t* lse_acc, void* hip_stream) try {
   FwdParams p;
   FwdStep st;
   BURST_TRY(check_fwd_step(shape, mask, k, v, &st));
@@ -357,11 +362,11 @@ int burst_attn_step_fwd(const burst_shape_t* shape, const burst_mask_t* mask, co
     e = launch_steps_fwd(p, &st, 1, stream);
   }
   return e == hipSuccess ? BURST_OK : hip_fail(e);
-}
+} BURST_NO_THROW
 
 int burst_attn_steps_fwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks, const burst_tensor_t* q,
                          const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* o_acc,
-                         const burst_rowvec_t* lse_acc, void* hip_stream) {
+                         const burst_rowvec_t* lse_acc, void* hip_stream) try {
   if (n_steps < 0 || (n_steps > 0 && (!shapes || !masks || !k || !v))) return BURST_ERR_INVALID_ARG;
   if (n_steps > BURST_MAX_STEPS) return BURST_ERR_UNSUPPORTED;
   std::vector<FwdParams> p(n_steps);
@@ -389,7 +394,7 @@ int burst_attn_steps_fwd(int32_t n_steps, const burst_shape_t* shapes, const bur
     if (e != hipSuccess) return hip_fail(e);
   }
   return BURST_OK;
-}
+} BURST_NO_THROW
 
 int burst_attn_lse_merge(const burst_shape_t* shape, const burst_tensor_t* o_acc, const burst_rowvec_t* lse_acc,
                          const burst_tensor_t* o_part, const burst_rowvec_t* lse_part,
@@ -436,19 +441,19 @@ int burst_attn_step_bwd(const burst_shape_t* shape, const burst_mask_t* mask, co
                         const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* d_o,
                         const burst_rowvec_t* lse, const burst_rowvec_t* d, const burst_tensor_t* dq,
                         const burst_tensor_t* dk, const burst_tensor_t* dv, int32_t accumulate_flags,
-                        void* hip_stream) {
+                        void* hip_stream) try {
   BwdParams p;
   BwdStep st;
   BURST_TRY(check_bwd_step(shape, mask, k, v, dk, dv, &st));
   BURST_TRY(check_bwd(shape, q, d_o, lse, d, dq, dk != nullptr, accumulate_flags, &p));
   const hipError_t e = run_bwd(p, &st, 1, (hipStream_t)hip_stream);
   return e == hipSuccess ? BURST_OK : hip_fail(e);
-}
+} BURST_NO_THROW
 
 int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks, const burst_tensor_t* q,
                          const burst_tensor_t* k, const burst_tensor_t* v, const burst_tensor_t* d_o, const burst_rowvec_t* lse,
                          const burst_rowvec_t* d, const burst_tensor_t* dq, const burst_tensor_t* dk, const burst_tensor_t* dv,
-                         int32_t accumulate_flags, void* hip_stream) {
+                         int32_t accumulate_flags, void* hip_stream) try {
   if (n_steps < 0 || (n_steps > 0 && (!shapes || !masks || !k || !v))) return BURST_ERR_INVALID_ARG;
   if (n_steps > BURST_MAX_STEPS) return BURST_ERR_UNSUPPORTED;
   std::vector<BwdParams> p(n_steps);
@@ -487,7 +492,7 @@ int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const bur
     if (e != hipSuccess) return hip_fail(e);
   }
   return BURST_OK;
-}
+} BURST_NO_THROW
 
 static int fill_common(int32_t dev_i, int32_t shard_j, int32_t G, int64_t N, burst_mask_t* out) {
   if (!out || G < 1 || dev_i < 0 || dev_i >= G || shard_j < 0 || shard_j >= G || N < 0) return BURST_ERR_INVALID_ARG;
@@ -663,13 +668,13 @@ int burst_attn_set_chunk_rows(int32_t rows) {
   return rows < 256 ? 256 : rows;
 }
 
-int burst_attn_chunk_plan(const burst_mask_t* mask, int32_t query_axis, int32_t max_ranges, int64_t* out) {
+int burst_attn_chunk_plan(const burst_mask_t* mask, int32_t query_axis, int32_t max_ranges, int64_t* out) try {
   if (!mask || !out || max_ranges < 0 || mask->q_nseg < 1 || mask->k_nseg < 1) return BURST_ERR_INVALID_ARG;
   const int64_t sq = mask->q_nseg * mask->q_seg_len, sk = mask->k_nseg * mask->k_seg_len;
   MaskDev mk;
   BURST_TRY(check_mask(mask, sq, sk, &mk));
   return chunk_plan(mk, (int)sq, (int)sk, query_axis != 0, max_ranges, out);
-}
+} BURST_NO_THROW
 
 int burst_attn_mfma_probe(int32_t random_operands, int32_t iterations, float* sink, int64_t* flops_out,
                           void* hip_stream) {

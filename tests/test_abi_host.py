@@ -4,6 +4,8 @@ anything could reach a GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -543,3 +545,26 @@ def test_ring_masks_are_the_masks_of_the_steps_in_ring_order(lib, kind):
         lib.burst_attn_fill_ring_masks("zigzag", 0, G, N + 1)
     with pytest.raises(lib.BurstError):
         lib.burst_attn_fill_ring_masks("causal", G, G, N)
+
+
+def test_calls_that_run_out_of_host_memory_return_an_error(lib):
+    """No exception leaves the C entry: in a process of its own whose address space has no room for the list of the steps."""
+    code = """
+import ctypes as C, resource, sys
+from paper_2509_19836_amd import binding as lib
+n, d = lib.BURST_MAX_STEPS, 64
+good, f32 = (lib.burst_tensor_t(4096, t, 0, 64 * 2 * d, 2 * d, d) for t in (lib.BURST_BF16, lib.BURST_F32))
+vec = lib.burst_rowvec_t(4096, 128, 64)
+shapes = bytes((lib.burst_shape_t * n)(*[lib.shape(1, 2, 2, d, 64, 64, 0.125)] * n))
+masks = (lib.burst_mask_t * n)(*[lib.burst_attn_fill_contiguous_mask(0, 0, 1, 64, False)] * n)
+ks, fs = bytes((lib.burst_tensor_t * n)(*[good] * n)), bytes((lib.burst_tensor_t * n)(*[f32] * n))
+raw, ref = lib.raw(), C.byref
+pages = int(open("/proc/self/statm").read().split()[0])
+resource.setrlimit(resource.RLIMIT_AS, (pages * resource.getpagesize() + 65536,) * 2)
+status = (raw.burst_attn_steps_fwd(n, shapes, masks, ref(good), ks, ks, ref(f32), ref(vec), None), raw.burst_attn_last_hip_error(),
+          raw.burst_attn_steps_bwd(n, shapes, masks, ref(good), ks, ks, ref(good), ref(vec), ref(vec), ref(f32), fs, fs, 7, None),
+          raw.burst_attn_last_hip_error())
+sys.exit(0 if status == (lib.BURST_ERR_HIP, 2, lib.BURST_ERR_HIP, 2) else 1)   # 2: hipErrorOutOfMemory
+"""
+    env = dict(os.environ, MALLOC_MMAP_THRESHOLD_="65536", PYTHONPATH=ROOT)   # (large blocks never come out of free heap)
+    assert subprocess.run([sys.executable, "-c", code], env=env, cwd=ROOT, stderr=subprocess.DEVNULL).returncode == 0
