@@ -12,6 +12,7 @@
 #include "../../include/burst_attn_diag.h"
 #include "../../include/burst_lm_head.h"
 #include "kernels.hpp"
+#include "spans.hpp"
 
 namespace burst {
 // Rows of a streamed axis per launch of a step kernel (kernels.hpp: chunk_ranges); process-wide.
@@ -325,10 +326,6 @@ bool same_queries(const Params& p, const Step& s, const Params& p2, const Step& 
          !s.mask.blk && !s2.mask.blk;
 }
 
-// Addresses from the first to the last element (empty: begin == end).  Overlapping spans may still name different elements.
-struct Span {
-  uintptr_t begin, end;
-};
 Span span_of(const TensorDev& t, int64_t batch, int64_t rows, int64_t heads, int64_t head_dim) {
   if (!t.ptr || batch == 0 || rows == 0) return Span{0, 0};
   const int64_t last = (batch - 1) * t.sb + (rows - 1) * t.ss + (heads - 1) * t.sh + head_dim;
@@ -338,7 +335,6 @@ Span span_of(const RowvecDev& t, int64_t batch, int64_t heads, int64_t rows) {
   if (!t.ptr || rows == 0) return Span{0, 0};
   return Span{(uintptr_t)t.ptr, (uintptr_t)t.ptr + (uintptr_t)((batch - 1) * t.sb + (heads - 1) * t.sh + rows) * 4};
 }
-bool overlap(const Span& a, const Span& b) { return a.begin < b.end && b.begin < a.end; }
 
 }  // namespace
 
@@ -465,21 +461,17 @@ int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const bur
   for (int i = 0, end; i < n_steps; i = end) {
     for (end = i + 1; end < n_steps && same_queries(p[i], st[i], p[end], st[end]);) ++end;
     if (i > 0) p[i].acc_dq = 1;
-    // What a step writes must be nothing that another one reads or writes
+    // what a step writes must be nothing that another one reads or writes
     bool apart = true;
-    for (int x = i; x < end && apart; ++x)
-      for (int y = i; y < end && apart; ++y) {
-        if (x == y) continue;
-        const Span writes[3] = {span_of(st[x].dk, p[i].batch, st[x].sk, p[i].kv_heads, p[i].head_dim),
-                                span_of(st[x].dv, p[i].batch, st[x].sk, p[i].kv_heads, p[i].head_dim),
-                                span_of(p[i].dq, p[i].batch, p[i].sq, p[i].q_heads, p[i].head_dim)};
-        const Span others[4] = {span_of(st[y].dk, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
-                                span_of(st[y].dv, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
-                                span_of(st[y].k, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim),
-                                span_of(st[y].v, p[i].batch, st[y].sk, p[i].kv_heads, p[i].head_dim)};
-        for (const Span& w : writes)
-          for (const Span& o : others) apart = apart && !overlap(w, o);
-      }
+    if (end - i > 1) {
+      std::vector<Use> uses;
+      uses.reserve(4 * (end - i) + 1);
+      uses.push_back({span_of(p[i].dq, p[i].batch, p[i].sq, p[i].q_heads, p[i].head_dim), -1, true});
+      for (int x = i; x < end; ++x)
+        for (const TensorDev* t : {&st[x].dk, &st[x].dv, &st[x].k, &st[x].v})
+          uses.push_back({span_of(*t, p[i].batch, st[x].sk, p[i].kv_heads, p[i].head_dim), x, t == &st[x].dk || t == &st[x].dv});
+      apart = steps_apart(uses);
+    }
     hipError_t e = hipSuccess;
     if (apart) {
       e = run_bwd(p[i], &st[i], end - i, (hipStream_t)hip_stream);
