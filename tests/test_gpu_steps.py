@@ -318,3 +318,32 @@ def test_steps_without_keys_in_one_call(lib, empty, flags):
     if len(empty) == G:
         assert bool((o[0] == 0.5).all()) and bool((lse[0] == 1.0).all())
         assert bool((g["dq"] == (1.0 if flags else 0.0)).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what", ["a value is infinite", "a score is -inf", "all scores of a step are -inf", "a score is inf"])
+def test_infinities_in_one_call_as_in_steps_one_by_one(lib, what, d):
+    import torch
+    G, n, H = 4, 200, 2
+    for t in range(G):     # the step it is in
+        print(what, d, t, flush=True)
+        s = _state(lib, (("causal", G, G - 1, n, 0, 0), (H, H), d, 1, 32768))
+        s["q"][..., 0] = 1.0
+        if what == "a value is infinite":
+            s["v"][t][0, 7, 0, 3], s["v"][t][0, 9, 1, 5] = math.inf, -math.inf
+        elif what == "a score is inf":
+            s["k"][t][0, 7, :, 0] = math.inf
+        else:
+            s["k"][t][0, slice(None) if what.startswith("all") else 7, :, 0] = -math.inf
+        o = [s["new"](H) for _ in range(2)]
+        lse = [torch.full((1, H, n), -math.inf, device="cuda") for _ in range(2)]
+        lib.burst_attn_steps_fwd(s["shapes"], s["masks"], s["q"], s["k"], s["v"], o[0], lse[0])
+        for i in range(G):
+            lib.burst_attn_step_fwd(s["shapes"][i], s["masks"][i], s["q"], s["k"][i], s["v"][i], o_acc=o[1], lse_acc=lse[1])
+        torch.cuda.synchronize()
+        for x, y, tol in ((o[0], o[1], FWD_TOL), (lse[0], lse[1], 1e-5)):
+            assert torch.equal(torch.isnan(x), torch.isnan(y))
+            finite = torch.isfinite(y)
+            assert torch.equal(x[~finite & ~torch.isnan(y)], y[~finite & ~torch.isnan(y)])
+            if bool(finite.any()):
+                _close(x[finite], y[finite], tol)
