@@ -135,6 +135,7 @@ int burst_attn_step_fwd(const burst_shape_t* shape, const burst_mask_t* mask,
  * are resident): folded into (o_acc, lse_acc) as n_steps calls of burst_attn_step_fwd in this order would, up to rounding,
  * in as few launches as the steps allow.  shapes, masks, k and v are arrays of n_steps entries; batch, q_heads, head_dim and
  * sq must fit q and the running state in each.  All steps are checked before the first is enqueued.  At most BURST_MAX_STEPS.
+ * Steps run one by one where the memory between the first and the last element of a running state meets that of a k or v.
  */
 #define BURST_MAX_STEPS 1024
 int burst_attn_steps_fwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
@@ -185,6 +186,9 @@ int burst_attn_step_bwd(const burst_shape_t* shape, const burst_mask_t* mask,
  * Consecutive backward steps of one query chunk whose key/value chunks are all at hand: as n_steps calls of
  * burst_attn_step_bwd, up to rounding, in as few launches as the steps allow.  shapes, masks, k, v, dk and dv are arrays of
  * n_steps entries (dk and dv NULL to skip them).  dq receives the sum over the steps, on top of its contents with BURST_ACC_DQ.
+ * Steps run one by one, with the same results and without the gain, where the memory between the first and the last element of
+ * what a step writes meets that of what another one reads or writes.  That is so for gradients that interleave, as the shards of
+ * one [batch, seq, heads, head_dim] tensor do with batch > 1; with a batch of one, or a tensor for each shard, they are apart.
  */
 int burst_attn_steps_bwd(int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
                          const burst_tensor_t* q, const burst_tensor_t* k, const burst_tensor_t* v,

@@ -67,16 +67,17 @@ int burst_lm_head_loss(const burst_lm_head_shape_t* shape, const void* h_last, i
  * The same computation for callers that cannot allocate device memory or hand over a workspace of
  * their own: code running under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Arguments, results and errors are those of burst_lm_head_loss without the workspace
- * pair: the scratch memory is an array built into the library's code object, 256 MiB per GPU, present
- * from the moment the library is loaded until the process ends.  The call allocates nothing and
- * frees nothing, on the host or on the device.
- *   - A shape whose burst_lm_head_workspace_bytes() exceeds 64 MiB
- *     (burst_lm_head_static_scratch_bytes()) is refused with BURST_ERR_SCRATCH and nothing is enqueued
- *     (64 MiB holds e.g. tile_tokens = 256 with a 32000-word vocabulary and d = 4096); choose a
- *     smaller tile_tokens or use burst_lm_head_loss.
+ * pair: the scratch memory is an array built into the library's code object, 256 MiB on a GPU from the
+ * first call there until the process ends (the HIP runtime loads this code object, by default, when it is
+ * first needed, under capture too; a process that makes no such call has none of it).  The call itself
+ * allocates nothing and frees nothing, on the host or on the device.
+ *   - A shape whose burst_lm_head_workspace_bytes() exceeds 64 MiB is refused with BURST_ERR_SCRATCH and
+ *     nothing is enqueued (64 MiB holds e.g. tile_tokens = 256 with a 32000-word vocabulary and d = 4096);
+ *     choose a smaller tile_tokens or use burst_lm_head_loss.  burst_lm_head_static_scratch_bytes()
+ *     returns this limit, not the size of the array, whose rest is there to join short tiles.
  *   - Sequence tiles of 256 tokens get what the array holds: they are joined, and contractions are split
  *     where few work-groups would run, which changes the order in which fp32 sums are taken; longer tiles
- *     give the bits of burst_lm_head_loss.
+ *     are taken as asked for and give the bits of burst_lm_head_loss.
  *   - The array used is that of the GPU that is current on the calling thread when the call is
  *     made; the stream must belong to that GPU.
  *   - Every call on a GPU shares that GPU's array, which keeps whatever the last call left in it

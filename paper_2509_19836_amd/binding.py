@@ -344,6 +344,7 @@ def burst_lm_head_loss(shp, h_last, w_head, y, loss, workspace, lse=None, d_h=No
 
 
 def burst_lm_head_static_scratch_bytes():
+    """The workspace that a shape may need for burst_lm_head_loss_noalloc (the array itself is larger)."""
     return _lib.burst_lm_head_static_scratch_bytes()
 
 

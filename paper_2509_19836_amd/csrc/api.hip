@@ -179,6 +179,8 @@ int check_mask(const burst_mask_t* m, int64_t sq, int64_t sk, MaskDev* out) {
 // Scratch memory of burst_lm_head_loss_noalloc: one array per GPU, part of the loaded code object,
 // so the entry point never allocates.  The array's name is only a host-side handle: kernels get the
 // device address that hipGetSymbolAddress reports for the current device, looked up once per device.
+// The runtime puts the array on a GPU at the first call there, with this file's code object (nothing else is in it): attention
+// calls and the LM head with a workspace leave it out of memory.
 constexpr int64_t kStaticScratchBytes = (int64_t)64 << 20;   // what a shape's own tile may need
 constexpr int64_t kStaticArrayBytes = (int64_t)256 << 20;    // what is there: room to join short tiles (lm_joined_tile)
 static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
@@ -761,8 +763,9 @@ int64_t burst_lm_head_static_scratch_bytes(void) { return kStaticScratchBytes; }
 
 // Sequence tile the call without a workspace works in.  A tile of 256 tokens, what 64 MiB hold for 32000 words, gives dW four
 // k-tiles of products (6 us of a work-group) for each time it is read and written (23 us), and half-empty rounds to the
-// logits; so tiles below kLmShortTile are joined, evenly, as far as the array reaches.  (Longer ones stay as they are asked
-// for: they give the same bits as the call with a workspace.)  1000 tokens, d = 4096, 32000 words in tiles of 256 as asked
+// logits; so tiles below kLmShortTile are joined, evenly, as far as the array reaches.  As tiles are multiples of 256, those
+// are the tiles of 256.  The line is not one of speed: longer tiles, with the same short contraction in dW, stay as they are asked for
+// because they give the bits of the call with a workspace, which callers hold against each other.  1000 tokens, d = 4096, 32000 words in tiles of 256 as asked
 // for 1904 us, joined to one 784 (4096 tokens, d = 2048, 20000 words 3287, 1127; forward only, 1000 tokens, 425, 221).
 constexpr int64_t kLmShortTile = 512;
 static int64_t lm_joined_tile(const burst_lm_head_shape_t* s) {

@@ -720,7 +720,7 @@ static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
   if (e != hipSuccess || grid == 0) return e;
   constexpr int LDS = kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>;
   // a dQ work-group walks every step (three products a tile against two), a dK/dV one the heads of its group
-    const int dq_first = p.n_steps > 1 && 3 * p.n_steps > 4 * group, n_first = dq_first ? n_dq : n_dkdv;
+  const int dq_first = p.n_steps > 1 && 3 * p.n_steps > 4 * group, n_first = dq_first ? n_dq : n_dkdv;
   const bool multi = p.n_steps > 1;
   if (narrow && multi) hipLaunchKernelGGL((step_bwd_both_kernel<D, true, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
   else if (narrow) hipLaunchKernelGGL((step_bwd_both_kernel<D, false, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);

@@ -213,7 +213,8 @@ __host__ __device__ __forceinline__ void visible_rows(const MaskDev& mk, int pos
 
 // Largest of three (a NaN among them is left out, as by fmaxf).  fmaxf is not folded into it: each of its arguments that the
 // compiler cannot prove to be a quiet number costs an instruction that makes it one.  The compiler does not keep an
-// assembly statement away from an MFMA whose result it reads: mfma_results() goes before one that may follow closely.
+// assembly statement away from an MFMA whose result it reads: mfma_results() goes before one that may follow closely, or other
+// MFMAs stand between (rows_cols_stream).
 __device__ __forceinline__ float max3(float a, float b, float c) {
   float m;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));

@@ -15,8 +15,7 @@
 // 1840-1900 TFLOP/s; with operands that change from MFMA to MFMA 1900-1934 against 1786-1817).
 // Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
 // 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one card.  Counters: matrix pipe 66 % busy
-// at 1.86 GHz.  What is left, 16384 x 16384 rows, 1727 us: with half the LDS operand reads 1649, without exponentials 1666,
-// without any vector work 1614, with both halves of that gone 1482; on zeros, which draw less, 1456.
+// at 1.86 GHz, where zeros as data run at 2.24 GHz in the same clocks a tile (16384 x 16384 rows: 1727 and 1456 us).
 // At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
             // A row's P at its maximum is one and rounds to bf16 exactly.  A step that kept the maximum of the steps
             // before would lose that: 8 steps of 512 rows, window 700, error of O against 64 bits 1.64e-3 so, 1.17e-3
             // with a maximum for each step.  It is let down to 2^-12 of the largest at most: a step below that weighs little, and
-            // fp32 keeps its headroom (with 2^-6 heads scaled by 0.5 to 2 had 1 % more error).
+            // fp32 keeps its headroom, sums of P of up to 2^18 a key (with 2^-6 heads scaled by 0.5 to 2 had 1 % more error).
             m_top[nb] = fmaxf(m_top[nb], m_new);
             const bool first = limit[nb] == -INFINITY;
             fresh = first && m_new == -INFINITY;
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
     if (p.o_acc.ptr && alive) {   // a step that saw no key leaves the running state untouched
       float* lse_ptr = p.lse_acc.ptr + b * p.lse_acc.sb + hq * p.lse_acc.sh + orow;
       const float lse_old = *lse_ptr;
-      const float mm = fmaxf(lse_old, lse_cur);   // finite: lse_cur is
+      const float mm = fmaxf(lse_old, lse_cur);   // finite, or lse_cur is NaN and reaches everything below
       const float e_old = __expf(lse_old - mm), e_cur = __expf(lse_cur - mm);
       const float tot = e_old + e_cur;
       const float lse_new = mm + __logf(tot);

@@ -220,8 +220,11 @@ inline void offset_rows(TensorDev& t, int r0) { t.ptr = (char*)t.ptr + (int64_t)
 // 3621, 3579.  Beyond kShareLaunch tiles of 256 rows a step (4 per CU; key tiles of 128 rows are twice as many) there is
 // nothing to gain: 8 shards of 16384 rows, 32 heads, zigzag: forward 13753, 13778, dQ 18904, 18828, dK/dV 26695, 27106,
 // striped: 14816, 15190, 20535, 20615, 29172, 29317.
-// A step with a block mask goes alone, and a launch's walk is bounded by what stays in step in an L2, two ranges.  Steps of
-// which no query row sees anything are left out.  launch(first, end): steps [first, end) of `parts`.
+// (All without a window.  A windowed step's walks are shorter; its launches are shared by the same rule, whose line has not been
+// measured for them.)  A step with a block mask goes alone, and the walks of these launches are bounded by what stays in step in
+// an L2, two ranges.  Not so in the joint backward launch (launch_both_t), which takes up to kMaxSteps chunks of a range each: 1
+// head, 8 shards of 32768 rows, backward in calls of 1, 2 and 8 steps: full 13.42, 11.61, 11.53 ms, zigzag 9.02, 6.69, 6.87, striped
+// 11.62, 7.99, 8.87.  Steps of which no query row sees anything are left out.  launch(first, end): steps [first, end) of `parts`.
 constexpr int kShareLaunch = 1024;
 inline bool share_launch(int heads, int rows) { return (int64_t)heads * ((rows + 255) / 256) <= kShareLaunch; }
 template <class Step, class Launch>

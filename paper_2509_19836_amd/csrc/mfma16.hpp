@@ -531,12 +531,14 @@ __device__ __forceinline__ void rows_product_pair(uint32_t tile0, uint32_t tile1
 }
 
 // One stream of both: s = rows(kt) * q from zero, then o += cols(vt) * p, hook(i) behind operand i of the two.  The
-// first operands of the row-wise product come fetched, those of the second are fetched while the first runs.
+// first operands of the row-wise product come fetched, those of the second are fetched while the first runs.  s has to be the first
+// of the two: the forward kernel's max3 reads it in assembly statements, for which the compiler does not wait (common.hpp).
 template <int D, int MB, int NB, int AHEAD, class Hook = NoHook>
 __device__ __forceinline__ void rows_cols_stream(uint32_t kt, uint32_t vt, const OperandAddr<D>& ad, const bf16x8 (&q)[D / 32][NB],
                                                  f32x4 (&s)[MB][NB], const bf16x8 (&p)[MB / 2][NB], f32x4 (&o)[D / 16][NB],
                                                  const bf16x8 (&first)[AHEAD], Hook&& hook = Hook()) {
   constexpr int DB = D / 16, N1 = D / 32 * MB, N = N1 + MB / 2 * DB;
+  static_assert((N - N1) * NB >= 4, "the last of s is in its registers when the stream ends (16 wait states: mfma_results)");
   bf16x8 a[N];
   MatrixPhase prio;
 #pragma unroll

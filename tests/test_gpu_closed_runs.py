@@ -1,4 +1,4 @@
-"""Block masks with long runs of closed tiles: the cursors pass 64 tiles at a time (dK/dV) or one by one (forward, dQ).
+"""Block masks with long runs of closed tiles: the cursors of all three kernels find the open ones 64 tiles at a time.
 
 Runs of exactly 64 tiles, of 64 to 128 and of more than 128, at the start of a walk and inside it, behind which an open
 tile, the ragged last one or nothing follows; two query heads to a key head, so that a walk starts over."""

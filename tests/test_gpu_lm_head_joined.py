@@ -33,7 +33,7 @@ def test_joined_tiles_equal_the_tiles_one_by_one(lib, N, d, v, tile, dh):
         torch.cuda.synchronize()
         out[name] = [t.double().cpu().numpy() for t in (loss, lse, d_h, d_w)]
     (loss, lse, d_h, d_w), (loss0, lse0, d_h0, d_w0) = out["noalloc"], out["workspace"]
-    assert np.array_equal(loss, loss0) and np.array_equal(lse, lse0)      # a token's logits do not depend on the tile
+    assert np.array_equal(loss, loss0) and np.array_equal(lse, lse0)      # (d < 2048: the logits are not split)
     norm = np.linalg.norm
     assert norm(d_w - d_w0) <= 1e-5 * norm(d_w0)                          # fp32 sums in another order
     # dH: the contraction may be split otherwise; in bf16 a sum that lies between two numbers may go to the other one
