@@ -86,7 +86,7 @@ __device__ __forceinline__ bf16x8 zero_operand() {
 // 3377; 16384 rows, 32 heads, d = 128).  And it must stay five behind a vector instruction that wrote its address, as
 // v_readfirstlane_b32 or the return of a spilled scalar register from a lane do; the statement has two.  The addresses come from
 // scalar arithmetic, and the build refuses a kernel in which one does not (build.check_load_addresses).  A scalar copy of the
-// address in place of the s_nop would do without the check, at 0.5 % of every case.
+// address in place of the s_nop would do without the check, at 0.3-0.5 % of a case.
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
