@@ -21,7 +21,7 @@ struct Use {
 
 // Whether no step writes what another one reads or writes.  In order of their first address, a span meets an earlier one of
 // another step exactly if the furthest end of those lies behind its beginning.  (A backward call of 1024 steps up to its first launch,
-// all pairs compared: 17.5 ms; so: 2.1.)
+// all pairs compared: 16.7 ms; so: 0.6-0.9.)
 inline bool steps_apart(std::vector<Use>& uses) {
   struct Furthest {
     int step = INT32_MIN;

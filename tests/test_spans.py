@@ -45,7 +45,7 @@ def test_the_sweep_finds_what_all_pairs_find(tmp_path):
 
 def test_the_checks_of_a_call_grow_with_its_steps_and_not_with_their_pairs(lib):
     """The whole call up to its first launch, which may fail here, on addresses that belong to nothing: steps that share one buffer
-    with nobody.  8 times the steps: 8 to 16 times the time of the checks; all pairs took 60."""
+    with nobody.  16 times the steps take 25 times as long (37 on a busy machine); all pairs took 200."""
     if os.path.exists("/dev/kfd"):
         import pytest
         pytest.skip("on a machine with a GPU the call would launch")
@@ -67,4 +67,4 @@ def test_the_checks_of_a_call_grow_with_its_steps_and_not_with_their_pairs(lib):
         return best
 
     call(2)
-    assert call(1024) <= 30 * call(128)
+    assert call(1024) <= 100 * call(64)
