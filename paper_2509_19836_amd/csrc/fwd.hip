@@ -1,14 +1,14 @@
 // Forward step kernel: O_ij, Lse_cur of a query chunk against one key/value chunk (Eq. 5-6),
 // optionally folded into the running (O_i, Lse_i) in the epilogue (forward algorithm).
 //
-// One work-group = 8 waves = 256 query rows of one (batch, head); wave w owns rows [32w, 32w+32), two waves per
-// SIMD.  The key/value chunk (or several, of consecutive ring steps) streams through LDS in tiles of 64 rows.  Everything is
+// One work-group = 8 waves = 256 query rows of one (batch, head) at d = 128, 4 waves = 128 rows at d = 64; wave w owns rows
+// [32w, 32w+32).  The key/value chunk (or several, of consecutive ring steps) streams through LDS in tiles of 64 rows.  Everything is
 // computed transposed so that a lane always owns query rows (two of them):
 //   S^T = K Q^T   (A = K rows from LDS, B = Q held in registers),
 //   P^T = exp2(..) in the accumulator registers, packed to bf16 and fed straight back as the B operand of
 //   O^T = V^T P^T (A = V columns via transposing LDS reads).
 //
-// What bounds it at d = 128: the matrix pipe and the vector unit need about the same time for a tile (64 MFMAs of
+// What bounds it at d = 128, where two waves share a SIMD: the matrix pipe and the vector unit need about the same time for a tile (64 MFMAs of
 // 16 clocks; 117 vector instructions, of them 32 exponentials, about 900 clocks for a wave alone), and the chip
 // holds a power limit on top.  So the two waves of a SIMD take the phases in turn, and the products use
 // 16x16x32 MFMAs, which draw less than 32x32x16 on real data (register-fed, random operands: 2050-2110 against
@@ -16,21 +16,35 @@
 // Tiles arrive by direct global -> LDS loads: no staging registers, no LDS store instructions.
 // 131072 x 131072 rows x 32 heads, zigzag: 127.5 -> 109.1 ms (1103 -> 1290 TFLOP/s) on one card.  Counters: matrix pipe 66 % busy
 // at 1.86 GHz, where zeros as data run at 2.24 GHz in the same clocks a tile (16384 x 16384 rows: 1727 and 1456 us).
-// At d = 64 the vector unit alone is the bound (half the matrix work for the same scores): 857 -> 924 TFLOP/s.
+//
+// At d = 64 the vector unit is the bound (half the matrix work for the same scores): a tile costs a wave 32 exponentials of 16
+// clocks and 85 other vector instructions of 4, and 32 MFMAs take an issue slot of 4 each, 980 clocks a SIMD.  One wave alone, or
+// two that take turns, do not issue that fast (a vector instruction every 6 to 9 clocks), three do nearly: a wave needs 158
+// registers and a work-group of four 52 KB of LDS, so three work-groups share a CU and fill each other's matrix
+// phases, prologues and epilogues without a common rhythm.  Eight waves in turns, and this, us: 12 heads x 24749 rows 2140, 2050; 32 heads x
+// 16384 (an earlier shard) 1153, 1080; 64 x 8548 causal, batch 2, 1390, 1240; with a window (32 heads x 3010, batch 2) 98, 75; one step of 1500
+// rows, 4 x 12 heads 67, 47; 1 head x 20000 rows, 157 work-groups 330, 266.  Raised priority of the MFMAs, 2, 3 or 4 operands
+// ahead and a fence between the exponentials make no difference here.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
 
 namespace burst {
 
-constexpr int kFwdWaves = 8, kFwdBQ = 32 * kFwdWaves;   // query rows per work-group: 32 per wave
+template <int D>
+constexpr int kFwdWaves = D == 128 ? 8 : 4;     // two waves per SIMD that take turns; three work-groups per CU
+template <int D>
+constexpr int kFwdBQ = 32 * kFwdWaves<D>;   // query rows per work-group: 32 per wave
+template <int D>
+constexpr int kFwdSlots = D == 128 ? 4 : 3;   // tiles of K and V in LDS
 
 // BLK: with a block-wise sparse mask; MULTI: more than one step.  (A single step's arguments are asked for at once at the start;
 // steps picked by a variable are a second round trip, 1-2 us of a launch: dK/dV of three steps of 1500 rows 241, 246 us.)
 template <int D, int NW, bool BLK, bool MULTI>
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(FwdParams p) {
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int TILE = BK * 2 * D, SLOTS = 4, AHEAD = kAhead16;
+  constexpr int TILE = BK * 2 * D, SLOTS = kFwdSlots<D>, AHEAD = kAhead16;
+  constexpr bool TURNS = D == 128;   // the waves of a SIMD take turns
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
 
   // (a kernel argument indexed with a variable would be copied to scratch memory: read through the argument pointer)
@@ -113,7 +127,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
   // at priority 0 the waves' phases disturb each other.  dQ 1-3 %, dK/dV 1-6 %.
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
-  constexpr int LOADS = KvStream<D, BK, NW, BLK, true>::LOADS, NL = KvStream<D, BK, NW, BLK, true>::N;
+  constexpr int LOADS = KvStream<D, BK, NW, BLK, TURNS>::LOADS, NL = KvStream<D, BK, NW, BLK, TURNS>::N;
   // The steps one after the other; the state stays in registers
 #pragma clang loop unroll(disable)
   for (int step = 0; step < n_steps; ++step) {
@@ -128,7 +142,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
     tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
-    KvStream<D, BK, NW, BLK, true> walk;
+    KvStream<D, BK, NW, BLK, TURNS> walk;
     walk.init(mk, st.k, st.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
     wait_global_loads();
     if (step > 0) __syncthreads();   // the later half may still read the last tiles of the step before
@@ -208,7 +222,36 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
           __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (walk.valid()) {
+    if (!TURNS) {   // tile t in slot t mod 3: both products and the softmax one after the other, a barrier for each tile
+      if (walk.valid()) {
+        int kb = walk.cursor();
+        walk.issue(k_lds(0), v_lds(0), wave, lane);
+        int kc = walk.cursor();
+        walk.issue(k_lds(1), v_lds(1), wave, lane);
+        int slot = 0;
+        do {
+          wait_loads_barrier<LOADS>();   // tile t; and all waves have left tile t-1
+          const int free_slot = slot == 0 ? 2 : slot - 1;
+          const int kn = walk.cursor();
+          walk.issue(k_lds(free_slot), v_lds(free_slot), wave, lane);
+          if (tiles.some(kb)) {
+            const f32x4 zero[MB] = {};
+            bf16x8 first[AHEAD];
+            rows_fetch<D, MB, AHEAD>(k_lds(slot), ad, 0, first);
+            rows_product<D, MB, NB, AHEAD>(k_lds(slot), ad, 0, qreg, s, zero, first);
+            cols_fetch<D, AHEAD>(v_lds(slot), ad, 0, first);
+            mfma_results();
+            softmax(kb);
+            cols_product<D, MB / 2, NB, AHEAD>(v_lds(slot), ad, 0, pp, o, first);
+          }
+          kb = kc;
+          kc = kn;
+          slot = slot == 2 ? 0 : slot + 1;
+          pin(kb, kc, slot);
+        } while (kb >= 0);
+        wait_global_loads();             // tiles past the end of the walk
+      }
+    } else if (walk.valid()) {
       int kb = walk.k0;   // iteration t: kb, kc, kd are the first rows of tiles t+1, t+2, t+3
       walk.issue(k_lds(3), v_lds(3), wave, lane);   // set -1
       int kc = walk.cursor();
@@ -341,9 +384,9 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_fwd_kernel(FwdP
 
 // Query rows of a step that no launched work-group covers (their tiles see no key): the step
 // result for them is (0, -inf); the running state is left alone.
-__global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p) {
+__global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p, int tile_rows) {
   const int d4 = p.head_dim / 4;
-  const int n_tiles = (p.sq + kFwdBQ - 1) / kFwdBQ;
+  const int n_tiles = (p.sq + tile_rows - 1) / tile_rows;
   const int64_t total = (int64_t)p.batch * p.sq * p.q_heads * d4;
   for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
     const int cc = i % d4;
@@ -352,7 +395,7 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p) {
     rest /= p.q_heads;
     const int row = rest % p.sq;
     const int b = rest / p.sq;
-    const int tile = row / kFwdBQ;
+    const int tile = row / tile_rows;
     const bool covered = (tile >= p.q_runs.start[0] && tile < p.q_runs.start[0] + p.q_runs.len[0]) ||
                          (tile >= p.q_runs.start[1] && tile < p.q_runs.start[1] + p.q_runs.len[1]);
     if (covered || tile >= n_tiles) continue;
@@ -368,14 +411,14 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p) {
 
 template <int D>
 static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
-  constexpr int BQ = kFwdBQ;
-  constexpr int LDS = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
+  constexpr int BQ = kFwdBQ<D>, NW = kFwdWaves<D>;
+  constexpr int LDS = kFwdSlots<D> * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
   p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {
     const int64_t total = (int64_t)p.batch * p.sq * p.q_heads * (p.head_dim / 4);
     const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(fwd_fill_dead_rows_kernel, dim3((int)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(fwd_fill_dead_rows_kernel, dim3((int)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, stream, p, BQ);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -383,10 +426,10 @@ static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
   p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, n_keys, group, p.q_runs, BQ);
   const int grid = mapped_grid(n_keys, group, p.q_runs.total());
-  constexpr int NT = 64 * kFwdWaves;
-  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, true, false>), dim3(grid), dim3(NT), LDS, stream, p);
-  else if (p.n_steps > 1) hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false, true>), dim3(grid), dim3(NT), LDS, stream, p);
-  else hipLaunchKernelGGL((step_fwd_kernel<D, kFwdWaves, false, false>), dim3(grid), dim3(NT), LDS, stream, p);
+  constexpr int NT = 64 * NW;
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, NW, true, false>), dim3(grid), dim3(NT), LDS, stream, p);
+  else if (p.n_steps > 1) hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, true>), dim3(grid), dim3(NT), LDS, stream, p);
+  else hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, false>), dim3(grid), dim3(NT), LDS, stream, p);
   return hipGetLastError();
 }
 
