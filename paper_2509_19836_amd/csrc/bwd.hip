@@ -19,22 +19,35 @@
 //    whose A operands are the dO and Q tiles read column-wise from the LDS copies that served
 //    S and dP row-wise.  With grouped-query attention the work-group walks the query heads of its
 //    group, so dK and dV are summed over the group in registers.
+//
+// At d = 64 the vector unit is the bound, and it is filled by waves that keep no common rhythm (fwd.hip).  The dQ kernel runs four
+// waves a work-group, three work-groups a CU, 32 key rows after the other (144-150 registers); dK/dV, whose P-waves and dS-waves need
+// their rhythm, and the joint launch run two work-groups of eight waves a CU in 128 registers, with tiles asked for two ahead so that
+// three are in LDS, where the launch has more than one work-group for each CU and, joint, enough work (crowded).  us, one work-group a CU
+// and so: dQ 4 x 12 heads x 1500 rows 77, 57; 4 x 64/8 x 1879, window 504, three steps 232, 160; 1 x 20000 380, 292; 32 x 16384
+// 1412, 1393; 12 x 24749 2520, 2570; dK/dV 4 x 12 x 1500 90, 79; 32 x 3010, batch 2, window 1219 152, 122; 32 x 16384 1930, 1812; 12 x 24749
+// 3590, 3470; 64/16 x 8548 causal 2290, 2330.  (A dK/dV kernel without roles, a wave with K, V and both sums: two work-groups of four
+// waves a CU, 196 registers, 32 x 16384 2065; with 16 keys a wave, three work-groups, 2380.)
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
 
 namespace burst {
 
-constexpr int kDqWaves = 8, kDqBQ = 32 * kDqWaves;   // query rows per work-group of the dQ kernel: 32 per wave
+template <int D>
+constexpr int kDqWaves = D == 128 ? 8 : 4;       // of the dQ kernel: two per SIMD that take turns; three work-groups per CU (fwd.hip)
+// tiles of both streamed operands in LDS.  TURNS: one work-group has the CU and its waves take turns; else several share it
+template <bool TURNS>
+constexpr int kBwdSlots = TURNS ? 4 : 3;
 
 // lse in log2 units, with -inf mapped to +inf so that exp2(x - lse2) = 0 for a dead row
 __device__ __forceinline__ float lse_to_log2(float lse) { return lse == -INFINITY ? INFINITY : lse * kLog2e; }
 
 // ---------------------------------------------------------------------------------------------
-template <int D, int NW, bool BLK, bool MULTI, int AHEAD>   // BLK: with a block-wise sparse mask; MULTI: more than one step
+template <int D, int NW, bool BLK, bool MULTI, int AHEAD, bool TURNS>   // BLK: with a block-wise sparse mask; MULTI: more than one step
 __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int block) {   // smem: [SLOTS][K tile, V tile], open flags
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int TILE = BK * 2 * D, SLOTS = 4;
+  constexpr int TILE = BK * 2 * D, SLOTS = kBwdSlots<TURNS>;
 
   const int group = p.q_heads / p.kv_heads;
   const BlockMap bm = map_block<true>(block, p.batch * p.kv_heads, group, p.q_runs.total(), p.q_side_by_side);
@@ -120,6 +133,15 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
     if (step > 0) __syncthreads();   // the later half may still read the last tile of the step before
     pin(lds0);   // (LDS addresses worked out once for all steps would cost the registers)
     bf16x8 ds[MB / 2][NB];
+    // dS of 32 key rows for the query rows nb from their scores and dP
+    auto d_scores32 = [&](int nb, f32x4& x, f32x4& y, const f32x4& dpx, const f32x4& dpy) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (dpx[v] - dval[nb]);
+        y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (dpy[v] - dval[nb]);
+      }
+      return pack_pair(x, y);
+    };
     // dS of the tile at key row k0_, of which the wave sees something, for the query rows nb: from their scores and dP
     auto d_scores = [&](int k0_, int nb, auto&& score, auto&& d_p) {   // score(mb), d_p(mb): f32x4
       if (!tiles.full(k0_)) {
@@ -128,17 +150,56 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
           mask_rows32(score(2 * half), score(2 * half + 1), k0_ + 32 * half, g, klo[nb], khi[nb], windowed);
       }
 #pragma unroll
-      for (int ch = 0; ch < MB / 2; ++ch) {
-        f32x4 &x = score(2 * ch), &y = score(2 * ch + 1);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (d_p(2 * ch)[v] - dval[nb]);
-          y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (d_p(2 * ch + 1)[v] - dval[nb]);
-        }
-        ds[ch][nb] = pack_pair(x, y);
-      }
+      for (int ch = 0; ch < MB / 2; ++ch) ds[ch][nb] = d_scores32(nb, score(2 * ch), score(2 * ch + 1), d_p(2 * ch), d_p(2 * ch + 1));
     };
-    if (walk.valid()) {
+    if (!TURNS) {   // tile t in slot t mod 3: products and vector work one after the other, a barrier for each tile
+      if (walk.valid()) {
+        int kb = walk.cursor();
+        walk.issue(k_lds(0), v_lds(0), wave, lane);
+        int kc = walk.cursor();
+        walk.issue(k_lds(1), v_lds(1), wave, lane);
+        int slot = 0;
+        do {
+          wait_loads_barrier<LOADS>();   // tile t; and all waves have left tile t-1
+          const int free_slot = slot == 0 ? 2 : slot - 1;
+          const int kn = walk.cursor();
+          walk.issue(k_lds(free_slot), v_lds(free_slot), wave, lane);
+          if (tiles.some(kb)) {
+            bf16x8 first[AHEAD];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {   // 32 key rows after the other: registers
+              constexpr int HALF = 32 * 2 * D, NP = NW == 8 ? 1 : NB;   // (eight waves: and 16 query rows after the other)
+              const uint32_t kh = k_lds(slot) + half * HALF, vh = v_lds(slot) + half * HALF;
+#pragma unroll
+              for (int n0 = 0; n0 < NB; n0 += NP) {
+                f32x4 s[2][NP], dp[2][NP];
+                bf16x8 qp[DK][NP], dop[DK][NP];
+#pragma unroll
+                for (int i = 0; i < DK * NP; ++i) {
+                  qp[i / NP][i % NP] = qreg[i / NP][n0 + i % NP];
+                  dop[i / NP][i % NP] = doreg[i / NP][n0 + i % NP];
+                }
+                rows_fetch<D, 2, AHEAD>(kh, ad, 0, first);
+                rows_product_pair<D, 2, NP, AHEAD>(kh, vh, ad, qp, dop, s, dp, first);
+#pragma unroll
+                for (int nb = n0; nb < n0 + NP; ++nb) {
+                  f32x4 &x = s[0][nb - n0], &y = s[1][nb - n0];
+                  if (!tiles.full(kb)) mask_rows32(x, y, kb + 32 * half, g, klo[nb], khi[nb], windowed);
+                  ds[half][nb] = d_scores32(nb, x, y, dp[0][nb - n0], dp[1][nb - n0]);
+                }
+              }
+            }
+            cols_fetch<D, AHEAD>(k_lds(slot), ad, 0, first);
+            cols_product<D, MB / 2, NB, AHEAD>(k_lds(slot), ad, 0, ds, dq, first);
+          }
+          kb = kc;
+          kc = kn;
+          slot = slot == 2 ? 0 : slot + 1;
+          pin(kb, kc, slot);
+        } while (kb >= 0);
+        wait_global_loads();             // tiles past the end of the walk
+      }
+    } else if (walk.valid()) {
       int kb = walk.k0;   // iteration t: kb, kc are the first rows of tiles t+1, t+2
       walk.issue(k_lds(0), v_lds(0), wave, lane);
       int kc = walk.cursor();
@@ -280,6 +341,8 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 // SIMD hand the matrix pipe to each other.  Iteration t:
 //   P-wave:  matrix: dV^T += dO(t)^T P(t), then S(t+1) from Q(t+1) and -lse      vector: P(t+1), stored to LDS
 //   dS-wave: matrix: dK^T -= Q(t)^T dS(t), then D - dP(t+1) from dO(t+1) and D   vector: -dS(t+1) from P(t+1)
+// (With three tiles in LDS, at d = 64: tile t+2 is asked for while P-waves run the matrix phase of iteration t, by both roles; it is
+// there when the dS-waves have run theirs, and P-waves bring lse into its form at the head of the matrix phase that needs it.)
 // P(t+1) is stored in the phase before the one that reads it and read a phase before P(t+2) is stored: one copy.
 // Tile t+3 is asked for in the matrix phase of iteration t, into the slot (of four) of tile t-1, which the dS-waves
 // left a barrier ago; a wave waits for its share of tile t+2 at the end of that phase, two barriers before either
@@ -294,9 +357,9 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* smem, int blo
 // m0 instead of four.  16384 x 16384 rows, 32 heads, d = 128: 3605 -> 3377 us a step; 8192 rows, d = 64: 621 -> 518.
 // 128K-token ring backward 52.6 -> 48.7 ms against 32x32x16 MFMAs with tiles staged through registers by the P-waves
 // and the vector work sliced behind each wave's own MFMAs; d = 64, 1500 rows, 4 x 12 heads: 120 -> 95 us per step.
-template <int D>
+template <int D, bool TURNS>
 struct DkdvLds {
-  static constexpr int BQ = 64, SLOTS = 4, TILE = BQ * 2 * D;
+  static constexpr int BQ = 64, SLOTS = kBwdSlots<TURNS>, TILE = BQ * 2 * D;
   static constexpr int Q_OFF = 0, DO_OFF = SLOTS * TILE;
   static constexpr int ROW_OFF = DO_OFF + SLOTS * TILE, ROW = BQ * 4;   // [wave][slot]
   static constexpr int P_OFF = ROW_OFF + 8 * SLOTS * ROW, P_PAIR = BQ * 32 * 2;   // [pair][chunk, key block][lane]
@@ -306,10 +369,12 @@ struct DkdvLds {
 // BKV = 128: the four pairs own 32 key rows each and run through all 64 rows of a query tile.  BKV = 64, for launches
 // with too few key tiles to fill the CUs: two pairs share 32 key rows, each runs through 32 of the 64 query rows (the
 // same operand reads per MFMA, half the MFMAs per phase), and the second one's sums are added through LDS at the end.
-template <int D, int ROLE, bool BLK, int BKV>
+template <int D, int ROLE, bool BLK, int BKV, bool TURNS>
 __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st, char* smem, int b, int hk, int kv_tile, int wave) {
-  constexpr int BQ = 64, QS = 128 / BKV, ROWS = BQ / QS, MB = ROWS / 16, NB = 2, DK = D / 32, DB = D / 16, NW = 8, AHEAD = kAhead16;
-  using L = DkdvLds<D>;
+  constexpr int BQ = 64, QS = 128 / BKV, ROWS = BQ / QS, MB = ROWS / 16, NB = 2, DK = D / 32, DB = D / 16, NW = 8, AHEAD = TURNS ? kAhead16 : 3;
+  using L = DkdvLds<D, TURNS>;
+  constexpr int SLOTS = L::SLOTS;
+  constexpr bool NEAR = !TURNS;   // a tile is asked for two tiles ahead, not three
 
   const int group = p.q_heads / p.kv_heads;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4, pair = wave & 3;
@@ -372,6 +437,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
   auto q_lds = [&](int s_) { return lds0 + L::Q_OFF + s_ * L::TILE; };
   auto o_lds = [&](int s_) { return lds0 + L::DO_OFF + s_ * L::TILE; };
   auto row_off = [&](int s_) { return L::ROW_OFF + (wave * L::SLOTS + s_) * L::ROW; };
+  auto after = [](int s_) { return SLOTS == 4 ? (s_ + 1) & 3 : s_ == 2 ? 0 : s_ + 1; };
   // the wave's rows of the tile of the product that starts from a row vector, and of the product that fills acc
   auto rows_lds = [&](int s_) { return (ROLE == 0 ? q_lds(s_) : o_lds(s_)) + row0 * 2 * D; };
   auto cols_lds = [&](int s_) { return (ROLE == 0 ? o_lds(s_) : q_lds(s_)) + row0 * 2 * D; };
@@ -392,7 +458,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
   // The vector phase, of the tile at query row tile_q0.  `next`: the slot whose lse comes next.
   auto vector_phase = [&](int tile_q0, int next) {
     if (ROLE == 0) {
-      const float raw = *raw_rows(next);   // asked for here, needed behind the exponentials
+      const float raw = NEAR ? 0.f : *raw_rows(next);   // asked for here, needed behind the exponentials
       const int q0_ = tile_q0 + row0;
       const bool some = tiles.some(q0_);
       if (some && !tiles.full(q0_)) {
@@ -420,7 +486,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) ps[ch][nb] = zero_operand();
       }
-      *raw_rows(next) = -lse_to_log2(raw);
+      if (!NEAR) *raw_rows(next) = -lse_to_log2(raw);
 #pragma unroll
       for (int ch = 0; ch < MB / 2; ++ch)
 #pragma unroll
@@ -449,7 +515,13 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
   };
   // The barrier behind it: P has to be stored, while the AHEAD operands (two LDS reads each) fetched since stay in flight
   auto vector_barrier = [&]() {
-    if (ROLE == 0) stores_barrier<2 * AHEAD>();
+    if (ROLE == 0 && NEAR) stores_loads_barrier<2 * AHEAD>();   // tile t+2
+    else if (ROLE == 0) stores_barrier<2 * AHEAD>();
+    else phase_barrier();
+  };
+  auto matrix_barrier = [&]() {
+    if (!NEAR) wait_loads_barrier<LOADS>();      // tile t+2
+    else if (ROLE == 1) wait_loads_barrier<0>();
     else phase_barrier();
   };
 
@@ -459,8 +531,8 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
     int tb = walk.cursor();
     issue(1);
     int tc = walk.cursor();
-    issue(2);
-    wait_loads_barrier<2 * LOADS>();              // tile 0
+    if (!NEAR) issue(2);
+    wait_loads_barrier<(NEAR ? 1 : 2) * LOADS>();   // tile 0
     if (ROLE == 1) phase_barrier();
     bf16x8 first[AHEAD];
     if (ROLE == 0) *raw_rows(0) = -lse_to_log2(*raw_rows(0));
@@ -468,26 +540,30 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
     for (int mb = 0; mb < MB; ++mb) init_rows(0, mb);
     rows_fetch<D, MB, AHEAD>(rows_lds(0), ad, 0, first);
     rows_product<D, MB, NB, AHEAD>(rows_lds(0), ad, 0, xreg, s, init, first);
-    wait_loads_barrier<LOADS>();                  // tile 1
+    wait_loads_barrier<NEAR ? 0 : LOADS>();       // tile 1
+    if (NEAR && ROLE == 1) issue(2);
     vector_phase(ta, 1);
     cols_fetch<D, AHEAD>(cols_lds(0), ad, 0, first);
     vector_barrier();
     int slot = 0, tn = walk.cursor();
-    uint32_t ql = q_lds(3), ol = o_lds(3), rl = lds0 + row_off(3), ct = cols_lds(0), rt = rows_lds(1);
-    walk.begin(wave, lane);
+    uint32_t ql = q_lds(SLOTS - 1), ol = o_lds(SLOTS - 1), rl = lds0 + row_off(SLOTS - 1), ct = cols_lds(0), rt = rows_lds(1);
+    if (!NEAR || ROLE == 0) walk.begin(wave, lane);
+    float raw = 0.f;
     for (;;) {   // iteration t: tb, tc, tn are the first rows of tiles t+1, t+2, t+3
       // ---- matrix phase; everything else that an iteration computes stands behind its MFMAs or in the vector phase
       bf16x8 first_rows[AHEAD];
       constexpr int NCOLS = MB / 2 * DB;
       static_assert(LOADS <= NCOLS && MB <= NCOLS && AHEAD <= NCOLS, "a hook per operand");
       cols_product<D, MB / 2, NB, AHEAD>(ct, ad, 0, ps, acc, first, [&](int i) {
-        if (i < LOADS) walk.load(i, ql, ol, rl, wave);
-        if (!BLK) {
+        if (i < LOADS && (!NEAR || ROLE == 0)) walk.load(i, ql, ol, rl, wave);
+        if (NEAR && ROLE == 0 && i == 0) raw = *raw_rows(after(slot));
+        if (NEAR && ROLE == 0 && i == NCOLS / 2 - 1) *raw_rows(after(slot)) = -lse_to_log2(raw);
+        if (!BLK && (!NEAR || ROLE == 0)) {
 #pragma unroll
           for (int part = 0; part < walk.PARTS; ++part)
             if (i == min(LOADS + part, NCOLS - 1)) walk.end(part);
         }
-        if (i >= NCOLS - MB) init_rows((slot + 1) & 3, i - (NCOLS - MB));
+        if (i >= NCOLS - MB) init_rows(after(slot), i - (NCOLS - MB));
         if (i >= NCOLS - AHEAD) {
           const int f = i - (NCOLS - AHEAD);
           first_rows[f] = rows_operand<D>(rt, ad, 16 * (f % MB), f / MB);
@@ -495,22 +571,25 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
       });
       if (tb < 0) break;
       rows_product<D, MB, NB, AHEAD>(rt, ad, 0, xreg, s, init, first_rows);
-      wait_loads_barrier<LOADS>();                // tile t+2
+      matrix_barrier();
       // ---- vector phase
-      if (BLK) walk.advance();
+      if (BLK && (!NEAR || ROLE == 0)) walk.advance();
       ql = q_lds(slot);
       ol = o_lds(slot);
       rl = lds0 + row_off(slot);
-      slot = (slot + 1) & 3;
+      const int left_slot = slot;
+      slot = after(slot);
       ct = cols_lds(slot);
-      rt = rows_lds((slot + 1) & 3);
+      rt = rows_lds(after(slot));
       const int tile_q0 = tb;
       tb = tc;
       tc = tn;
       tn = walk.cursor();
-      walk.begin(wave, lane);
+      if (NEAR) tc = tn;
+      if (NEAR && ROLE == 1) issue(left_slot);
+      else walk.begin(wave, lane);
       pin(slot, ql, ol, rl, ct, rt, tb, tc, tn);
-      vector_phase(tile_q0, (slot + 1) & 3);
+      vector_phase(tile_q0, after(slot));
       cols_fetch<D, AHEAD>(ct, ad, 0, first);
       vector_barrier();
     }
@@ -550,7 +629,7 @@ __device__ __forceinline__ void dkdv_role(const BwdParams& p, const BwdStep& st,
   }
 }
 
-template <int D, bool BLK, bool MULTI, int BKV>
+template <int D, bool BLK, bool MULTI, int BKV, bool TURNS>
 __device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int block) {   // smem: laid out by DkdvLds, then the open flags
   int step = 0;   // the steps' work-groups one after the other
   while (MULTI && step + 1 < p.n_steps && block >= p.step[step + 1].first_block) ++step;
@@ -559,8 +638,8 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int b
   if (!bm.valid) return;
   const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 4) dkdv_role<D, 0, BLK, BKV>(p, st, smem, b, hk, bm.tile, wave);
-  else dkdv_role<D, 1, BLK, BKV>(p, st, smem, b, hk, bm.tile, wave);
+  if (wave < 4) dkdv_role<D, 0, BLK, BKV, TURNS>(p, st, smem, b, hk, bm.tile, wave);
+  else dkdv_role<D, 1, BLK, BKV, TURNS>(p, st, smem, b, hk, bm.tile, wave);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -571,22 +650,22 @@ __device__ __forceinline__ const BwdParams& launch_args() {
   return *(const BwdParams*)(args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
 }
 template <int D, int NW, bool BLK, bool MULTI>
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void step_bwd_dq_kernel(BwdParams p) {
+__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_bwd_dq_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int AHEAD = BLK ? 3 : kAhead16;   // (the block flags take the registers of one operand)
-  if constexpr (MULTI) dq_block<D, NW, BLK, true, AHEAD>(launch_args(), smem, blockIdx.x);
-  else dq_block<D, NW, BLK, false, AHEAD>(p, smem, blockIdx.x);
+  if constexpr (MULTI) dq_block<D, NW, BLK, true, AHEAD, D == 128>(launch_args(), smem, blockIdx.x);
+  else dq_block<D, NW, BLK, false, AHEAD, D == 128>(p, smem, blockIdx.x);
 }
-template <int D, bool BLK, bool MULTI, int BKV>
-__global__ __launch_bounds__(512, 1) void step_bwd_dkdv_kernel(BwdParams p) {
+template <int D, bool BLK, bool MULTI, int BKV, bool TURNS>
+__global__ __launch_bounds__(512, TURNS ? 1 : 4) void step_bwd_dkdv_kernel(BwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  if constexpr (MULTI) dkdv_block<D, BLK, true, BKV>(launch_args(), smem, blockIdx.x);
-  else dkdv_block<D, BLK, false, BKV>(p, smem, blockIdx.x);
+  if constexpr (MULTI) dkdv_block<D, BLK, true, BKV, TURNS>(launch_args(), smem, blockIdx.x);
+  else dkdv_block<D, BLK, false, BKV, TURNS>(p, smem, blockIdx.x);
 }
 // Both in one launch (they share nothing but inputs): the first n_first work-groups (a multiple of 8, as the mapping to
 // XCDs needs) are those of the kernel whose walks are the longer ones.
-template <int D, bool MULTI, int BKV>
-__global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams, int n_first, int dq_first) {
+template <int D, bool MULTI, int BKV, bool TURNS>
+__global__ __launch_bounds__(512, TURNS ? 1 : 4) void step_bwd_both_kernel(BwdParams, int n_first, int dq_first) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // each side reads its own arguments: loaded for both at the start they would not fit the scalar registers
   typedef const __attribute__((address_space(4))) BwdParams* args_ptr;
@@ -594,11 +673,10 @@ __global__ __launch_bounds__(512, 1) void step_bwd_both_kernel(BwdParams, int n_
   const int in_first = (int)blockIdx.x < n_first, block = blockIdx.x - (in_first ? 0 : n_first);
   if (in_first != dq_first) {
     asm volatile("" : "+s"(args));
-    dkdv_block<D, false, MULTI, BKV>(*(const BwdParams*)args, smem, block);
+    dkdv_block<D, false, MULTI, BKV, TURNS>(*(const BwdParams*)args, smem, block);
   } else {
     asm volatile("" : "+s"(args));
-    static_assert(kDqWaves * 64 == 512, "both kernels' work-groups have the same size");
-    dq_block<D, kDqWaves, false, MULTI, 3>(*(const BwdParams*)args, smem, block);
+    dq_block<D, 8, false, MULTI, TURNS ? 3 : 2, TURNS>(*(const BwdParams*)args, smem, block);
   }
 }
 
@@ -620,10 +698,10 @@ static bool narrow_key_tiles(const BwdParams& p) {
 }
 
 // The work-groups of a kernel: the tiles that see something, and zeros into what gets no work-group under "=".
-static hipError_t plan_dq(BwdParams& p, hipStream_t stream) {
-  p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, kDqBQ);
-  p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, kDqBQ);
-  if (!p.acc_dq && p.q_runs.total() < (p.sq + kDqBQ - 1) / kDqBQ)
+static hipError_t plan_dq(BwdParams& p, int BQ, hipStream_t stream) {
+  p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
+  p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, BQ);
+  if (!p.acc_dq && p.q_runs.total() < (p.sq + BQ - 1) / BQ)
     return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
   return hipSuccess;
 }
@@ -664,35 +742,44 @@ static int dkdv_grid(const BwdParams& p) {
 }
 
 template <int D>
-constexpr int kDqLds = 4 * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
-template <int D>
-constexpr int kDkdvLds = DkdvLds<D>::BYTES + kMaxBlockCacheTiles;
+constexpr int kDqLds = kBwdSlots<D == 128> * 2 * 64 * 2 * D;
+template <int D, bool TURNS>
+constexpr int kDkdvLds = DkdvLds<D, TURNS>::BYTES;
+constexpr int kFlagsLds = kMaxBlockCacheTiles;   // with a block mask
+constexpr int kAlone = 256;   // work-groups that have a CU for themselves
 
 template <int D>
 static hipError_t launch_dq_t(BwdParams& p, hipStream_t stream) {
-  const hipError_t e = plan_dq(p, stream);
+  const hipError_t e = plan_dq(p, 32 * kDqWaves<D>, stream);
   const int grid = dq_grid(p);
   if (e != hipSuccess || grid == 0) return e;
-  constexpr int NT = 64 * kDqWaves;
-  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, true, false>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
-  else if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false, true>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, kDqWaves, false, false>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
+  constexpr int NW = kDqWaves<D>, NT = 64 * NW;
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, NW, true, false>), dim3(grid), dim3(NT), kDqLds<D> + kFlagsLds, stream, p);
+  else if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_dq_kernel<D, NW, false, true>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
+  else hipLaunchKernelGGL((step_bwd_dq_kernel<D, NW, false, false>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
   return hipGetLastError();
 }
 
+template <int D, bool BLK, bool MULTI, int BKV, bool TURNS>
+static void launch_dkdv_kernel(const BwdParams& p, int grid, hipStream_t stream) {
+  constexpr int LDS = kDkdvLds<D, TURNS> + (BLK ? kFlagsLds : 0);
+  static_assert((TURNS ? 1 : 2) * LDS <= 160 * 1024, "LDS of a CU");
+  hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, BLK, MULTI, BKV, TURNS>), dim3(grid), dim3(512), LDS, stream, p);
+}
 template <int D>
 static hipError_t launch_dkdv_t(BwdParams& p, hipStream_t stream) {
-  static_assert(kDkdvLds<D> <= 160 * 1024, "LDS of a CU");
   bool narrow = false;
   const hipError_t e = plan_dkdv(p, narrow, stream);
   const int grid = dkdv_grid(p);
   if (e != hipSuccess || grid == 0) return e;
   const bool multi = p.n_steps > 1;
-  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, true, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else if (narrow && multi) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, true, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else if (narrow) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, false, 64>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else if (multi) hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, true, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
-  else hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, false, false, 128>), dim3(grid), dim3(512), kDkdvLds<D>, stream, p);
+  if (p.step[0].mask.blk) launch_dkdv_kernel<D, true, false, 128, true>(p, grid, stream);
+  else if (narrow && multi) launch_dkdv_kernel<D, false, true, 64, true>(p, grid, stream);
+  else if (narrow) launch_dkdv_kernel<D, false, false, 64, true>(p, grid, stream);
+  else if (D == 128 || grid <= kAlone) multi ? launch_dkdv_kernel<D, false, true, 128, true>(p, grid, stream)
+                                             : launch_dkdv_kernel<D, false, false, 128, true>(p, grid, stream);
+  else if constexpr (D == 64) multi ? launch_dkdv_kernel<D, false, true, 128, false>(p, grid, stream)
+                                    : launch_dkdv_kernel<D, false, false, 128, false>(p, grid, stream);
   return hipGetLastError();
 }
 
@@ -703,29 +790,70 @@ static hipError_t launch_dkdv_t(BwdParams& p, hipStream_t stream) {
 // (1536) on, 772 and 770, causal 422 and 428.  Several steps, twice as many: they go from longer to shorter walks, which a
 // part-empty round costs more.  Apart, dK/dV's first, dQ's first: 3 steps of 48 x 1500 rows, d = 64 (2016) 365, 334, 295 us;
 // 8 of 16/2 heads x 8192 (1344), whose key tiles walk 8 heads, 5861, 5771, 5947; 4 of 32 x 4096 (3584) 1591, 1583, 1636.
-constexpr int kBothLaunch = 1280;
+constexpr int kBothLaunch = 1280, kBothBQ = 256;   // (query rows of its dQ work-groups)
 
+// Whether the work-groups of a joint launch at d = 64 share CUs (two of up to 128 registers) instead of having one each: a shared CU
+// does more in a time, and each of its work-groups less.  So it pays where there are several times as many as CUs, and not where the
+// longest walks decide: the work of all has to be 1.1 times that of a longest one on every CU, and twice where the walks are uneven
+// (they are launched longest first, and sharing holds up just those).  In units of a product of 64 x 128 rows; first and last tile
+// stand for all.  us with a CU each and shared, by that measure: even 2.6 (4 x 12 heads x 1500 rows, full) 134, 118; 1.8 (8 x 12 x
+// 512) 49, 41; 1.2 (2 x 16 x 1000, two steps) 75, 68; uneven 4.6 (4 x 64/32 x 576, two steps) 164, 124; 2.2 (4 x 12 x 1500, three
+// steps) 294, 258; 1.7 (16 x 6000 causal) 267, 284; 0.4 (8 x 2048, zigzag, four steps) 148, 180.
+static bool crowded(const BwdParams& p, bool narrow) {
+  const int group = p.q_heads / p.kv_heads, tile = narrow ? 64 : 128, keys = p.batch * p.kv_heads;
+  int64_t first = 0, last = 0, total = 0, longest = 0;
+  bool uneven = uneven_q_walks(p.step, p.n_steps, p.sq, p.q_runs, kBothBQ);
+  for (int i = 0, nq = p.q_runs.total(); i < p.n_steps && nq > 0; ++i) {
+    first += 6 * q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, p.q_runs.tile_of(nq - 1), kBothBQ);
+    last += 6 * q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, p.q_runs.tile_of(0), kBothBQ);
+  }
+  total = (int64_t)keys * group * p.q_runs.total() * (first + last) / 2;
+  longest = first;
+  for (int i = 0; i < p.n_steps; ++i) {
+    const BwdStep& st = p.step[i];
+    const int n = st.k_runs.total();
+    if (n == 0) continue;
+    const int64_t per = (narrow ? 2 : 4) * group;
+    first = per * k_tile_walk(st.mask, p.sq, st.sk, st.k_runs.tile_of(0), tile);
+    last = per * k_tile_walk(st.mask, p.sq, st.sk, st.k_runs.tile_of(n - 1), tile);
+    total += (int64_t)keys * n * (first + last) / 2;
+    longest = std::max(longest, first);
+    uneven |= 2 * last <= first;
+  }
+  return 10 * total >= (uneven ? 20 : 11) * kAlone * longest;
+}
+template <int D, bool MULTI, int BKV, bool TURNS>
+static void launch_both_kernel(const BwdParams& p, int grid, int n_first, int dq_first, hipStream_t stream) {
+  constexpr int DQ_LDS = kBwdSlots<TURNS> * 2 * 64 * 2 * D, LDS = std::max(kDkdvLds<D, TURNS>, DQ_LDS);
+  hipLaunchKernelGGL((step_bwd_both_kernel<D, MULTI, BKV, TURNS>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
+}
 // One launch of both kernels; `done` says whether it was taken.
 template <int D>
 static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  int64_t most = (int64_t)n_keys * group * ((p.sq + kDqBQ - 1) / kDqBQ);
+  int64_t most = (int64_t)n_keys * group * ((p.sq + kBothBQ - 1) / kBothBQ);
   for (int i = 0; i < p.n_steps; ++i) most += (int64_t)n_keys * ((p.step[i].sk + 127) / 128);
   done = most <= (p.n_steps > 1 ? 2 : 1) * kBothLaunch;
   if (!done) return hipSuccess;
   bool narrow = false;
-  hipError_t e = plan_dq(p, stream);
+  hipError_t e = plan_dq(p, kBothBQ, stream);
   if (e == hipSuccess) e = plan_dkdv(p, narrow, stream);
   const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
   if (e != hipSuccess || grid == 0) return e;
-  constexpr int LDS = kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>;
   // a dQ work-group walks every step (three products a tile against two), a dK/dV one the heads of its group
   const int dq_first = p.n_steps > 1 && 3 * p.n_steps > 4 * group, n_first = dq_first ? n_dq : n_dkdv;
   const bool multi = p.n_steps > 1;
-  if (narrow && multi) hipLaunchKernelGGL((step_bwd_both_kernel<D, true, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
-  else if (narrow) hipLaunchKernelGGL((step_bwd_both_kernel<D, false, 64>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
-  else if (multi) hipLaunchKernelGGL((step_bwd_both_kernel<D, true, 128>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
-  else hipLaunchKernelGGL((step_bwd_both_kernel<D, false, 128>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
+  const bool alone = D == 128 || grid <= kAlone || !crowded(p, narrow);
+  auto launch = [&](auto m, auto bkv) {
+    if (alone) launch_both_kernel<D, m.value, bkv.value, true>(p, grid, n_first, dq_first, stream);
+    else if constexpr (D == 64) launch_both_kernel<D, m.value, bkv.value, false>(p, grid, n_first, dq_first, stream);
+  };
+  using narrow_tile = std::integral_constant<int, 64>;
+  using wide_tile = std::integral_constant<int, 128>;
+  if (narrow && multi) launch(std::true_type(), narrow_tile());
+  else if (narrow) launch(std::false_type(), narrow_tile());
+  else if (multi) launch(std::true_type(), wide_tile());
+  else launch(std::false_type(), wide_tile());
   return hipGetLastError();
 }
 

@@ -119,6 +119,14 @@ __device__ __forceinline__ void stores_barrier() {
   asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
+// The same and all of this wave's global loads done.
+template <int N>
+__device__ __forceinline__ void stores_loads_barrier() {
+  static_assert(N <= 15, "lgkmcnt has four bits");
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 // Nothing moves across: the LDS stores that stores_barrier counts on stay in front of the reads it leaves in flight.
 __device__ __forceinline__ void keep_order() {
   asm volatile("" ::: "memory");
@@ -170,7 +178,9 @@ struct DirectStager {
   uint32_t off[N];
   __device__ __forceinline__ int row_of(int i, int wave, int lane) const { return (i * NW + wave) * RPI + lane / (PITCH / 16); }
   __device__ __forceinline__ uint32_t offset(int row, int lane_row, int64_t ss, int lane) const {
-    return 2u * ((uint32_t)row * (uint32_t)ss + (uint32_t)(((lane % (PITCH / 16)) ^ swz<D>(lane_row)) * 8));
+    uint32_t x = 2u * ((uint32_t)row * (uint32_t)ss + (uint32_t)(((lane % (PITCH / 16)) ^ swz<D>(lane_row)) * 8));
+    asm("" : "+v"(x));   // (a product's low half otherwise keeps a pair of registers)
+    return x;
   }
   __device__ __forceinline__ void init(int64_t ss, int wave, int lane) {
 #pragma unroll
@@ -309,6 +319,7 @@ struct KvStream {
     }
   }
   __device__ __forceinline__ void end() {
+#pragma unroll
     for (int i = 0; i < PARTS; ++i) end(i);
   }
   __device__ __forceinline__ void issue(uint32_t k_lds, uint32_t v_lds, int wave, int lane) {
@@ -413,6 +424,7 @@ struct QStream {
   }
   __device__ __forceinline__ void advance() {
     if (!BLK) {
+#pragma unroll
       for (int i = 0; i < PARTS; ++i) end(i);
       return;
     }

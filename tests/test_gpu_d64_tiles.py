@@ -13,3 +13,47 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("sq,sk", [(1, 1), (1, 257), (31, 64), (33, 65), (127, 128), (128, 129), (129, 192), (160, 193), (255, 320), (385, 63)])
 def test_tiles_of_narrow_heads(lib, sq, sk, causal):
     step_case(lib, 1, 6, 3, 64, sq, sk, causal, 500 + sq + sk, q_pos=40)
+
+
+@pytest.mark.parametrize("sq,sk,causal,window", [(513, 513, False, 0), (640, 577, True, 0), (500, 700, True, 130), (129, 1025, False, 0)])
+@pytest.mark.parametrize("blocks", [False, True])
+def test_work_groups_that_share_a_cu(lib, sq, sk, causal, window, blocks):
+    """Gradients of enough heads for several work-groups per CU: all in one call, dQ alone, dK and dV alone."""
+    import numpy as np
+    import torch
+    from oracle import burst_oracle as oc
+    from paper_2509_19836_amd import workloads as wl
+    from tests import helpers as hp
+    B, Hq, Hkv, d = 8, 24, 12, 64
+    rng = np.random.Generator(np.random.PCG64(wl.BASE_SEED + 73000 + sq + sk))
+    draw = lambda *shape: wl.f32_to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+    qb, kb, vb, gb = draw(B, sq, Hq, d), draw(B, sk, Hkv, d), draw(B, sk, Hkv, d), draw(B, sq, Hq, d)
+    mask = lib.burst_mask_t()
+    mask.mode = lib.BURST_MASK_CAUSAL if causal else lib.BURST_MASK_FULL
+    mask.q_nseg = mask.k_nseg = mask.pos_stride = 1
+    mask.q_seg_len, mask.k_seg_len, mask.window = sq, sk, window
+    q_pos = 150 if causal else 0
+    mask.q_seg_pos[0] = q_pos
+    vis = oc.visibility(q_pos + np.arange(sq), np.arange(sk), causal, window)
+    if blocks:
+        bm = rng.integers(0, 2, (-(-sq // 256), -(-sk // 128))).astype(np.uint8)
+        bm[0, 0] = 1
+        on_gpu = torch.from_numpy(bm).cuda()
+        lib.set_block_mask(mask, on_gpu, 256, 128)
+        vis = (np.ones((sq, sk), bool) if vis is None else vis) & (np.kron(bm, np.ones((256, 128), np.uint8))[:sq, :sk] != 0)
+    scale = d ** -0.5
+    lse = rng.normal(3.0, 0.3, (B, Hq, sq)).astype(np.float32)
+    D = rng.standard_normal((B, Hq, sq)).astype(np.float32)
+    ref = oc.mha_step_bwd(*(hp.widen(x) for x in (qb, kb, vb, gb)), lse.astype(np.float64), D.astype(np.float64), scale, vis)
+    q, k, v, g = (hp.dev_bf16(x) for x in (qb, kb, vb, gb))
+    shp = lib.shape(B, Hq, Hkv, d, sq, sk, scale)
+    nan = lambda *shape: torch.full(shape, float("nan"), device="cuda", dtype=torch.float32)
+    for want in ("dQ dK dV", "dQ", "dK dV"):
+        out = {n: nan(B, sq, Hq, d) if n == "dQ" else nan(B, sk, Hkv, d) for n in want.split()}
+        print(sq, sk, causal, window, blocks, want, flush=True)
+        lib.burst_attn_step_bwd(shp, mask, q, k, v, g, torch.from_numpy(lse).cuda(), torch.from_numpy(D).cuda(),
+                                **{n.lower(): t for n, t in out.items()})
+        torch.cuda.synchronize()
+        for n, r in zip(("dQ", "dK", "dV"), ref):
+            if n in out:
+                assert hp.rel_err(out[n].cpu().numpy(), r) <= hp.REL_TOL, (n, want)
