@@ -929,7 +929,10 @@ static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, i
         p.d.ptr += rg.r0;
         if (&rg != &ranges.front()) p.acc_dk = p.acc_dv = 1;
       }
-      auto share = [&](const BwdStep& st) { return !st.mask.blk && share_launch(p.batch * p.kv_heads, st.sk); };
+      auto share = [&](const BwdStep& st) {
+        return !st.mask.blk && (share_launch(p.batch * p.kv_heads, st.sk) ||
+                                p.q_heads / p.kv_heads * longest_k_walk(st.mask, p.sq, st.sk) <= kShareKeyWalk);
+      };
       for (int first = 0, end; first < n; first = end) {
         for (end = first + 1; end < n && end - first < kMaxSteps && share(parts[first]) && share(parts[end]);) ++end;
         put(parts, first, end);

@@ -139,6 +139,15 @@ inline bool uneven_k_walks(const MaskDev& mk, int sq, int sk, const TileRuns& ru
   const int n = runs.total();
   return n > 0 && 2 * k_tile_walk(mk, sq, sk, runs.tile_of(n - 1), tile_rows) <= k_tile_walk(mk, sq, sk, runs.tile_of(0), tile_rows);
 }
+// About the longest walk of a step's query tiles of 256 rows, or key tiles of 128: of the first, the middle and the last one.
+inline int longest_q_walk(const MaskDev& mk, int sq, int sk) {
+  const int n = (sq + 255) / 256;
+  return std::max({q_tile_walk(mk, sq, sk, 0, 256), q_tile_walk(mk, sq, sk, n / 2, 256), q_tile_walk(mk, sq, sk, n - 1, 256)});
+}
+inline int longest_k_walk(const MaskDev& mk, int sq, int sk) {
+  const int n = (sk + 127) / 128;
+  return std::max({k_tile_walk(mk, sq, sk, 0, 128), k_tile_walk(mk, sq, sk, n / 2, 128), k_tile_walk(mk, sq, sk, n - 1, 128)});
+}
 // Whether a launch runs the keys of an XCD (of two or more) side by side (map_block).  A block mask makes any walks uneven.
 template <class Step>
 inline bool q_side_by_side(const Step* steps, int n_steps, int sq, int n_keys, int group, const TileRuns& runs, int tile_rows) {
@@ -220,12 +229,17 @@ inline void offset_rows(TensorDev& t, int r0) { t.ptr = (char*)t.ptr + (int64_t)
 // 3621, 3579.  Beyond kShareLaunch tiles of 256 rows a step (4 per CU; key tiles of 128 rows are twice as many) there is
 // nothing to gain: 8 shards of 16384 rows, 32 heads, zigzag: forward 13753, 13778, dQ 18904, 18828, dK/dV 26695, 27106,
 // striped: 14816, 15190, 20535, 20615, 29172, 29317.
-// (All without a window.  A windowed step's walks are shorter; its launches are shared by the same rule, whose line has not been
-// measured for them.)  A step with a block mask goes alone, and the walks of these launches are bounded by what stays in step in
-// an L2, two ranges.  Not so in the joint backward launch (launch_both_t), which takes up to kMaxSteps chunks of a range each: 1
+// Walks of up to kShareWalk tiles are short enough for what every step costs beside its tiles (the first loads, O or dQ read and
+// written) to count however many there are.  us step by step and shared, forward and dQ: 8 shards of 16384 rows, 32 heads, striped, with
+// a window of 4000 tokens (12 tiles a step) 2446, 1830 and 2801, 2104; of 12000 (28) 3934, 3390 and 4897, 4440; of 32768 (68) 7213, 6931 and
+// 9464, 9076; of 65536 (132) 11125, 11091 and 14923, 14842; 8 of 4096 rows, 2 x 64/8 heads (64) 3857, 3417 and 5201, 4678; 4 of 3000, 8 x
+// 16 (47) 1927, 1768 and 2557, 2398; 4 of 8000, 64 (125) 3679, 3836 and 4905, 5186.  Key tiles up to kShareKeyWalk: dK/dV with the window of 1000
+// (6 tiles) 3008, 2819; 4000 (10) 3940, 3763; 12000 6730, 6622; 32768 13049, 13130; at d = 64 8 x 16 x 3000 (47) 2030, 2046-2110.
+// A step with a block mask goes alone, and the walks of these launches together are bounded by what stays in step in an L2, two
+// ranges.  Not so in the joint backward launch (launch_both_t), which takes up to kMaxSteps chunks of a range each: 1
 // head, 8 shards of 32768 rows, backward in calls of 1, 2 and 8 steps: full 13.42, 11.61, 11.53 ms, zigzag 9.02, 6.69, 6.87, striped
 // 11.62, 7.99, 8.87.  Steps of which no query row sees anything are left out.  launch(first, end): steps [first, end) of `parts`.
-constexpr int kShareLaunch = 1024;
+constexpr int kShareLaunch = 1024, kShareWalk = 80, kShareKeyWalk = 40;
 inline bool share_launch(int heads, int rows) { return (int64_t)heads * ((rows + 255) / 256) <= kShareLaunch; }
 template <class Step, class Launch>
 inline hipError_t for_step_groups(std::vector<Step>& parts, int sq, int heads, Launch&& launch) {
@@ -235,11 +249,14 @@ inline hipError_t for_step_groups(std::vector<Step>& parts, int sq, int heads, L
   const bool share = share_launch(heads, sq);
   for (int first = 0, end = 0; first < n; first = end) {
     int64_t rows = 0;
+    bool all = true;   // so far, walks short enough for the others to join
     for (; end < n; ++end) {
-      if (end > first && (!share || parts[end].mask.blk || parts[first].mask.blk || end - first == kMaxSteps ||
-                          rows + parts[end].sk > 2ll * chunk_rows()))
+      const int walk = n > 1 ? longest_q_walk(parts[end].mask, sq, parts[end].sk) : 0;
+      all = all && (share || walk <= kShareWalk);
+      if (end > first && (!all || parts[end].mask.blk || parts[first].mask.blk || end - first == kMaxSteps ||
+                          rows + 64ll * walk > 2ll * chunk_rows()))
         break;
-      rows += parts[end].sk;
+      rows += 64ll * walk;
     }
     const hipError_t e = launch(first, end);
     if (e != hipSuccess) return e;
