@@ -25,6 +25,9 @@
 // 16384 (an earlier shard) 1153, 1080; 64 x 8548 causal, batch 2, 1390, 1240; with a window (32 heads x 3010, batch 2) 98, 75; one step of 1500
 // rows, 4 x 12 heads 67, 47; 1 head x 20000 rows, 157 work-groups 330, 266.  Raised priority of the MFMAs, 2, 3 or 4 operands
 // ahead and a fence between the exponentials make no difference here.
+//
+// A launch of few query tiles is bound by its longest walk, a chain of products and softmax that leaves most CUs idle: there the four
+// waves of a work-group share 32 query rows and deal the key tiles among themselves (SPLIT; when: split_walks).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
@@ -38,14 +41,21 @@ constexpr int kFwdBQ = 32 * kFwdWaves<D>;   // query rows per work-group: 32 per
 template <int D>
 constexpr int kFwdSlots = D == 128 ? 4 : 3;   // tiles of K and V in LDS
 
+// Work-groups whose waves share their query rows (SPLIT)
+constexpr int kSplitWaves = 4, kSplitBQ = 32;
+struct SplitRow {
+  float m, l, lse_before;   // of a wave and a row: maximum and sum of its keys, the running Lse (the first wave's)
+};
+
 // BLK: with a block-wise sparse mask; MULTI: more than one step.  (A single step's arguments are asked for at once at the start;
 // steps picked by a variable are a second round trip, 1-2 us of a launch: dK/dV of three steps of 1500 rows 241, 246 us.)
-template <int D, int NW, bool BLK, bool MULTI>
-__global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(FwdParams p) {
-  constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = 32 * NW, NT = 64 * NW;
-  constexpr int TILE = BK * 2 * D, SLOTS = kFwdSlots<D>, AHEAD = kAhead16;
-  constexpr bool TURNS = D == 128;   // the waves of a SIMD take turns
-  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], open flags
+// SPLIT: the waves share 32 query rows and deal the key tiles among themselves.
+template <int D, int NW, bool BLK, bool MULTI, bool SPLIT>
+__global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_kernel(FwdParams p) {
+  constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = SPLIT ? 32 : 32 * NW, NT = 64 * NW;
+  constexpr int TILE = BK * 2 * D, SLOTS = SPLIT ? NW : kFwdSlots<D>, AHEAD = kAhead16;
+  constexpr bool TURNS = D == 128 && !SPLIT;   // the waves of a SIMD take turns
+  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], SplitRow[NW][BQ] (SPLIT), open flags
 
   // (a kernel argument indexed with a variable would be copied to scratch memory: read through the argument pointer)
   typedef const __attribute__((address_space(4))) FwdParams* args_ptr;
@@ -62,7 +72,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
   const MaskDev q_side = p.step[0].mask;   // all steps have the same
   const int q_blk0 = p.q_runs.tile_of(bm.tile) * BQ;     // first row of the work-group
   const int q_blk1 = min(q_blk0 + BQ, sq);
-  const int q_w0 = q_blk0 + wave * 32;                   // first row of the wave
+  const int q_w0 = SPLIT ? q_blk0 : q_blk0 + wave * 32;  // first row of the wave
   const int q_w1 = min(q_w0 + 32, sq);                   // may be <= q_w0: the wave only helps staging
 
   // Q as the B operand of S^T = K Q^T: lane holds rows q_w0 + 16 nb + r, columns 32 ks + 8g .. +7
@@ -96,7 +106,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
   if (BLK) {
-    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE);
+    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE + (SPLIT ? NW * BQ * sizeof(SplitRow) : 0));
     fill_open_flags<true, BK>(q_side, open_flags, q_blk0, p.step[0].sk, tid, NT);
     __syncthreads();
   }
@@ -127,7 +137,8 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
   // at priority 0 the waves' phases disturb each other.  dQ 1-3 %, dK/dV 1-6 %.
   auto k_lds = [&](int s_) { return lds0 + s_ * 2 * TILE; };
   auto v_lds = [&](int s_) { return lds0 + s_ * 2 * TILE + TILE; };
-  constexpr int LOADS = KvStream<D, BK, NW, BLK, TURNS>::LOADS, NL = KvStream<D, BK, NW, BLK, TURNS>::N;
+  using Walk = KvStream<D, BK, SPLIT ? 1 : NW, BLK, TURNS>;
+  constexpr int LOADS = Walk::LOADS, NL = Walk::N;
   // The steps one after the other; the state stays in registers
 #pragma clang loop unroll(disable)
   for (int step = 0; step < n_steps; ++step) {
@@ -142,10 +153,10 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
     tiles.init(row_intervals<false>(mk, qlo_w, qhi_w, sk, q_w0 >= q_w1), sk, BK);
-    KvStream<D, BK, NW, BLK, TURNS> walk;
-    walk.init(mk, st.k, st.v, b, hk, sk, qlo_blk, qhi_blk, wave, lane, open_flags);
+    Walk walk;
+    walk.init(mk, st.k, st.v, b, hk, sk, qlo_blk, qhi_blk, SPLIT ? 0 : wave, lane, open_flags);
     wait_global_loads();
-    if (step > 0) __syncthreads();   // the later half may still read the last tiles of the step before
+    if (step > 0 && !SPLIT) __syncthreads();   // the later half may still read the last tiles of the step before
     pin(lds0);   // (LDS addresses worked out once for all steps would cost the registers)
     f32x4 s[MB][NB];
     bf16x8 pp[MB / 2][NB];
@@ -222,7 +233,48 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
           __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (!TURNS) {   // tile t in slot t mod 3: both products and the softmax one after the other, a barrier for each tile
+    if constexpr (SPLIT) {   // tiles wave, wave + NW, .. in the wave's own slot: K of the next one comes behind the vector work, V behind O
+      const uint32_t kt = k_lds(wave), vt = v_lds(wave);
+      auto load = [&](bool v) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+          if (v) walk.load_v(i, vt, 0);
+          else walk.load_k(i, kt, 0);
+        }
+      };
+      walk.skip(wave);
+      if (walk.valid()) {
+        walk.begin(0, lane);
+        load(false);
+        load(true);
+        for (;;) {
+          const int kb = walk.k0;
+          walk.skip(NW);
+          const bool more = walk.valid(), live = tiles.some(kb);
+          wait_loads<NL>();   // K
+          const f32x4 zero[MB] = {};
+          bf16x8 first[AHEAD];
+          if (live) {
+            rows_fetch<D, MB, AHEAD>(kt, ad, 0, first);
+            rows_product<D, MB, NB, AHEAD>(kt, ad, 0, qreg, s, zero, first);
+            mfma_results();
+          }
+          if (more) {
+            walk.begin(0, lane);
+            load(false);
+          }
+          if (live) softmax(kb);
+          if (more) wait_loads<NL>();   // V
+          else wait_loads<0>();
+          if (live) {
+            cols_fetch<D, AHEAD>(vt, ad, 0, first);
+            cols_product<D, MB / 2, NB, AHEAD>(vt, ad, 0, pp, o, first);
+          }
+          if (!more) break;
+          load(true);
+        }
+      }
+    } else if (!TURNS) {   // tile t in slot t mod 3: both products and the softmax one after the other, a barrier for each tile
       if (walk.valid()) {
         int kb = walk.cursor();
         walk.issue(k_lds(0), v_lds(0), wave, lane);
@@ -330,45 +382,93 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
     }
   }
 
+  float l_sum[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    l_sum[nb] = (l_run[nb][0] + l_run[nb][1]) + (l_run[nb][2] + l_run[nb][3]);
+    l_sum[nb] += __shfl_xor(l_sum[nb], 16, 64);
+    l_sum[nb] += __shfl_xor(l_sum[nb], 32, 64);
+  }
+  // SPLIT: the waves' sums meet in LDS (each where its tiles were), and wave w goes on with columns of blocks w DBO ..
+  constexpr int DBO = SPLIT ? DB / NW : DB;
+  const int col0 = 4 * g + (SPLIT ? 16 * DBO * wave : 0);
+  const bool writes_lse = g == 0 && (!SPLIT || wave == 0);
+  float lse_before[NB];
+  if constexpr (SPLIT) {
+    SplitRow* const rows = reinterpret_cast<SplitRow*>(smem + SLOTS * 2 * TILE);
+    f32x4* const sums = reinterpret_cast<f32x4*>(smem) + lane;
+    constexpr int PER_WAVE = 2 * TILE / 16;
+    static_assert(DB * NB * 64 <= PER_WAVE, "a wave's sums fit where its tiles were");
+#pragma unroll
+    for (int i = 0; i < DB * NB; ++i) sums[wave * PER_WAVE + i * 64] = o[i / NB][i % NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int orow = q_w0 + 16 * nb + r;
+      if (g == 0) {
+        rows[wave * BQ + 16 * nb + r] = {m_run[nb], l_sum[nb],
+                                         wave == 0 && p.o_acc.ptr && orow < sq ? p.lse_acc.ptr[b * p.lse_acc.sb + hq * p.lse_acc.sh + orow] : 0.f};
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      SplitRow part[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) part[w] = rows[w * BQ + 16 * nb + r];
+      lse_before[nb] = part[0].lse_before;
+      m_run[nb] = part[0].m;
+#pragma unroll
+      for (int w = 1; w < NW; ++w) m_run[nb] = fmaxf(m_run[nb], part[w].m);
+      l_sum[nb] = 0.f;
+#pragma unroll
+      for (int i = 0; i < DBO; ++i) o[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {   // (a wave without keys for the row: zeros of weight one or zero)
+        const float weight = part[w].m == m_run[nb] ? 1.f : __builtin_amdgcn_exp2f(c * (part[w].m - m_run[nb]));
+        l_sum[nb] += weight * part[w].l;
+#pragma unroll
+        for (int i = 0; i < DBO; ++i) o[i][nb] += weight * sums[w * PER_WAVE + ((wave * DBO + i) * NB + nb) * 64];
+      }
+    }
+  }
+
   // Epilogue: normalise, Lse in natural-log units, optional online-softmax merge.
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    float l_tot = (l_run[nb][0] + l_run[nb][1]) + (l_run[nb][2] + l_run[nb][3]);
-    l_tot += __shfl_xor(l_tot, 16, 64);
-    l_tot += __shfl_xor(l_tot, 32, 64);
+    const float l_tot = l_sum[nb];
     const int orow = q_w0 + 16 * nb + r;
     if (orow >= sq) continue;
     const bool alive = l_tot != 0.f;   // (zero: no key seen; NaN is seen)
     const float inv = alive ? 1.f / l_tot : 0.f;
     const float lse_cur = alive ? (c * m_run[nb] + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
     if (p.o_part.ptr) {
-      const int64_t off = b * p.o_part.sb + (int64_t)orow * p.o_part.ss + hq * p.o_part.sh + 4 * g;
+      const int64_t off = b * p.o_part.sb + (int64_t)orow * p.o_part.ss + hq * p.o_part.sh + col0;
       if (p.o_part.is_f32) {
         float* dst = (float*)p.o_part.ptr + off;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = o[db][nb] * inv;
+        for (int db = 0; db < DBO; ++db) *reinterpret_cast<f32x4*>(dst + 16 * db) = o[db][nb] * inv;
       } else {
         __bf16* dst = (__bf16*)p.o_part.ptr + off;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+        for (int db = 0; db < DBO; ++db) {
           const f32x4 x = o[db][nb] * inv;
           *reinterpret_cast<bf16x4*>(dst + 16 * db) = bf16x4{(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
         }
       }
-      if (g == 0) p.lse_part.ptr[b * p.lse_part.sb + hq * p.lse_part.sh + orow] = lse_cur;
+      if (writes_lse) p.lse_part.ptr[b * p.lse_part.sb + hq * p.lse_part.sh + orow] = lse_cur;
     }
     if (p.o_acc.ptr && alive) {   // a step that saw no key leaves the running state untouched
       float* lse_ptr = p.lse_acc.ptr + b * p.lse_acc.sb + hq * p.lse_acc.sh + orow;
-      const float lse_old = *lse_ptr;
+      const float lse_old = SPLIT ? lse_before[nb] : *lse_ptr;
       const float mm = fmaxf(lse_old, lse_cur);   // finite, or lse_cur is NaN and reaches everything below
       const float e_old = __expf(lse_old - mm), e_cur = __expf(lse_cur - mm);
       const float tot = e_old + e_cur;
       const float lse_new = mm + __logf(tot);
       const float w_old = e_old / tot, w_cur_n = e_cur / tot * inv;
       const bool has_old = lse_old != -INFINITY;
-      float* dst = (float*)p.o_acc.ptr + b * p.o_acc.sb + (int64_t)orow * p.o_acc.ss + hq * p.o_acc.sh + 4 * g;
+      float* dst = (float*)p.o_acc.ptr + b * p.o_acc.sb + (int64_t)orow * p.o_acc.ss + hq * p.o_acc.sh + col0;
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
+      for (int db = 0; db < DBO; ++db) {
         f32x4* q4 = reinterpret_cast<f32x4*>(dst + 16 * db);
         // a running state that is still (anything, -inf) has weight zero and is not read as a number:
         // the buffer may hold whatever it was allocated with (0 * NaN would poison the row)
@@ -377,7 +477,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 3) void step_fwd_kernel(Fwd
         *q4 = o[db][nb] * w_cur_n + old * w_old;
       }
       // the four lanes of a row read lse_old above, in lockstep, before this store
-      if (g == 0) *lse_ptr = lse_new;
+      if (writes_lse) *lse_ptr = lse_new;
     }
   }
 }
@@ -409,10 +509,29 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p, in
   }
 }
 
-template <int D>
+// Whether the waves of a work-group share 32 query rows and deal the key tiles among themselves (SPLIT).  A launch of few query
+// tiles is as long as its longest walk, and shared out to four waves that walk is four times shorter, on eight (d = 64: four)
+// times as many work-groups.  A wave alone with its tiles, two products and the softmax one after the other, takes 1.2 (d = 64: 2.3) times as long
+// for one as the kernel whose waves take turns, and brings every tile for 32 rows: beyond two work-groups a CU, or one
+// and a half with uneven walks, which work-groups of four short walks even out, the other one is faster.  By work-groups times their mean walk over the
+// longest; first and last tile stand for all.  us of a pass with its fills, d = 128 (d = 64): full 2 x 256 rows (16) 28.7, 18.8 (19.5, 17.4); 4 x 1024
+// (128) 44.5, 24.6 (29.6, 22.1); 1 x 8192 (256) 190, 73 (119, 59); 16 x 1024 (512) 46.7, 37.8 (30.5, 25.9); 20 x 1024 (640) 48.6, 50.3 (30.9, 31.9);
+// 32 x 1000 (1024) 54, 66 (33, 38); causal 1 x 16384 (256) 352, 130 (222, 98); 1 x 32768 (512) 684, 441 (425, 244); 16 x 2048 (540) 72.3, 69.9
+// (44.7, 39.4); 48 x 512, two steps (576) 53.9, 57.7 (33.6, 37.6); 1 x 49546 (775) 1013, 968 (653, 494); zigzag 16 x 2048, four steps (950) 147, 169 (91, 88).
+constexpr int kSplitLoad = 544;
+static bool split_walks(const FwdParams& p) {
+  const int n = (p.sq + kSplitBQ - 1) / kSplitBQ;
+  int64_t first = 0, last = 0;
+  for (int i = 0; i < p.n_steps; ++i) {
+    first += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, n - 1, kSplitBQ);
+    last += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, 0, kSplitBQ);
+  }
+  return (int64_t)p.batch * p.q_heads * n * (first + last) <= 2 * kSplitLoad * std::max(first, last);
+}
+template <int D, bool SPLIT>
 static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
-  constexpr int BQ = kFwdBQ<D>, NW = kFwdWaves<D>;
-  constexpr int LDS = kFwdSlots<D> * 2 * 64 * 2 * D + kMaxBlockCacheTiles;
+  constexpr int BQ = SPLIT ? kSplitBQ : kFwdBQ<D>, NW = SPLIT ? kSplitWaves : kFwdWaves<D>;
+  constexpr int LDS = (SPLIT ? NW * (2 * 64 * 2 * D + BQ * (int)sizeof(SplitRow)) : kFwdSlots<D> * 2 * 64 * 2 * D) + kMaxBlockCacheTiles;
   p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {
@@ -427,10 +546,14 @@ static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
   p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, n_keys, group, p.q_runs, BQ);
   const int grid = mapped_grid(n_keys, group, p.q_runs.total());
   constexpr int NT = 64 * NW;
-  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, NW, true, false>), dim3(grid), dim3(NT), LDS, stream, p);
-  else if (p.n_steps > 1) hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, true>), dim3(grid), dim3(NT), LDS, stream, p);
-  else hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, false>), dim3(grid), dim3(NT), LDS, stream, p);
+  if (p.step[0].mask.blk) hipLaunchKernelGGL((step_fwd_kernel<D, NW, true, false, SPLIT>), dim3(grid), dim3(NT), LDS, stream, p);
+  else if (p.n_steps > 1) hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, true, SPLIT>), dim3(grid), dim3(NT), LDS, stream, p);
+  else hipLaunchKernelGGL((step_fwd_kernel<D, NW, false, false, SPLIT>), dim3(grid), dim3(NT), LDS, stream, p);
   return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_fwd_steps(FwdParams& p, hipStream_t stream) {
+  return split_walks(p) ? launch_fwd_t<D, true>(p, stream) : launch_fwd_t<D, false>(p, stream);
 }
 
 // With the fused merge and no separate step result, a key axis longer than two ranges is cut into ranges, each walked as
@@ -442,7 +565,7 @@ static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, i
   if (!p.o_acc.ptr || p.o_part.ptr) {
     p.n_steps = 1;
     p.step[0] = steps[0];
-    return launch_fwd_t<D>(p, stream);
+    return launch_fwd_steps<D>(p, stream);
   }
   std::vector<FwdStep> parts;
   for (int i = 0; i < n; ++i) {
@@ -462,7 +585,7 @@ static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, i
   return for_step_groups(parts, p.sq, p.batch * p.q_heads, [&](int first, int end) {
     p.n_steps = end - first;
     std::copy(parts.begin() + first, parts.begin() + end, p.step);
-    return launch_fwd_t<D>(p, stream);
+    return launch_fwd_steps<D>(p, stream);
   });
 }
 

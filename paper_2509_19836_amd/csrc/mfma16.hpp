@@ -103,6 +103,13 @@ __device__ __forceinline__ void wait_loads_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
+// The same wait without the meeting, for tiles that a wave brings for itself.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 // The same meeting without waiting for loads: between two phases of a wave.
 __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
@@ -321,6 +328,20 @@ struct KvStream {
   __device__ __forceinline__ void end() {
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) end(i);
+  }
+  // n tiles on; past the end the walk is over
+  __device__ __forceinline__ void skip(int n) {
+    static_assert(!LAG, "moves K and V of one tile");
+    if (BLK) {
+      for (int i = 0; i < n; ++i) end();
+      return;
+    }
+    const int more = negative_mask(n - left), m = n & more;
+    left = (left - n) & more;
+    k0 += m * BK;
+    k_tile += m * k_step;
+    v_tile += m * v_step;
+    pin(left, k0, k_tile, v_tile);
   }
   __device__ __forceinline__ void issue(uint32_t k_lds, uint32_t v_lds, int wave, int lane) {
     begin(wave, lane);
