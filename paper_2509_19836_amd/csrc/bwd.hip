@@ -643,6 +643,322 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, char* smem, int b
 }
 
 // ---------------------------------------------------------------------------------------------
+// Launches of few tiles (split_walks below): a work-group of four waves has 32 rows of dQ, or 32 key rows of dK and dV, and its
+// waves deal the tiles of the other axis among themselves, each with two tiles in an LDS slot pair of its own and no barrier until the sums meet.
+// What bounds such a launch is the chain of a walk (load, products, vector work, products), not a unit of the chip: it is four times
+// shorter so, on eight (dQ) and two or four (dK/dV) times as many CUs.  A wave has up to 512 registers: K, V and both sums fit one.
+template <int D>
+struct SplitWalk {
+  static constexpr int NW = 4, ROWS = 32, NB = ROWS / 16, DK = D / 32, DB = D / 16, AHEAD = 3;
+  static constexpr int BT = 4096 / D, MB = BT / 16, TILE = BT * 2 * D;    // rows of a tile of the walked axis: 8 KiB of each tensor
+  static constexpr int SLOT = 2 * TILE, WAVE = 2 * SLOT, VEC = BT * 4;
+  static constexpr int VEC_OFF = NW * WAVE;                               // [wave][slot][lse, D]: 64 values, BT of them read
+  static constexpr int BYTES = VEC_OFF + NW * 2 * 2 * 256;
+  static constexpr int DBO = DB / NW;                                     // column blocks of a wave when the sums have met
+};
+
+// acc of the waves, at `sums` [wave][DB * NB][lane]: the sum of all for column blocks wave * DBO .. of this wave
+template <int D>
+__device__ __forceinline__ f32x4 split_sum(const f32x4* sums, int stride, int wave, int i, int nb) {
+  using W = SplitWalk<D>;
+  f32x4 x = sums[((wave * W::DBO + i) * W::NB + nb) * 64];
+#pragma unroll
+  for (int w = 1; w < W::NW; ++w) x += sums[w * stride + ((wave * W::DBO + i) * W::NB + nb) * 64];
+  return x;
+}
+// Rows of a result from the waves' sums
+template <int D>
+__device__ __forceinline__ void split_store(const TensorDev& t, int b, int head, int row0, int rows, const f32x4* sums, int stride, float mul, int accumulate,
+                                            int wave, int lane) {
+  using W = SplitWalk<D>;
+  const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int nb = 0; nb < W::NB; ++nb) {
+    const int row = row0 + 16 * nb + r;
+    if (row >= rows) continue;
+    float* dst = (float*)t.ptr + b * t.sb + (int64_t)row * t.ss + head * t.sh + 16 * W::DBO * wave + 4 * g;
+    f32x4 old[W::DBO];
+#pragma unroll
+    for (int i = 0; i < W::DBO; ++i) old[i] = accumulate ? *reinterpret_cast<const f32x4*>(dst + 16 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < W::DBO; ++i) *reinterpret_cast<f32x4*>(dst + 16 * i) = split_sum<D>(sums + lane, stride, wave, i, nb) * mul + old[i];
+  }
+}
+
+template <int D, bool MULTI>
+__device__ __forceinline__ void dq_split_block(const BwdParams& p, char* smem, int block) {
+  using W = SplitWalk<D>;
+  constexpr int NB = W::NB, DK = W::DK, DB = W::DB, MB = W::MB, BT = W::BT, AHEAD = W::AHEAD;
+  const int group = p.q_heads / p.kv_heads;
+  const BlockMap bm = map_block<true>(block, p.batch * p.kv_heads, group, p.q_runs.total(), p.q_side_by_side);
+  if (!bm.valid) return;
+  const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, hq = hk * group + bm.head_in_group;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sq = p.sq, n_steps = MULTI ? p.n_steps : 1;
+  const MaskDev q_side = p.step[0].mask;   // all steps have the same
+  const int row0 = p.q_runs.tile_of(bm.tile) * W::ROWS, row1 = min(row0 + W::ROWS, sq);
+  bf16x8 qreg[DK][NB], doreg[DK][NB];
+  int q_pos[NB], klo[NB], khi[NB];
+  float lse2[NB], dval[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = min(row0 + 16 * nb + r, sq - 1);
+    q_pos[nb] = axis_position(axis_of<true>(q_side), row);
+    const __bf16* qs = (const __bf16*)p.q.ptr + b * p.q.sb + hq * p.q.sh + (int64_t)row * p.q.ss + 8 * g;
+    const __bf16* gs = (const __bf16*)p.d_o.ptr + b * p.d_o.sb + hq * p.d_o.sh + (int64_t)row * p.d_o.ss + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      qreg[ks][nb] = *reinterpret_cast<const bf16x8*>(qs + ks * 32);
+      doreg[ks][nb] = *reinterpret_cast<const bf16x8*>(gs + ks * 32);
+    }
+    lse2[nb] = lse_to_log2(p.lse.ptr[b * p.lse.sb + hq * p.lse.sh + row]);
+    dval[nb] = p.d.ptr[b * p.d.sb + hq * p.d.sh + row];
+  }
+  const float c = p.scale * kLog2e;
+  f32x4 dq[DB][NB];
+#pragma unroll
+  for (int i = 0; i < DB * NB; ++i) dq[i / NB][i % NB] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int qlo, qhi;
+  range_minmax<true>(q_side, row0, row1, qlo, qhi);
+  OperandAddr<D> ad;
+  ad.init(lane);
+  const uint32_t lds = (uint32_t)(uintptr_t)(lds_bytes)smem + wave * W::WAVE;
+  using Walk = KvStream<D, BT, 1, false, false>;
+#pragma clang loop unroll(disable)
+  for (int step = 0; step < n_steps; ++step) {
+    const BwdStep& st = p.step[MULTI ? step : 0];
+    const MaskDev mk = st.mask;
+    const int sk = st.sk;
+    const bool windowed = mk.window != kNoWindow;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) visible_rows<true>(mk, q_pos[nb], sk, klo[nb], khi[nb]);
+    TileRanges tiles;
+    tiles.init(row_intervals<false>(mk, qlo, qhi, sk, false), sk, BT);
+    Walk walk;
+    walk.init(mk, st.k, st.v, b, hk, sk, qlo, qhi, 0, lane, nullptr);
+    wait_global_loads();
+    walk.skip(wave);
+    if (!walk.valid()) continue;
+    auto ask = [&](uint32_t slot) {
+      walk.begin(0, lane);
+#pragma unroll
+      for (int i = 0; i < Walk::N; ++i) walk.load_k(i, slot, 0);
+#pragma unroll
+      for (int i = 0; i < Walk::N; ++i) walk.load_v(i, slot + W::TILE, 0);
+    };
+    uint32_t slot = lds, other = lds + W::SLOT;
+    ask(slot);
+    for (;;) {
+      const int k0 = walk.k0;
+      walk.skip(W::NW);
+      const bool more = walk.valid();
+      if (more) {
+        ask(other);
+        wait_loads<Walk::LOADS>();
+      } else {
+        wait_loads<0>();
+      }
+      if (tiles.some(k0)) {
+        f32x4 s[MB][NB], dp[MB][NB];
+        bf16x8 ds[MB / 2][NB], first[AHEAD];
+        rows_fetch<D, MB, AHEAD>(slot, ad, 0, first);
+        rows_product_pair<D, MB, NB, AHEAD>(slot, slot + W::TILE, ad, qreg, doreg, s, dp, first);
+        cols_fetch<D, AHEAD>(slot, ad, 0, first);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int ch = 0; ch < MB / 2; ++ch) {
+            f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+            if (!tiles.full(k0)) mask_rows32(x, y, k0 + 32 * ch, g, klo[nb], khi[nb], windowed);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              x[v] = __builtin_amdgcn_exp2f(c * x[v] - lse2[nb]) * (dp[2 * ch][nb][v] - dval[nb]);
+              y[v] = __builtin_amdgcn_exp2f(c * y[v] - lse2[nb]) * (dp[2 * ch + 1][nb][v] - dval[nb]);
+            }
+            ds[ch][nb] = pack_pair(x, y);
+          }
+        cols_product<D, MB / 2, NB, AHEAD>(slot, ad, 0, ds, dq, first);
+      }
+      if (!more) break;
+      const uint32_t x = slot;
+      slot = other;
+      other = x;
+    }
+  }
+  f32x4* const sums = reinterpret_cast<f32x4*>(smem);
+  constexpr int STRIDE = W::WAVE / 16;
+  static_assert(DB * NB * 64 <= STRIDE, "a wave's sums fit where its tiles were");
+#pragma unroll
+  for (int i = 0; i < DB * NB; ++i) sums[wave * STRIDE + i * 64 + lane] = dq[i / NB][i % NB];
+  __syncthreads();
+  split_store<D>(p.dq, b, hq, row0, sq, sums, STRIDE, p.scale, p.acc_dq, wave, lane);
+}
+
+template <int D, bool MULTI>
+__device__ __forceinline__ void dkdv_split_block(const BwdParams& p, char* smem, int block) {
+  using W = SplitWalk<D>;
+  constexpr int NB = W::NB, DK = W::DK, DB = W::DB, MB = W::MB, BT = W::BT, AHEAD = W::AHEAD;
+  int step = 0;   // the steps' work-groups one after the other
+  while (MULTI && step + 1 < p.n_steps && block >= p.step[step + 1].first_block) ++step;
+  const BwdStep& st = p.step[MULTI ? step : 0];
+  const BlockMap bm = map_block<false>(block - st.first_block, p.batch * p.kv_heads, 1, st.k_runs.total(), st.k_side_by_side);
+  if (!bm.valid) return;
+  const int b = __builtin_amdgcn_readfirstlane(bm.key / p.kv_heads), hk = bm.key - b * p.kv_heads, group = p.q_heads / p.kv_heads;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sq = p.sq, sk = st.sk;
+  const MaskDev mk = st.mask;
+  const int row0 = st.k_runs.tile_of(bm.tile) * W::ROWS, row1 = min(row0 + W::ROWS, sk);
+  const float c = p.scale * kLog2e;
+  // scale * log2(e) * K and -V, as in dkdv_role
+  bf16x8 kreg[DK][NB], vreg[DK][NB];
+  int qlo[NB], qhi[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = min(row0 + 16 * nb + r, sk - 1);
+    visible_rows<false>(mk, axis_position(axis_of<false>(mk), row), sq, qlo[nb], qhi[nb]);
+    const __bf16* ks_ = (const __bf16*)st.k.ptr + b * st.k.sb + hk * st.k.sh + (int64_t)row * st.k.ss + 8 * g;
+    const __bf16* vs_ = (const __bf16*)st.v.ptr + b * st.v.sb + hk * st.v.sh + (int64_t)row * st.v.ss + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      kreg[ks][nb] = *reinterpret_cast<const bf16x8*>(ks_ + ks * 32);
+      vreg[ks][nb] = *reinterpret_cast<const bf16x8*>(vs_ + ks * 32);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        kreg[ks][nb][e] = (__bf16)((float)kreg[ks][nb][e] * c);
+        vreg[ks][nb][e] = -vreg[ks][nb][e];
+      }
+    }
+  }
+  f32x4 dk[DB][NB], dv[DB][NB];
+#pragma unroll
+  for (int i = 0; i < DB * NB; ++i) dk[i / NB][i % NB] = dv[i / NB][i % NB] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int lo, hi;
+  range_minmax<false>(mk, row0, row1, lo, hi);
+  TileRanges tiles;
+  tiles.init(row_intervals<true>(mk, lo, hi, sq, false), sq, BT);
+  const TileRun run = visible_tiles<true, BT>(mk, lo, hi, sq);
+  const int start = __builtin_amdgcn_readfirstlane(run.start), len = __builtin_amdgcn_readfirstlane(run.len);
+  OperandAddr<D> ad;
+  ad.init(lane);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem, lds = lds0 + wave * W::WAVE;
+  const uint32_t vec_off = W::VEC_OFF + wave * 2 * 512;
+  // The walk: head after head, the tiles wave, wave + NW, .. of each (heads take turns in which wave starts)
+  using Stager = DirectStager<D, BT, 1>;
+  constexpr int LOADS = 2 * Stager::N + 2;
+  Stager q_rows, o_rows;
+  uint32_t vec_lane = 0;
+  const char *q_head = reinterpret_cast<const char*>((const __bf16*)p.q.ptr + b * p.q.sb + hk * group * p.q.sh);
+  const char *o_head = reinterpret_cast<const char*>((const __bf16*)p.d_o.ptr + b * p.d_o.sb + hk * group * p.d_o.sh);
+  const char *l_head = reinterpret_cast<const char*>(p.lse.ptr + b * p.lse.sb + hk * group * p.lse.sh);
+  const char *d_head = reinterpret_cast<const char*>(p.d.ptr + b * p.d.sb + hk * group * p.d.sh);
+  int valid = 0;   // rows the lanes' offsets are clamped to
+  int head = 0, at = wave;
+  auto settle = [&]() {   // to the next tile there is; head == group: none
+    while (head < group && at >= len) {
+      at -= len;
+      ++head;
+    }
+    pin(head, at);
+  };
+  auto ask = [&](int n) {   // the cursor's tile into slot n
+    const int first_row = (start + at) * BT, rows = min(sq - first_row, BT);
+    if (rows != valid) {
+      valid = rows;
+      q_rows.clamp(p.q.ss, rows, 0, lane);
+      o_rows.clamp(p.d_o.ss, rows, 0, lane);
+      vec_lane = 4u * (uint32_t)min(lane, rows - 1);
+    }
+    const char* q_tile = q_head + 2 * ((int64_t)head * p.q.sh + (int64_t)first_row * p.q.ss);
+    const char* o_tile = o_head + 2 * ((int64_t)head * p.d_o.sh + (int64_t)first_row * p.d_o.ss);
+    const char* l_tile = l_head + 4 * ((int64_t)head * p.lse.sh + first_row);
+    const char* d_tile = d_head + 4 * ((int64_t)head * p.d.sh + first_row);
+    pin(q_tile, o_tile, l_tile, d_tile);
+    const uint32_t q_lds = lds + n * W::SLOT, vec = lds0 + vec_off + n * 512;
+    load_dword_to_lds(l_tile, vec_lane, vec);
+    load_dword_to_lds(d_tile, vec_lane, vec + 256);
+#pragma unroll
+    for (int i = 0; i < Stager::N; ++i) q_rows.load_one(q_tile, i, q_lds, 0);
+#pragma unroll
+    for (int i = 0; i < Stager::N; ++i) o_rows.load_one(o_tile, i, q_lds + W::TILE, 0);
+  };
+  wait_global_loads();
+  if (len > 0) settle();
+  else head = group;
+  if (head < group) {
+    int n = 0;
+    ask(0);
+    for (;;) {
+      const int q0 = (start + at) * BT;
+      at += W::NW;
+      settle();
+      const bool more = head < group;
+      if (more) {
+        ask(n ^ 1);
+        wait_loads<LOADS>();
+      } else {
+        wait_loads<0>();
+      }
+      if (tiles.some(q0)) {
+        const uint32_t qt = lds + n * W::SLOT, ot = qt + W::TILE;
+        const char* vec = smem + vec_off + n * 512;
+        f32x4 s[MB][NB], dp[MB][NB], init[MB];
+        bf16x8 pp[MB / 2][NB], ds[MB / 2][NB], first[AHEAD];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(vec + 4 * (16 * mb + 4 * g));
+#pragma unroll
+          for (int v = 0; v < 4; ++v) init[mb][v] = -lse_to_log2(x[v]);
+        }
+        rows_fetch<D, MB, AHEAD>(qt, ad, 0, first);
+        rows_product<D, MB, NB, AHEAD>(qt, ad, 0, kreg, s, init, first);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) init[mb] = *reinterpret_cast<const f32x4*>(vec + 256 + 4 * (16 * mb + 4 * g));
+        rows_fetch<D, MB, AHEAD>(ot, ad, 0, first);
+        rows_product<D, MB, NB, AHEAD>(ot, ad, 0, vreg, dp, init, first);   // D - dP
+        cols_fetch<D, AHEAD>(ot, ad, 0, first);
+#pragma unroll
+        for (int ch = 0; ch < MB / 2; ++ch)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb], &dx = dp[2 * ch][nb], &dy = dp[2 * ch + 1][nb];
+            if (!tiles.full(q0)) mask_rows32(x, y, q0 + 32 * ch, g, qlo[nb], qhi[nb], true);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              x[v] = __builtin_amdgcn_exp2f(x[v]);
+              y[v] = __builtin_amdgcn_exp2f(y[v]);
+            }
+            pp[ch][nb] = pack_pair(x, y);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              dx[v] *= (float)pp[ch][nb][v];
+              dy[v] *= (float)pp[ch][nb][v + 4];
+            }
+            ds[ch][nb] = pack_pair(dx, dy);   // -dS
+          }
+        cols_product<D, MB / 2, NB, AHEAD>(ot, ad, 0, pp, dv, first);
+        cols_fetch<D, AHEAD>(qt, ad, 0, first);
+        cols_product<D, MB / 2, NB, AHEAD>(qt, ad, 0, ds, dk, first);
+      }
+      if (!more) break;
+      n ^= 1;
+    }
+  }
+  f32x4* const sums = reinterpret_cast<f32x4*>(smem);
+  constexpr int STRIDE = W::WAVE / 16, HALF = DB * NB * 64;
+  static_assert(2 * HALF <= STRIDE, "a wave's sums fit where its tiles were");
+#pragma unroll
+  for (int i = 0; i < DB * NB; ++i) {
+    sums[wave * STRIDE + i * 64 + lane] = dk[i / NB][i % NB];
+    sums[wave * STRIDE + HALF + i * 64 + lane] = dv[i / NB][i % NB];
+  }
+  __syncthreads();
+  split_store<D>(st.dk, b, hk, row0, sk, sums, STRIDE, -p.scale, p.acc_dk, wave, lane);
+  split_store<D>(st.dv, b, hk, row0, sk, sums + HALF, STRIDE, 1.f, p.acc_dv, wave, lane);
+}
+
+// ---------------------------------------------------------------------------------------------
 // A kernel argument indexed with a variable would be copied to scratch memory: several steps are read through the argument
 // pointer, a single one (MULTI false) directly, all at once at the start.
 __device__ __forceinline__ const BwdParams& launch_args() {
@@ -680,6 +996,22 @@ __global__ __launch_bounds__(512, TURNS ? 1 : 4) void step_bwd_both_kernel(BwdPa
   }
 }
 
+// Both with walks dealt to the waves of a work-group
+template <int D, bool MULTI>
+__global__ __launch_bounds__(64 * SplitWalk<D>::NW, 1) void step_bwd_split_kernel(BwdParams, int n_first, int dq_first) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  typedef const __attribute__((address_space(4))) BwdParams* args_ptr;
+  args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int in_first = (int)blockIdx.x < n_first, block = blockIdx.x - (in_first ? 0 : n_first);
+  if (in_first != dq_first) {
+    asm volatile("" : "+s"(args));
+    dkdv_split_block<D, MULTI>(*(const BwdParams*)args, smem, block);
+  } else {
+    asm volatile("" : "+s"(args));
+    dq_split_block<D, MULTI>(*(const BwdParams*)args, smem, block);
+  }
+}
+
 // Whether the dK/dV kernel takes key tiles of 64 rows.  A tile of 64 costs 0.6-0.7 of one of 128 (more barriers and LDS
 // traffic per MFMA), so it pays where the tiles of 128 leave half the CUs idle, and, up to one per CU, where the walks
 // are uneven, as the mask makes them, and the longest one decides.  One step, full mask, tiles of 128: 64 of them 61 us
@@ -705,14 +1037,11 @@ static hipError_t plan_dq(BwdParams& p, int BQ, hipStream_t stream) {
     return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
   return hipSuccess;
 }
-static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
+static hipError_t plan_dkdv_tiles(BwdParams& p, int tile, hipStream_t stream) {
   const int n_keys = p.batch * p.kv_heads;
-  for (int i = 0; i < p.n_steps; ++i) p.step[i].k_runs = nonempty_k_runs(p.step[i].mask, p.sq, p.step[i].sk, 128);
-  narrow = narrow_key_tiles(p);
-  const int tile = narrow ? 64 : 128;
   for (int i = 0; i < p.n_steps; ++i) {
     BwdStep& st = p.step[i];
-    if (narrow) st.k_runs = nonempty_k_runs(st.mask, p.sq, st.sk, 64);
+    st.k_runs = nonempty_k_runs(st.mask, p.sq, st.sk, tile);
     st.k_side_by_side = k_side_by_side(st.mask, p.sq, st.sk, n_keys, st.k_runs, tile);
     if (st.k_runs.total() < (st.sk + tile - 1) / tile) {
       hipError_t e = hipSuccess;
@@ -735,11 +1064,19 @@ static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
   }
   return hipSuccess;
 }
+static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
+  for (int i = 0; i < p.n_steps; ++i) p.step[i].k_runs = nonempty_k_runs(p.step[i].mask, p.sq, p.step[i].sk, 128);
+  narrow = narrow_key_tiles(p);
+  return plan_dkdv_tiles(p, narrow ? 64 : 128, stream);
+}
 static int dq_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total()); }
 static int dkdv_grid(const BwdParams& p) {
   const BwdStep& last = p.step[p.n_steps - 1];
   return last.first_block + mapped_grid(p.batch * p.kv_heads, 1, last.k_runs.total());
 }
+
+// a dQ work-group walks every step (three products a tile against two), a dK/dV one the heads of its group
+static bool longer_dq_walks(const BwdParams& p) { return p.n_steps > 1 && 3 * p.n_steps > 4 * (p.q_heads / p.kv_heads); }
 
 template <int D>
 constexpr int kDqLds = kBwdSlots<D == 128> * 2 * 64 * 2 * D;
@@ -827,6 +1164,48 @@ static void launch_both_kernel(const BwdParams& p, int grid, int n_first, int dq
   constexpr int DQ_LDS = kBwdSlots<TURNS> * 2 * 64 * 2 * D, LDS = std::max(kDkdvLds<D, TURNS>, DQ_LDS);
   hipLaunchKernelGGL((step_bwd_both_kernel<D, MULTI, BKV, TURNS>), dim3(grid), dim3(512), LDS, stream, p, n_first, dq_first);
 }
+// Whether the walks of a joint launch are dealt to the waves of its work-groups.  By the time of the longest walk or, if longer,
+// of the work spread over the CUs, in products of a wave (a product of 64 x 32; d = 128 0.3 us, d = 64 0.15): three for a tile of dQ, four for one
+// of dK/dV, and about eight to start a further work-group on a CU.  The other kernels' work-groups have a CU each: a tile costs dQ, for 256
+// rows, 6 (d = 64: 8) of them, and dK/dV, whose waves share a tile as it is, 3 (4).  So splitting pays by dQ's walks and for few of them.
+// us of backward with D and fills, d = 128 (d = 64): full 2 x 256 rows 35.9, 27.9 (28.0, 23.5); 4 x 1024 59.0, 45.5 (43.6, 32.0); 1 x 4096 140, 98 (97.5,
+// 56.7); 8 x 1024 62.7, 61.7 (44.7, 41.7); 12 x 1024 67.8, 89.3 (47.2, 55.8); 64 x 128 32.0, 37.1 (25.1, 29.8); 8/1 x 1024 132, 164 (91, 88); causal 8 x
+// 1024 62.4, 53.0 (45.0, 38.3); 1 x 16384 512, 498 (344, 265); 1 x 24576 976, 1075 (631, 556); 12 x 1500 93.7, 106 (67.6, 73.4).
+template <int D>
+static bool split_walks(const BwdParams& p) {
+  constexpr int ROWS = SplitWalk<D>::ROWS, kStart = 8, kDq = D == 128 ? 6 : 8, kDkdv = D == 128 ? 3 : 4;
+  const int64_t keys = (int64_t)p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
+  const int nq = (p.sq + ROWS - 1) / ROWS;
+  int64_t groups = keys * group * nq, first = 0, last = 0;
+  for (int i = 0; i < p.n_steps; ++i) {
+    first += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, nq - 1, ROWS);
+    last += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, 0, ROWS);
+  }
+  const int64_t dq = std::max(first, last);
+  int64_t work = 3 * groups * (first + last) / 2, dkdv = 0;
+  for (int i = 0; i < p.n_steps; ++i) {
+    const BwdStep& st = p.step[i];
+    const int nk = (st.sk + ROWS - 1) / ROWS;
+    first = group * k_tile_walk(st.mask, p.sq, st.sk, 0, ROWS);
+    last = group * k_tile_walk(st.mask, p.sq, st.sk, nk - 1, ROWS);
+    work += 4 * keys * nk * (first + last) / 2;
+    groups += keys * nk;
+    dkdv = std::max({dkdv, first, last});
+  }
+  return std::max({3 * dq, 4 * dkdv, work / kAlone}) + (groups - 1) / kAlone * kStart <= std::max(kDq * dq, kDkdv * dkdv);
+}
+template <int D>
+static hipError_t launch_split_t(BwdParams& p, hipStream_t stream) {
+  using W = SplitWalk<D>;
+  hipError_t e = plan_dq(p, W::ROWS, stream);
+  if (e == hipSuccess) e = plan_dkdv_tiles(p, W::ROWS, stream);
+  const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
+  if (e != hipSuccess || grid == 0) return e;
+  const int dq_first = longer_dq_walks(p), n_first = dq_first ? n_dq : n_dkdv;
+  if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_split_kernel<D, true>), dim3(grid), dim3(64 * W::NW), W::BYTES, stream, p, n_first, dq_first);
+  else hipLaunchKernelGGL((step_bwd_split_kernel<D, false>), dim3(grid), dim3(64 * W::NW), W::BYTES, stream, p, n_first, dq_first);
+  return hipGetLastError();
+}
 // One launch of both kernels; `done` says whether it was taken.
 template <int D>
 static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
@@ -835,13 +1214,13 @@ static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
   for (int i = 0; i < p.n_steps; ++i) most += (int64_t)n_keys * ((p.step[i].sk + 127) / 128);
   done = most <= (p.n_steps > 1 ? 2 : 1) * kBothLaunch;
   if (!done) return hipSuccess;
+  if (split_walks<D>(p)) return launch_split_t<D>(p, stream);
   bool narrow = false;
   hipError_t e = plan_dq(p, kBothBQ, stream);
   if (e == hipSuccess) e = plan_dkdv(p, narrow, stream);
   const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
   if (e != hipSuccess || grid == 0) return e;
-  // a dQ work-group walks every step (three products a tile against two), a dK/dV one the heads of its group
-  const int dq_first = p.n_steps > 1 && 3 * p.n_steps > 4 * group, n_first = dq_first ? n_dq : n_dkdv;
+  const int dq_first = longer_dq_walks(p), n_first = dq_first ? n_dq : n_dkdv;
   const bool multi = p.n_steps > 1;
   const bool alone = D == 128 || grid <= kAlone || !crowded(p, narrow);
   auto launch = [&](auto m, auto bkv) {
