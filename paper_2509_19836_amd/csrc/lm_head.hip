@@ -3,8 +3,8 @@
 // Per sequence tile of B_s tokens, four launches:
 //   1. lm_logits_kernel       Logits^T tile = W_head H_i^T on the matrix cores (bf16 in, fp32 out).
 //                             Computed transposed so that a lane owns a token: the per-token
-//                             (max, sum of exp) over the wave's 128 words is a reduction over the
-//                             lane's own registers, as in the attention forward.  The fp32 logits of
+//                             (max, sum of exp) over 128 words starts as a reduction over
+//                             a lane's own registers, as in the attention forward.  The fp32 logits of
 //                             the tile go to the workspace (the algorithm keeps them between its two
 //                             sweeps over the vocabulary); the partial (max, sum) pairs go to a side array.
 //   2. lm_loss_dlogits_kernel one work-group per token: merges the partial pairs into Lse_i, writes
@@ -13,9 +13,10 @@
 //   3. lm_dh_kernel           dH_i  = dLogits W_head          (contraction over the vocabulary)
 //   4. lm_transpose_h_kernel + lm_dw_kernel
 //                             dW^T += H_i^T dLogits           (contraction over the tile's tokens)
-// The three GEMMs share one main loop (LmGemm below).  An operand whose contraction index is the storage row is
+// The three GEMMs share one main loop (LmGemm below), or where tiles of 256 x 256 are few or short LmGemmSmall (lm_plan).  An operand whose contraction index is the storage row is
 // read with the transposing LDS read; only H_i, a few MB per sequence tile, is ever transposed in memory.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -36,11 +37,12 @@ constexpr int kLmBM = 256, kLmBN = 256, kLmBK = 64, kLmThreads = 512;
 //                 transposing read, which hands out rows 16 (e / 4) + 4 g + e % 4 of 32, gives k = 8 g + e as the
 //                 row-wise operand has it.  lim = valid k rows; a k-tile that reaches past them reads copies of
 //                 the last one.
-template <bool COLS>
+template <bool COLS, int X, int NW>   // X rows or columns of the output tile, brought by NW waves
 struct LmOperand {
-  static constexpr int N = 4, BYTES = 256 * kLmBK * 2;
-  using Rows = DirectStager<64, 256, 8>;
-  using Cols = DirectStager<128, kLmBK, 8>;   // one of the two tiles
+  static constexpr int N = 4, BYTES = X * kLmBK * 2;
+  static_assert(BYTES == N * NW * 1024, "four loads per wave");
+  using Rows = DirectStager<64, X, NW>;
+  using Cols = DirectStager<128, kLmBK, NW>;   // one of the X / 128 tiles
   Rows rows;
   uint32_t col_off[Cols::N];
   const char* tile;     // k-tile to ask for
@@ -56,13 +58,13 @@ struct LmOperand {
       valid = lim;
       offsets(wave, lane);
     } else {
-      rows.clamp(ld, min(256, lim - x0), wave, lane);
+      rows.clamp(ld, min(X, lim - x0), wave, lane);
     }
   }
   __device__ __forceinline__ void offsets(int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < Cols::N; ++i) {
-      const int at = (i * 8 + wave) * Cols::RPI + lane / 16;   // row in LDS
+      const int at = (i * NW + wave) * Cols::RPI + lane / 16;   // row in LDS
       const int k = (at & 32) + 8 * ((at >> 2) & 3) + 4 * ((at >> 4) & 1) + (at & 3);
       col_off[i] = 2u * ((uint32_t)min(k, valid - 1) * (uint32_t)ld + (uint32_t)(((lane % 16) ^ swz<128>(at)) * 8));
     }
@@ -78,7 +80,8 @@ struct LmOperand {
     }
   }
   __device__ __forceinline__ void load(int i, uint32_t lds, int wave) const {
-    if (COLS) load_to_lds(tile + (i / 2) * 256, col_off[i % 2], lds + (i / 2) * Cols::BYTES + ((i % 2) * 8 + wave) * 1024);
+    constexpr int PER = Cols::N;   // loads of a tile
+    if (COLS) load_to_lds(tile + (i / PER) * 256, col_off[i % PER], lds + (i / PER) * Cols::BYTES + ((i % PER) * NW + wave) * 1024);
     else rows.load_one(tile, i, lds, wave);
   }
 };
@@ -98,8 +101,9 @@ struct LmOperand {
 // the rest of logits and dW (13 and 23 us per output tile) is their fp32 output, which all CUs write at the same time.
 template <bool B_COLS>
 struct LmGemm {
-  using OpA = LmOperand<false>;
-  using OpB = LmOperand<B_COLS>;
+  using OpA = LmOperand<false, kLmBM, 8>;
+  using OpB = LmOperand<B_COLS, kLmBN, 8>;
+  static constexpr int BM = kLmBM, BN = kLmBN, HALVES = 2, THREADS = kLmThreads;
   static constexpr int SLOT = OpA::BYTES + OpB::BYTES, LDS = 2 * SLOT, AHEAD = 3;
   f32x4 acc[2][4][4];   // [half][mb][nb]: rows 128 half + 64 wm + 16 mb + 4 g + v, column 64 wn + 16 nb + r
   bf16x8 bf[2][4];      // [k-step][nb]
@@ -111,7 +115,7 @@ struct LmGemm {
     return rows_operand<64>(slot + half * (OpA::BYTES / 2) + wm * (64 * 128), ad, 16 * (i % 4), i / 4);
   }
   __device__ __forceinline__ bf16x8 b_operand(uint32_t slot, int wn, int ks, int nb) const {
-    if (B_COLS) return cols_operand<128>(slot + OpA::BYTES + (wn >> 1) * LmOperand<true>::Cols::BYTES, adc, 32 * ks, nb);
+    if (B_COLS) return cols_operand<128>(slot + OpA::BYTES + (wn >> 1) * OpB::Cols::BYTES, adc, 32 * ks, nb);
     return rows_operand<64>(slot + OpA::BYTES + wn * (64 * 128), ad, 16 * nb, ks);
   }
   // The 32 MFMAs of a phase, hook(i) behind the four of operand i.  The next phase reads half HALF ^ 1 from slot `next`.
@@ -191,17 +195,77 @@ struct LmGemm {
   }
 };
 
+// Output tiles of 128 x 128 by four waves, two work-groups per CU, for short contractions and for few output tiles: a work-group's first
+// loads and its fp32 output, which a CU with one work-group waits for at each end, pass while the other one multiplies.  Where the
+// contraction is long this is the slower loop: it brings twice the bytes, and reads a third more from LDS, per product.
+// Tile t + 2 is asked for when all waves have left tile t; the other work-group's matrix phases cover its way.
+template <bool B_COLS>
+struct LmGemmSmall {
+  static constexpr int BM = 128, BN = 128, HALVES = 1, THREADS = 256;
+  using OpA = LmOperand<false, BM, 4>;
+  using OpB = LmOperand<B_COLS, BN, 4>;
+  static constexpr int SLOT = OpA::BYTES + OpB::BYTES, LDS = 2 * SLOT;
+  f32x4 acc[1][4][4];   // [0][mb][nb]: rows 64 wm + 16 mb + 4 g + v, column 64 wn + 16 nb + r
+
+  __device__ __forceinline__ void run(char* smem, OpA& a, OpB& b, int nk, int wm, int wn, int wave, int lane) {
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes)smem;
+    OperandAddr<64> ad;
+    OperandAddr<128> adc;
+    ad.init(lane);
+    adc.init(lane);
+    adc.cols ^= (uint32_t)wn << 7;         // column blocks 4 .. 7 of the tile
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][i / 4][i % 4] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto ask = [&](uint32_t slot) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a.load(i, slot, wave);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b.load(i, slot + OpA::BYTES, wave);
+      a.next(wave, lane);
+      b.next(wave, lane);
+    };
+    wait_global_loads();
+    ask(lds0);
+    ask(lds0 + SLOT);
+    uint32_t slot = lds0, other = lds0 + SLOT;
+    for (int t = 0; t < nk; ++t) {
+      wait_loads_barrier<8>();             // tile t
+      bf16x8 x[2][4], y[2][4];             // [k-step]: A, B
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[ks][i] = rows_operand<64>(slot + wm * (64 * 128), ad, 16 * i, ks);
+          y[ks][i] = B_COLS ? cols_operand<128>(slot + OpA::BYTES, adc, 32 * ks, i) : rows_operand<64>(slot + OpA::BYTES + wn * (64 * 128), ad, 16 * i, ks);
+        }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[0][i / 4][i % 4] = mfma16(x[ks][i / 4], y[ks][i % 4], acc[0][i / 4][i % 4]);
+      phase_barrier();                     // all waves have left the slot
+      ask(slot);
+      const uint32_t z = slot;
+      slot = other;
+      other = z;
+    }
+    wait_global_loads();                   // tiles past the end
+  }
+};
+template <bool SMALL, bool B_COLS>
+using LmGemmOf = std::conditional_t<SMALL, LmGemmSmall<B_COLS>, LmGemm<B_COLS>>;
+
 // Work-group -> output tile and, where the contraction is split, its part of the k-tiles.  Work-group n runs on XCD
 // n mod 8.
 //  - More than one work-group per CU (kLmOneRound): each XCD takes groups of 4 x 8 tiles (one per CU), so the 32
 //    work-groups that share an L2 at a time read 4 + 8 operand panels.
 //  - Else every XCD takes an eighth of the tiles, neighbours in m first: what counts is that no CU gets two while
 //    another has none (16 tiles of dH for 256 tokens are one group of eight on two XCDs).
-constexpr int kLmOneRound = 256;
+constexpr int kLmOneRound = 256;   // (128 x 128 tiles: twice as many)
+template <class G>
 __device__ __forceinline__ bool lm_tile(int bid, int TM, int TN, int splits, int& tm, int& tn, int& split) {
   const int xcd = bid & 7, slot = bid >> 3, total = TM * TN * splits;
   split = 0;
-  if (total <= kLmOneRound) {
+  if (total <= kLmOneRound * (G::HALVES == 1 ? 2 : 1)) {
     const int per = (total + 7) / 8, i = xcd * per + slot;
     if (slot >= per || i >= total) return false;
     split = i / (TM * TN);
@@ -218,9 +282,9 @@ __device__ __forceinline__ bool lm_tile(int bid, int TM, int TN, int splits, int
   tn = gn * 8 + (within >> 2);
   return tm < TM && tn < TN;
 }
-int lm_grid(int TM, int TN, int splits = 1) {
+int lm_grid(int TM, int TN, int splits, bool small) {
   const int total = TM * TN * splits;
-  if (total <= kLmOneRound) return (total + 7) / 8 * 8;
+  if (total <= kLmOneRound * (small ? 2 : 1)) return (total + 7) / 8 * 8;
   const int groups = ((TM + 3) / 4) * ((TN + 7) / 8);
   return (groups + 7) / 8 * 8 * 32;
 }
@@ -231,9 +295,9 @@ int lm_grid(int TM, int TN, int splits = 1) {
 // a part, below which starting a work-group and the extra pass over the partial sums cost more than they give.
 // 256 tokens, d = 4096, 32000 words (16 output tiles, 7 parts): dH 650 -> 117 us with the sum; the call over 1000
 // tokens in such tiles 3866 -> 1887 us.
-int lm_dh_splits(const LmHeadParams& p, int TM, int TN) {
-  const int64_t fits = (int64_t)p.tile_tokens * p.v_pad / ((int64_t)TM * kLmBM * p.d_model);
-  const int64_t s = std::min<int64_t>({kLmOneRound / (TM * TN), fits, p.vocab / (16 * kLmBK)});
+int lm_dh_splits(const LmHeadParams& p, int TM, int TN, bool small) {
+  const int64_t fits = (int64_t)p.tile_tokens * p.v_pad / ((int64_t)TM * (small ? 128 : kLmBM) * p.d_model);
+  const int64_t s = std::min<int64_t>({kLmOneRound * (small ? 2 : 1) / (TM * TN), fits, p.vocab / (16 * kLmBK)});
   return (int)std::max<int64_t>(s, 1);
 }
 
@@ -251,6 +315,40 @@ int lm_logit_splits(const LmHeadParams& p, int TM, int TN) {
   return (int)std::max<int64_t>(s, 1);
 }
 
+// Tiles of one of the three products over a sequence tile
+struct LmPlan {
+  int TM, TN, splits;
+  bool small;   // tiles of 128 x 128 (LmGemmSmall)
+  int tile() const { return small ? 128 : kLmBM; }
+  // Tenths of a microsecond, by rounds of work-groups: 1.5 us a k-tile and 14 us for first loads and output of a 256 x 256 tile; 1.1 and
+  // 5 us of two work-groups with a 128 x 128 tile each.
+  int64_t time(int nk) const {
+    const int64_t groups = (int64_t)TM * TN * splits, parts = (nk + splits - 1) / splits;
+    return small ? (groups + 2 * kLmOneRound - 1) / (2 * kLmOneRound) * (11 * parts + 50) : (groups + kLmOneRound - 1) / kLmOneRound * (15 * parts + 140);
+  }
+};
+// The small tiles where they are clearly ahead by that: a tenth for the logits, a fifth for the other two, whose small tiles a long run of rounds
+// holds up more than it says (dW of 281 tokens x 73783 words, d = 768, 0.85 of the time by it: 9 us slower).  The whole call, us, with
+// 256 x 256 tiles and with small ones for that product alone: logits, d = 768, 2426 tokens x 8354 words (2 rounds, 3) 193, 169; 281 x 73783 297,
+// 278; d = 1024, 242 x 8216 87, 73; d = 2048, 64 x 113750 603, 555; against the rule: d = 768, 2048 x 60455 787, 863; d = 4096, 1000 x 32000 767, 854.
+// dW: d = 768, 2426 x 8354 (99 tiles) 193, 178; 2048 x 9304 164, 152; d = 2048, 129 x 17229 123, 118; against: d = 512, 4096 x 29660 581, 627.  dH:
+// d = 2560, 207 x 10874 (4 parts, by the room for them) 166, 146; d = 1024, 242 x 8216 87, 78; against: d = 768, 635 x 52993 311, 316.
+LmPlan lm_plan(const LmPlan& big, const LmPlan& small, int nk, int tenths) { return 10 * small.time(nk) <= tenths * big.time(nk) ? small : big; }
+LmPlan lm_plan_logits(const LmHeadParams& p, int n_rows) {
+  LmPlan big{p.v_pad / kLmBM, (n_rows + kLmBN - 1) / kLmBN, 1, false};
+  big.splits = lm_logit_splits(p, big.TM, big.TN);
+  return lm_plan(big, LmPlan{(p.vocab + 127) / 128, (n_rows + 127) / 128, 1, true}, p.d_model / kLmBK, 9);
+}
+LmPlan lm_plan_dh(const LmHeadParams& p, int n_rows) {
+  LmPlan big{(n_rows + kLmBM - 1) / kLmBM, p.d_model / kLmBN, 1, false}, small{(n_rows + 127) / 128, p.d_model / 128, 1, true};
+  big.splits = lm_dh_splits(p, big.TM, big.TN, false);
+  small.splits = lm_dh_splits(p, small.TM, small.TN, true);
+  return lm_plan(big, small, (p.vocab + kLmBK - 1) / kLmBK, 8);
+}
+LmPlan lm_plan_dw(const LmHeadParams& p, int n_rows) {
+  return lm_plan(LmPlan{p.d_model / kLmBM, p.v_pad / kLmBN, 1, false}, LmPlan{p.d_model / 128, (p.vocab + 127) / 128, 1, true}, (n_rows + kLmBK - 1) / kLmBK, 8);
+}
+
 // (max, sum of exp(x - max)) pairs combine like the log-sum-exp merge of the attention forward.
 __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l2) {
   const float mm = fmaxf(m, m2);
@@ -261,17 +359,18 @@ __device__ __forceinline__ void lm_combine(float& m, float& l, float m2, float l
 // ---------------------------------------------------------------------------------------------
 // 1. Logits^T tile (rows: words, columns: tokens of the sequence tile), Alg. 3 forward sweep.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
-  using G = LmGemm<false>;
+template <bool SMALL>
+__global__ __launch_bounds__((LmGemmOf<SMALL, false>::THREADS), 2) void lm_logits_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
+  using G = LmGemmOf<SMALL, false>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn, split;
-  if (!lm_tile(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
+  if (!lm_tile<G>(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk_all = p.d_model / kLmBK;
+  const int m0 = tm * G::BM, n0 = tn * G::BN, nk_all = p.d_model / kLmBK;
   const int kt0 = nk_all * split / splits, nk = nk_all * (split + 1) / splits - kt0, k0 = kt0 * kLmBK;
-  G::OpA a;
-  G::OpB b;
+  typename G::OpA a;
+  typename G::OpB b;
   a.init(p.w + k0, p.ld_w, p.vocab, m0, nk, wave, lane);
   b.init(p.h + (int64_t)s0 * p.ld_h + k0, p.ld_h, n_rows, n0, nk, wave, lane);
   G gemm;
@@ -281,19 +380,24 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p
   if (splits > 1) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
-      float* dst = p.logits + ((int64_t)split * TN * kLmBN + n0 + wn * 64 + 16 * nb + r) * p.v_pad + word0;
+      float* dst = p.logits + ((int64_t)split * TN * G::BN + n0 + wn * 64 + 16 * nb + r) * p.v_pad + word0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb];
+      for (int i = 0; i < 4 * G::HALVES; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb];
     }
     return;
   }
+  // (max, sum of exp) of a token over 128 consecutive words, from the 16 words of each of eight lanes in two waves: the same sums in the
+  // same order for either tile, so that Lse does not depend on which of them a sequence tile takes.
+  constexpr int PITCH = 9;                 // pairs of a token and 128 words: eight, and one to spread the banks
+  float2* const pairs = reinterpret_cast<float2*>(smem);
+  float2 lane_pair[G::HALVES][4];
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) {
     const int token = n0 + wn * 64 + 16 * nb + r;      // < tile_tokens: the tile count covers n_rows only
     float* dst = p.logits + (int64_t)token * p.v_pad + word0;
-    float mx = -INFINITY;
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+    for (int half = 0; half < G::HALVES; ++half) {
+      float mx = -INFINITY;
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) {
         f32x4& x = gemm.acc[half][mb][nb];
@@ -304,21 +408,30 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p
           mx = fmaxf(mx, x[v]);
         }
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    float sum = 0.f;
-    if (mx != -INFINITY) {
+      const float from = mx == -INFINITY ? 0.f : mx;   // (words all at -inf: no share, and a NaN among them, which the maximum leaves out, stays one)
+      float sum = 0.f;
 #pragma unroll
-      for (int half = 0; half < 2; ++half)
+      for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sum += __expf(gemm.acc[half][mb][nb][v] - mx);
+        for (int v = 0; v < 4; ++v) sum += __expf(gemm.acc[half][mb][nb][v] - from);
+      lane_pair[half][nb] = float2{mx, sum};
     }
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
-    if (g == 0) p.part[(int64_t)(tm * 2 + wm) * p.tile_tokens + token] = float2{mx, sum};
   }
+  phase_barrier();                         // all waves have left the tiles (the logits' stores go on)
+#pragma unroll
+  for (int i = 0; i < 4 * G::HALVES; ++i) pairs[((i / 4) * G::BN + wn * 64 + 16 * (i % 4) + r) * PITCH + 4 * wm + g] = lane_pair[i / 4][i % 4];
+  stores_barrier<0>();
+  if (tid >= G::HALVES * G::BN) return;
+  float2 x[8];
+  float mx = -INFINITY, sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    x[i] = pairs[tid * PITCH + i];
+    mx = fmaxf(mx, x[i].x);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sum += x[i].x == mx ? x[i].y : x[i].y * __expf(x[i].x - mx);
+  p.part[(int64_t)(tm * G::HALVES + tid / G::BN) * p.tile_tokens + n0 + tid % G::BN] = float2{mx, sum};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -329,7 +442,7 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_logits_kernel(LmHeadParams p
 // SPLIT: the logits come as `splits` partial sums, `part` rows apart; their sum goes where the first of them was.
 constexpr int lm_loss_threads(bool split) { return split ? 1024 : 256; }   // (few tokens: more of a row's loads in flight)
 template <bool SPLIT>
-__global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel(LmHeadParams p, int s0, int n_rows, int want_grad, int splits, int part) {
+__global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel(LmHeadParams p, int s0, int n_rows, int want_grad, int n_part, int splits, int part) {
   constexpr int NT = lm_loss_threads(SPLIT), STEP = 8 * NT;
   __shared__ float red_m[NT / 64], red_l[NT / 64], target;
   const int i = blockIdx.x, tid = threadIdx.x;
@@ -368,7 +481,6 @@ __global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel
       if (j < p.vocab) lm_combine(m, l, mx, sum);
     }
   } else {
-    const int n_part = p.v_pad / 128;
     for (int pp = tid; pp < n_part; pp += NT) {
       const float2 x = p.part[(int64_t)pp * p.tile_tokens + i];
       lm_combine(m, l, x.x, x.y);
@@ -413,27 +525,28 @@ __global__ __launch_bounds__(lm_loss_threads(SPLIT)) void lm_loss_dlogits_kernel
 // ---------------------------------------------------------------------------------------------
 // 3. dH_i = dLogits W_head (rows: tokens, columns: hidden, contraction: words).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kLmThreads, 2) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
-  using G = LmGemm<true>;
+template <bool SMALL>
+__global__ __launch_bounds__((LmGemmOf<SMALL, true>::THREADS), 2) void lm_dh_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int splits) {
+  using G = LmGemmOf<SMALL, true>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn, split;
-  if (!lm_tile(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
+  if (!lm_tile<G>(blockIdx.x, TM, TN, splits, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk_all = (p.vocab + kLmBK - 1) / kLmBK;
+  const int m0 = tm * G::BM, n0 = tn * G::BN, nk_all = (p.vocab + kLmBK - 1) / kLmBK;
   const int kt0 = (int)((int64_t)nk_all * split / splits), nk = (int)((int64_t)nk_all * (split + 1) / splits) - kt0;
   const int word0 = kt0 * kLmBK;
-  G::OpA a;
-  G::OpB b;
+  typename G::OpA a;
+  typename G::OpB b;
   a.init(p.dlogits + word0, p.v_pad, p.tile_tokens, m0, nk, wave, lane);
   b.init(p.w + (int64_t)word0 * p.ld_w, p.ld_w, p.vocab - word0, n0, nk, wave, lane);
   G gemm;
   gemm.run(smem, a, b, nk, wm, wn, wave, lane);   // dLogits is zero beyond the vocabulary
   const bool partial = splits > 1;
-  float* out_f32 = partial ? p.logits + (int64_t)split * TM * kLmBM * p.d_model : (float*)p.dh + (int64_t)s0 * p.ld_dh;
+  float* out_f32 = partial ? p.logits + (int64_t)split * TM * G::BM * p.d_model : (float*)p.dh + (int64_t)s0 * p.ld_dh;
   const int64_t ld = partial ? p.d_model : p.ld_dh;
 #pragma unroll
-  for (int half = 0; half < 2; ++half)
+  for (int half = 0; half < G::HALVES; ++half)
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -502,16 +615,17 @@ __global__ __launch_bounds__(256) void lm_transpose_h_kernel(LmHeadParams p, int
   }
 }
 
-__global__ __launch_bounds__(kLmThreads, 2) void lm_dw_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int accumulate) {
-  using G = LmGemm<true>;
+template <bool SMALL>
+__global__ __launch_bounds__((LmGemmOf<SMALL, true>::THREADS), 2) void lm_dw_kernel(LmHeadParams p, int s0, int n_rows, int TM, int TN, int accumulate) {
+  using G = LmGemmOf<SMALL, true>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int tm, tn, split;
-  if (!lm_tile(blockIdx.x, TM, TN, 1, tm, tn, split)) return;
+  if (!lm_tile<G>(blockIdx.x, TM, TN, 1, tm, tn, split)) return;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
-  const int m0 = tm * kLmBM, n0 = tn * kLmBN, nk = (n_rows + kLmBK - 1) / kLmBK;      // m0: hidden column, n0: word
-  G::OpA a;
-  G::OpB b;
+  const int m0 = tm * G::BM, n0 = tn * G::BN, nk = (n_rows + kLmBK - 1) / kLmBK;      // m0: hidden column, n0: word
+  typename G::OpA a;
+  typename G::OpB b;
   a.init(p.ht, p.tile_tokens, p.d_model, m0, nk, wave, lane);
   b.init(p.dlogits, p.v_pad, p.tile_tokens, n0, nk, wave, lane);
   G gemm;
@@ -521,15 +635,15 @@ __global__ __launch_bounds__(kLmThreads, 2) void lm_dw_kernel(LmHeadParams p, in
     const int word = n0 + wn * 64 + 16 * nb + r;
     if (word >= p.vocab) continue;
     float* dst = p.dw + (int64_t)word * p.ld_dw + m0 + wm * 64 + 4 * g;
-    f32x4 old[2][4];
+    f32x4 old[G::HALVES][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) old[i / 4][i % 4] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4 * G::HALVES; ++i) old[i / 4][i % 4] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (accumulate) {   // all loads before the first store
 #pragma unroll
-      for (int i = 0; i < 8; ++i) old[i / 4][i % 4] = *reinterpret_cast<const f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4));
+      for (int i = 0; i < 4 * G::HALVES; ++i) old[i / 4][i % 4] = *reinterpret_cast<const f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4));
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb] + old[i / 4][i % 4];
+    for (int i = 0; i < 4 * G::HALVES; ++i) *reinterpret_cast<f32x4*>(dst + 128 * (i / 4) + 16 * (i % 4)) = gemm.acc[i / 4][i % 4][nb] + old[i / 4][i % 4];
   }
 }
 
@@ -549,35 +663,36 @@ int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_mo
 
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {
   const int want_grad = (p.dh || p.dw) ? 1 : 0;
-  const int TD = p.d_model / kLmBN, TV = p.v_pad / kLmBM;   // column tiles of dH / dW, row tiles over the vocabulary
-  constexpr int kLdsLogits = LmGemm<false>::LDS, kLdsGrad = LmGemm<true>::LDS;
   if (p.n_tokens == 0 && p.dw && !p.acc_dw) {
     hipLaunchKernelGGL(lm_zero_dw_kernel, dim3(2048), dim3(256), 0, stream, p);
     return hipGetLastError();
   }
   for (int s0 = 0; s0 < p.n_tokens; s0 += p.tile_tokens) {
     const int n_rows = p.n_tokens - s0 < p.tile_tokens ? p.n_tokens - s0 : p.tile_tokens;
-    const int TT = (n_rows + kLmBM - 1) / kLmBM, TTn = (n_rows + kLmBN - 1) / kLmBN, k_rows = (n_rows + 63) / 64 * 64;
-    const int parts = lm_logit_splits(p, TV, TTn);
-    hipLaunchKernelGGL(lm_logits_kernel, dim3(lm_grid(TV, TTn, parts)), dim3(kLmThreads), kLdsLogits, stream, p, s0,
-                       n_rows, TV, TTn, parts);
+    auto launch = [&](const LmPlan& g, auto* big, auto* small, int last) {
+      const dim3 grid(lm_grid(g.TM, g.TN, g.splits, g.small));
+      if (g.small) hipLaunchKernelGGL(small, grid, dim3(LmGemmSmall<true>::THREADS), LmGemmSmall<true>::LDS, stream, p, s0, n_rows, g.TM, g.TN, last);
+      else hipLaunchKernelGGL(big, grid, dim3(kLmThreads), LmGemm<true>::LDS, stream, p, s0, n_rows, g.TM, g.TN, last);
+    };
+    const int k_rows = (n_rows + 63) / 64 * 64;
+    const LmPlan logits = lm_plan_logits(p, n_rows), dh = lm_plan_dh(p, n_rows), dw = lm_plan_dw(p, n_rows);
+    launch(logits, lm_logits_kernel<false>, lm_logits_kernel<true>, logits.splits);
     const dim3 loss_grid(want_grad ? k_rows : n_rows);
-    if (parts > 1)
-      hipLaunchKernelGGL((lm_loss_dlogits_kernel<true>), loss_grid, dim3(lm_loss_threads(true)), 0, stream, p, s0, n_rows, want_grad, parts, TTn * kLmBN);
+    if (logits.splits > 1)
+      hipLaunchKernelGGL((lm_loss_dlogits_kernel<true>), loss_grid, dim3(lm_loss_threads(true)), 0, stream, p, s0, n_rows, want_grad, 0, logits.splits,
+                         logits.TN * logits.tile());
     else
-      hipLaunchKernelGGL((lm_loss_dlogits_kernel<false>), loss_grid, dim3(lm_loss_threads(false)), 0, stream, p, s0, n_rows, want_grad, 1, 0);
+      hipLaunchKernelGGL((lm_loss_dlogits_kernel<false>), loss_grid, dim3(lm_loss_threads(false)), 0, stream, p, s0, n_rows, want_grad,
+                         (p.vocab + 127) / 128, 1, 0);
     if (p.dh) {
-      const int splits = lm_dh_splits(p, TT, TD);
-      hipLaunchKernelGGL(lm_dh_kernel, dim3(lm_grid(TT, TD, splits)), dim3(kLmThreads), kLdsGrad, stream, p, s0, n_rows, TT, TD,
-                         splits);
-      if (splits > 1)
+      launch(dh, lm_dh_kernel<false>, lm_dh_kernel<true>, dh.splits);
+      if (dh.splits > 1)
         hipLaunchKernelGGL(lm_dh_sum_kernel, dim3((uint32_t)(((int64_t)n_rows * (p.d_model / 8) + 255) / 256)), dim3(256), 0, stream,
-                           p, s0, n_rows, splits, (int64_t)TT * kLmBM * p.d_model);
+                           p, s0, n_rows, dh.splits, (int64_t)dh.TM * dh.tile() * p.d_model);
     }
     if (p.dw) {
       hipLaunchKernelGGL(lm_transpose_h_kernel, dim3(k_rows / 64, p.d_model / 64), dim3(256), 0, stream, p, s0, n_rows);
-      hipLaunchKernelGGL(lm_dw_kernel, dim3(lm_grid(p.d_model / kLmBM, p.v_pad / kLmBN)), dim3(kLmThreads), kLdsGrad, stream, p,
-                         s0, n_rows, p.d_model / kLmBM, p.v_pad / kLmBN, (p.acc_dw || s0 > 0) ? 1 : 0);
+      launch(dw, lm_dw_kernel<false>, lm_dw_kernel<true>, (p.acc_dw || s0 > 0) ? 1 : 0);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
