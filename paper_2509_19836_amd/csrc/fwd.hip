@@ -47,15 +47,69 @@ struct SplitRow {
   float m, l, lse_before;   // of a wave and a row: maximum and sum of its keys, the running Lse (the first wave's)
 };
 
+// The maxima of the rows' scores in the last tiles of a walk, and the rounds each wave has posted them for, in LDS.  A wave that posts
+// for round t + 2 knows of every other one that it has posted for round t at least: it does not read tiles before round t - 1 any
+// more, and four rounds are kept.  (A wave's LDS instructions complete in order.)
+struct SplitPosts {
+  static constexpr int ROUNDS = 4, TILES = ROUNDS * kSplitWaves, BYTES = 16 + TILES * kSplitBQ * 4;
+  typedef volatile __attribute__((address_space(3))) int* lds_ints;
+  typedef volatile __attribute__((address_space(3))) float* lds_floats;
+  lds_bytes lds;   // rounds posted: [wave]; maxima: [tile % TILES][row]
+  __device__ __forceinline__ lds_ints posted() const { return (lds_ints)lds; }
+  __device__ __forceinline__ lds_floats maxima(int tile) const { return (lds_floats)(lds + 16) + (tile & (TILES - 1)) * kSplitBQ; }
+  __device__ __forceinline__ void init(int tid) const {
+    if (tid < kSplitWaves) posted()[tid] = 0;
+  }
+  // The rows of nb are 16 nb + lane % 16; the lanes of a row have the same value
+  __device__ __forceinline__ void post(int round, int wave, int lane, const float (&top)[2]) const {
+    const lds_floats m = maxima(round * kSplitWaves + wave);
+    if (lane < 16) {
+      m[lane] = top[0];
+      m[16 + lane] = top[1];
+    }
+    keep_order();
+    done(round, wave, lane);
+  }
+  // All of the wave's tiles of rounds up to `round` are there
+  __device__ __forceinline__ void done(int round, int wave, int lane) const {
+    if (lane == 0) posted()[wave] = round + 1;
+    keep_order();
+  }
+  __device__ __forceinline__ float top(int tile, int nb, int r) const { return maxima(tile)[16 * nb + r]; }
+  // read() again and again until the tiles between the wave's last one and this one are there: those of this round of the waves
+  // before it, and those of the round before of the waves behind it.
+  template <class Read>
+  __device__ __forceinline__ void wait(int round, int wave, int lane, Read&& read) const {
+    const int w = lane & (kSplitWaves - 1), need = w < wave ? round + 1 : w > wave ? round : 0;
+    for (;;) {
+      const int have = posted()[w];
+      keep_order();
+      read();
+      if (__all(have >= need)) return;
+    }
+  }
+};
+
+// Largest value of the four lanes r, r + 16, r + 32 and r + 48, without the LDS
+__device__ __forceinline__ float max_of_row(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  x = max3(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]), -INFINITY);
+  const uint32_t v = __builtin_bit_cast(uint32_t, x);
+  const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return max3(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]), -INFINITY);
+}
+
 // BLK: with a block-wise sparse mask; MULTI: more than one step.  (A single step's arguments are asked for at once at the start;
 // steps picked by a variable are a second round trip, 1-2 us of a launch: dK/dV of three steps of 1500 rows 241, 246 us.)
 // SPLIT: the waves share 32 query rows and deal the key tiles among themselves.
 template <int D, int NW, bool BLK, bool MULTI, bool SPLIT>
-__global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(64 * NW, SPLIT ? 2 : D == 128 ? 1 : 3) void step_fwd_kernel(FwdParams p) {
   constexpr int BK = 64, MB = BK / 16, NB = 2, DK = D / 32, DB = D / 16, BQ = SPLIT ? 32 : 32 * NW, NT = 64 * NW;
-  constexpr int TILE = BK * 2 * D, SLOTS = SPLIT ? NW : kFwdSlots<D>, AHEAD = kAhead16;
+  constexpr int TILE = BK * 2 * D, SLOTS = SPLIT ? NW : kFwdSlots<D>;
+  constexpr int AHEAD = SPLIT && MULTI && D == 128 ? 2 : kAhead16;   // (registers)
   constexpr bool TURNS = D == 128 && !SPLIT;   // the waves of a SIMD take turns
-  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], SplitRow[NW][BQ] (SPLIT), open flags
+  extern __shared__ __attribute__((aligned(1024))) char smem[];  // [SLOTS][K tile, V tile], SplitRow[NW][BQ] and SplitPosts (SPLIT), open flags
 
   // (a kernel argument indexed with a variable would be copied to scratch memory: read through the argument pointer)
   typedef const __attribute__((address_space(4))) FwdParams* args_ptr;
@@ -97,6 +151,15 @@ __global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_k
   float m_run[NB] = {-INFINITY, -INFINITY}, limit[NB] = {-INFINITY, -INFINITY}, msub[NB] = {0.f, 0.f};
   f32x4 l_run[NB] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // four independent chains
   float m_top[NB] = {-INFINITY, -INFINITY};   // MULTI: largest maximum of the steps so far
+  float m_sums[NB] = {-INFINITY, -INFINITY};   // SPLIT: the maximum that this wave's sums are against
+  constexpr int ROWS = SPLIT ? NW * BQ * (int)sizeof(SplitRow) : 0;
+  const SplitPosts posts{(lds_bytes)smem + SLOTS * 2 * TILE + ROWS};
+  int round = 0;   // SPLIT: of NW tiles, over all steps
+  if constexpr (SPLIT) {
+    static_assert(NW == kSplitWaves, "waves that post");
+    posts.init(tid);
+    __syncthreads();
+  }
 
   // Positions of the work-group's and the wave's query rows
   int qlo_blk, qhi_blk, qlo_w = 0, qhi_w = 0;
@@ -106,7 +169,7 @@ __global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_k
   // Open flags of the key tiles against this work-group's query block (block-wise sparse mask)
   uint8_t* open_flags = nullptr;
   if (BLK) {
-    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE + (SPLIT ? NW * BQ * sizeof(SplitRow) : 0));
+    open_flags = reinterpret_cast<uint8_t*>(smem + SLOTS * 2 * TILE + ROWS + (SPLIT ? SplitPosts::BYTES : 0));
     fill_open_flags<true, BK>(q_side, open_flags, q_blk0, p.step[0].sk, tid, NT);
     __syncthreads();
   }
@@ -160,15 +223,84 @@ __global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_k
     pin(lds0);   // (LDS addresses worked out once for all steps would cost the registers)
     f32x4 s[MB][NB];
     bf16x8 pp[MB / 2][NB];
-    // P of the tile at key row k0_, of which the wave sees something, from its scores
-    auto softmax = [&](int k0_) {
+    // Scores of the tile at key row k0_ without those of pairs that are not visible
+    auto mask_scores = [&](int k0_) {
       if (!tiles.full(k0_)) {
 #pragma unroll
         for (int half = 0; half < MB / 2; ++half)
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) mask_rows32(s[2 * half][nb], s[2 * half + 1][nb], k0_ + 32 * half, g, klo[nb], khi[nb], windowed);
       }
-      // Largest score among this lane's keys of the tile (a query row's keys are spread over four lanes).
+    };
+    // Largest score among this lane's keys of the tile (a query row's keys are spread over four lanes)
+    auto lane_max = [&](int nb) {
+      float m5[5];   // eight v_max3_f32 for sixteen scores (fifteen with fmaxf: 1795 and 1769 us at 16384 rows, 32 heads, d = 128)
+#pragma unroll
+      for (int i = 0; i < 5; ++i)
+        m5[i] = max3(s[3 * i / 4][nb][3 * i % 4], s[(3 * i + 1) / 4][nb][(3 * i + 1) % 4], s[(3 * i + 2) / 4][nb][(3 * i + 2) % 4]);
+      return max3(max3(m5[0], m5[1], m5[2]), max3(m5[3], m5[4], s[3][nb][3]), -INFINITY);
+    };
+    auto row_max = [&](float mx) {
+      const float m = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      return fmaxf(m, __shfl_xor(m, 32, 64));
+    };
+    // The running maximum of a row whose keys in a tile reach m_new, where some row of the wave has grown
+    auto raise = [&](int nb, float m_new) {
+      bool fresh = false;   // the row has seen no key of this step, and sees none in this tile
+      if (MULTI) {
+        // A row's P at its maximum is one and rounds to bf16 exactly.  A step that kept the maximum of the steps
+        // before would lose that: 8 steps of 512 rows, window 700, error of O against 64 bits 1.64e-3 so, 1.17e-3
+        // with a maximum for each step.  It is let down to 2^-12 of the largest at most: a step below that weighs little, and
+        // fp32 keeps its headroom, sums of P of up to 2^18 a key (with 2^-6 heads scaled by 0.5 to 2 had 1 % more error).
+        m_top[nb] = fmaxf(m_top[nb], m_new);
+        const bool first = limit[nb] == -INFINITY;
+        fresh = first && m_new == -INFINITY;
+        m_new = fresh ? m_run[nb] : fmaxf(m_new, first ? m_top[nb] - 2.f * slack : m_run[nb]);
+      } else {
+        m_new = fmaxf(m_run[nb], m_new);
+      }
+      m_run[nb] = m_new;
+      limit[nb] = fresh ? -INFINITY : m_new + slack;
+      msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
+    };
+    auto grows = [&](const float (&x)[NB]) { return __any(x[0] > limit[0] || x[1] > limit[1]); };
+    auto follow = [&](const float (&x)[NB]) {   // a tile of the walk, with the rows' maxima x
+      if (!grows(x)) return;
+      raise(0, x[0]);
+      raise(1, x[1]);
+    };
+    // The sums so far, of weights against m_old, against m_new
+    auto rescale = [&](int nb, float m_old, float m_new) {
+      const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_old - m_new));
+      l_run[nb] *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[db][nb][v] *= alpha;
+    };
+    // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
+    // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
+    // exponential, few enough to keep the intermediate values out of the register budget.  The fence keeps the
+    // groups apart: with the 32 exponentials in a row the d = 64 kernel is 2-3 % slower (12 heads x 12000 rows 665, 636 us).
+    auto exponentials = [&](const float (&offset)[NB]) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int ch = 0; ch < MB / 2; ++ch) {
+          f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            x[v] = __builtin_amdgcn_exp2f(c * x[v] - offset[nb]);
+            y[v] = __builtin_amdgcn_exp2f(c * y[v] - offset[nb]);
+          }
+          l_run[nb] += x + y;
+          pp[ch][nb] = pack_pair(x, y);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // P of the tile at key row k0_, of which the wave sees something, from its scores
+    auto softmax = [&](int k0_) {
+      mask_scores(k0_);
       // Rescale lazily: keep a stale maximum while no row of the wave has grown by more than
       // 2^kLazyLog2 (any common per-row offset gives the same result; fp32 has the headroom).  A row has
       // grown exactly if one of its four lanes has, and the vote runs over the whole wave, so the lanes
@@ -178,101 +310,116 @@ __global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_k
       bool grow = false;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
-        float m5[5];   // eight v_max3_f32 for sixteen scores (fifteen with fmaxf: 1795 and 1769 us at 16384 rows, 32 heads, d = 128)
-#pragma unroll
-        for (int i = 0; i < 5; ++i)
-          m5[i] = max3(s[3 * i / 4][nb][3 * i % 4], s[(3 * i + 1) / 4][nb][(3 * i + 1) % 4], s[(3 * i + 2) / 4][nb][(3 * i + 2) % 4]);
-        mx[nb] = max3(max3(m5[0], m5[1], m5[2]), max3(m5[3], m5[4], s[3][nb][3]), -INFINITY);
+        mx[nb] = lane_max(nb);
         grow |= mx[nb] > limit[nb];
       }
       if (__any(grow)) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          float m_new = fmaxf(mx[nb], __shfl_xor(mx[nb], 16, 64));
-          m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
-          bool fresh = false;   // the row has seen no key of this step, and sees none in this tile
-          if (MULTI) {
-            // A row's P at its maximum is one and rounds to bf16 exactly.  A step that kept the maximum of the steps
-            // before would lose that: 8 steps of 512 rows, window 700, error of O against 64 bits 1.64e-3 so, 1.17e-3
-            // with a maximum for each step.  It is let down to 2^-12 of the largest at most: a step below that weighs little, and
-            // fp32 keeps its headroom, sums of P of up to 2^18 a key (with 2^-6 heads scaled by 0.5 to 2 had 1 % more error).
-            m_top[nb] = fmaxf(m_top[nb], m_new);
-            const bool first = limit[nb] == -INFINITY;
-            fresh = first && m_new == -INFINITY;
-            m_new = fresh ? m_run[nb] : fmaxf(m_new, first ? m_top[nb] - 2.f * slack : m_run[nb]);
-          } else {
-            m_new = fmaxf(m_run[nb], m_new);
-          }
-          const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(c * (m_run[nb] - m_new));
-          m_run[nb] = m_new;
-          limit[nb] = fresh ? -INFINITY : m_new + slack;
-          msub[nb] = (m_new == -INFINITY) ? 0.f : c * m_new;
-          l_run[nb] *= alpha;
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[db][nb][v] *= alpha;
+          const float m_old = m_run[nb];
+          raise(nb, row_max(mx[nb]));
+          rescale(nb, m_old, m_run[nb]);
         }
       }
-      // P = exp2(c S - c m) as packed bf16; the row sum is taken in fp32 before rounding (Lse must hold to
-      // 1e-3 also for rows with a handful of keys).  Eight scores at a time: enough to cover the latency of the
-      // exponential, few enough to keep the intermediate values out of the register budget.  The fence keeps the
-      // groups apart: with the 32 exponentials in a row the d = 64 kernel is 2-3 % slower (12 heads x 12000 rows 665, 636 us).
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int ch = 0; ch < MB / 2; ++ch) {
-          f32x4 &x = s[2 * ch][nb], &y = s[2 * ch + 1][nb];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            x[v] = __builtin_amdgcn_exp2f(c * x[v] - msub[nb]);
-            y[v] = __builtin_amdgcn_exp2f(c * y[v] - msub[nb]);
-          }
-          l_run[nb] += x + y;
-          pp[ch][nb] = pack_pair(x, y);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+      exponentials(msub);
     };
-    if constexpr (SPLIT) {   // tiles wave, wave + NW, .. in the wave's own slot: K of the next one comes behind the vector work, V behind O
+    if constexpr (SPLIT) {
+      // Round after round, of NW tiles: the wave has tile `wave` of each in a slot of its own; K of the next one comes behind the
+      // products of S, V behind O of the tile before.  P is formed against the maximum that one walk over all tiles would have at
+      // that tile, so that it rounds to the same bf16 numbers as in the other kernels: the waves post their rows' maxima of every
+      // tile, and each follows them tile by tile up to its own.  That needs the tiles before it only, which wait for earlier ones
+      // at most: every wait ends.  The products of O, of the tile before, stand between a post and the reading.
+      // Against a maximum of its own in each wave O would be 1e-3 from what the other kernels give for the same row.  us so and with
+      // posts, d = 128 (d = 64): 4 x 1024 rows 13.8, 14.7 (10.7, 10.7); 1 x 8192 62, 70 (46, 48); causal 1 x 16384 121, 138 (87, 96); four
+      // steps of 8 x 2048 79, 90 (45, 51).  With a barrier for each round 1 x 8192 takes 85 (48).
       const uint32_t kt = k_lds(wave), vt = v_lds(wave);
-      auto load = [&](bool v) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-          if (v) walk.load_v(i, vt, 0);
-          else walk.load_k(i, kt, 0);
-        }
-      };
+      WaveStager<D, BK, D == 64> k_rows, v_rows;
+      k_rows.init(st.k.ss, lane);
+      v_rows.init(st.v.ss, lane);
+      auto load_k = [&]() { k_rows.load(walk.k_tile, st.k.ss, sk - walk.k0, kt, lane); };
+      const int round0 = round, n_tiles = walk.left;   // (rounds are counted over all steps; n_tiles: without a block mask)
       walk.skip(wave);
       if (walk.valid()) {
-        walk.begin(0, lane);
-        load(false);
-        load(true);
-        for (;;) {
-          const int kb = walk.k0;
-          walk.skip(NW);
-          const bool more = walk.valid(), live = tiles.some(kb);
-          wait_loads<NL>();   // K
-          const f32x4 zero[MB] = {};
-          bf16x8 first[AHEAD];
-          if (live) {
-            rows_fetch<D, MB, AHEAD>(kt, ad, 0, first);
-            rows_product<D, MB, NB, AHEAD>(kt, ad, 0, qreg, s, zero, first);
-            mfma_results();
-          }
-          if (more) {
-            walk.begin(0, lane);
-            load(false);
-          }
-          if (live) softmax(kb);
-          if (more) wait_loads<NL>();   // V
+        load_k();
+        bool live = false, more = true;
+        bf16x8 first[AHEAD];
+        auto add_o = [&]() {   // P V of the tile before
+          if (more) wait_loads<NL>();
           else wait_loads<0>();
           if (live) {
             cols_fetch<D, AHEAD>(vt, ad, 0, first);
             cols_product<D, MB / 2, NB, AHEAD>(vt, ad, 0, pp, o, first);
           }
+        };
+        any_value(pp);
+        wait_loads<0>();        // K of the first one
+        for (;; ++round) {
+          const int kb = walk.k0;
+          const char* const v_tile = walk.v_tile;
+          walk.skip(NW);
+          more = walk.valid();
+          const bool now = tiles.some(kb);
+          const f32x4 zero[MB] = {};
+          float top[NB] = {-INFINITY, -INFINITY};
+          if (now) {
+            rows_fetch<D, MB, AHEAD>(kt, ad, 0, first);
+            rows_product<D, MB, NB, AHEAD>(kt, ad, 0, qreg, s, zero, first);
+            mfma_results();
+          }
+          if (more) load_k();
+          if (now) {
+            mask_scores(kb);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) top[nb] = max_of_row(lane_max(nb));
+          }
+          posts.post(round, wave, lane, top);
+          add_o();
+          v_rows.load(v_tile, st.v.ss, sk - kb, vt, lane);
+          live = now;
+          float x[NW][NB];   // of the NW tiles up to this one; before the step's first -inf
+          posts.wait(round, wave, lane, [&]() {
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+              for (int nb = 0; nb < NB; ++nb) x[i][nb] = posts.top((round - 1) * NW + wave + 1 + i, nb, r);
+          });
+          float most[NB];
+#pragma unroll
+          for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+              if (round == round0 && i + wave < NW - 1) x[i][nb] = -INFINITY;
+              if (i == NW - 1) most[nb] = max3(max3(x[0][nb], x[1][nb], x[2][nb]), x[3][nb], -INFINITY);
+            }
+          if (grows(most)) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) follow(x[i]);
+          }
+          if (live) {
+            if (__any(m_run[0] != m_sums[0] || m_run[1] != m_sums[1])) {
+#pragma unroll
+              for (int nb = 0; nb < NB; ++nb) {
+                rescale(nb, m_sums[nb], m_run[nb]);
+                m_sums[nb] = m_run[nb];
+              }
+            }
+            exponentials(msub);
+          }
           if (!more) break;
-          load(true);
+          wait_loads<NL>();     // K of the next one
         }
+        ++round;
+        add_o();
+      }
+      if (MULTI && step + 1 < n_steps) {   // and the tiles behind the wave's last one, for the maximum the next step starts with
+        int tile = round > round0 ? (round - 1) * NW + wave + 1 : round0 * NW;
+        stores_barrier<0>();
+        for (; tile < round0 * NW + n_tiles; ++tile) {
+          const float x[NB] = {posts.top(tile, 0, r), posts.top(tile, 1, r)};
+          follow(x);
+        }
+        round = round0 + (n_tiles + NW - 1) / NW;
+        posts.done(round - 1, wave, lane);   // (also where the last round had no tile for it)
       }
     } else if (!TURNS) {   // tile t in slot t mod 3: both products and the softmax one after the other, a barrier for each tile
       if (walk.valid()) {
@@ -405,7 +552,7 @@ __global__ __launch_bounds__(64 * NW, SPLIT || D == 128 ? 1 : 3) void step_fwd_k
     for (int nb = 0; nb < NB; ++nb) {
       const int orow = q_w0 + 16 * nb + r;
       if (g == 0) {
-        rows[wave * BQ + 16 * nb + r] = {m_run[nb], l_sum[nb],
+        rows[wave * BQ + 16 * nb + r] = {m_sums[nb], l_sum[nb],
                                          wave == 0 && p.o_acc.ptr && orow < sq ? p.lse_acc.ptr[b * p.lse_acc.sb + hq * p.lse_acc.sh + orow] : 0.f};
       }
     }
@@ -531,7 +678,7 @@ static bool split_walks(const FwdParams& p) {
 template <int D, bool SPLIT>
 static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
   constexpr int BQ = SPLIT ? kSplitBQ : kFwdBQ<D>, NW = SPLIT ? kSplitWaves : kFwdWaves<D>;
-  constexpr int LDS = (SPLIT ? NW * (2 * 64 * 2 * D + BQ * (int)sizeof(SplitRow)) : kFwdSlots<D> * 2 * 64 * 2 * D) + kMaxBlockCacheTiles;
+  constexpr int LDS = (SPLIT ? NW * (2 * 64 * 2 * D + BQ * (int)sizeof(SplitRow)) + SplitPosts::BYTES : kFwdSlots<D> * 2 * 64 * 2 * D) + kMaxBlockCacheTiles;
   p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {

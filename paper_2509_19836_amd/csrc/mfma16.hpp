@@ -203,6 +203,39 @@ struct DirectStager {
   }
 };
 
+// The same by one wave alone, whose many loads of a tile would need a register each.  Eight rows of a tile after the other have the
+// same offsets from their first one (swz has that period): KEEP_ALL false holds those of eight rows only.
+template <int D, int ROWS, bool KEEP_ALL>
+struct WaveStager {
+  using Each = DirectStager<D, ROWS, 1>;
+  static constexpr int N = Each::N, PER = KEEP_ALL ? N : 8 / Each::RPI;   // loads of a tile; offsets
+  uint32_t off[PER];
+  static __device__ __forceinline__ uint32_t offset(int i, int last, int64_t ss, int lane) {
+    const int row = Each().row_of(i, 0, lane);
+    return Each().offset(min(row, last), row, ss, lane);
+  }
+  __device__ __forceinline__ void init(int64_t ss, int lane) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) off[i] = offset(i, ROWS, ss, lane);
+  }
+  // rows of the tile beyond `valid` - 1 are read as copies of that one
+  __device__ __forceinline__ void load(const char* tile, int64_t ss, int valid, uint32_t lds, int lane) const {
+    if (valid >= ROWS) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        load_to_lds(tile, off[i % PER], lds + i * 1024);
+        if (i % PER == PER - 1) {
+          tile += 2 * PER * Each::RPI * ss;
+          pin(tile);
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) load_to_lds(tile, offset(i, valid - 1, ss, lane), lds + i * 1024);
+  }
+};
+
 // The tiles of the walked axis that a block-wise sparse mask leaves open, in order: the flags of 64 tiles at a time as bits
 // of a scalar register, one LDS read for each 64 tiles of the axis.
 struct OpenTiles {

@@ -156,3 +156,44 @@ def test_backward(lib, case, d, batch):
         got = t.cpu().numpy()
         assert np.array_equal(got, np.broadcast_to(got[:1], got.shape)), name
         assert np.abs(got[:1] - ref).max() <= hp.REL_TOL * top[name[:2]], name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("case", CASES + [(96, (1500, 700), True, 0, False), (50, (1000,), False, 0, False)], ids=lambda c: str(c[:4]))
+def test_forward_does_not_depend_on_the_batch(lib, case, d):
+    """The same rows from a launch of few tiles and from one of many: P is rounded to bf16 against the same maximum either way, and what
+    is left is the order of fp32 sums.  Up to 2200 keys, 35 tiles of 64: the products and rescalings of 35 tiles and four waves' sums,
+    each 2^-24 of at most the largest |V|, 4: 1e-5 of it, where P against maxima that differ, 2^-9 a key, is 1e-3."""
+    import torch
+    sq, sks = case[:2]
+    Hq, Hkv, _, qb, _, kv, pattern = _inputs(case, d)
+    scale = d ** -0.5
+    got = []
+    for batch in (FEW, MANY):
+        print(case, d, batch, flush=True)
+        many = lambda x: x.expand(batch, *x.shape[1:])     # (inputs may share memory)
+        masks, ks, vs, at = [], [], [], 0
+        for (kb, vb), sk in zip(kv, sks):
+            masks.append(_mask(lib, case, sk, at, pattern)[0])
+            at += sk
+            # keys that grow along the chunk: a maximum that rises from tile to tile
+            k = hp.dev_bf16(kb) * (1 + torch.arange(sk, device="cuda") / sk)[:, None, None]
+            ks.append(many(k.to(torch.bfloat16)))
+            vs.append(many(hp.dev_bf16(vb)))
+        q = many(hp.dev_bf16(qb))
+        o = torch.zeros((batch, sq, Hq, d), device="cuda")
+        lse = torch.full((batch, Hq, sq), -np.inf, device="cuda")
+        out = [o, lse]
+        if len(sks) == 1:
+            part = [torch.full_like(o, 7.0), torch.full_like(lse, 7.0)]
+            lib.burst_attn_step_fwd(lib.shape(batch, Hq, Hkv, d, sq, sks[0], scale), masks[0], q, ks[0], vs[0], o_part=part[0],
+                                    lse_part=part[1], o_acc=o, lse_acc=lse)
+            out += part
+        else:
+            lib.burst_attn_steps_fwd([lib.shape(batch, Hq, Hkv, d, sq, sk, scale) for sk in sks], masks, q, ks, vs, o, lse)
+        torch.cuda.synchronize()
+        got.append([x[:1].cpu().numpy() for x in out])
+    for few, many in zip(*got):
+        live = np.isfinite(many)
+        assert np.array_equal(np.isfinite(few), live)
+        assert np.abs(few[live] - many[live]).max(initial=0.0) <= 4e-5
