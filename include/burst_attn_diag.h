@@ -58,6 +58,19 @@ int burst_attn_set_chunk_rows(int32_t rows);
  * describes to the kernel.  One range means one launch with the step's own mask. */
 int burst_attn_chunk_plan(const burst_mask_t* mask, int32_t query_axis, int32_t max_ranges, int64_t* out);
 
+/* Host view of the launches of step kernels that a call with these steps makes (no GPU involved): which kernel each of them takes.
+ * call: 0 forward steps into the running state, 1 one forward step with a result of its own, 2 backward steps, 3 the same for dQ
+ * alone, 4 for dK and dV alone.  The steps have the same query side.  Returns the number of launches (negative burst_status_t on a bad
+ * argument) and fills out[i], for the first max_launches of them, with the bits below: 0 is a forward launch, DQ and DKDV say what a
+ * backward launch computes. */
+#define BURST_KERNEL_DQ 1
+#define BURST_KERNEL_DKDV 2
+#define BURST_KERNEL_DEALT 4          /* the four waves of a work-group share 32 rows and deal the walk among themselves */
+#define BURST_KERNEL_SHARED_CU 8      /* head_dim 64, dK/dV: two work-groups of eight waves per CU */
+#define BURST_KERNEL_KEY_TILES_64 16  /* dK/dV: key tiles of 64 rows instead of 128 */
+int burst_attn_launch_plan(int32_t call, int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
+                           int32_t max_launches, int32_t* out);
+
 #ifdef __cplusplus
 }
 #endif

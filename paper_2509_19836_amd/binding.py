@@ -25,6 +25,7 @@ BURST_BF16, BURST_F32 = 0, 1
 BURST_MASK_FULL, BURST_MASK_CAUSAL = 0, 1
 BURST_ACC_DQ, BURST_ACC_DK, BURST_ACC_DV = 1, 2, 4
 BURST_MAX_STEPS = 1024
+BURST_KERNEL_DQ, BURST_KERNEL_DKDV, BURST_KERNEL_DEALT, BURST_KERNEL_SHARED_CU, BURST_KERNEL_KEY_TILES_64 = 1, 2, 4, 8, 16
 
 
 class burst_shape_t(C.Structure):
@@ -88,6 +89,8 @@ _lib.burst_attn_visible_rows.restype = C.c_int
 _lib.burst_attn_visible_rows.argtypes = [_P(burst_mask_t), C.c_int32, C.c_int64, _P(C.c_int32 * 2)]
 _lib.burst_attn_set_chunk_rows.restype = C.c_int
 _lib.burst_attn_set_chunk_rows.argtypes = [C.c_int32]
+_lib.burst_attn_launch_plan.restype = C.c_int
+_lib.burst_attn_launch_plan.argtypes = [C.c_int32, C.c_int32, _P(burst_shape_t), _P(burst_mask_t), C.c_int32, _P(C.c_int32)]
 _lib.burst_attn_chunk_plan.restype = C.c_int
 _lib.burst_attn_chunk_plan.argtypes = [_P(burst_mask_t), C.c_int32, C.c_int32, _P(C.c_int64)]
 _lib.burst_attn_mfma_probe.restype = C.c_int
@@ -120,7 +123,7 @@ EXPORTS = ["burst_attn_step_fwd", "burst_attn_steps_fwd", "burst_attn_steps_bwd"
            "burst_attn_lse_merge", "burst_attn_preprocess_bwd", "burst_attn_step_bwd",
            "burst_attn_fill_zigzag_mask", "burst_attn_fill_contiguous_mask", "burst_attn_fill_striped_mask",
            "burst_attn_fill_block_striped_mask",
-           "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
+           "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_launch_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
            "burst_attn_version", "burst_lm_head_workspace_bytes", "burst_lm_head_loss",
            "burst_lm_head_static_scratch_bytes", "burst_lm_head_loss_noalloc"]
 
@@ -385,6 +388,16 @@ def burst_attn_chunk_plan(mask, query_axis, max_ranges=4096):
         _check(n)
     keys = ("r0", "r1", "nseg", "seg_len", "pos0", "period", "blk_offset")
     return [dict(zip(keys, out[7 * i:7 * i + 7])) for i in range(min(n, max_ranges))]
+
+
+def burst_attn_launch_plan(call, shapes, masks, max_launches=4096):
+    """Kernels (BURST_KERNEL_ bits) of the launches of a call; call: "fwd", "fwd_part", "bwd", "dq" or "dkdv"."""
+    out = (C.c_int32 * max_launches)()
+    n = _lib.burst_attn_launch_plan(("fwd", "fwd_part", "bwd", "dq", "dkdv").index(call), len(shapes), (burst_shape_t * len(shapes))(*shapes),
+                                    (burst_mask_t * len(masks))(*masks), max_launches, out)
+    if n < 0:
+        _check(n)
+    return list(out[:min(n, max_launches)])
 
 
 def burst_attn_mfma_probe(random_operands, iterations, stream=None):

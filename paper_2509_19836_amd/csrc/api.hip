@@ -670,6 +670,56 @@ int burst_attn_chunk_plan(const burst_mask_t* mask, int32_t query_axis, int32_t 
   return chunk_plan(mk, (int)sq, (int)sk, query_axis != 0, max_ranges, out);
 } BURST_NO_THROW
 
+int burst_attn_launch_plan(int32_t call, int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
+                           int32_t max_launches, int32_t* out) try {
+  if (call < 0 || call > 4 || n_steps < 1 || !shapes || !masks || max_launches < 0 || (max_launches > 0 && !out)) return BURST_ERR_INVALID_ARG;
+  if (n_steps > BURST_MAX_STEPS) return BURST_ERR_UNSUPPORTED;
+  if (call == 1 && n_steps > 1) return BURST_ERR_INVALID_ARG;
+  alignas(16) static char any[16];   // what is asked for has an address; nothing is read or written
+  FwdParams f, f0;
+  FwdStep first;
+  BwdParams b;
+  std::memset(&f, 0, sizeof(f));
+  std::memset(&b, 0, sizeof(b));
+  std::vector<FwdStep> fs;
+  std::vector<BwdStep> bs;
+  for (int i = 0; i < n_steps; ++i) {
+    BURST_TRY(check_shape(&shapes[i]));
+    FwdStep x;
+    std::memset(&x, 0, sizeof(x));
+    BURST_TRY(check_mask(&masks[i], shapes[i].sq, shapes[i].sk, &x.mask));
+    x.sk = (int32_t)shapes[i].sk;
+    f.batch = b.batch = shapes[i].batch;
+    f.q_heads = b.q_heads = shapes[i].q_heads;
+    f.kv_heads = b.kv_heads = shapes[i].kv_heads;
+    f.head_dim = b.head_dim = shapes[i].head_dim;
+    f.sq = b.sq = (int32_t)shapes[i].sq;
+    f.scale = b.scale = shapes[i].scale;
+    if (i == 0) {
+      f0 = f;
+      first = x;
+    }
+    if (i > 0 && !same_queries(f0, first, f, x)) return BURST_ERR_INVALID_ARG;
+    if (x.sk == 0) continue;
+    BwdStep y;
+    std::memset(&y, 0, sizeof(y));
+    y.mask = x.mask;
+    y.sk = x.sk;
+    if (call != 3) y.dk.ptr = y.dv.ptr = any;
+    fs.push_back(x);
+    bs.push_back(y);
+  }
+  LaunchLog log;
+  (call == 1 ? f.o_part.ptr : f.o_acc.ptr) = any;
+  if (call != 4) b.dq.ptr = any;
+  if (f.sq > 0 && !fs.empty()) {
+    if (call < 2) launch_steps_fwd(f, fs.data(), (int)fs.size(), nullptr, &log);
+    else launch_steps_bwd(b, bs.data(), (int)bs.size(), nullptr, &log);
+  }
+  std::copy_n(log.begin(), std::min<size_t>(log.size(), (size_t)max_launches), out);
+  return (int)log.size();
+} BURST_NO_THROW
+
 int burst_attn_mfma_probe(int32_t random_operands, int32_t iterations, float* sink, int64_t* flops_out,
                           void* hip_stream) {
   if (iterations < 1 || iterations > (1 << 24)) return BURST_ERR_INVALID_ARG;

@@ -1030,20 +1030,20 @@ static bool narrow_key_tiles(const BwdParams& p) {
 }
 
 // The work-groups of a kernel: the tiles that see something, and zeros into what gets no work-group under "=".
-static hipError_t plan_dq(BwdParams& p, int BQ, hipStream_t stream) {
+static hipError_t plan_dq(BwdParams& p, int BQ, hipStream_t stream, LaunchLog* log) {
   p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
   p.q_side_by_side = q_side_by_side(p.step, p.n_steps, p.sq, p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs, BQ);
-  if (!p.acc_dq && p.q_runs.total() < (p.sq + BQ - 1) / BQ)
+  if (!log && !p.acc_dq && p.q_runs.total() < (p.sq + BQ - 1) / BQ)
     return launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
   return hipSuccess;
 }
-static hipError_t plan_dkdv_tiles(BwdParams& p, int tile, hipStream_t stream) {
+static hipError_t plan_dkdv_tiles(BwdParams& p, int tile, hipStream_t stream, LaunchLog* log) {
   const int n_keys = p.batch * p.kv_heads;
   for (int i = 0; i < p.n_steps; ++i) {
     BwdStep& st = p.step[i];
     st.k_runs = nonempty_k_runs(st.mask, p.sq, st.sk, tile);
     st.k_side_by_side = k_side_by_side(st.mask, p.sq, st.sk, n_keys, st.k_runs, tile);
-    if (st.k_runs.total() < (st.sk + tile - 1) / tile) {
+    if (!log && st.k_runs.total() < (st.sk + tile - 1) / tile) {
       hipError_t e = hipSuccess;
       if (!p.acc_dk) e = launch_zero_tensor(st.dk, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
       if (e == hipSuccess && !p.acc_dv) e = launch_zero_tensor(st.dv, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
@@ -1064,10 +1064,10 @@ static hipError_t plan_dkdv_tiles(BwdParams& p, int tile, hipStream_t stream) {
   }
   return hipSuccess;
 }
-static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream) {
+static hipError_t plan_dkdv(BwdParams& p, bool& narrow, hipStream_t stream, LaunchLog* log) {
   for (int i = 0; i < p.n_steps; ++i) p.step[i].k_runs = nonempty_k_runs(p.step[i].mask, p.sq, p.step[i].sk, 128);
   narrow = narrow_key_tiles(p);
-  return plan_dkdv_tiles(p, narrow ? 64 : 128, stream);
+  return plan_dkdv_tiles(p, narrow ? 64 : 128, stream, log);
 }
 static int dq_grid(const BwdParams& p) { return mapped_grid(p.batch * p.kv_heads, p.q_heads / p.kv_heads, p.q_runs.total()); }
 static int dkdv_grid(const BwdParams& p) {
@@ -1086,10 +1086,14 @@ constexpr int kFlagsLds = kMaxBlockCacheTiles;   // with a block mask
 constexpr int kAlone = 256;   // work-groups that have a CU for themselves
 
 template <int D>
-static hipError_t launch_dq_t(BwdParams& p, hipStream_t stream) {
-  const hipError_t e = plan_dq(p, 32 * kDqWaves<D>, stream);
+static hipError_t launch_dq_t(BwdParams& p, hipStream_t stream, LaunchLog* log) {
+  const hipError_t e = plan_dq(p, 32 * kDqWaves<D>, stream, log);
   const int grid = dq_grid(p);
   if (e != hipSuccess || grid == 0) return e;
+  if (log) {
+    log->push_back(BURST_KERNEL_DQ);
+    return hipSuccess;
+  }
   constexpr int NW = kDqWaves<D>, NT = 64 * NW;
   if (p.step[0].mask.blk) hipLaunchKernelGGL((step_bwd_dq_kernel<D, NW, true, false>), dim3(grid), dim3(NT), kDqLds<D> + kFlagsLds, stream, p);
   else if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_dq_kernel<D, NW, false, true>), dim3(grid), dim3(NT), kDqLds<D>, stream, p);
@@ -1104,17 +1108,21 @@ static void launch_dkdv_kernel(const BwdParams& p, int grid, hipStream_t stream)
   hipLaunchKernelGGL((step_bwd_dkdv_kernel<D, BLK, MULTI, BKV, TURNS>), dim3(grid), dim3(512), LDS, stream, p);
 }
 template <int D>
-static hipError_t launch_dkdv_t(BwdParams& p, hipStream_t stream) {
+static hipError_t launch_dkdv_t(BwdParams& p, hipStream_t stream, LaunchLog* log) {
   bool narrow = false;
-  const hipError_t e = plan_dkdv(p, narrow, stream);
+  const hipError_t e = plan_dkdv(p, narrow, stream, log);
   const int grid = dkdv_grid(p);
   if (e != hipSuccess || grid == 0) return e;
-  const bool multi = p.n_steps > 1;
+  const bool multi = p.n_steps > 1, alone = D == 128 || p.step[0].mask.blk || narrow || grid <= kAlone;
+  if (log) {
+    log->push_back(BURST_KERNEL_DKDV | (narrow ? BURST_KERNEL_KEY_TILES_64 : 0) | (alone ? 0 : BURST_KERNEL_SHARED_CU));
+    return hipSuccess;
+  }
   if (p.step[0].mask.blk) launch_dkdv_kernel<D, true, false, 128, true>(p, grid, stream);
   else if (narrow && multi) launch_dkdv_kernel<D, false, true, 64, true>(p, grid, stream);
   else if (narrow) launch_dkdv_kernel<D, false, false, 64, true>(p, grid, stream);
-  else if (D == 128 || grid <= kAlone) multi ? launch_dkdv_kernel<D, false, true, 128, true>(p, grid, stream)
-                                             : launch_dkdv_kernel<D, false, false, 128, true>(p, grid, stream);
+  else if (alone) multi ? launch_dkdv_kernel<D, false, true, 128, true>(p, grid, stream)
+                        : launch_dkdv_kernel<D, false, false, 128, true>(p, grid, stream);
   else if constexpr (D == 64) multi ? launch_dkdv_kernel<D, false, true, 128, false>(p, grid, stream)
                                     : launch_dkdv_kernel<D, false, false, 128, false>(p, grid, stream);
   return hipGetLastError();
@@ -1175,32 +1183,28 @@ template <int D>
 static bool split_walks(const BwdParams& p) {
   constexpr int ROWS = SplitWalk<D>::ROWS, kStart = 8, kDq = D == 128 ? 6 : 8, kDkdv = D == 128 ? 3 : 4;
   const int64_t keys = (int64_t)p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
-  const int nq = (p.sq + ROWS - 1) / ROWS;
-  int64_t groups = keys * group * nq, first = 0, last = 0;
+  const Walks q = q_walks(p.step, p.n_steps, p.sq, ROWS);
+  int64_t groups = keys * group * q.tiles, work = 3 * keys * group * q.total, dkdv = 0;
   for (int i = 0; i < p.n_steps; ++i) {
-    first += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, nq - 1, ROWS);
-    last += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, 0, ROWS);
+    const Walks k = k_walks(p.step[i].mask, p.sq, p.step[i].sk, ROWS);
+    groups += keys * k.tiles;
+    work += 4 * keys * group * k.total;
+    dkdv = std::max(dkdv, group * k.longest);
   }
-  const int64_t dq = std::max(first, last);
-  int64_t work = 3 * groups * (first + last) / 2, dkdv = 0;
-  for (int i = 0; i < p.n_steps; ++i) {
-    const BwdStep& st = p.step[i];
-    const int nk = (st.sk + ROWS - 1) / ROWS;
-    first = group * k_tile_walk(st.mask, p.sq, st.sk, 0, ROWS);
-    last = group * k_tile_walk(st.mask, p.sq, st.sk, nk - 1, ROWS);
-    work += 4 * keys * nk * (first + last) / 2;
-    groups += keys * nk;
-    dkdv = std::max({dkdv, first, last});
-  }
-  return std::max({3 * dq, 4 * dkdv, work / kAlone}) + (groups - 1) / kAlone * kStart <= std::max(kDq * dq, kDkdv * dkdv);
+  if (q.longest == 0) return false;
+  return std::max({3 * q.longest, 4 * dkdv, work / kAlone}) + (groups - 1) / kAlone * kStart <= std::max(kDq * q.longest, kDkdv * dkdv);
 }
 template <int D>
-static hipError_t launch_split_t(BwdParams& p, hipStream_t stream) {
+static hipError_t launch_split_t(BwdParams& p, hipStream_t stream, LaunchLog* log) {
   using W = SplitWalk<D>;
-  hipError_t e = plan_dq(p, W::ROWS, stream);
-  if (e == hipSuccess) e = plan_dkdv_tiles(p, W::ROWS, stream);
+  hipError_t e = plan_dq(p, W::ROWS, stream, log);
+  if (e == hipSuccess) e = plan_dkdv_tiles(p, W::ROWS, stream, log);
   const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
   if (e != hipSuccess || grid == 0) return e;
+  if (log) {
+    log->push_back(BURST_KERNEL_DQ | BURST_KERNEL_DKDV | BURST_KERNEL_DEALT);
+    return hipSuccess;
+  }
   const int dq_first = longer_dq_walks(p), n_first = dq_first ? n_dq : n_dkdv;
   if (p.n_steps > 1) hipLaunchKernelGGL((step_bwd_split_kernel<D, true>), dim3(grid), dim3(64 * W::NW), W::BYTES, stream, p, n_first, dq_first);
   else hipLaunchKernelGGL((step_bwd_split_kernel<D, false>), dim3(grid), dim3(64 * W::NW), W::BYTES, stream, p, n_first, dq_first);
@@ -1208,21 +1212,25 @@ static hipError_t launch_split_t(BwdParams& p, hipStream_t stream) {
 }
 // One launch of both kernels; `done` says whether it was taken.
 template <int D>
-static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
+static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream, LaunchLog* log) {
   const int n_keys = p.batch * p.kv_heads, group = p.q_heads / p.kv_heads;
   int64_t most = (int64_t)n_keys * group * ((p.sq + kBothBQ - 1) / kBothBQ);
   for (int i = 0; i < p.n_steps; ++i) most += (int64_t)n_keys * ((p.step[i].sk + 127) / 128);
   done = most <= (p.n_steps > 1 ? 2 : 1) * kBothLaunch;
   if (!done) return hipSuccess;
-  if (split_walks<D>(p)) return launch_split_t<D>(p, stream);
+  if (split_walks<D>(p)) return launch_split_t<D>(p, stream, log);
   bool narrow = false;
-  hipError_t e = plan_dq(p, kBothBQ, stream);
-  if (e == hipSuccess) e = plan_dkdv(p, narrow, stream);
+  hipError_t e = plan_dq(p, kBothBQ, stream, log);
+  if (e == hipSuccess) e = plan_dkdv(p, narrow, stream, log);
   const int n_dkdv = dkdv_grid(p), n_dq = dq_grid(p), grid = n_dkdv + n_dq;
   if (e != hipSuccess || grid == 0) return e;
   const int dq_first = longer_dq_walks(p), n_first = dq_first ? n_dq : n_dkdv;
   const bool multi = p.n_steps > 1;
   const bool alone = D == 128 || grid <= kAlone || !crowded(p, narrow);
+  if (log) {
+    log->push_back(BURST_KERNEL_DQ | BURST_KERNEL_DKDV | (narrow ? BURST_KERNEL_KEY_TILES_64 : 0) | (alone ? 0 : BURST_KERNEL_SHARED_CU));
+    return hipSuccess;
+  }
   auto launch = [&](auto m, auto bkv) {
     if (alone) launch_both_kernel<D, m.value, bkv.value, true>(p, grid, n_first, dq_first, stream);
     else if constexpr (D == 64) launch_both_kernel<D, m.value, bkv.value, false>(p, grid, n_first, dq_first, stream);
@@ -1237,7 +1245,7 @@ static hipError_t launch_both_t(BwdParams& p, bool& done, hipStream_t stream) {
 }
 
 template <int D>
-static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, int n, hipStream_t stream) {
+static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, int n, hipStream_t stream, LaunchLog* log) {
   BwdParams p = p0;
   const bool dkdv = steps[0].dk.ptr != nullptr;
   hipError_t e = hipSuccess;
@@ -1248,12 +1256,13 @@ static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, i
       whole.push_back(st);
       continue;
     }
+    if (log) continue;
     if (dkdv && !p.acc_dk) e = launch_zero_tensor(st.dk, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
     if (e == hipSuccess && dkdv && !p.acc_dv) e = launch_zero_tensor(st.dv, p.batch, st.sk, p.kv_heads, p.head_dim, stream);
     if (e != hipSuccess) return e;
   }
   n = (int)whole.size();
-  if (n == 0) return p.dq.ptr && !p.acc_dq ? launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream) : hipSuccess;
+  if (n == 0) return !log && p.dq.ptr && !p.acc_dq ? launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream) : hipSuccess;
   bool together = p.dq.ptr && dkdv && p.sq <= chunk_rows();
   for (const BwdStep& st : whole) together = together && !st.mask.blk && st.sk <= chunk_rows();
   auto put = [&](const std::vector<BwdStep>& from, int first, int end) {
@@ -1263,7 +1272,7 @@ static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, i
   if (together && n <= kMaxSteps) {
     bool done = false;
     put(whole, 0, n);
-    e = launch_both_t<D>(p, done, stream);
+    e = launch_both_t<D>(p, done, stream, log);
     if (done) return e;
   }
   if (p0.dq.ptr) {   // the dQ kernel streams the key axis
@@ -1285,12 +1294,12 @@ static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, i
     bool any = false;
     e = for_step_groups(parts, p.sq, p.batch * p.q_heads, [&](int first, int end) {
       put(parts, first, end);
-      const hipError_t err = launch_dq_t<D>(p, stream);
+      const hipError_t err = launch_dq_t<D>(p, stream, log);
       p.acc_dq = 1;
       any = true;
       return err;
     });
-    if (e == hipSuccess && !any && !p0.acc_dq) e = launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
+    if (e == hipSuccess && !any && !p0.acc_dq && !log) e = launch_zero_tensor(p.dq, p.batch, p.sq, p.q_heads, p.head_dim, stream);
     if (e != hipSuccess) return e;
   }
   if (dkdv) {   // the dK/dV kernel streams the query axis
@@ -1315,7 +1324,7 @@ static hipError_t launch_bwd_groups(const BwdParams& p0, const BwdStep* steps, i
       for (int first = 0, end; first < n; first = end) {
         for (end = first + 1; end < n && end - first < kMaxSteps && share(parts[first]) && share(parts[end]);) ++end;
         put(parts, first, end);
-        e = launch_dkdv_t<D>(p, stream);
+        e = launch_dkdv_t<D>(p, stream, log);
         if (e != hipSuccess) return e;
       }
     }
@@ -1344,9 +1353,9 @@ int chunk_plan(const MaskDev& mk, int sq, int sk, bool query_axis, int max_range
   return (int)ranges.size();
 }
 
-hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream) {
-  if (p.head_dim == 128) return launch_bwd_groups<128>(p, steps, n, stream);
-  return launch_bwd_groups<64>(p, steps, n, stream);
+hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream, LaunchLog* log) {
+  if (p.head_dim == 128) return launch_bwd_groups<128>(p, steps, n, stream, log);
+  return launch_bwd_groups<64>(p, steps, n, stream, log);
 }
 
 }  // namespace burst

@@ -658,28 +658,29 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p, in
 
 // Whether the waves of a work-group share 32 query rows and deal the key tiles among themselves (SPLIT).  A launch of few query
 // tiles is as long as its longest walk, and shared out to four waves that walk is four times shorter, on eight (d = 64: four)
-// times as many work-groups.  A wave alone with its tiles, two products and the softmax one after the other, takes 1.2 (d = 64: 2.3) times as long
-// for one as the kernel whose waves take turns, and brings every tile for 32 rows: beyond two work-groups a CU, or one
-// and a half with uneven walks, which work-groups of four short walks even out, the other one is faster.  By work-groups times their mean walk over the
-// longest; first and last tile stand for all.  us of a pass with its fills, d = 128 (d = 64): full 2 x 256 rows (16) 28.7, 18.8 (19.5, 17.4); 4 x 1024
-// (128) 44.5, 24.6 (29.6, 22.1); 1 x 8192 (256) 190, 73 (119, 59); 16 x 1024 (512) 46.7, 37.8 (30.5, 25.9); 20 x 1024 (640) 48.6, 50.3 (30.9, 31.9);
-// 32 x 1000 (1024) 54, 66 (33, 38); causal 1 x 16384 (256) 352, 130 (222, 98); 1 x 32768 (512) 684, 441 (425, 244); 16 x 2048 (540) 72.3, 69.9
-// (44.7, 39.4); 48 x 512, two steps (576) 53.9, 57.7 (33.6, 37.6); 1 x 49546 (775) 1013, 968 (653, 494); zigzag 16 x 2048, four steps (950) 147, 169 (91, 88).
+// times as many work-groups.  A wave alone with its tiles, two products and the softmax one after the other, takes 1.3 (d = 64: 2.3) times as long
+// for one as the kernel whose waves take turns, and brings every tile for 32 rows, so that the other one is faster where there are more than
+// about two work-groups a CU whose walks are all as long as the longest; where they are uneven, work-groups times their mean walk over the longest
+// one count, up to four a CU under a causal mask.  us of a step by the kernels of one walk a wave and by this one, d = 128 (d = 64), with that count: full
+// 2 x 256 rows (16) 17.7, 8.3 (8.6, 6.7); 4 x 1024 (128) 33, 15 (18.5, 10.8); 1 x 8192 (256) 179, 70 (109, 47); 16 x 1024 (512) 34.5, 27.8 (19.3,
+// 13.8); 20 x 1024 (640) 36, 40 (19.5, 20.7); 32 x 1000 (1024) 38, 54 (20, 25); causal 1 x 16384 (256) 340, 138 (210, 96); 1 x 32768 (512) 667, 497 (414,
+// 239); 16 x 2048 (528) 56.5, 58.7 (33, 28); 48 x 512, two steps (576) 41, 50 (22, 28); 1 x 49546 (775) 1000, 1108 (643, 512); window of 1000 tokens 4 x 4096 (480) 43,
+// 34 (24, 17); 8 x 4096 (960) 47, 63 (25, 29); zigzag with a window, 32 heads, the shard one place ahead: 16384 rows, window 6000 (3040) 347, 692 (217, 316); 65536
+// rows, window 30000 (15040) 6840, 13600 (4220, 8630).
 constexpr int kSplitLoad = 544;
 static bool split_walks(const FwdParams& p) {
-  const int n = (p.sq + kSplitBQ - 1) / kSplitBQ;
-  int64_t first = 0, last = 0;
-  for (int i = 0; i < p.n_steps; ++i) {
-    first += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, n - 1, kSplitBQ);
-    last += q_tile_walk(p.step[i].mask, p.sq, p.step[i].sk, 0, kSplitBQ);
-  }
-  return (int64_t)p.batch * p.q_heads * n * (first + last) <= 2 * kSplitLoad * std::max(first, last);
+  const Walks w = q_walks(p.step, p.n_steps, p.sq, kSplitBQ);
+  return w.longest > 0 && (int64_t)p.batch * p.q_heads * w.total <= kSplitLoad * w.longest;
 }
 template <int D, bool SPLIT>
-static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
+static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream, LaunchLog* log) {
   constexpr int BQ = SPLIT ? kSplitBQ : kFwdBQ<D>, NW = SPLIT ? kSplitWaves : kFwdWaves<D>;
   constexpr int LDS = (SPLIT ? NW * (2 * 64 * 2 * D + BQ * (int)sizeof(SplitRow)) + SplitPosts::BYTES : kFwdSlots<D> * 2 * 64 * 2 * D) + kMaxBlockCacheTiles;
   p.q_runs = nonempty_q_runs(p.step, p.n_steps, p.sq, BQ);
+  if (log) {
+    if (p.q_runs.total() > 0) log->push_back(SPLIT ? BURST_KERNEL_DEALT : 0);
+    return hipSuccess;
+  }
   const int n_tiles = (p.sq + BQ - 1) / BQ;
   if (p.o_part.ptr && p.q_runs.total() < n_tiles) {
     const int64_t total = (int64_t)p.batch * p.sq * p.q_heads * (p.head_dim / 4);
@@ -699,20 +700,20 @@ static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 template <int D>
-static hipError_t launch_fwd_steps(FwdParams& p, hipStream_t stream) {
-  return split_walks(p) ? launch_fwd_t<D, true>(p, stream) : launch_fwd_t<D, false>(p, stream);
+static hipError_t launch_fwd_steps(FwdParams& p, hipStream_t stream, LaunchLog* log) {
+  return split_walks(p) ? launch_fwd_t<D, true>(p, stream, log) : launch_fwd_t<D, false>(p, stream, log);
 }
 
 // With the fused merge and no separate step result, a key axis longer than two ranges is cut into ranges, each walked as
 // a step of its own: the same online-softmax merge the ring applies from step to step, so the result is the step's up to
 // rounding.  The step result itself (o_part, lse_part) cannot be cut this way and is always one launch.
 template <int D>
-static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, int n, hipStream_t stream) {
+static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, int n, hipStream_t stream, LaunchLog* log) {
   FwdParams p = p0;
   if (!p.o_acc.ptr || p.o_part.ptr) {
     p.n_steps = 1;
     p.step[0] = steps[0];
-    return launch_fwd_steps<D>(p, stream);
+    return launch_fwd_steps<D>(p, stream, log);
   }
   std::vector<FwdStep> parts;
   for (int i = 0; i < n; ++i) {
@@ -732,13 +733,13 @@ static hipError_t launch_fwd_groups(const FwdParams& p0, const FwdStep* steps, i
   return for_step_groups(parts, p.sq, p.batch * p.q_heads, [&](int first, int end) {
     p.n_steps = end - first;
     std::copy(parts.begin() + first, parts.begin() + end, p.step);
-    return launch_fwd_steps<D>(p, stream);
+    return launch_fwd_steps<D>(p, stream, log);
   });
 }
 
-hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream) {
-  if (p.head_dim == 128) return launch_fwd_groups<128>(p, steps, n, stream);
-  return launch_fwd_groups<64>(p, steps, n, stream);
+hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream, LaunchLog* log) {
+  if (p.head_dim == 128) return launch_fwd_groups<128>(p, steps, n, stream, log);
+  return launch_fwd_groups<64>(p, steps, n, stream, log);
 }
 
 }  // namespace burst

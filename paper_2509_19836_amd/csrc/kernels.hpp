@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "../../include/burst_attn_diag.h"
 #include "common.hpp"
 
 namespace burst {
@@ -123,6 +124,53 @@ inline int k_tile_walk(const MaskDev& mk, int sq, int sk, int tile, int tile_row
   int lo, hi;
   range_minmax<false>(mk, tile * tile_rows, end < sk ? end : sk, lo, hi);
   return visible_tiles<true, 64>(mk, lo, hi, sq).len;
+}
+// A launch's tiles of one axis that see something: how many, about the sum of their walks, and about the longest one.  From up to
+// eight of them, the first and the last one and some between at places that no regular pattern of walks repeats: two at the ends
+// would stand for none where only rows in the middle see something, as against the shard one place ahead under the zigzag split with a window,
+// and for half of the work under a window, whose walks are all alike but the first few.  (A block mask is not looked at.)
+struct Walks {
+  int64_t tiles, total, longest;
+};
+template <class Walk>
+inline Walks sample_walks(int first, int end, bool alike, Walk&& walk) {
+  constexpr int S = 8, at[S] = {0, 158, 61, 219, 37, 195, 98, 255};   // of 256, in an eighth of the tiles each; mirrored, so that walks that grow evenly average exactly
+  const int64_t n = std::max(end - first, 0), s = alike ? std::min<int64_t>(n, 1) : std::min<int64_t>(n, S);
+  Walks w{n, 0, 0};
+  for (int i = 0; i < s; ++i) {
+    const int64_t t = n <= S ? i : i == S - 1 ? n - 1 : (256 * i + at[i]) * n / (256 * S);
+    const int64_t len = walk(first + (int)t);
+    w.total += len;
+    w.longest = std::max(w.longest, len);
+  }
+  if (s > 0) w.total = w.total * n / s;
+  return w;
+}
+template <class Step>
+inline Walks q_walks(const Step* steps, int n_steps, int sq, int tile_rows) {
+  int lo = sq, hi = 0;
+  bool alike = true;
+  for (int i = 0; i < n_steps; ++i) {
+    int olo, ohi;
+    range_minmax<false>(steps[i].mask, 0, steps[i].sk, olo, ohi);
+    const RowIntervals iv = row_intervals<true>(steps[i].mask, olo, ohi, sq, false);
+    if (iv.some_lo >= iv.some_hi) continue;
+    lo = std::min(lo, iv.some_lo);
+    hi = std::max(hi, iv.some_hi);
+    alike = alike && !steps[i].mask.causal;
+  }
+  return sample_walks(lo / tile_rows, (hi + tile_rows - 1) / tile_rows, alike, [&](int t) {
+    int64_t len = 0;
+    for (int i = 0; i < n_steps; ++i) len += q_tile_walk(steps[i].mask, sq, steps[i].sk, t, tile_rows);
+    return len;
+  });
+}
+inline Walks k_walks(const MaskDev& mk, int sq, int sk, int tile_rows) {
+  int olo, ohi;
+  range_minmax<true>(mk, 0, sq, olo, ohi);
+  const RowIntervals iv = row_intervals<false>(mk, olo, ohi, sk, false);
+  const int end = iv.some_lo < iv.some_hi ? (iv.some_hi + tile_rows - 1) / tile_rows : 0;
+  return sample_walks(iv.some_lo / tile_rows, end, !mk.causal, [&](int t) { return (int64_t)k_tile_walk(mk, sq, sk, t, tile_rows); });
 }
 // Whether the walk of the tile that is launched last is at most half as long as that of the first one.
 template <class Step>
@@ -290,8 +338,10 @@ int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_mo
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream);
 
 // n steps of the query chunk that `p` describes (its own step array is not read).  More than one only without o_part.
-hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream);
-hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream);
+// With a log nothing is launched: it gets the kernel (BURST_KERNEL_ bits) of each launch of step kernels that there would be.
+typedef std::vector<int32_t> LaunchLog;
+hipError_t launch_steps_fwd(const FwdParams& p, const FwdStep* steps, int n, hipStream_t stream, LaunchLog* log = nullptr);
+hipError_t launch_steps_bwd(const BwdParams& p, const BwdStep* steps, int n, hipStream_t stream, LaunchLog* log = nullptr);
 // rows of the streamed axis per launch of a step kernel (longer axes are cut into several launches)
 void set_chunk_rows(int rows);
 int chunk_plan(const MaskDev& mk, int sq, int sk, bool query_axis, int max_ranges, int64_t* out);
