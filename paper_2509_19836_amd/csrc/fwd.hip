@@ -667,10 +667,18 @@ __global__ __launch_bounds__(256) void fwd_fill_dead_rows_kernel(FwdParams p, in
 // 239); 16 x 2048 (528) 56.5, 58.7 (33, 28); 48 x 512, two steps (576) 41, 50 (22, 28); 1 x 49546 (775) 1000, 1108 (643, 512); window of 1000 tokens 4 x 4096 (480) 43,
 // 34 (24, 17); 8 x 4096 (960) 47, 63 (25, 29); zigzag with a window, 32 heads, the shard one place ahead: 16384 rows, window 6000 (3040) 347, 692 (217, 316); 65536
 // rows, window 30000 (15040) 6840, 13600 (4220, 8630).
-constexpr int kSplitLoad = 544;
+// At d = 64 two work-groups share a CU, and of a second, part-empty round each has the CU to itself and is faster: with walks that
+// are long beside what a work-group starts and ends with, the line lies higher.  d = 64: 64 tiles a walk, 5 x 4096 rows (640) 59, 55; 6 x 4096 (768) 60, 56; 8 x
+// 4096 (1024) 60, 65; causal 12 x 4096 (780) 64, 59; 16 x 4096 (1040) 64, 78; 1 x 60000 (940) 786, 718; 16 tiles, 17 x 1024 (544) 19.8, 21.5.  d = 128: causal
+// 8 x 4096 (520) 97, 88; 1 x 17000 (532) 359, 375; 5 x 4096 (640) 98, 105.
+template <int D>
+static int64_t split_load(int64_t longest) {
+  return D == 128 ? 520 : longest < 64 ? 544 : 800;
+}
+template <int D>
 static bool split_walks(const FwdParams& p) {
   const Walks w = q_walks(p.step, p.n_steps, p.sq, kSplitBQ);
-  return w.longest > 0 && (int64_t)p.batch * p.q_heads * w.total <= kSplitLoad * w.longest;
+  return w.longest > 0 && (int64_t)p.batch * p.q_heads * w.total <= split_load<D>(w.longest) * w.longest;
 }
 template <int D, bool SPLIT>
 static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream, LaunchLog* log) {
@@ -701,7 +709,7 @@ static hipError_t launch_fwd_t(FwdParams& p, hipStream_t stream, LaunchLog* log)
 }
 template <int D>
 static hipError_t launch_fwd_steps(FwdParams& p, hipStream_t stream, LaunchLog* log) {
-  return split_walks(p) ? launch_fwd_t<D, true>(p, stream, log) : launch_fwd_t<D, false>(p, stream, log);
+  return split_walks<D>(p) ? launch_fwd_t<D, true>(p, stream, log) : launch_fwd_t<D, false>(p, stream, log);
 }
 
 // With the fused merge and no separate step result, a key axis longer than two ranges is cut into ranges, each walked as

@@ -6,7 +6,6 @@ import pytest
 
 from tests import helpers as hp
 
-FWD_LIMIT = 544      # work-groups of 32 query rows, in units of one with the longest walk
 SLACK = 1.3          # a few tiles stand for all
 
 
@@ -21,9 +20,10 @@ def walks(lib, mask, of_queries, rows=32):
     return [lib.burst_attn_visible_tile_runs(mask, not of_queries, 64, r0, min(r0 + rows, n))[0][1] for r0 in range(0, n, rows)]
 
 
-def forward_load(lib, masks, heads):
+def forward_load(lib, masks, heads, d):
+    """Work-groups of 32 query rows, in units of one with the longest walk, and up to how many of them the walks are dealt."""
     w = [sum(x) for x in zip(*(walks(lib, m, True) for m in masks))]
-    return heads * sum(w) / max(w) if max(w) else 0.0
+    return heads * sum(w) / max(w) if max(w) else 0.0, 520 if d == 128 else 544 if max(w) < 64 else 800
 
 
 @pytest.mark.parametrize("kind,G,dev,j,rows,window,N_blk", [
@@ -36,9 +36,22 @@ def forward_load(lib, masks, heads):
 @pytest.mark.parametrize("d", [64, 128])
 def test_launches_of_many_tiles_under_a_window(lib, kind, G, dev, j, rows, window, N_blk, d):
     mask = hp.fill_mask(lib, kind, dev, j, G, rows * G, window, N_blk)
-    assert forward_load(lib, [mask], 32) > 2 * FWD_LIMIT
+    load, limit = forward_load(lib, [mask], 32, d)
+    assert load > 2 * limit
     for call in ("fwd", "fwd_part"):
         assert plan(lib, call, [mask], 1, 32, 32, d) == [0]
+
+
+@pytest.mark.parametrize("kind,heads,rows,d,dealt", [
+    ("full", 16, 1024, 128, True), ("full", 17, 1024, 128, False),      # 512 and 544 work-groups, all alike
+    ("full", 17, 1024, 64, True), ("full", 18, 1024, 64, False),        # short walks
+    ("full", 6, 4096, 64, True), ("full", 7, 4096, 64, False),          # 768 and 896, walks of 64 tiles
+    ("causal", 8, 4096, 128, True), ("causal", 9, 4096, 128, False),    # 1024 and 1152 that walk half of the longest
+    ("causal", 12, 4096, 64, True), ("causal", 13, 4096, 64, False),
+])
+def test_the_line_of_the_forward_rule(lib, kind, heads, rows, d, dealt):
+    mask = hp.fill_mask(lib, kind, 0, 0, 1, rows)
+    assert plan(lib, "fwd", [mask], 1, heads, heads, d) == [lib.BURST_KERNEL_DEALT if dealt else 0]
 
 
 def test_few_tiles_are_dealt(lib):
@@ -72,12 +85,12 @@ def test_a_few_tiles_stand_for_all(lib, seed):
     masks = [hp.fill_mask(lib, kind, dev, (dev - t) % G, G, rows * G, window, per * G) for t in range(rng.randint(1, min(G, 4)))]
     batch, kv, group, d = rng.choice([1, 1, 2]), rng.choice([1, 2, 4, 8, 16]), rng.choice([1, 1, 4]), rng.choice([64, 128])
     if len(masks) == 1:
-        f = forward_load(lib, masks, batch * kv * group)
+        f, limit = forward_load(lib, masks, batch * kv * group, d)
         got = plan(lib, "fwd", masks, batch, kv * group, kv, d)
         if f == 0:
             assert got == []
-        elif not FWD_LIMIT / SLACK < f < FWD_LIMIT * SLACK:
-            assert got == [lib.BURST_KERNEL_DEALT if f <= FWD_LIMIT else 0], f
+        elif not limit / SLACK < f < limit * SLACK:
+            assert got == [lib.BURST_KERNEL_DEALT if f <= limit else 0], f
     masks = [m for m in masks if any(walks(lib, m, True))]
     got = plan(lib, "bwd", masks, batch, kv * group, kv, d) if masks else []
     if len(got) == 1 and got[0] & lib.BURST_KERNEL_DQ and got[0] & lib.BURST_KERNEL_DKDV:
