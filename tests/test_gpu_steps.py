@@ -284,9 +284,9 @@ def test_steps_that_may_not_share_a_launch_in_one_call(lib, what, flags):
     G, n, d, H = 5, 512, 64, 4
     s = _state(lib, (("striped", G, 4, n, 0, 0), (H, H), d, 1, 32768))
     shapes, masks = list(s["shapes"]), list(s["masks"])
+    pattern = torch.tensor([[1, 0, 0, 1], [0, 1, 1, 0]], dtype=torch.uint8, device="cuda")   # (outlives the calls)
     for t in (1, 4):
         if what == "block masks":
-            pattern = torch.tensor([[1, 0, 0, 1], [0, 1, 1, 0]], dtype=torch.uint8, device="cuda")
             lib.set_block_mask(masks[t], pattern, 256, 128)
         elif what == "scales":
             shapes[t] = lib.shape(1, H, H, d, n, n, 0.5 * d ** -0.5)
