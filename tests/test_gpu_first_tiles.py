@@ -1,7 +1,8 @@
 """The first two key tiles of a walk, with key rows so far apart that the loads of each tile take long.
 
 Eight waves bring a tile together, and the waves of one half start on a tile a phase before those of the other: each
-must find the other half's share of the second tile there as well."""
+must find the other half's share of the second tile there as well.  That is so where the kernels of one walk a wave run: the
+launches here have few tiles and deal their walks, each wave with tiles of its own; test_gpu_whole_walks.py runs the same on the others."""
 import numpy as np
 import pytest
 
