@@ -6,6 +6,7 @@
 #define BURST_ATTN_DIAG_H
 
 #include "burst_attn.h"
+#include "burst_lm_head.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -70,6 +71,10 @@ int burst_attn_chunk_plan(const burst_mask_t* mask, int32_t query_axis, int32_t 
 #define BURST_KERNEL_KEY_TILES_64 16  /* dK/dV: key tiles of 64 rows instead of 128 */
 int burst_attn_launch_plan(int32_t call, int32_t n_steps, const burst_shape_t* shapes, const burst_mask_t* masks,
                            int32_t max_launches, int32_t* out);
+
+/* Host view of the LM head's products over the first sequence tile of a call with this shape (tile_tokens as given; no GPU involved): for
+ * the logits, dH and dW the edge of an output tile (128 or 256) and the parts its contraction is split in, out = {edge, parts} x 3. */
+int burst_lm_head_tile_plan(const burst_lm_head_shape_t* shape, int32_t out[6]);
 
 #ifdef __cplusplus
 }

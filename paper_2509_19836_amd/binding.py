@@ -102,6 +102,8 @@ class burst_lm_head_shape_t(C.Structure):
                 ("grad_scale", C.c_float), ("_pad", C.c_int32)]
 
 
+_lib.burst_lm_head_tile_plan.restype = C.c_int
+_lib.burst_lm_head_tile_plan.argtypes = [_P(burst_lm_head_shape_t), _P(C.c_int32)]
 _lib.burst_lm_head_workspace_bytes.restype = C.c_int64
 _lib.burst_lm_head_workspace_bytes.argtypes = [_P(burst_lm_head_shape_t)]
 _lib.burst_lm_head_loss.restype = C.c_int
@@ -125,7 +127,7 @@ EXPORTS = ["burst_attn_step_fwd", "burst_attn_steps_fwd", "burst_attn_steps_bwd"
            "burst_attn_fill_block_striped_mask",
            "burst_attn_visible_pairs", "burst_attn_tile_class", "burst_attn_visible_tile_runs", "burst_attn_visible_rows", "burst_attn_mfma_probe", "burst_attn_set_chunk_rows", "burst_attn_chunk_plan", "burst_attn_launch_plan", "burst_attn_status_string", "burst_attn_last_hip_error",
            "burst_attn_version", "burst_lm_head_workspace_bytes", "burst_lm_head_loss",
-           "burst_lm_head_static_scratch_bytes", "burst_lm_head_loss_noalloc"]
+           "burst_lm_head_static_scratch_bytes", "burst_lm_head_tile_plan", "burst_lm_head_loss_noalloc"]
 
 
 class BurstError(RuntimeError):
@@ -398,6 +400,13 @@ def burst_attn_launch_plan(call, shapes, masks, max_launches=4096):
     if n < 0:
         _check(n)
     return list(out[:min(n, max_launches)])
+
+
+def burst_lm_head_tile_plan(shp):
+    """(edge of an output tile, parts of its contraction) of the logits, dH and dW of the first sequence tile."""
+    out = (C.c_int32 * 6)()
+    _check(_lib.burst_lm_head_tile_plan(C.byref(shp), out))
+    return [tuple(out[2 * i:2 * i + 2]) for i in range(3)]
 
 
 def burst_attn_mfma_probe(random_operands, iterations, stream=None):

@@ -740,6 +740,20 @@ static int check_lm_shape(const burst_lm_head_shape_t* s) {
   return BURST_OK;
 }
 
+int burst_lm_head_tile_plan(const burst_lm_head_shape_t* shape, int32_t out[6]) {
+  BURST_TRY(check_lm_shape(shape));
+  if (!out || shape->n_tokens == 0) return BURST_ERR_INVALID_ARG;
+  LmHeadParams p;
+  std::memset(&p, 0, sizeof(p));
+  p.n_tokens = (int32_t)shape->n_tokens;
+  p.d_model = (int32_t)shape->d_model;
+  p.vocab = (int32_t)shape->vocab;
+  p.tile_tokens = (int32_t)shape->tile_tokens;
+  p.v_pad = (int32_t)((shape->vocab + 255) / 256 * 256);
+  lm_head_tile_plan(p, out);
+  return BURST_OK;
+}
+
 int64_t burst_lm_head_workspace_bytes(const burst_lm_head_shape_t* shape) {
   if (check_lm_shape(shape) != BURST_OK) return -1;
   return lm_head_workspace_bytes(shape->tile_tokens, shape->vocab, shape->d_model);

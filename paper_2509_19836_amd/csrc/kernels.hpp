@@ -335,6 +335,7 @@ struct LmHeadParams {
   __bf16* ht;           // workspace [d_model][tile_tokens]: the sequence tile's rows of h, transposed
 };
 int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_model);
+void lm_head_tile_plan(const LmHeadParams& p, int32_t out[6]);   // burst_lm_head_tile_plan, from the sizes in p
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream);
 
 // n steps of the query chunk that `p` describes (its own step array is not read).  More than one only without o_part.

@@ -29,11 +29,11 @@ namespace {
 // Output tile of a work-group of eight waves, and the k-tile; 128 accumulator registers per wave.
 constexpr int kLmBM = 256, kLmBN = 256, kLmBK = 64, kLmThreads = 512;
 
-// One GEMM operand: where its k-tiles come from and how they lie in LDS (32 KiB).  A k-tile is four direct loads
-// per wave.
-//   COLS = false: storage [x][k], k contiguous.  LDS: [256 x][64 k].  lim = valid storage rows; rows beyond are
+// One GEMM operand: where its k-tiles come from and how they lie in LDS (X rows or columns of 128 bytes: 32 KiB for the 256 of an
+// output tile of eight waves, 16 KiB for the 128 of one of four).  A k-tile is four direct loads per wave.
+//   COLS = false: storage [x][k], k contiguous.  LDS: [X x][64 k].  lim = valid storage rows; rows beyond are
 //                 read as the last one (folded into the per-lane offsets once).
-//   COLS = true : storage [k][x], x contiguous.  LDS: two tiles [64 k][128 x], the k rows permuted so that the
+//   COLS = true : storage [k][x], x contiguous.  LDS: X / 128 tiles [64 k][128 x], the k rows permuted so that the
 //                 transposing read, which hands out rows 16 (e / 4) + 4 g + e % 4 of 32, gives k = 8 g + e as the
 //                 row-wise operand has it.  lim = valid k rows; a k-tile that reaches past them reads copies of
 //                 the last one.
@@ -659,6 +659,15 @@ __global__ __launch_bounds__(256) void lm_zero_dw_kernel(LmHeadParams p) {
 int64_t lm_head_workspace_bytes(int64_t tile_tokens, int64_t vocab, int64_t d_model) {
   const int64_t v_pad = (vocab + 255) / 256 * 256;
   return tile_tokens * v_pad * 4 + tile_tokens * v_pad * 2 + (v_pad / 128) * tile_tokens * 8 + d_model * tile_tokens * 2;
+}
+
+void lm_head_tile_plan(const LmHeadParams& p, int32_t out[6]) {
+  const int n_rows = std::min(p.n_tokens, p.tile_tokens);
+  const LmPlan plans[3] = {lm_plan_logits(p, n_rows), lm_plan_dh(p, n_rows), lm_plan_dw(p, n_rows)};
+  for (int i = 0; i < 3; ++i) {
+    out[2 * i] = plans[i].tile();
+    out[2 * i + 1] = plans[i].splits;
+  }
 }
 
 hipError_t launch_lm_head_loss(const LmHeadParams& p, hipStream_t stream) {

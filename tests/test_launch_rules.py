@@ -106,3 +106,17 @@ def test_launch_plan_refuses_what_the_calls_refuse(lib):
         with pytest.raises(lib.BurstError):
             plan(lib, call, masks, 1, heads, 2, 128)
     assert plan(lib, "fwd", [mask, mask], 1, 2, 2, 128) == [lib.BURST_KERNEL_DEALT]
+
+
+@pytest.mark.parametrize("N,d,v,tile,edges", [
+    (207, 2560, 10874, 256, [128, 128, 256]), (2426, 768, 8354, 4096, [128, 256, 128]),
+    (1000, 256, 15361, 1024, [256, 128, 128]), (16384, 4096, 32000, 8192, [256, 256, 256]),
+])
+def test_tiles_of_the_lm_head(lib, N, d, v, tile, edges):
+    assert [edge for edge, _ in lib.burst_lm_head_tile_plan(lib.lm_head_shape(N, d, v, tile))] == edges
+
+
+def test_tile_plan_of_the_lm_head_refuses_what_the_call_refuses(lib):
+    for shape in ((0, 256, 64, 256), (64, 200, 64, 256), (64, 256, 64, 200)):
+        with pytest.raises(lib.BurstError):
+            lib.burst_lm_head_tile_plan(lib.lm_head_shape(*shape))
