@@ -20,7 +20,8 @@
 //    S and dP row-wise.  With grouped-query attention the work-group walks the query heads of its
 //    group, so dK and dV are summed over the group in registers.
 //
-// At d = 64 the vector unit is the bound, and it is filled by waves that keep no common rhythm (fwd.hip).  The dQ kernel runs four
+// At d = 64 the vector unit is what dQ needs most (75 % busy, matrix pipe 60 %; 32 heads x 16384 rows), and it is filled by waves that keep no common
+// rhythm (fwd.hip); dK/dV needs both alike (57 and 58 %) and waits for LDS.  The dQ kernel runs four
 // waves a work-group, three work-groups a CU, 32 key rows after the other (144-150 registers); dK/dV, whose P-waves and dS-waves need
 // their rhythm, and the joint launch run two work-groups of eight waves a CU in 128 registers, with tiles asked for two ahead so that
 // three are in LDS, where the launch has more than one work-group for each CU and, joint, enough work (crowded).  us, one work-group a CU

@@ -21,7 +21,8 @@
 // clocks and 85 other vector instructions of 4, and 32 MFMAs take an issue slot of 4 each, 980 clocks a SIMD.  One wave alone, or
 // two that take turns, do not issue that fast (a vector instruction every 6 to 9 clocks), three do nearly: a wave needs 158
 // registers and a work-group of four 52 KB of LDS, so three work-groups share a CU and fill each other's matrix
-// phases, prologues and epilogues without a common rhythm.  Eight waves in turns, and this, us: 12 heads x 24749 rows 2140, 2050; 32 heads x
+// phases, prologues and epilogues without a common rhythm.  Counters: vector unit 81 % busy, matrix pipe 52 % (32 heads x 16384 rows, full); 58 and 34 %
+// in a step of 1500 rows, 4 x 12 heads, which does not fill the chip for long enough.  Eight waves in turns, and this, us: 12 heads x 24749 rows 2140, 2050; 32 heads x
 // 16384 (an earlier shard) 1153, 1080; 64 x 8548 causal, batch 2, 1390, 1240; with a window (32 heads x 3010, batch 2) 98, 75; one step of 1500
 // rows, 4 x 12 heads 67, 47; 1 head x 20000 rows, 157 work-groups 330, 266.  Raised priority of the MFMAs, 2, 3 or 4 operands
 // ahead and a fence between the exponentials make no difference here.
